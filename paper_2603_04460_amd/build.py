@@ -20,6 +20,8 @@ HIPCC_FLAGS = [
 EXTRA_FLAGS = {
     # one wavefront per SIMD with 512 registers: score accumulators go to the vector registers the softmax reads
     "vs_dense.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    # the same: 280 fewer register copies per 32-token block
+    "vs_train.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

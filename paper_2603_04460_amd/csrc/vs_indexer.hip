@@ -464,7 +464,7 @@ struct IndexerWs {
 IndexerWs indexer_ws_layout(int kv_heads, int64_t n, int d_h) {
     IndexerWs w;
     w.hi_off = 0;
-    w.lo_off = vs::round_up(static_cast<size_t>(d_h) * 256 * 2, 256);
+    w.lo_off = vs::indexer_split_lo_offset(d_h);
     w.part_off = 2 * w.lo_off;
     w.tiles_per_head = static_cast<int>((n + kTokTile - 1) / kTokTile);
     w.parts_per_head = static_cast<int>((n + 63) / 64);

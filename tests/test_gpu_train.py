@@ -58,6 +58,27 @@ def test_train_step_matches_oracle(hk, n, d_h, act):
         _check(got, want, name)
 
 
+@pytest.mark.parametrize("hk,n,d_h,act", [
+    (1, 32 * 128 + 5, 256, 1),                               # 129 blocks of 32 tokens on 128 workgroups: one step and two
+    (3, 1057, 1024, 0),                                      # 102 blocks on 32 workgroups: three steps and four
+    (2, 2600, 1024, 1),                                      # 164 on 32: five and six, KL sums over three blocks of 1024
+    (1, 32 * 256 + 1, 64, 0),                                # half of the wavefronts without hidden units
+])
+def test_train_pipeline_over_several_blocks(hk, n, d_h, act):
+    """Workgroups with one to six 32-token blocks: fill, steady state and drain of the backward kernel's pipeline.  Same
+    bar as above: W_U and the pre-activation gradients carry 2^-17, sums are fp32 over at most 200 tokens per lane."""
+    rng = np.random.default_rng(n + d_h)
+    _, k, v = synth.qkv(170 + n, 1, hk, n, local_structure=True)
+    W = synth.indexer_weights(n, d_h, act, gain=4.0)
+    t_v, t_s = _targets(rng, hk, n)
+    loss, grads = _gpu_step(k.cuda(), v.cuda(), W, act, t_v, t_s)
+    ref = oracle.index_train(synth.to_bits(k), synth.to_bits(v), *W, t_v.astype(np.float64), t_s.astype(np.float64), 0.4, -0.3,
+                             act=act)
+    assert abs(loss - ref[0]) <= 1e-3 * abs(ref[0]), (loss, ref[0])
+    for got, want, name in zip(grads, ref[1:], ("dW_U", "db_U", "dW_V", "dW_S")):
+        _check(got, want, name)
+
+
 def test_train_step_on_aggregated_attention_targets_and_descent():
     """Targets from vs_aggregate (the distillation targets of the paper, here of synthetic Q / K); the step is
     deterministic, and a small move against the gradient lowers the loss."""
