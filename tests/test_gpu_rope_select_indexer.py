@@ -28,6 +28,35 @@ def test_rope_matches_oracle(heads, n, pos0, theta, pairing):
     assert (diff != 0).mean() < 1e-4
 
 
+@pytest.mark.parametrize("heads,n,pairing", [(1, 15, 0), (5, 17, 1), (9, 33, 0)])
+def test_rope_all_magnitudes(heads, n, pairing):
+    """Values over the whole exponent range, zeros and planes that cancel: most results come from the fp32 interval test, the
+    rest from fp64, and both must be the fp64 result rounded once (bar as above).  Ragged batches of heads and positions."""
+    g = torch.Generator().manual_seed(heads * 100 + n)
+    x = torch.randn(heads, n, 128, generator=g) * 2.0 ** torch.randint(-120, 120, (heads, n, 1), generator=g)
+    x[:, ::4] = torch.randn(heads, (n + 3) // 4, 128, generator=g)
+    x[:, 1::4, ::2] = x[:, 1::4, 1::2]
+    x[:, 2::8] = 0.0
+    x = x.to(torch.bfloat16)
+    bits = synth.to_bits(x)
+    got = synth.to_bits(vs.rope_apply(x.cuda(), 70001, 1e6, pairing))
+    ref = oracle.rope_bf16(bits, 70001, 1e6, pairing)
+    diff = got.astype(np.int32) - ref.astype(np.int32)
+    assert np.abs(diff).max() <= 1 and (diff != 0).mean() < 1e-4
+
+
+def test_rope_special_values():
+    """A NaN or an infinity makes its own plane non-finite and nothing else."""
+    x = torch.ones(3, 20, 128, dtype=torch.bfloat16)
+    x[1, 7, 10] = float("nan")
+    x[2, 9, 64] = float("inf")
+    y = vs.rope_apply(x.cuda(), 5, 1e6, 0).float().cpu()
+    bad = torch.zeros_like(y, dtype=torch.bool)
+    bad[1, 7, 10:12] = True
+    bad[2, 9, 64:66] = True
+    assert not torch.isfinite(y[bad]).any() and torch.isfinite(y[~bad]).all()
+
+
 # ---------------------------------------------------------------- selection
 def _gpu_select(a_v, a_s, budget, use_ws=True):
     heads, n = a_v.shape
