@@ -5,52 +5,66 @@
 //   1. row sweep:    lse2[i] = log2 sum_j 2^(c s_ij), c = scale * log2(e): the normaliser of every row
 //   2. column sweep: A[i,j] = 2^(c s_ij - lse2[i]) is recomputed tile by tile and added to its column sum A_v[j], to its
 //                    diagonal sum A_s[i-j] and, where the mask keeps (i,j), to the recall.
-// Both sweeps are the same kernel with the operands exchanged.  A workgroup (8 wavefronts) keeps 256 rows of the
-// RESIDENT operand in registers (32 rows per wavefront, as the B operand of v_mfma_f32_32x32x16_bf16) and streams 32-row
-// tiles of the other operand through LDS (A operand).  A lane then holds the scores of ONE resident row against 16
-// streamed rows, so the reduction over the streamed index is in-lane:
+// Both sweeps are the same kernel with the operands exchanged.  A workgroup (4 wavefronts) keeps 256 rows of the
+// RESIDENT operand in registers (two blocks of 32 rows per wavefront, as the B operand of v_mfma_f32_32x32x16_bf16) and
+// streams 32-row tiles of the other operand through LDS (A operand).  A lane then holds the scores of ONE resident row
+// against 16 streamed rows, so the reduction over the streamed index is in-lane:
 //   row sweep:    resident = queries, streamed = keys 0 .. diagonal  -> per-lane online max / sum over keys
 //   column sweep: resident = keys,    streamed = queries diagonal .. n-1 -> per-lane sum over queries = column sum, kept
 //                 in a register for the whole sweep and written once.
-// Diagonal sums: element (streamed row r, resident key kq) of a tile belongs to offset o = i - j.  Inside a tile the 16
-// accumulator registers of a lane are 16 different rows r of ONE key; register e is rotated by its row number across the
-// 32 lanes of its half-wave (ds_bpermute), after which lane l holds, in every register, an element with kq - r = l
-// (mod 32), i.e. of diagonal -l or 32 - l.  A plain sum and a sum weighted with a precomputed 0/1 "wrapped" factor
-// separate the two, so a tile costs 16 lane permutes and ONE LDS float atomic per lane (63 distinct offsets), instead of
-// one atomic per element.  The atomics go to a 512-entry ring in LDS indexed by o mod 512.  The offsets a workgroup can
-// still touch form a window of 319 consecutive values that advances by 64 per stage, so the 64 offsets that fall out of
-// the window are flushed to global memory (one float atomic each) after every stage.
+// Two workgroups share a compute unit, so that one wavefront's matrix instructions run under the other's vector work.
+// What bounds both sweeps is the vector work per score: scale and subtract, exponential (a quarter of the rate), add; the
+// column sweep also adds every probability to its diagonal.
+//
+// The streamed rows are staged in an order that makes register e of a lane row 16 hh + e of the tile.
+//
+// Diagonal sums: element (streamed row r, resident key k) of a tile belongs to offset o = (first row - first key) + r - k.
+// Tile (t, block c + 1) and tile (t - 1, block c) of a wavefront's two blocks hold the same offsets in the same places:
+// they are added element by element first, and the diagonals are taken once for the two.  There, with k = 16 kh + l, register
+// e moved e lanes down inside its row of 16 lanes (an operand modifier of the add) puts an element into the lane of its
+// offset, 16 hh - 16 kh - l (d0), or, moved out at the lower end and in again at the upper, at 16 more (d1): 31 adds.  Of
+// d1, the lanes of kh = 1 belong to the offsets of d0's lanes of kh = 0, those of kh = 0 to the offsets of the NEXT tile's d0
+// lanes of kh = 1.  So every offset a half wavefront meets is finished in one place, once, and is stored, without a
+// read or an atomic, to a 512-entry LDS ring that the half owns, indexed by o mod 512.  The offsets a workgroup can still touch
+// form a window of 319 consecutive values that advances by 64 per stage; the 64 that fall out of it are added over the eight
+// rings and flushed to global memory (one float atomic each) every stage.
+// (n = 16384, 32 / 8 heads with recall: 4.2 ms with one resident block per wavefront, a permutation through the LDS crossbar,
+// two adds per element and LDS float atomics; 2.2 ms with all this but the atomics, two per pair of tiles, whose rate was
+// the limit; now 1.3.  Row sweep 1.9 -> 1.05 ms.)
+// Recall: a tile that no selected offset crosses adds its column sums where the column is selected; only crossed tiles look
+// at single elements.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
+#include "vs_attn_device.h"
 #include "vs_common.h"
 #include "vs_device.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kD = 128;
-constexpr int kThreads = 512;
+constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
-constexpr int kGroupRows = 32 * kWaves;        // resident rows per workgroup
-constexpr int kRowBytes = 272;                 // streamed row: 256 B + 16 B pad, conflict-free for the 16-byte fragment reads
-constexpr int kTileBytes = 32 * kRowBytes;
-constexpr int kRingTiles = 6;                  // three stages of two tiles
-constexpr int kNormOff = kRingTiles * kTileBytes;           // per streamed row of the ring: its normaliser (column sweep)
-constexpr int kDiagOff = kNormOff + kRingTiles * 32 * 4;
-constexpr int kDiagRing = 512;                 // residues of the offset ring
-constexpr int kSmemBytes = kDiagOff + kDiagRing * 4;
-constexpr uint64_t kAll63 = 0x7fffffffffffffffull;
+constexpr int kGroupRows = 64 * kWaves;        // resident rows per workgroup
+constexpr int kStages = 2;                     // stages of two streamed tiles: one being read, one in flight
+constexpr int kNormOff = kStages * 2 * kTileBytes;          // per streamed row of a stage: minus its normaliser (column sweep)
+constexpr int kDiagRing = 512;                 // residues of an offset ring
+constexpr int kDiagPitch = kDiagRing + 16;     // words from one ring to the next: the halves' offsets are 16 apart, their banks 32
+constexpr int kRings = 2 * kWaves;             // one per half wavefront
+constexpr int kDiagOff = kNormOff + kStages * 64 * 4;
+constexpr int kSmemBytes = kDiagOff + kRings * kDiagPitch * 4;
 
 struct SweepParams {
     const uint16_t* q;              // [q_heads, n, 128]
     const uint16_t* k;              // [kv_heads, n, 128]
-    float* lse2;                    // [q_heads, n]: written by the row sweep, read by the column sweep
+    float* lse2;                    // [q_heads, n]: row normalisers in the log2 domain, written by the row sweep
+    const float* lse;               // what the column sweep reads: lse2, or the caller's natural-log normalisers
+    float lse_scale;                // to the log2 domain
     float* a_v;                     // [out_heads, n], zeroed before the column sweep
     float* a_s;
     float* recall;                  // [out_heads] or null
@@ -63,18 +77,25 @@ struct SweepParams {
     int sw, vw, index_per_q;
 };
 
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
 }
 
-__device__ __forceinline__ float half_swap_sum(float x) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+// x moved down by S lanes (row_shl) or up by S lanes (row_shr) inside every row of 16 lanes; lanes without a source get 0
+template <int CTRL>
+__device__ __forceinline__ float row_move(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
 }
 
 // COLUMNS == false: row sweep (resident queries, streamed keys).  COLUMNS == true: column sweep.
 template <bool COLUMNS, bool RECALL>
-__global__ __launch_bounds__(kThreads) void vs_sweep_kernel(const SweepParams p) {
+__global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams p) {
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
     float* const norm_ring = reinterpret_cast<float*>(smem + kNormOff);
     float* const diag = reinterpret_cast<float*>(smem + kDiagOff);
@@ -92,17 +113,18 @@ __global__ __launch_bounds__(kThreads) void vs_sweep_kernel(const SweepParams p)
     const int grp = COLUMNS ? blockIdx.x / p.q_heads : ngroups - 1 - blockIdx.x / p.q_heads;
     const int g = h / p.group;
     const int r0_wg = kGroupRows * grp;
-    const int my_r0 = r0_wg + 32 * wave;
+    const int my_r0 = r0_wg + 64 * wave;                     // rows my_r0 .. + 31 (block 0) and my_r0 + 32 .. + 63 (block 1)
+    const int my_b0 = my_r0 >> 5;
     const uint16_t* __restrict__ res_base = COLUMNS ? p.k + static_cast<size_t>(g) * n * kD : p.q + static_cast<size_t>(h) * n * kD;
     const uint16_t* __restrict__ str_base = COLUMNS ? p.q + static_cast<size_t>(h) * n * kD : p.k + static_cast<size_t>(g) * n * kD;
-    const float* __restrict__ lse2 = p.lse2 + static_cast<size_t>(h) * n;
 
     // ---- resident fragments: B operand; lane holds resident row qi, d = 16 kk + 8 hh .. +7 ----
-    bf16x8 rf[8];
-    {
-        const uint16_t* src = res_base + static_cast<size_t>(min(my_r0 + qi, n - 1)) * kD + 8 * hh;
+    bf16x8 rf[2][8];
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) rf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * kk));
+    for (int b = 0; b < 2; ++b) {
+        const uint16_t* src = res_base + static_cast<size_t>(min(my_r0 + 32 * b + qi, n - 1)) * kD + 8 * hh;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) rf[b][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * kk));
     }
 
     // ---- streamed tiles: keys 0 .. last resident row (rows), queries first resident row .. n-1 (columns) ----
@@ -111,220 +133,267 @@ __global__ __launch_bounds__(kThreads) void vs_sweep_kernel(const SweepParams p)
     const int nstages = (t_end - t_begin + 1) >> 1;
 
     if (COLUMNS) {
-        for (int s = tid; s < kDiagRing; s += kThreads) diag[s] = 0.f;
+        for (int s = tid; s < kRings * kDiagPitch; s += kThreads) diag[s] = 0.f;
     }
 
-    // ---- staging: thread moves 16-byte chunk (tid & 15) of row (tid >> 4) of each of the two tiles of a stage ----
-    const int st_row = tid >> 4, st_chunk = tid & 15;
-    u32x4 sreg[2];
-    float nreg = 0.f;
-    // rows past the sequence and the padding tile of an odd count read row 0: such tiles are skipped or masked, and an
-    // unpredicated load keeps the number of loads in flight independent of the path
-    auto load_stage = [&](int st) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int t = t_begin + 2 * st + u;
-            int row = 32 * t + st_row;
-            if (t >= t_end || row >= n) row = 0;
-            sreg[u] = *reinterpret_cast<const u32x4*>(str_base + static_cast<size_t>(row) * kD + st_chunk * 8);
-        }
-        if (COLUMNS && tid < 64) {
-            // normaliser of streamed query row: 2^(c s - lse2 - log2_norm) is the entry of A / (n * heads averaged);
-            // +inf for rows that do not exist makes their entries zero
-            const int t = t_begin + 2 * st + (tid >> 5);
-            const int row = 32 * t + (tid & 31);
-            nreg = (t < t_end && row < n) ? lse2[row] + p.log2_norm : INFINITY;
-        }
-    };
-    auto store_stage = [&](int buf) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            *reinterpret_cast<u32x4*>(smem + (2 * buf + u) * kTileBytes + st_row * kRowBytes + st_chunk * 16) = sreg[u];
-        if (COLUMNS && tid < 64) norm_ring[64 * buf + tid] = nreg;
-    };
-    const int a_off = qi * kRowBytes + hh * 16;              // A fragment: lane holds streamed row qi, d = 16 kk + 8 hh ..
-    auto read_a = [&](int slot, bf16x8 (&af)[8]) __attribute__((always_inline)) {
-        const unsigned char* at = smem + slot * kTileBytes + a_off;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) af[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at + kk * 32));
-    };
-
-    // ---- per-lane state ----
-    float m_run = NEG_INF, l_run = 0.f;                      // row sweep: running max (log2 domain) and sum of this lane's keys
-    float col_sum = 0.f, rec_sum = 0.f;                      // column sweep
     // recall: the resident key of this lane is a selected column -> every causal entry of the column is kept
     const int ih = p.index_per_q ? h : g;
-    uint32_t col_keep = 0u;
+    uint32_t col_keep[2] = {0u, 0u};
     const uint32_t* __restrict__ sbit = nullptr;
     if (RECALL) {
         sbit = p.sbit + static_cast<size_t>(ih) * p.sw;
-        const int key = my_r0 + qi;
-        if (key < n && ((p.vbit[static_cast<size_t>(ih) * p.vw + (key >> 5)] >> (key & 31)) & 1u)) col_keep = 0xffffffffu;
-    }
-
-    // diagonal sums: source lane of the rotation of register e (row 8a + 4hh + c of the tile) and its "wrapped" factor
-    int rot_src[16];
-    float rot_wrap[16];
-    if (COLUMNS) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int x = qi + 4 * hh + 8 * (e >> 2) + (e & 3);      // key this lane receives = x mod 32
-            rot_src[e] = 4 * (32 * hh + (x & 31));
-            rot_wrap[e] = x >= 32 ? 1.f : 0.f;                       // wrapped: diagonal 32 - qi, else -qi
+        for (int b = 0; b < 2; ++b) {
+            const int key = my_r0 + 32 * b + qi;
+            if (key < n && ((p.vbit[static_cast<size_t>(ih) * p.vw + (key >> 5)] >> (key & 31)) & 1u)) col_keep[b] = 0xffffffffu;
         }
     }
 
-    // One 32 x 32 tile of scores: acc element E = 4a + c of lane (qi, hh) is (streamed row 8a + 4hh + c, resident row qi).
-    auto tile = [&](int t, int slot, const f32x16& acc, uint64_t win) __attribute__((always_inline)) {
-        const int s0 = 32 * t;                               // first streamed row of the tile
-        if (!COLUMNS) {
-            // keys s0 .. s0+31 against query my_r0 + qi: causal where key <= query
-            float x[16];
-            const bool diag_tile = s0 + 31 > my_r0;
-            const int lim = my_r0 + qi - s0 - 4 * hh;        // element (a, c) is causal iff 8a + c <= lim
-            float mt = NEG_INF;
+    // ---- staging (the K layout of the attention kernels): wavefront w fills groups w and w + 4 of a tile, i.e. slots
+    //      4 w + L / 16 and 16 more; slot 8 a + 4 h + c, which the matrix instruction returns in element 4 a + c of half h, holds
+    //      row 16 h + 4 a + c; rows that do not exist read the last one (masked, or their normaliser is infinite) ----
+    const int st_row = 16 * (wave & 1) + 4 * (wave >> 1) + (lane >> 4);
+    const uint32_t st_b = static_cast<uint32_t>(16 * (4 * ((lane >> 2) & 3) + (((lane & 3) - (lane >> 4)) & 3)));
+    // Requested with a stage and used one step later: used at once, they would be waited for together with the stage's rows
+    // (memory requests return in order).
+    float nreg = 0.f;                                        // normaliser of streamed row `tid` of the stage
+    uint32_t wreg[3] = {0u, 0u, 0u};                         // offset bitmap from bit 32 (first tile - my block 0) + 32
+    auto load_stage = [&](int st) __attribute__((always_inline)) {
+        const int row0 = 32 * (t_begin + 2 * st);
+        if (COLUMNS && tid < 64) nreg = p.lse[static_cast<size_t>(h) * n + min(row0 + tid, n - 1)];
+        if (RECALL) {
+            const uint32_t* const at = sbit + max(t_begin + 2 * st - my_b0, 0) + 1;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                x[e] = acc[e] * p.c;
-                if (diag_tile && 8 * (e >> 2) + (e & 3) > lim) x[e] = NEG_INF;
-                mt = fmaxf(mt, x[e]);
-            }
-            if (mt > m_run) {
-                l_run *= __builtin_amdgcn_exp2f(m_run - mt);  // m_run = -inf: l_run is 0 and stays 0
-                m_run = mt;
-            }
-            if (m_run > NEG_INF) {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) l_run += __builtin_amdgcn_exp2f(x[e] - m_run);
-            }
-        } else {
-            // queries s0 .. s0+31 against key my_r0 + qi: causal where query >= key
-            const float* nr = norm_ring + 32 * slot + 4 * hh;
-            const bool diag_tile = s0 < my_r0 + 32;
-            const int lim = my_r0 + qi - s0 - 4 * hh;        // element (a, c) is causal iff 8a + c >= lim
-            uint32_t keep = 0u;
-            if (RECALL) keep = static_cast<uint32_t>(win >> (31 - qi + 4 * hh)) | col_keep;   // bit 8a + c: (i, j) kept by the mask
-            float psum = 0.f, rsum = 0.f, dsum = 0.f, dwrap = 0.f;
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const f32x4 nv = *reinterpret_cast<const f32x4*>(nr + 8 * a);
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    float pr = __builtin_amdgcn_exp2f(acc[4 * a + c] * p.c - nv[c]);
-                    if (diag_tile && 8 * a + c < lim) pr = 0.f;
-                    psum += pr;
-                    if (RECALL) {                            // adds pr where the keep-bit is set: bit spread over a word, and, add
-                        uint32_t m;
-                        asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(keep), "n"(8 * a + c));
-                        rsum += __uint_as_float(__float_as_uint(pr) & m);
-                    }
-                    const float rot = __int_as_float(__builtin_amdgcn_ds_bpermute(rot_src[4 * a + c], __float_as_int(pr)));
-                    dsum += rot;
-                    dwrap = fmaf(rot, rot_wrap[4 * a + c], dwrap);
-                }
-            }
-            col_sum += psum;
-            rec_sum += rsum;
-            // both halves hold rows of the same two diagonals; lanes 0..31 then add diagonal -qi, lanes 32..63 add 32 - qi
-            dsum = half_swap_sum(dsum);
-            dwrap = half_swap_sum(dwrap);
-            atomicAdd(diag + ((s0 - my_r0 + 32 * hh - qi) & (kDiagRing - 1)), hh ? dwrap : dsum - dwrap);
+            for (int i = 0; i < 3; ++i) wreg[i] = at[i];
         }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int row = min(row0 + 32 * u + 8 * x + st_row, n - 1);
+                lds_load16s((static_cast<uint32_t>(row) << 8) + st_b, str_base,
+                            smem + (2 * (st & 1) + u) * kTileBytes + (wave + kWaves * x) * kGroupBytes);
+            }
+    };
+    // A fragment kk: chunk 2 kk + hh of slot qi
+    const int a_row = (qi >> 2) * kGroupBytes + (qi & 3) * 256;
+    const int a_off0 = a_row + 16 * ((hh + qi) & 3), a_off2 = a_row + 16 * ((hh + qi + 2) & 3);
+
+    // ---- per-lane state ----
+    float m_run[2] = {NEG_INF, NEG_INF}, l_run[2] = {0.f, 0.f};   // row sweep: running max (log2 domain) and sum of this lane's keys
+    float col_sum[2] = {0.f, 0.f}, rec_sum = 0.f;                 // column sweep
+    f32x16 pend;                                             // column sweep: block 0's entries of the previous tile
+#pragma unroll
+    for (int e = 0; e < 16; ++e) pend[e] = 0.f;
+    const int diag_lane = 16 * hh - (lane & 31);
+    float* const my_diag = diag + kDiagPitch * (2 * wave + hh);
+    const bool kh = (lane & 16) != 0;
+    float d1_prev = 0.f;                                     // kh = 1: d1 of the previous tile's lanes of kh = 0
+    uint64_t win_prev = 0ull;                                // block 0's window of the previous tile = block 1's of this one
+
+    // diagonals of one 32 x 32 set of entries; base: first row - first key
+    auto diagonals = [&](const f32x16& x, int base) __attribute__((always_inline)) {
+        float d0[2] = {0.f, 0.f}, d1[2] = {0.f, 0.f};        // two chains each
+        static_for<16>([&](auto e_tag) __attribute__((always_inline)) {
+            constexpr int e = decltype(e_tag)::value;
+            if constexpr (e == 0) d0[0] = x[0];
+            else {
+                d0[e & 1] += row_move<0x100 + e>(x[e]);
+                d1[e & 1] += row_move<0x110 + 16 - e>(x[e]);
+            }
+        });
+        const float e1 = d1[0] + d1[1];
+        const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(e1), __float_as_uint(e1), false, false);
+        const unsigned low = sw[0], high = sw[1];            // the values of kh = 0 / kh = 1 in all lanes
+        my_diag[(base + diag_lane) & (kDiagRing - 1)] = (d0[0] + d0[1]) + (kh ? d1_prev : __uint_as_float(high));
+        d1_prev = __uint_as_float(low);
     };
 
-    // ---- pipeline: step s computes stage s from LDS, prefetches the fragments of stage s+1 and refills the buffer of
-    //      stage s-1 with stage s+2, whose global loads were issued at the top of the step ----
+    // Streamed tile t in slot `slot` against both resident blocks.  acc element e of lane (qi, hh) is (streamed row 16 hh +
+    // e, resident row qi).  MASKED: the tile may hold entries past the diagonal.
+    auto tile = [&](int t, int slot, uint32_t w0, uint32_t w1, auto masked_tag) __attribute__((always_inline)) {
+        constexpr bool MASKED = decltype(masked_tag)::value;
+        const unsigned char* const at = smem + slot * kTileBytes;
+        f32x16 acc[2];
+        {
+            bf16x8 af[8];
 #pragma unroll
-    for (int st = 0; st < 2; ++st) {
-        if (st < nstages) {
-            load_stage(st);
-            store_stage(st);
-        }
-    }
-    __syncthreads();
-    int buf = 0;
-    for (int st = 0; st < nstages; ++st) {
-        if (st > 0) __syncthreads();
-        const int buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf1 == 2 ? 0 : buf1 + 1;
-        if (COLUMNS && st > 0 && tid < 64) {
-            // offsets below 64 st - 255 can no longer be touched: flush the 64 that became final with the last stage
-            const int o = 64 * (st - 1) - (kGroupRows - 1) + tid;
-            if (o >= 0 && o < n) {
-                const int s = o & (kDiagRing - 1);
-                const float v = diag[s];
-                diag[s] = 0.f;
-                if (v != 0.f) unsafeAtomicAdd(p.a_s + static_cast<size_t>(p.reduce_group ? g : h) * n + o, v);
+            for (int kk = 0; kk < 8; ++kk)
+                af[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at + ((kk & 1) ? a_off2 : a_off0) + 64 * (kk >> 1)));
+            f32x16 zero;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk) {
+                acc[0] = mfma32(af[kk], rf[0][kk], kk == 0 ? zero : acc[0]);
+                acc[1] = mfma32(af[kk], rf[1][kk], kk == 0 ? zero : acc[1]);
             }
         }
-        const bool more = st + 2 < nstages;
-        load_stage(st + 2);
-        const int t0 = t_begin + 2 * st, t1 = t0 + 1;
-        // a tile is live for this wavefront if any of its entries is causal
-        const bool live0 = my_r0 < n && (COLUMNS ? 32 * t0 + 31 >= my_r0 : 32 * t0 <= my_r0 + 31);
-        const bool live1 = t1 < t_end && my_r0 < n && (COLUMNS ? 32 * t1 + 31 >= my_r0 : 32 * t1 <= my_r0 + 31);
-        uint64_t win0 = 0ull, win1 = 0ull;
-        if (RECALL) {
-            // selected offsets dlt-31 .. dlt+31 of a tile at bits 0..62, dlt = first query - first key
-            if (live0) win0 = window64(sbit, 32 * t0 - my_r0 + 33) & kAll63;
-            if (live1) win1 = window64(sbit, 32 * t1 - my_r0 + 33) & kAll63;
-        }
-        if (live0 || live1) {
-            bf16x8 a0[8], a1[8];
-            f32x16 s0, s1;
+        const int s0 = 32 * t;                               // first streamed row of the tile
+        if constexpr (!COLUMNS) {
+            // keys s0 .. s0+31 against queries: causal where key <= query
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s0[e] = s1[e] = 0.f;
-            if (live0) read_a(2 * buf, a0);
-            if (live1) read_a(2 * buf + 1, a1);
-            if (live0 && live1) {
+            for (int b = 0; b < 2; ++b) {
+                f32x16& x = acc[b];
+                if constexpr (MASKED) {
+                    const int lim = my_r0 + 32 * b + qi - s0 - 16 * hh;   // element e is causal iff e <= lim
 #pragma unroll
-                for (int kk = 0; kk < 8; ++kk) {             // two independent accumulation chains
-                    s0 = mfma32(a0[kk], rf[kk], s0);
-                    s1 = mfma32(a1[kk], rf[kk], s1);
+                    for (int e = 0; e < 16; ++e)
+                        if (e > lim) x[e] = NEG_INF;
                 }
-            } else if (live0) {
+                float mt = fmaxf(fmaxf(x[0], x[1]), x[2]);
 #pragma unroll
-                for (int kk = 0; kk < 8; ++kk) s0 = mfma32(a0[kk], rf[kk], s0);
-            } else {
+                for (int e = 3; e < 15; e += 2) mt = fmaxf(fmaxf(mt, x[e]), x[e + 1]);
+                mt = fmaxf(mt, x[15]) * p.c;
+                // the maximum is only moved when it grew by more than 2^8 (false where both are -inf)
+                if (__ballot(mt - m_run[b] > kRescaleThreshold)) {
+                    const float m_new = fmaxf(m_run[b], mt);
+                    l_run[b] *= m_new == NEG_INF ? 1.f : __builtin_amdgcn_exp2f(m_run[b] - m_new);
+                    m_run[b] = m_new;
+                }
+                const float mc = m_run[b] == NEG_INF ? 0.f : m_run[b];
+                float sum[2] = {0.f, 0.f};
 #pragma unroll
-                for (int kk = 0; kk < 8; ++kk) s1 = mfma32(a1[kk], rf[kk], s1);
+                for (int e = 0; e < 16; ++e) sum[e & 1] += __builtin_amdgcn_exp2f(fmaf(x[e], p.c, -mc));
+                l_run[b] += sum[0] + sum[1];
             }
-            if (live0) tile(t0, 2 * buf, s0, win0);
-            if (live1) tile(t1, 2 * buf + 1, s1, win1);
+        } else {
+            // queries s0 .. s0+31 against keys: causal where query >= key
+            const float* const nr = norm_ring + 32 * slot + 16 * hh;
+            f32x4 nv[4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) nv[a] = *reinterpret_cast<const f32x4*>(nr + 4 * a);
+            uint64_t win[2] = {0ull, 0ull};
+            if (RECALL) {
+                // selected offsets dlt-31 .. dlt+31 of a tile at bits 0..62, dlt = first query - first key
+                // (w0, w1: bits dlt - 32 .. dlt + 31)
+                win[0] = ((static_cast<uint64_t>(w1) << 32) | w0) >> 1;
+                win[1] = win_prev;
+                win_prev = win[0];
+            }
+            float psum[2];
+#pragma unroll
+            for (int b = 1; b >= 0; --b) {
+                f32x16& x = acc[b];
+                float sum[2] = {0.f, 0.f};
+                const int lim = my_r0 + 32 * b + qi - s0 - 16 * hh;       // element e is causal iff e >= lim
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    float pr = __builtin_amdgcn_exp2f(fmaf(x[e], p.c, nv[e >> 2][e & 3]));
+                    if (MASKED && e < lim) pr = 0.f;
+                    x[e] = pr;
+                    sum[e & 1] += pr;
+                    if (b == 1) pend[e] += pr;
+                }
+                psum[b] = sum[0] + sum[1];
+                col_sum[b] += psum[b];
+            }
+            diagonals(pend, s0 - my_r0 - 32);
+            pend = acc[0];
+            if (RECALL) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    float rsum = __uint_as_float(__float_as_uint(psum[b]) & col_keep[b]);
+                    if (win[b] != 0ull) {
+                        const uint32_t keep = static_cast<uint32_t>(win[b] >> (31 - qi + 16 * hh)) | col_keep[b];   // bit e: (i, j) kept
+                        rsum = 0.f;
+                        static_for<16>([&](auto e_tag) __attribute__((always_inline)) {
+                            constexpr int e = decltype(e_tag)::value;
+                            uint32_t m;                      // the keep-bit spread over a word
+                            asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(keep), "n"(e));
+                            rsum += __uint_as_float(__float_as_uint(acc[b][e]) & m);
+                        });
+                    }
+                    rec_sum += rsum;
+                }
+            }
         }
-        if (more) store_stage(buf2);
-        buf = buf1;
+    };
+    auto tile_any = [&](int t, int slot, uint32_t w0, uint32_t w1) __attribute__((always_inline)) {
+        // live if any of its entries is causal for one of the two blocks
+        const bool live = t < t_end && my_r0 < n && (COLUMNS ? t >= my_b0 : t <= my_b0 + 1);
+        if (!live) return;
+        if (COLUMNS ? t <= my_b0 + 1 : t >= my_b0) tile(t, slot, w0, w1, std::true_type{});
+        else tile(t, slot, w0, w1, std::false_type{});
+    };
+
+    // ---- pipeline: step s computes stage s; the loads of stage s + 1 are issued at its top, over stage s - 1 ----
+    load_stage(0);
+    for (int st = 0; st < nstages; ++st) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);                  // this wavefront's part of stage st (and the resident rows) has arrived
+        if (COLUMNS && tid < 64) {
+            // 2^(c s - lse2 - log2_norm) is the entry of A / (n * heads averaged); rows that do not exist get 2^-inf
+            const bool exists = 32 * (t_begin + 2 * st) + tid < n;
+            norm_ring[64 * (st & 1) + tid] = exists ? -fmaf(nreg, p.lse_scale, p.log2_norm) : NEG_INF;
+        }
+        uint32_t w[3] = {0u, 0u, 0u};
+        if (RECALL) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) w[i] = __builtin_amdgcn_readfirstlane(wreg[i]);
+        }
+        __syncthreads();
+        if (COLUMNS && st > 0) {
+            // offsets below 64 st - 255 can no longer be touched: flush the 64 that became final with the last stage, 16 per
+            // wavefront; a row of 16 lanes adds two rings
+            const int o = 64 * (st - 1) - (kGroupRows - 1) + 16 * wave + (lane & 15);
+            float* const at = diag + 2 * kDiagPitch * (lane >> 4) + (o & (kDiagRing - 1));
+            float v = at[0] + at[kDiagPitch];
+            at[0] = at[kDiagPitch] = 0.f;
+            const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+            const unsigned low = sw[0], high = sw[1];
+            v = half_swap_sum(__uint_as_float(low) + __uint_as_float(high));
+            if (lane < 16 && o >= 0 && o < n && v != 0.f)
+                unsafeAtomicAdd(p.a_s + static_cast<size_t>(p.reduce_group ? g : h) * n + o, v);
+        }
+        if (st + 1 < nstages) load_stage(st + 1);
+        const int t0 = t_begin + 2 * st;
+        tile_any(t0, 2 * (st & 1), w[0], w[1]);
+        tile_any(t0 + 1, 2 * (st & 1) + 1, w[1], w[2]);
     }
 
     // ---- results ----
-    if (!COLUMNS) {
-        // the two halves of the wavefront hold disjoint keys of the same query: merge (max, sum) pairs
-        const auto mo = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_run), __float_as_uint(m_run), false, false);
-        const auto lo = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
-        const float m_a = __uint_as_float(mo[0]), m_b = __uint_as_float(mo[1]);
-        const float l_a = __uint_as_float(lo[0]), l_b = __uint_as_float(lo[1]);
-        const float m2 = fmaxf(m_a, m_b);
-        float l2 = 0.f;
-        if (m_a > NEG_INF) l2 += l_a * __builtin_amdgcn_exp2f(m_a - m2);
-        if (m_b > NEG_INF) l2 += l_b * __builtin_amdgcn_exp2f(m_b - m2);
-        const int row = my_r0 + qi;
-        if (row < n && hh == 0) p.lse2[static_cast<size_t>(h) * n + row] = m2 + __log2f(l2);
+    if constexpr (!COLUMNS) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            // the two halves of the wavefront hold disjoint keys of the same query: merge (max, sum) pairs
+            const auto mo = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_run[b]), __float_as_uint(m_run[b]), false, false);
+            const auto lo = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run[b]), __float_as_uint(l_run[b]), false, false);
+            const float m_a = __uint_as_float(mo[0]), m_b = __uint_as_float(mo[1]);
+            const float l_a = __uint_as_float(lo[0]), l_b = __uint_as_float(lo[1]);
+            const float m2 = fmaxf(m_a, m_b);
+            float l2 = 0.f;
+            if (m_a > NEG_INF) l2 += l_a * __builtin_amdgcn_exp2f(m_a - m2);
+            if (m_b > NEG_INF) l2 += l_b * __builtin_amdgcn_exp2f(m_b - m2);
+            const int row = my_r0 + 32 * b + qi;
+            if (row < n && hh == 0) p.lse2[static_cast<size_t>(h) * n + row] = m2 + __log2f(l2);
+        }
     } else {
+        if (my_r0 < n) {
+            // block 0's entries of the last tile have no partner; what they leave in d1_prev has no next tile
+            const int base = 32 * (t_end - 1) - my_r0;
+            diagonals(pend, base);
+            my_diag[(base + 32 + diag_lane) & (kDiagRing - 1)] = kh ? d1_prev : 0.f;
+        }
         __syncthreads();
         // what is still in the ring: the last 319 offsets the workgroup touched
-        if (tid < kGroupRows + 64) {
-            const int o = 64 * (nstages - 1) - (kGroupRows - 1) + tid;
+        const int out_head = p.reduce_group ? g : h;
+        for (int i = tid; i < kGroupRows + 64; i += kThreads) {
+            const int o = 64 * (nstages - 1) - (kGroupRows - 1) + i;
             if (o >= 0 && o < n) {
-                const int s = o & (kDiagRing - 1);
-                const float v = diag[s];
-                if (v != 0.f) unsafeAtomicAdd(p.a_s + static_cast<size_t>(p.reduce_group ? g : h) * n + o, v);
+                float v = 0.f;
+#pragma unroll
+                for (int r = 0; r < kRings; ++r) v += diag[r * kDiagPitch + (o & (kDiagRing - 1))];
+                if (v != 0.f) unsafeAtomicAdd(p.a_s + static_cast<size_t>(out_head) * n + o, v);
             }
         }
-        const int out_head = p.reduce_group ? g : h;
-        const float cs = half_swap_sum(col_sum);
-        const int key = my_r0 + qi;
-        if (key < n && hh == 0) {
-            if (p.reduce_group) unsafeAtomicAdd(p.a_v + static_cast<size_t>(out_head) * n + key, cs);
-            else p.a_v[static_cast<size_t>(out_head) * n + key] = cs;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const float cs = half_swap_sum(col_sum[b]);
+            const int key = my_r0 + 32 * b + qi;
+            if (key < n && hh == 0) {
+                if (p.reduce_group) unsafeAtomicAdd(p.a_v + static_cast<size_t>(out_head) * n + key, cs);
+                else p.a_v[static_cast<size_t>(out_head) * n + key] = cs;
+            }
         }
         if (RECALL) {
             float r = rec_sum;
@@ -335,15 +404,15 @@ __global__ __launch_bounds__(kThreads) void vs_sweep_kernel(const SweepParams p)
     }
 }
 
-__global__ void fill_float_kernel(float* p, size_t count, float value) {
+// outputs are accumulated with atomics and bitmaps with bit atomics: all of them start at zero (one launch)
+__global__ void clear_kernel(float* a_v, float* a_s, size_t count, float* recall, int heads, uint32_t* bits, size_t words) {
     const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = value;
-}
-
-// natural-log row normalisers (as written by the dense attention call) -> log2 domain
-__global__ void lse_to_log2_kernel(const float* lse, float* lse2, size_t count) {
-    const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count) lse2[i] = lse[i] * 1.4426950408889634f;
+    if (i < count) {
+        a_v[i] = 0.f;
+        a_s[i] = 0.f;
+    }
+    if (recall && i < static_cast<size_t>(heads)) recall[i] = 0.f;
+    if (i < words) bits[i] = 0u;
 }
 
 struct AggWs {
@@ -411,21 +480,15 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     p.log2_norm = log2f(static_cast<float>(n)) + (p.reduce_group ? log2f(static_cast<float>(p.group)) : 0.f);
     p.index_per_q = (want_recall && index_heads == q_heads && q_heads != kv_heads) ? 1 : 0;
 
-    // outputs are accumulated with atomics
     const size_t out_count = static_cast<size_t>(out_heads) * n;
-    hipLaunchKernelGGL(fill_float_kernel, dim3(static_cast<unsigned>((out_count + 255) / 256)), dim3(256), 0, st, a_v, out_count, 0.f);
-    VS_LAUNCH_CHECK();
-    hipLaunchKernelGGL(fill_float_kernel, dim3(static_cast<unsigned>((out_count + 255) / 256)), dim3(256), 0, st, a_s, out_count, 0.f);
+    uint32_t* sbit = reinterpret_cast<uint32_t*>(base + w.sbit_off);
+    uint32_t* vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);
+    const size_t words = want_recall ? (w.total - w.sbit_off) / 4 : 0;
+    const size_t most = words > out_count ? words : out_count;   // (at least one output per head: recall rides along)
+    hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>((most + 255) / 256)), dim3(256), 0, st, a_v, a_s, out_count, recall,
+                       out_heads, sbit, words);
     VS_LAUNCH_CHECK();
     if (want_recall) {
-        hipLaunchKernelGGL(fill_float_kernel, dim3(static_cast<unsigned>((out_heads + 255) / 256)), dim3(256), 0, st, recall,
-                           static_cast<size_t>(out_heads), 0.f);
-        VS_LAUNCH_CHECK();
-        uint32_t* sbit = reinterpret_cast<uint32_t*>(base + w.sbit_off);
-        uint32_t* vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);
-        const size_t words = (w.total - w.sbit_off) / 4;
-        hipLaunchKernelGGL(fill_zero_kernel, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256), 0, st, sbit, words);
-        VS_LAUNCH_CHECK();
         hipLaunchKernelGGL(set_bits_kernel, dim3((cap_s + 255) / 256, index_heads), dim3(256), 0, st, idx_s, cnt_s, cap_s,
                            static_cast<int>(n), sbit, w.sw, 64);
         VS_LAUNCH_CHECK();
@@ -439,13 +502,12 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     }
     const int64_t blocks = static_cast<int64_t>(q_heads) * ((n + kGroupRows - 1) / kGroupRows);
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
-    const size_t rows = static_cast<size_t>(q_heads) * n;
-    if (lse) {
-        hipLaunchKernelGGL(lse_to_log2_kernel, dim3(static_cast<unsigned>((rows + 255) / 256)), dim3(256), 0, st, lse, p.lse2, rows);
-    } else {
+    p.lse = lse ? lse : p.lse2;
+    p.lse_scale = lse ? 1.4426950408889634f : 1.f;
+    if (!lse) {
         hipLaunchKernelGGL((vs_sweep_kernel<false, false>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
+        VS_LAUNCH_CHECK();
     }
-    VS_LAUNCH_CHECK();
     if (want_recall) hipLaunchKernelGGL((vs_sweep_kernel<true, true>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
     else hipLaunchKernelGGL((vs_sweep_kernel<true, false>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
     VS_LAUNCH_CHECK();

@@ -15,10 +15,6 @@ __device__ __forceinline__ uint64_t window64(const uint32_t* __restrict__ bm, in
 }
 
 // ---- index lists -> bitmaps ----
-__global__ void fill_zero_kernel(uint32_t* p, size_t words) {
-    const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < words) p[i] = 0u;
-}
 
 // bit (e + bit_shift) of head ih's bitmap is set for every valid list entry e in [0, n)
 __global__ void set_bits_kernel(const int32_t* idx, const int32_t* cnt, int cap, int n, uint32_t* bits, int words_per_head,

@@ -73,6 +73,22 @@ def test_aggregate_per_query_head(hq, hk, n):
     assert np.abs(a_v.sum(axis=1) - 1).max() < 1e-4 and np.abs(a_s.sum(axis=1) - 1).max() < 1e-4
 
 
+@pytest.mark.parametrize("n", [31, 32, 65, 191, 225, 289, 545, 1569])
+def test_aggregate_tile_edges(n):
+    """Lengths around the 32-row tile, a wavefront's two blocks, the 256-row workgroup and the 512-entry diagonal rings, with
+    the recall of a mask whose offsets start and end inside a tile."""
+    hq, hk = 2, 1
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(500 + n, hq, hk, n, local=True)
+    iv, cv = lists([np.sort(rng.choice(n, max(1, n // 20), replace=False))])
+    is_, cs = lists([np.unique(np.clip(np.concatenate([[0, 1, 31, 32, 33], np.arange(n // 2, n // 2 + 20), [n - 1]]), 0, n - 1))])
+    a_v, a_s, rec = _run(q, k, hq, mask=(iv, cv, is_, cs))
+    ref_v, ref_s, ref_r = _oracle(qb, kb, hq // hk, mask=(iv, cv, is_, cs))
+    _close(a_v, ref_v)
+    _close(a_s, ref_s)
+    assert np.abs(rec - ref_r).max() <= RECALL_ABS, (rec, ref_r)
+
+
 def test_aggregate_8192_one_head_elementwise():
     """n = 8192, one head: 32 resident-key workgroups, 128 streamed stages each, the 512-entry diagonal ring wraps 16
     times and every flush window is compared, element by element, together with the recall of a mask."""
