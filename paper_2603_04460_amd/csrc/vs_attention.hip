@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     // one queue of units per KV head.  A workgroup starts in the queue of head (its XCD number) % kv_heads, so an XCD's
     // L2 mostly sees one head's K / V, and moves on to the next queue when its own is empty, so that heads with a
     // larger budget do not become the critical path.  Every wavefront leaves the loop at the same point.  (Without
-    // counters, more than 32 KV heads: one workgroup per unit, heads rotated over the XCDs.)
+    // counters: one workgroup per unit, heads rotated over the XCDs.)
     int bid = blockIdx.x;
     int queue = 0;
     // statistics of this workgroup over all its units, added to the workspace counters once, at the end: one atomic per
@@ -102,18 +102,39 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     for (;;) {
     if (p.work_counter) {
         __syncthreads();                                     // LDS and the slots below are free again
-        if (threadIdx.x == 0) {
+        if (threadIdx.x < 64) {
+            // wavefront 0: the own queue first; when it is empty, look at all counters with one load and try only queues that
+            // have units left (a stale value costs one vain attempt).  Every workgroup that walked all queues with atomics at
+            // the end, on counters in one cache line, was 4096 atomics of ~12 ns in a row: the larger part of a small call.
+            const int ln = threadIdx.x;
             int q = queue, unit = -1;
-            for (int t = 0; t < p.kv_heads; ++t) {
-                const int u = static_cast<int>(atomicAdd(p.work_counter + q, 1u));
-                if (u < units_per_head) {
-                    unit = u;
-                    break;
+            auto claim = [&](int which) -> int {
+                int u = 0;
+                if (ln == 0) u = static_cast<int>(atomicAdd(p.work_counter + which * p.work_stride, 1u));
+                return __builtin_amdgcn_readfirstlane(u);
+            };
+            int u = claim(q);
+            if (u < units_per_head) unit = u;
+            for (int base = 0; unit < 0 && base < p.kv_heads; base += 64) {
+                // head (queue + 1 + base + lane) modulo the number of heads
+                const int off = base + ln;
+                const int head = (queue + 1 + off) % p.kv_heads;
+                const bool some = off < p.kv_heads - 1 &&
+                                  static_cast<int>(__hip_atomic_load(p.work_counter + head * p.work_stride, __ATOMIC_RELAXED,
+                                                                     __HIP_MEMORY_SCOPE_AGENT)) < units_per_head;
+                uint64_t left = __ballot(some);
+                while (left != 0ull && unit < 0) {
+                    const int l = __builtin_ctzll(left);
+                    left &= left - 1;
+                    q = (queue + 1 + base + l) % p.kv_heads;
+                    u = claim(q);
+                    if (u < units_per_head) unit = u;
                 }
-                q = q + 1 == p.kv_heads ? 0 : q + 1;
             }
-            wtot[31] = unit;
-            wtot[30] = q;
+            if (ln == 0) {
+                wtot[31] = unit;
+                wtot[30] = q;
+            }
         }
         __syncthreads();
         queue = __builtin_amdgcn_readfirstlane(wtot[30]);
@@ -273,43 +294,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     };
     const int bcap = kListCap / nsub;                        // listed blocks per round
     const int my_sub = wave / p.hc;
-    // Tile record of a listed block for one 32-row sub-block, made once per unit by the thread that lists the block, so
-    // that a step of the tile loop reads one flag word (scalar instructions cost this loop as much as vector ones):
-    //   x, y: 64-bit window wz; lane (q, h) keeps key kj iff bit 31 + q - kj of wz is set and bit kj of kw (word z) is:
-    //         element-exact mode: wz = selected offsets dlt-31 .. dlt+31, kw = columns not listed
-    //         tile-granular mode: wz = causal offsets, kw = keys that some row of the block reaches through a selected
-    //         offset, listed columns taken out
-    //   w: bit 0 live, bit 1 a mask is needed, bits 2..: the key block (so that one word per tile tells a step all it
-    //      needs for the staging loads and the tests; the rest is read only where a mask is applied)
-    // sub_i0: first row of the sub-block; b: key block; w: the offset window prepared with the diagonal list; xw: the block's
-    // column word
-    auto make_record = [&](int sub_i0, int b, uint64_t w, uint32_t xw) __attribute__((always_inline)) -> uint4 {
-        const int dlt = sub_i0 - 32 * b;                     // offset of (row 0, key 0) of the 32x32 tile
-        uint64_t wz = w;
-        uint32_t kw = ~xw;
-        bool live = w != 0ull, need = w != kAll63 || xw != 0u;
-        if (p.gran == 32) {
-            // Tile-granular slash: key kj is kept for every causal row of this 32-row block if ANY of its rows reaches it
-            // through a selected offset, i.e. if the window has a bit in [31 - kj, 62 - kj].
-            // x bit s = OR of window bits s .. s+len-1, len = rows of this block that exist (32 except at the end of
-            // the sequence): doubling up to the largest power of two pw <= len, then two overlapping windows
-            const int len = max(1, min(32, n_pos - sub_i0));
-            uint64_t x = w;
-            int pw = 1;
-            while (2 * pw <= len) {
-                x |= x >> pw;
-                pw *= 2;
-            }
-            x |= x >> (len - pw);
-            wz = dlt >= 31 ? kAll63 : (dlt < -31 ? 0ull : ((kAll63 << (31 - dlt)) & kAll63));   // offsets >= 0
-            kw = __builtin_bitreverse32(static_cast<uint32_t>(x)) & ~xw;
-            live = kw != 0u && wz != 0ull;
-            need = !(kw == 0xffffffffu && wz == kAll63);
-        }
-        if (dlt < -31 || sub_i0 >= n_pos) live = false;      // every key lies after every row / padding rows
-        return make_uint4(static_cast<uint32_t>(wz), static_cast<uint32_t>(wz >> 32), kw,
-                          (live ? 1u : 0u) | (need ? 2u : 0u) | (static_cast<uint32_t>(b) << 2));
-    };
+    // Tile records (tile_record) are made once per unit by the thread that lists the block, so that a step of the tile loop
+    // reads one flag word (scalar instructions cost this loop as much as vector ones).
     const int rcap = bcap + kRecPad;                         // records per sub-block
     const uint4* const my_rec = list_rec + my_sub * rcap;
     // t: position in the block list; d: word w of its record
@@ -603,7 +589,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                 const int b = qb0 - dl[rbase + e];
                 const uint32_t xw = vbit[b];
                 for (int r = 0; r < nsub; ++r)
-                    list_rec[r * rcap + e] = make_record(i0 + 32 * r, b, wl[static_cast<size_t>(rbase + e) * 4 + r], xw);
+                    list_rec[r * rcap + e] = tile_record(p.gran, n_pos, i0 + 32 * r, b, wl[static_cast<size_t>(rbase + e) * 4 + r], xw);
             } else if (tid < count + kRecPad) {
                 for (int r = 0; r < nsub; ++r) list_rec[r * rcap + tid] = make_uint4(0u, 0u, 0u, 0u);
             }
@@ -681,9 +667,8 @@ struct PrepParams {
     int cap_s;
     int n, nsub, nblk;
     int shift;                      // pos0 % 32: row blocks start at positions 32 t + shift
-    uint32_t* sbit;                 // per head: bit (o + 64) set iff offset o selected (64-bit zero guard in front, zero tail)
     uint32_t* vbit;
-    int sw, vw;
+    int sw, vw;                     // words of the offset bitmap (LDS only: bit (o + 64), 64-bit zero guard, zero tail), of vbit
     int32_t* dlist;
     unsigned long long* wlist;
     int dcap;
@@ -691,16 +676,20 @@ struct PrepParams {
     int32_t* ncol32;
     int nq32;
     int32_t* vfirst;
-    uint32_t* counters;             // tile counter and the work queues' counters at the head of the workspace, zeroed here
+    uint32_t* counters;             // tile counters at the head of the workspace and the work queues' counters, zeroed here
     int ncounters;
+    uint32_t* queues;
+    int nqueues, queue_stride;
 };
 
 __global__ __launch_bounds__(kPrepThreads) void vs_prepare_kernel(const PrepParams p) {
     extern __shared__ __align__(16) uint32_t bm[];           // max(sw, vw) words, then 32 words of scan scratch
     const int ih = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     uint32_t* const scan = bm + max(p.sw, p.vw);
-    if (ih == 0)
+    if (ih == 0) {
         for (int i = tid; i < p.ncounters; i += kPrepThreads) p.counters[i] = 0u;
+        for (int i = tid; i < p.nqueues; i += kPrepThreads) p.queues[static_cast<size_t>(i) * p.queue_stride] = 0u;
+    }
     // offsets
     for (int w = tid; w < p.sw; w += kPrepThreads) bm[w] = 0u;
     __syncthreads();
@@ -710,8 +699,6 @@ __global__ __launch_bounds__(kPrepThreads) void vs_prepare_kernel(const PrepPara
         if (e >= 0 && e < p.n) atomicOr(&bm[(e + 64) >> 5], 1u << ((e + 64) & 31));
     }
     __syncthreads();
-    uint32_t* const sbit = p.sbit + static_cast<size_t>(ih) * p.sw;
-    for (int w = tid; w < p.sw; w += kPrepThreads) sbit[w] = bm[w];
     // Block diagonals.  A query tile whose first row block starts at position 32 qb + shift looks, for diagonal delta, at
     // key block qb - delta; its 32-row block r < nsub then sees that block through the offsets 32 (delta + r) + shift - 31
     // .. + 31.  Candidate c stands for delta = c + dmin.  A thread owns a run of consecutive candidates; an exclusive
@@ -780,8 +767,8 @@ __global__ __launch_bounds__(kPrepThreads) void vs_prepare_kernel(const PrepPara
 }
 
 struct SparseWs {
-    size_t counter_off, sbit_off, vbit_off, ncol_off, ndiag_off, vfirst_off, dlist_off, wlist_off, total;
-    int sw, vw, nq32, dcap;
+    size_t counter_off, queue_off, vbit_off, ncol_off, ndiag_off, vfirst_off, dlist_off, wlist_off, total;
+    int sw, vw, nq32, dcap, queue_stride;
 };
 
 SparseWs sparse_ws_layout(int kv_heads, int index_heads, int64_t n) {
@@ -792,9 +779,12 @@ SparseWs sparse_ws_layout(int kv_heads, int index_heads, int64_t n) {
     w.vw = static_cast<int>(vs::round_up(static_cast<size_t>(nblk + 4), 4));
     w.nq32 = static_cast<int>(nblk);
     w.dcap = static_cast<int>(nblk + 4);
-    w.counter_off = 0;                                      // three 8-byte tile counters, then from byte 64 one counter per KV head
-    w.sbit_off = vs::round_up(64 + static_cast<size_t>(kv_heads) * 4, 256);
-    w.vbit_off = w.sbit_off + ih * w.sw * 4;
+    w.counter_off = 0;                                      // three 8-byte tile counters
+    // Work-queue counters, one per KV head, 128 bytes apart (atomics on one cache line are served one after the other); very
+    // short sequences, which have few units, get what fits.  (The area has the size of the offset bitmaps, which stay in LDS.)
+    w.queue_off = vs::round_up(64 + static_cast<size_t>(kv_heads) * 4, 256);
+    w.queue_stride = w.sw < 32 ? w.sw : 32;
+    w.vbit_off = w.queue_off + ih * w.sw * 4;
     w.ncol_off = vs::round_up(w.vbit_off + ih * w.vw * 4, 256);
     w.ndiag_off = vs::round_up(w.ncol_off + ih * w.nq32 * 4, 256);
     w.vfirst_off = vs::round_up(w.ndiag_off + ih * w.nq32 * 4, 256);
@@ -892,8 +882,9 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     p.nq32 = w.nq32;
     p.vfirst = reinterpret_cast<const int32_t*>(base + w.vfirst_off);
     p.tile_counter = reinterpret_cast<unsigned long long*>(base + w.counter_off);
-    // one queue counter per KV head from byte 64 of the counter block (zeroed by the preparation kernel)
-    p.work_counter = reinterpret_cast<unsigned int*>(base + w.counter_off + 64);
+    // one queue counter per KV head (zeroed by the preparation kernel)
+    p.work_counter = reinterpret_cast<unsigned int*>(base + w.queue_off);
+    p.work_stride = w.queue_stride;
 
     DeviceInfo info;
     int rc = device_info(info);
@@ -909,7 +900,6 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     pp.nsub = kWaves / p.hc;
     pp.nblk = w.nq32;
     pp.shift = static_cast<int>(pos0 % 32);
-    pp.sbit = reinterpret_cast<uint32_t*>(base + w.sbit_off);
     pp.vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);
     pp.sw = w.sw;
     pp.vw = w.vw;
@@ -921,7 +911,10 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     pp.nq32 = w.nq32;
     pp.vfirst = reinterpret_cast<int32_t*>(base + w.vfirst_off);
     pp.counters = reinterpret_cast<uint32_t*>(base + w.counter_off);
-    pp.ncounters = 16 + kv_heads;
+    pp.ncounters = 16;
+    pp.queues = reinterpret_cast<uint32_t*>(base + w.queue_off);
+    pp.nqueues = kv_heads;
+    pp.queue_stride = w.queue_stride;
     const size_t prep_lds = (static_cast<size_t>(w.sw > w.vw ? w.sw : w.vw) + 32) * 4;
     if (prep_lds > 160 * 1024) return VS_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(vs_prepare_kernel, dim3(index_heads), dim3(kPrepThreads), prep_lds, st, pp);

@@ -9,27 +9,7 @@
 
 #include "vs_common.h"
 
-namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4t __attribute__((__vector_size__(4 * sizeof(__bf16))));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kD = 128;
-// A tile is staged with loads that write LDS directly: one wavefront instruction deposits its 64 16-byte pieces
-// back to back, which makes 4 rows of 256 B a contiguous 1 KB group.  Groups are 64 B apart and the pieces are rotated
-// inside a group so that fragment reads spread over all banks:
-//   K (16-byte reads, 16 rows at one chunk c): chunk c of row r sits at 64 (c / 4) + 16 ((c + r) % 4) of its row
-//   V (transposing reads, 4 rows x 64 B):      byte x of row r sits at 64 ((x / 64 + r) % 4) + x % 64 of its row
-constexpr int kGroupBytes = 4 * 256 + 64;      // four rows and the gap to the next group
-constexpr int kTileBytes = 8 * kGroupBytes;    // one 32-key tile of K or V
-constexpr int kSlotBytes = 2 * kTileBytes;     // one LDS slot: a K tile, then the V tile of the same keys
-constexpr int kSlots = 6;                      // ring of three stages of two tiles
-constexpr uint64_t kAll63 = 0x7fffffffffffffffull;
-constexpr float kRescaleThreshold = 8.0f;      // log2 units: stale maxima up to 2^8 are tolerated
+namespace vs {
 
 struct AttnParams {
     const uint16_t* q;
@@ -58,8 +38,35 @@ struct AttnParams {
     const int32_t* vfirst;          // per head: position of the first non-negative entry of the column list
     unsigned long long* tile_counter;
     unsigned int* work_counter;     // persistent launch: next unit of every KV head's queue (zero at launch); null: one unit per workgroup
+    int work_stride;                // counters of consecutive KV heads are this many words apart
     int work_total;                 // units of work (query tiles x KV heads x head chunks)
 };
+
+}  // namespace vs
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4t __attribute__((__vector_size__(4 * sizeof(__bf16))));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kD = 128;
+// A tile is staged with loads that write LDS directly: one wavefront instruction deposits its 64 16-byte pieces
+// back to back, which makes 4 rows of 256 B a contiguous 1 KB group.  Groups are 64 B apart and the pieces are rotated
+// inside a group so that fragment reads spread over all banks:
+//   K (16-byte reads, 16 rows at one chunk c): chunk c of row r sits at 64 (c / 4) + 16 ((c + r) % 4) of its row
+//   V (transposing reads, 4 rows x 64 B):      byte x of row r sits at 64 ((x / 64 + r) % 4) + x % 64 of its row
+constexpr int kGroupBytes = 4 * 256 + 64;      // four rows and the gap to the next group
+constexpr int kTileBytes = 8 * kGroupBytes;    // one 32-key tile of K or V
+constexpr int kSlotBytes = 2 * kTileBytes;     // one LDS slot: a K tile, then the V tile of the same keys
+constexpr int kSlots = 6;                      // ring of three stages of two tiles
+constexpr uint64_t kAll63 = 0x7fffffffffffffffull;
+constexpr float kRescaleThreshold = 8.0f;      // log2 units: stale maxima up to 2^8 are tolerated
+
+using vs::AttnParams;
 
 __device__ __forceinline__ float half_swap_max(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -107,6 +114,42 @@ __device__ __forceinline__ void mask_elements(f32x16& acc, uint32_t keep, uint32
     acc[4 * A + 2] = __uint_as_float((m2 & __float_as_uint(acc[4 * A + 2])) | (~m2 & dead_bits));
     acc[4 * A + 3] = __uint_as_float((m3 & __float_as_uint(acc[4 * A + 3])) | (~m3 & dead_bits));
     if constexpr (A + 1 < 4) mask_elements<A + 1>(acc, keep, dead_bits);
+}
+
+// Tile record of a listed key block b for one 32-row sub-block whose first position is sub_i0; w: the offset window prepared
+// with the diagonal list; xw: the block's column word; n_pos: positions that exist.
+//   x, y: 64-bit window wz; lane (q, h) keeps key kj iff bit 31 + q - kj of wz is set and bit kj of kw (word z) is:
+//         element-exact mode: wz = selected offsets dlt-31 .. dlt+31, kw = columns not listed
+//         tile-granular mode: wz = causal offsets, kw = keys that some row of the block reaches through a selected
+//         offset, listed columns taken out
+//   w: bit 0 live, bit 1 a mask is needed, bits 2..: the key block (so that one word per tile tells a step all it
+//      needs for the staging loads and the tests; the rest is read only where a mask is applied)
+__device__ __forceinline__ uint4 tile_record(int gran, int n_pos, int sub_i0, int b, uint64_t w, uint32_t xw) {
+    const int dlt = sub_i0 - 32 * b;                         // offset of (row 0, key 0) of the 32x32 tile
+    uint64_t wz = w;
+    uint32_t kw = ~xw;
+    bool live = w != 0ull, need = w != kAll63 || xw != 0u;
+    if (gran == 32) {
+        // Tile-granular slash: key kj is kept for every causal row of this 32-row block if ANY of its rows reaches it
+        // through a selected offset, i.e. if the window has a bit in [31 - kj, 62 - kj].
+        // x bit s = OR of window bits s .. s+len-1, len = rows of this block that exist (32 except at the end of
+        // the sequence): doubling up to the largest power of two pw <= len, then two overlapping windows
+        const int len = max(1, min(32, n_pos - sub_i0));
+        uint64_t x = w;
+        int pw = 1;
+        while (2 * pw <= len) {
+            x |= x >> pw;
+            pw *= 2;
+        }
+        x |= x >> (len - pw);
+        wz = dlt >= 31 ? kAll63 : (dlt < -31 ? 0ull : ((kAll63 << (31 - dlt)) & kAll63));   // offsets >= 0
+        kw = __builtin_bitreverse32(static_cast<uint32_t>(x)) & ~xw;
+        live = kw != 0u && wz != 0ull;
+        need = !(kw == 0xffffffffu && wz == kAll63);
+    }
+    if (dlt < -31 || sub_i0 >= n_pos) live = false;          // every key lies after every row / padding rows
+    return make_uint4(static_cast<uint32_t>(wz), static_cast<uint32_t>(wz >> 32), kw,
+                      (live ? 1u : 0u) | (need ? 2u : 0u) | (static_cast<uint32_t>(b) << 2));
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane L's piece lands at lds_base + 16 L (lds_base is
