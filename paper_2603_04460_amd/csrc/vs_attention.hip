@@ -68,6 +68,7 @@ constexpr size_t kGatherOff = kScratchOff + 128;
 constexpr size_t kLdsBytes = kGatherOff + kGatherCap * 4;
 static_assert(kLdsBytes <= kLdsBudget, "two workgroups per compute unit");
 static_assert(kGatherCap % 64 == 0, "whole stages");
+constexpr int kShortUnits = 128;               // units of four row blocks up to which vs_short.hip takes a call
 
 // (the second launch bound caps the registers at 256 per lane, i.e. two wavefronts per SIMD: without it the compiler
 // takes accumulation registers for its spills and only one workgroup fits a compute unit)
@@ -863,6 +864,12 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     p.group = q_heads / kv_heads;
     p.index_per_q = (index_heads == q_heads && q_heads != kv_heads) ? 1 : 0;
     p.hc = heads_per_workgroup(p.group, p.index_per_q != 0);
+    // Few row blocks and one query head per workgroup: the kernel that splits the keys of a row block over wavefronts.  One head,
+    // n = 16384 (128 units): 94 us here, 58 there; 32 heads with lists of their own, n = 4096 (1024 units): 243 here, 292
+    // there.  With several query heads in a workgroup a unit is 32 rows and this kernel has enough of them (8 KV heads,
+    // n = 1024: 52 us here, 74 there).
+    const bool few_rows = p.hc == 1 && static_cast<int64_t>(q_heads) * ((nq + 127) / 128) <= kShortUnits;
+    if (few_rows) p.hc = vs::short_heads(p.hc);
     p.gran = slash_granularity;
     p.n = static_cast<int>(n);
     p.nq = static_cast<int>(nq);
@@ -897,7 +904,7 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     pp.cnt_s = cnt_s;
     pp.cap_s = cap_s;
     pp.n = p.n;
-    pp.nsub = kWaves / p.hc;
+    pp.nsub = few_rows ? vs::short_subblocks(p.hc) : kWaves / p.hc;
     pp.nblk = w.nq32;
     pp.shift = static_cast<int>(pos0 % 32);
     pp.vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);
@@ -919,7 +926,7 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     if (prep_lds > 160 * 1024) return VS_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(vs_prepare_kernel, dim3(index_heads), dim3(kPrepThreads), prep_lds, st, pp);
     VS_LAUNCH_CHECK();
-    return launch_attention(p, st);
+    return few_rows ? vs::launch_short_sparse(p, st) : launch_attention(p, st);
 }
 
 }  // namespace

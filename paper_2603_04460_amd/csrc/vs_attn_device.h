@@ -42,6 +42,13 @@ struct AttnParams {
     int work_total;                 // units of work (query tiles x KV heads x head chunks)
 };
 
+// Attention for launches with few row blocks (vs_short.hip); p.hc and, for the sparse form, the prepared lists must be those
+// of short_heads() / short_subblocks().
+int launch_short_dense(AttnParams& p, hipStream_t stream);
+int launch_short_sparse(AttnParams& p, hipStream_t stream);
+inline int short_heads(int hc) { return hc >= 2 ? 2 : 1; }   // query heads a workgroup takes: its two row blocks
+inline int short_subblocks(int hc) { return 2 / short_heads(hc); }
+
 }  // namespace vs
 
 namespace {

@@ -1,0 +1,354 @@
+// Attention for launches with few row blocks (short sequences, short chunks of long ones, few heads), sparse and dense.
+//
+// The kernels of vs_attention.hip and vs_dense.hip give every row block of 32 query rows to one wavefront, which walks all
+// its keys: a chunk of 500 rows is 64 workgroups on 256 compute units, each as long as the context.  Here a row block's
+// tiles are dealt to four wavefronts.  A workgroup (8 wavefronts, two per SIMD, one workgroup per compute unit) owns two row
+// blocks (two query heads of the KV group, or 64 consecutive rows of one head); a stage is four 32-key tiles, wavefront
+// (s, rb) takes tile s of the stage for row block rb; two stages live in LDS.  At the end the four partial results of a
+// row block (maximum, sum, O) meet in LDS and every wavefront finishes a quarter of the 128 channels.  Arithmetic, tile
+// layout, records and gather lists are those of vs_attention.hip.
+//
+// Measured (8 KV / 32 query heads unless stated): dense, 500 rows against 32768 keys 727 -> 361 us; 1024 x 1024 32 -> 22 us; one
+// head, 16384 x 16384 364 -> 139 us; sparse, one head, n = 4096, 68 scattered columns and 190 offsets 106 -> 48 us.  A step (four
+// tiles, 64 KB staged) takes 1.07 us while few workgroups run: the chain barrier - fragment reads - scores - softmax - P V of
+// a single tile per wavefront; with a workgroup on every compute unit 1.46 us: only two row blocks use a staged tile, and
+// the L2 then delivers 11 TB/s.
+#include <hip/hip_runtime.h>
+#include <limits.h>
+#include <math.h>
+#include <stdint.h>
+
+#include <type_traits>
+
+#include "vs_attn_device.h"
+
+namespace {
+
+constexpr int kThreads = 512;
+constexpr int kRowBlocks = 2;
+constexpr int kSplits = 4;                     // wavefronts per row block = tiles per stage
+constexpr int kListCap = 256;                  // block list: kListCap / nsub entries per pass
+constexpr int kGatherCap = 2432;               // gather list entries per pass
+constexpr int kRecPad = 2 * kSplits;           // dead records after the last listed block (a step looks one stage ahead)
+constexpr size_t kRingBytes = 2 * kSplits * kSlotBytes;
+constexpr size_t kRecOff = kRingBytes;
+constexpr size_t kGatherOff = kRecOff + (kListCap + 2 * kRecPad) * 16;
+constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4;
+constexpr size_t kPartOff = 0;                 // after the last stage: O of the 8 wavefronts, 64 registers x 64 lanes each
+constexpr size_t kStatOff = 8 * 64 * 64 * 4;   // (maximum, sum) per wavefront and lane
+static_assert(kStatOff + 8 * 64 * 8 <= kRingBytes, "partial results in the idle ring");
+static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
+static_assert(kGatherCap % (32 * kSplits) == 0, "whole stages");
+
+template <bool DENSE>
+__global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char* const kvbuf = smem;
+    uint4* const list_rec = reinterpret_cast<uint4*>(smem + kRecOff);
+    int* const glist = reinterpret_cast<int*>(smem + kGatherOff);
+    const float NEG_INF = -INFINITY;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qi = lane & 31, hh = lane >> 5;
+    const int rb = wave % kRowBlocks, split = wave / kRowBlocks;
+    const int rest = blockIdx.x / p.kv_heads, g = blockIdx.x % p.kv_heads;
+    const int hchunks = p.group / p.hc;
+    const int hchunk = rest % hchunks;
+    const int tile = p.tiles - 1 - rest / hchunks;          // longest tiles first
+    const int nsub = kRowBlocks / p.hc, BQ = 32 * nsub;
+    const int i0 = p.pos0 + tile * BQ;                      // positions are absolute; the tile grid starts at the chunk
+    const int n = p.n, n_pos = p.pos0 + p.nq;
+    const int i_last = min(i0 + BQ, n_pos) - 1;
+    const int my_head = g * p.group + hchunk * p.hc + rb % p.hc;
+    const int my_sub = rb / p.hc;
+    const int my_i0 = i0 + 32 * my_sub;
+    const bool my_rows = my_i0 < n_pos;
+    const uint16_t* __restrict__ kbase = p.k + static_cast<size_t>(g) * n * kD;
+    const uint16_t* __restrict__ vbase = p.v + static_cast<size_t>(g) * n * kD;
+
+    // Q fragments: B operand of S^T = K Q^T; lane holds query qi, d = 16 kk + 8 hh .. +7
+    bf16x8 qf[8];
+    {
+        const int row = min(my_i0 + qi, n_pos - 1);          // rows that do not exist are not stored
+        const uint16_t* src = p.q + (static_cast<size_t>(my_head) * p.nq + (row - p.pos0)) * kD + 8 * hh;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * kk));
+    }
+    f32x16 oacc[4];
+    float m_run = NEG_INF, l_run = 0.f;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
+
+    // staging: wavefront w fills group w (rows 4 w + L / 16) of the K and of the V tile of every slot of the stage
+    const int st_row = tid >> 4;
+    const int st_rho = (lane >> 4) & 3;
+    const uint32_t st_bk = static_cast<uint32_t>(16 * (4 * ((lane >> 2) & 3) + (((lane & 3) - st_rho) & 3)));
+    const uint32_t st_bv = static_cast<uint32_t>(16 * (4 * ((((lane >> 2) & 3) - st_rho) & 3) + (lane & 3)));
+    auto load_tile = [&](int row, int slot) __attribute__((always_inline)) {
+        unsigned char* const dst = kvbuf + slot * kSlotBytes + wave * kGroupBytes;
+        const uint32_t off = static_cast<uint32_t>(min(row, n - 1)) << 8;      // rows that do not exist are masked
+        lds_load16s(off + st_bk, kbase, dst);
+        lds_load16s(off + st_bv, vbase, dst + kTileBytes);
+    };
+    // fragment addresses as in vs_attention.hip
+    const int li = lane & 15, dsel = (lane >> 4) & 1;
+    const int k_row = (qi >> 2) * kGroupBytes + (qi & 3) * 256;
+    const int k_off0 = k_row + 16 * ((hh + qi) & 3), k_off2 = k_row + 16 * ((hh + qi + 2) & 3);
+    const int v_rho = (li >> 2) & 3;
+    const int v_lane = kTileBytes + hh * kGroupBytes + v_rho * 256 + 32 * dsel + 8 * (li & 3);
+    int v_off[4];
+#pragma unroll
+    for (int sgr = 0; sgr < 4; ++sgr) v_off[sgr] = v_lane + 64 * ((sgr + v_rho) & 3);
+    typedef __attribute__((address_space(3))) bf16x4t* lds_ptr_t;
+
+    // One tile for this wavefront: slot in LDS; need: mask with the keep-bits (bit 27 - 8a - c of element 4a + c) that keep() gives.
+    auto compute = [&](int slot, bool need, auto keep) __attribute__((always_inline)) {
+        const unsigned char* const at = kvbuf + slot * kSlotBytes;
+        bf16x8 kf[8], vf[8];
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk)
+            kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(at + ((kk & 1) ? k_off2 : k_off0) + 64 * (kk >> 1)));
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 sa, sb;                                       // two chains of matrix instructions
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sa[e] = sb[e] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; kk += 2) {
+            sa = mfma32(kf[kk], qf[kk], sa);
+            sb = mfma32(kf[kk + 1], qf[kk + 1], sb);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {                        // j = 2 db + t16: d block db, keys 16 t16 ..
+            const unsigned char* a0 = at + v_off[j >> 1] + 4 * (j & 1) * kGroupBytes;
+            const bf16x4t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0));
+            const bf16x4t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0 + 2 * kGroupBytes));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                vf[j][e] = lo[e];
+                vf[j][4 + e] = hi[e];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sa[e] += sb[e];
+        if (need) mask_elements<0>(sa, keep(), __float_as_uint(NEG_INF));
+        float mx = fmaxf(fmaxf(sa[0], sa[1]), sa[2]);
+#pragma unroll
+        for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, sa[e]), sa[e + 1]);
+        const float m_new = fmaxf(m_run, half_swap_max(fmaxf(mx, sa[15])));
+        if (__ballot((m_new - m_run) * p.c > kRescaleThreshold)) {   // false when both are -inf
+            const float alpha = (m_new == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * p.c);
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+            l_run *= alpha;
+            m_run = m_new;
+        }
+        const float mc = (m_run == NEG_INF) ? 0.f : m_run * p.c;
+        bf16x8 pb[2];
+        float lsum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            const float x0 = __builtin_amdgcn_exp2f(fmaf(sa[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(sa[e + 1], p.c, -mc));
+            lsum[0] += x0;
+            lsum[1] += x1;
+            const f32x2 two = {x0, x1};
+            const bf16x2 r = __builtin_convertvector(two, bf16x2);
+            pb[e >> 3][e & 7] = r[0];
+            pb[e >> 3][(e & 7) + 1] = r[1];
+        }
+        l_run += lsum[0] + lsum[1];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int db = 0; db < 4; ++db) oacc[db] = mfma32(vf[2 * db + t], pb[t], oacc[db]);
+    };
+    // Pipeline over the stages of one phase: load(st, buf) requests the four tiles of stage st; step(st, slot) computes this
+    // wavefront's tile of stage st.  One barrier per step publishes stage st and frees the buffer of stage st - 1.
+    auto run_phase = [&](int ntiles, auto load, auto step) __attribute__((always_inline)) {
+        const int nst = (ntiles + kSplits - 1) / kSplits;
+        load(0, 0);
+        for (int st = 0; st < nst; ++st) {
+            __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's part of stage st has arrived
+            __syncthreads();
+            if (st + 1 < nst) load(st + 1, (st + 1) & 1);
+            step(st, kSplits * (st & 1) + split);
+        }
+        __syncthreads();                                     // the ring and the lists are reused
+    };
+    unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
+
+    if constexpr (DENSE) {
+        const int nblk = i_last / 32 + 1;
+        run_phase(
+            nblk,
+            [&](int st, int buf) __attribute__((always_inline)) {
+#pragma unroll
+                for (int u = 0; u < kSplits; ++u) load_tile(32 * (kSplits * st + u) + st_row, kSplits * buf + u);
+            },
+            [&](int st, int slot) __attribute__((always_inline)) {
+                const int dlt = my_i0 - 32 * (kSplits * st + split);          // offset of (row 0, key 0)
+                if (dlt < -31 || !my_rows) return;
+                compute(slot, dlt < 31, [&]() __attribute__((always_inline)) {
+                    const uint64_t w = (kAll63 << (31 - dlt)) & kAll63;       // offsets >= 0
+                    return static_cast<uint32_t>(w >> (qi + 4 - 4 * hh));
+                });
+            });
+    } else {
+        const int ih = p.index_per_q ? my_head : g;
+        const uint32_t* __restrict__ vbit = p.vbit + static_cast<size_t>(ih) * p.vw;
+        const int32_t* __restrict__ iv = p.idx_v + static_cast<size_t>(ih) * p.cap_v;
+        const int32_t* __restrict__ ncol = p.ncol32 + static_cast<size_t>(ih) * p.nq32;
+        const int32_t* __restrict__ dl = p.dlist + static_cast<size_t>(ih) * p.dcap;
+        const unsigned long long* __restrict__ wl = p.wlist + static_cast<size_t>(ih) * p.dcap * 4;
+        const int qb0 = i0 >> 5;
+        const int ndiag = p.ndiag[static_cast<size_t>(ih) * p.nq32 + qb0];
+        const int ncand = ncol[i_last >> 5];
+        int cursor = min(p.vfirst[ih], ncand);
+        const int bcap = kListCap / nsub, rcap = bcap + kRecPad;
+        const uint4* const my_rec = list_rec + my_sub * rcap;
+        // 1. slash part: key blocks qb0 - delta in the order of the diagonal list, in rounds of bcap blocks
+        for (int rbase = 0; rbase < ndiag; rbase += bcap) {
+            const int count = min(bcap, ndiag - rbase);
+            if (tid < count) {
+                const int b = qb0 - dl[rbase + tid];
+                const uint32_t xw = vbit[b];
+                for (int r = 0; r < nsub; ++r)
+                    list_rec[r * rcap + tid] = tile_record(p.gran, n_pos, i0 + 32 * r, b, wl[static_cast<size_t>(rbase + tid) * 4 + r], xw);
+            } else if (tid < count + kRecPad) {
+                for (int r = 0; r < nsub; ++r) list_rec[r * rcap + tid] = make_uint4(0u, 0u, 0u, 0u);
+            }
+            __syncthreads();
+            staged_block += static_cast<unsigned int>(count);
+            run_phase(
+                count,
+                [&](int st, int buf) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int u = 0; u < kSplits; ++u)
+                        load_tile(32 * static_cast<int>(list_rec[kSplits * st + u].w >> 2) + st_row, kSplits * buf + u);
+                },
+                [&](int st, int slot) __attribute__((always_inline)) {
+                    const uint4* const rec = my_rec + kSplits * st + split;
+                    const uint32_t fl = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(rec->w));
+                    if (!(fl & 1u)) return;
+                    ++tiles_done;
+                    compute(slot, (fl & 2u) != 0u, [&]() __attribute__((always_inline)) {
+                        const uint4 r = *rec;                // one broadcast read
+                        const uint64_t wz = (static_cast<uint64_t>(r.y) << 32) | r.x;
+                        return static_cast<uint32_t>(wz >> (qi + 4 - 4 * hh)) & (__builtin_bitreverse32(r.z) >> (4 - 4 * hh));
+                    });
+                });
+        }
+        // 2. vertical part: the causal columns, gathered row by row, in rounds of kGatherCap
+        while (cursor < ncand) {
+            const int count = min(ncand - cursor, kGatherCap);
+            const int padded = (count + 32 * kSplits - 1) / (32 * kSplits) * (32 * kSplits);
+            for (int t = tid; t < padded; t += kThreads) glist[t] = t < count ? iv[cursor + t] : INT_MAX;
+            cursor += count;
+            __syncthreads();
+            const int ntiles = (count + 31) >> 5;
+            staged_gather += static_cast<unsigned int>(ntiles);
+            run_phase(
+                ntiles,
+                [&](int st, int buf) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int u = 0; u < kSplits; ++u) load_tile(glist[32 * (kSplits * st + u) + st_row], kSplits * buf + u);
+                },
+                [&](int st, int slot) __attribute__((always_inline)) {
+                    const int* const cols = glist + 32 * (kSplits * st + split);
+                    const int cmin = __builtin_amdgcn_readfirstlane(cols[0]), cmax = __builtin_amdgcn_readfirstlane(cols[31]);
+                    if (!my_rows || cmin > my_i0 + 31) return;               // ascending, INT_MAX padding
+                    ++tiles_done;
+                    compute(slot, cmax > my_i0, [&]() __attribute__((always_inline)) {
+                        uint32_t keep = 0u;                  // column <= row
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) {
+                            const int4 c4 = *reinterpret_cast<const int4*>(cols + 8 * a + 4 * hh);
+                            const int row = my_i0 + qi;
+                            keep |= (c4.x <= row ? 1u << (27 - 8 * a) : 0u) | (c4.y <= row ? 1u << (26 - 8 * a) : 0u) |
+                                    (c4.z <= row ? 1u << (25 - 8 * a) : 0u) | (c4.w <= row ? 1u << (24 - 8 * a) : 0u);
+                        }
+                        return keep;
+                    });
+                });
+        }
+    }
+
+    // ---- the four partial results of a row block meet (the ring is idle: every phase ends with a barrier) ----
+    float* const part = reinterpret_cast<float*>(smem + kPartOff);
+    float2* const stat = reinterpret_cast<float2*>(smem + kStatOff);
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) part[(wave * 64 + 16 * db + e) * 64 + lane] = oacc[db][e];
+    stat[wave * 64 + lane] = make_float2(m_run, half_swap_sum(l_run));
+    __syncthreads();
+    float m_tot = NEG_INF, l_tot = 0.f, f[kSplits];
+#pragma unroll
+    for (int s = 0; s < kSplits; ++s) m_tot = fmaxf(m_tot, stat[(kRowBlocks * s + rb) * 64 + lane].x);
+#pragma unroll
+    for (int s = 0; s < kSplits; ++s) {
+        const float2 x = stat[(kRowBlocks * s + rb) * 64 + lane];
+        f[s] = x.x == NEG_INF ? 0.f : __builtin_amdgcn_exp2f((x.x - m_tot) * p.c);
+        l_tot = fmaf(x.y, f[s], l_tot);
+    }
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const int row = my_i0 + qi;
+    if (row >= n_pos) return;
+    uint16_t* const dst = p.o + (static_cast<size_t>(my_head) * p.nq + (row - p.pos0)) * kD + 32 * split + 4 * hh;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < kSplits; ++s)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                x[c] = fmaf(part[((kRowBlocks * s + rb) * 64 + 16 * split + 4 * a + c) * 64 + lane], f[s], x[c]);
+        const f32x2 x01 = {x[0] * inv, x[1] * inv}, x23 = {x[2] * inv, x[3] * inv};
+        uint2 out;
+        out.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(x01, bf16x2));
+        out.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(x23, bf16x2));
+        *reinterpret_cast<uint2*>(dst + 8 * a) = out;
+    }
+    if (p.lse && split == 0 && hh == 0)
+        p.lse[static_cast<size_t>(my_head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_tot * p.scale + __logf(l_tot) : NEG_INF;
+    if constexpr (!DENSE) {
+        if (p.tile_counter && lane == 0 && tiles_done) atomicAdd(p.tile_counter, static_cast<unsigned long long>(tiles_done));
+        if (p.tile_counter && tid == 0) {
+            if (staged_gather) atomicAdd(p.tile_counter + 1, static_cast<unsigned long long>(staged_gather));
+            if (staged_block) atomicAdd(p.tile_counter + 2, static_cast<unsigned long long>(staged_block));
+        }
+    }
+}
+
+template <bool DENSE>
+int launch_short(AttnParams& p, hipStream_t stream) {
+    static vs::PerDeviceOnce once;
+    const size_t lds = DENSE ? kRingBytes : kSparseLds;
+    const int rc = once.run(nullptr, [lds](int) -> int {
+        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vs_short_kernel<DENSE>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   static_cast<int>(lds)));
+        return VS_OK;
+    });
+    if (rc != VS_OK) return rc;
+    const int BQ = 32 * (kRowBlocks / p.hc);
+    p.tiles = (p.nq + BQ - 1) / BQ;
+    // KV head = block % kv_heads: workgroups are dealt to the 8 XCDs round-robin, so a head's K / V stay in one XCD's L2
+    const long long blocks = static_cast<long long>(p.kv_heads) * (p.group / p.hc) * p.tiles;
+    if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
+    hipLaunchKernelGGL(vs_short_kernel<DENSE>, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, stream, p);
+    VS_LAUNCH_CHECK();
+    return VS_OK;
+}
+
+}  // namespace
+
+namespace vs {
+int launch_short_dense(AttnParams& p, hipStream_t stream) { return launch_short<true>(p, stream); }
+int launch_short_sparse(AttnParams& p, hipStream_t stream) { return launch_short<false>(p, stream); }
+}  // namespace vs

@@ -1,0 +1,77 @@
+"""GPU parity of the attention kernel for launches with few row blocks (vs_short.hip: the keys of a row block split over four
+wavefronts): sparse calls of up to 128 four-block units with one query head per workgroup, dense calls of up to 128
+workgroups.  Bars as everywhere: exact kept-key sets (gpu_util.check_key_set), 2e-2 on bf16 outputs, 2e-3 on the LSE."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_04460_amd as vs
+import synth
+from gpu_util import make_qkv, lists, run_sparse, run_dense, check_attention, check_key_set
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("gran", [None, 32])
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 65, 127, 129, 513])
+def test_sparse_tile_edges(n, gran):
+    """Fewer tiles than wavefronts, ragged last tiles and stages, row blocks that do not exist."""
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(600 + n, 1, 1, n)
+    iv, cv = lists([rng.choice(n, size=max(1, n // 3), replace=False)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=max(1, n // 9), replace=False)]))])
+    check_key_set(k, iv, cv, is_, cs, 1, np.arange(n), granularity=gran)
+    o, lse, _ = run_sparse(q, k, v, iv, cv, is_, cs, granularity=gran)
+    ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, granularity=gran or 1)
+    check_attention(o, lse, ref_o, ref_lse)
+
+
+def test_sparse_several_rounds():
+    """One head, n = 16384 (128 units, the last size of the rule): scattered offsets list all 512 key blocks (rounds of 128), and
+    5000 columns take several gather rounds (2432 each)."""
+    n = 16384
+    rng = np.random.default_rng(3)
+    (q, k, v), (qb, kb, vb) = make_qkv(61, 1, 1, n)
+    iv, cv = lists([rng.choice(n, size=5000, replace=False)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=1500, replace=False)]))])
+    rows = synth.sample_rows(3, n, 40, 72, 48)
+    check_key_set(k, iv, cv, is_, cs, 1, rows)
+    o, lse, _ = run_sparse(q, k, v, iv, cv, is_, cs)
+    ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, rows=rows)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+def test_sparse_rows_without_keys():
+    """Columns after every row and no offsets: zeros and -inf, from all four partial results."""
+    n = 200
+    (q, k, v), _ = make_qkv(62, 1, 1, n)
+    iv, cv = lists([[150, 199]])
+    is_, cs = np.zeros((1, 1), np.int32), np.zeros(1, np.int32)
+    o, lse, _ = run_sparse(q, k, v, iv, cv, is_, cs)
+    assert (o[0, :150] == 0).all() and torch.isneginf(lse[0, :150]).all() and torch.isfinite(lse[0, 150:]).all()
+    assert torch.allclose(o[0, 150:199].float(), v[0, 150].float().expand(49, 128), atol=1e-2)
+
+
+@pytest.mark.parametrize("hq,hk,n", [(1, 1, 1), (2, 1, 31), (3, 1, 33), (4, 1, 64), (8, 2, 129), (6, 3, 257)])
+def test_dense_tile_edges(hq, hk, n):
+    (q, k, v), (qb, kb, vb) = make_qkv(700 + n, hq, hk, n)
+    o, lse = run_dense(q, k, v)
+    ref_o, ref_lse = oracle.dense_attention(qb, kb, vb)
+    check_attention(o, lse, ref_o, ref_lse)
+
+
+@pytest.mark.parametrize("n_q", [1024, 1025])
+def test_dense_both_sides_of_the_line(n_q):
+    """32 / 8 heads: 1024 rows are 128 workgroups (this kernel), 1025 are 136 (vs_dense.hip)."""
+    hq, hk, n = 32, 8, 1100
+    (q, k, v), (qb, kb, vb) = make_qkv(63, hq, hk, n)
+    pos0 = n - n_q
+    qc = q[:, pos0:].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, k, v, o, lse, pos0=pos0)
+    torch.cuda.synchronize()
+    rows = synth.sample_rows(9, n_q, 40, 40, 40)
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:], kb, vb, pos0=pos0)
+    check_attention(o, lse, ref_o[:, rows], ref_lse[:, rows], rows=rows)
