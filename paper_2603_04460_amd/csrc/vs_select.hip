@@ -75,7 +75,13 @@ struct Pick {
     bool none;
 };
 
+// Keys of one lane.  J > 0: the problem has at most J * kSelThreads scores; every lane reads its J keys once and keeps them in
+// registers through all passes (five sweeps over memory with one load in flight each were half of the kernel's time at
+// n = 4096).  J == 0: any length, scores are read again in every pass.
+constexpr int kSelRegs[2] = {4, 16};           // the J that are built (32 do not fit the registers of 16 wavefronts)
+
 // redo: null, or per problem (head * 2 + dir) non-zero where this kernel has work
+template <int J>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, const int32_t* redo) {
     __shared__ SelShared sh;
     const int head = blockIdx.x, dir = blockIdx.y;
@@ -87,6 +93,47 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
     const int cap = p.cap[dir];
     int st = 0;
     if (tid == 0) sh.status = 0;
+    // each wavefront owns a contiguous range of scores
+    const int per_wave = ((n + kWaves - 1) / kWaves + 63) & ~63;
+    const int w_lo = min(wave * per_wave, n), w_hi = min(w_lo + per_wave, n);
+    uint32_t keys[J > 0 ? J : 1];
+    if constexpr (J > 0) {
+        float x[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) x[j] = w_lo + 64 * j < w_hi ? a[min(w_lo + 64 * j + lane, n - 1)] : 0.f;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            int bits = 0;
+            keys[j] = score_key(x[j], bits);
+            if (w_lo + 64 * j + lane < w_hi) st |= bits;
+        }
+    }
+    // f(index, key, exists) for the lane's scores in ascending order, all lanes of the wavefront together
+    auto each = [&](auto f) __attribute__((always_inline)) {
+        if constexpr (J > 0) {
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int i = w_lo + 64 * j + lane;
+                if (w_lo + 64 * j < w_hi) f(i, keys[j], i < w_hi);
+            }
+        } else {
+            constexpr int kBatch = 4;                        // loads in flight
+            for (int base = w_lo; base < w_hi; base += 64 * kBatch) {
+                float x[kBatch];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) x[j] = a[min(base + 64 * j + lane, n - 1)];
+#pragma unroll
+                for (int j = 0; j < kBatch; ++j) {
+                    const int i = base + 64 * j + lane;
+                    if (base + 64 * j >= w_hi) break;
+                    int bits = 0;
+                    const uint32_t key = score_key(x[j], bits);
+                    if (i < w_hi) st |= bits;
+                    f(i, key, i < w_hi);
+                }
+            }
+        }
+    };
 
     // radix descent.  by_count: rank target is a count (krem) instead of a mass (trem).  tau >= 0 (first descent of the
     // threshold rule): the first pass sees every element, so its histogram also gives the total mass; the target
@@ -109,16 +156,15 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
             }
             __syncthreads();
             const bool collect = first && pass == 0;
-            for (int i = tid; i < n; i += kSelThreads) {
-                if (skip_forced && i < nforced) continue;
+            each([&](int i, uint32_t key, bool exists) __attribute__((always_inline)) {
+                if (!exists || (skip_forced && i < nforced)) return;
+                if ((key & pmask) != prefix) return;
                 int dummy = 0;
-                const uint32_t key = score_key(a[i], collect ? st : dummy);
-                if ((key & pmask) != prefix) continue;
                 const uint32_t b = (key >> shf) & (nb - 1);
                 atomicAdd(&sh.hist_cnt[b], 1u);
                 if (!by_count) atomicAdd(&sh.hist_mass[b], key_mass(key, collect ? st : dummy));
                 else if (collect) (void)key_mass(key, st);
-            }
+            });
             __syncthreads();
             // buckets in descending order; thread owns `per` consecutive ones
             const int per = nb >= kSelThreads ? nb / kSelThreads : 1;
@@ -214,48 +260,40 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
         return pk;
     };
 
-    // ---- total mass, threshold ----
-    Pick pk;
-    if (p.mode == 0) {
-        pk = descend(false, false, 0, 0u, p.tau[dir], true);
-    } else {
-        const uint32_t kfix = static_cast<uint32_t>(min(p.kfix[dir], n));
-        if (kfix == 0) {                                     // nothing ranked in: the status bits still need their sweep
-            for (int i = tid; i < n; i += kSelThreads) {
-                const uint32_t key = score_key(a[i], st);
-                (void)key_mass(key, st);
-            }
-        }
-        pk = descend(true, false, 0, kfix, -1.0, true);
+    bool by_count = p.mode != 0;
+    const uint32_t kfix = static_cast<uint32_t>(min(p.kfix[dir], n));
+    if (by_count && kfix == 0) {                             // nothing ranked in: the status bits still need their sweep
+        each([&](int, uint32_t key, bool exists) __attribute__((always_inline)) {
+            if (exists) (void)key_mass(key, st);
+        });
     }
+    uint32_t krem = by_count ? kfix : 0u;
 
-    // ---- ordered emission: each wavefront owns a contiguous range, ranks come from ballots ----
-    const int per_wave = ((n + kWaves - 1) / kWaves + 63) & ~63;
-    const int w_lo = min(wave * per_wave, n), w_hi = min(w_lo + per_wave, n);
+    // ---- ordered emission: ranks come from ballots ----
     const u64 lt_mask = (1ull << lane) - 1ull;
     int32_t* __restrict__ out = p.idx[dir] + static_cast<size_t>(head) * cap;
 
     bool skip_forced = false;
+    // (one call of descend in the program: its sweeps over the register keys are unrolled)
     for (int attempt = 0; attempt < 2; ++attempt) {
+        const Pick pk = descend(by_count, skip_forced, 0, krem, by_count ? -1.0 : p.tau[dir], attempt == 0);
         // sweep 1: per wavefront, the ties, the ties among the forced entries, and the entries that are in whatever the
         // ties decide (forced, or ranked above the crossing value).  Ties are taken in index order and the forced entries
         // are the lowest indices, so the number of selected entries of a wavefront follows from these three counts.
         uint32_t eqc = 0, eqf = 0, inc = 0;
-        for (int base = w_lo; base < w_hi; base += 64) {
-            const int i = base + lane;
-            bool eq = false, in = false, forced = false;
-            if (i < w_hi) {
-                int dummy = 0;
-                const uint32_t key = score_key(a[i], dummy);
-                forced = i < nforced;
-                const bool ranked = !pk.none && !(skip_forced && forced);
-                eq = ranked && key == pk.vstar;
-                in = forced || (ranked && key > pk.vstar);
-            }
+        auto classify = [&](int i, uint32_t key, bool exists, bool& eq, bool& in, bool& forced) __attribute__((always_inline)) {
+            forced = exists && i < nforced;
+            const bool ranked = exists && !pk.none && !(skip_forced && forced);
+            eq = ranked && key == pk.vstar;
+            in = forced || (ranked && key > pk.vstar);
+        };
+        each([&](int i, uint32_t key, bool exists) __attribute__((always_inline)) {
+            bool eq, in, forced;
+            classify(i, key, exists, eq, in, forced);
             eqc += __popcll(__ballot(eq));
             eqf += __popcll(__ballot(eq && forced));
             inc += __popcll(__ballot(in));
-        }
+        });
         if (lane == 0) {
             sh.wave_eq[wave] = eqc;
             sh.wave_eqf[wave] = eqf;
@@ -277,37 +315,26 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
             }
         }
         __syncthreads();
-        auto selected = [&](int i, uint32_t& tie_run) -> bool {
-            bool in = false, eq = false;
-            if (i < w_hi) {
-                const bool forced = i < nforced;
-                int dummy = 0;
-                const uint32_t key = score_key(a[i], dummy);
-                const bool ranked = !pk.none && !(skip_forced && forced);
-                eq = ranked && key == pk.vstar;
-                in = forced || (ranked && key > pk.vstar);
-            }
-            const u64 eb = __ballot(eq);
-            if (eq && tie_run + __popcll(eb & lt_mask) < pk.ties) in = true;
-            tie_run += __popcll(eb);
-            return in;
-        };
-        uint32_t tie_run = tie_base;
         if (total > static_cast<uint32_t>(cap) && attempt == 0) {
             // keep the forced entries and the best-ranked others: count-ranked pick over the rest
             st |= VS_STATUS_OVERFLOW;
             skip_forced = true;
-            pk = descend(true, true, 0, static_cast<uint32_t>(cap - nforced), -1.0, false);
+            by_count = true;
+            krem = static_cast<uint32_t>(cap - nforced);
             continue;
         }
         // sweep 2: write
-        tie_run = tie_base;
-        for (int base = w_lo; base < w_hi; base += 64) {
-            const bool in = selected(base + lane, tie_run);
+        uint32_t tie_run = tie_base;
+        each([&](int i, uint32_t key, bool exists) __attribute__((always_inline)) {
+            bool eq, in, forced;
+            classify(i, key, exists, eq, in, forced);
+            const u64 eb = __ballot(eq);
+            if (eq && tie_run + __popcll(eb & lt_mask) < pk.ties) in = true;
+            tie_run += __popcll(eb);
             const u64 sb = __ballot(in);
-            if (in) out[pos + __popcll(sb & lt_mask)] = base + lane;
+            if (in) out[pos + __popcll(sb & lt_mask)] = i;
             pos += __popcll(sb);
-        }
+        });
         if (tid == 0) p.cnt[dir][head] = static_cast<int32_t>(total);
         break;
     }
@@ -320,6 +347,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
 constexpr int kChunk = 8192;                   // scores per workgroup
 constexpr int kChunkThreads = 512;
 constexpr int kChunkWaves = kChunkThreads / 64;
+constexpr int kChunkRegs = kChunk / kChunkThreads;   // scores per thread: all requested at the top of a kernel, before its scan
 constexpr int kMinSplitN = 32768;              // shorter problems stay with one workgroup (fewer launches)
 
 // descent state of one problem after a pass (written by the workgroup of chunk 0, read by the next kernel)
@@ -463,6 +491,9 @@ __global__ __launch_bounds__(kChunkThreads) void split_pass_kernel(const SplitPa
     constexpr int shifts[3] = {20, 8, 0};
     constexpr int nbs[3] = {4096, 4096, 256};
 
+    float x[kChunkRegs];
+#pragma unroll
+    for (int j = 0; j < kChunkRegs; ++j) x[j] = a[min(lo + j * kChunkThreads + tid, n - 1)];
     SelState st{};
     if (PASS == 1) {
         st.krem = static_cast<uint32_t>(min(p.kfix[dir], n));
@@ -497,9 +528,11 @@ __global__ __launch_bounds__(kChunkThreads) void split_pass_kernel(const SplitPa
         }
         __syncthreads();
         int stbits = 0, matched = 0;
-        for (int i = lo + tid; i < hi; i += kChunkThreads) {
+#pragma unroll
+        for (int j = 0; j < kChunkRegs; ++j) {
+            if (lo + j * kChunkThreads + tid >= hi) continue;
             int dummy = 0;
-            const uint32_t key = score_key(a[i], PASS == 0 ? stbits : dummy);
+            const uint32_t key = score_key(x[j], PASS == 0 ? stbits : dummy);
             if ((key & st.pmask) != st.prefix) continue;
             matched = 1;
             const uint32_t b = (key >> shf) & (nb - 1);
@@ -525,9 +558,12 @@ __global__ __launch_bounds__(kChunkThreads) void split_pass_kernel(const SplitPa
         __syncthreads();
         const int nforced = min(p.nforced[dir], n);
         uint32_t inc = 0, eqc = 0, eqf = 0;
-        for (int i = lo + tid; i < hi; i += kChunkThreads) {
+#pragma unroll
+        for (int j = 0; j < kChunkRegs; ++j) {
+            const int i = lo + j * kChunkThreads + tid;
+            if (i >= hi) continue;
             int dummy = 0;
-            const uint32_t key = score_key(a[i], dummy);
+            const uint32_t key = score_key(x[j], dummy);
             const bool forced = i < nforced;
             const bool ranked = !st.none;
             const bool eq = ranked && key == st.vstar;
@@ -564,6 +600,12 @@ __global__ __launch_bounds__(kChunkThreads) void split_emit_kernel(const SplitPa
     const float* __restrict__ a = p.a[dir] + static_cast<size_t>(head) * n;
     const int nforced = min(p.nforced[dir], n);
     const int cap = p.cap[dir];
+    const int lo = chunk * kChunk, hi = min(lo + kChunk, n);
+    constexpr int per_wave = kChunk / kChunkWaves;
+    const int w_lo = min(lo + wave * per_wave, hi), w_hi = min(w_lo + per_wave, hi);
+    float x[per_wave / 64];
+#pragma unroll
+    for (int j = 0; j < per_wave / 64; ++j) x[j] = a[min(w_lo + 64 * j + lane, n - 1)];
     const SelState st = q.state[pr * 4 + 3];
     if (tid < q.chunks) {
         const uint32_t* c = q.chunk_cnt + (static_cast<size_t>(pr) * q.chunks + tid) * 3;
@@ -587,15 +629,13 @@ __global__ __launch_bounds__(kChunkThreads) void split_emit_kernel(const SplitPa
         return;
     }
     if (chunk == 0 && tid == 0) p.cnt[dir][head] = static_cast<int32_t>(total);
-    const int lo = chunk * kChunk, hi = min(lo + kChunk, n);
-    const int per_wave = kChunk / kChunkWaves;
-    const int w_lo = min(lo + wave * per_wave, hi), w_hi = min(w_lo + per_wave, hi);
     const u64 lt_mask = (1ull << lane) - 1ull;
-    auto classify = [&](int i, bool& eq, bool& in, bool& forced) {
+    auto classify = [&](int j, bool& eq, bool& in, bool& forced) __attribute__((always_inline)) {
         eq = in = forced = false;
+        const int i = w_lo + 64 * j + lane;
         if (i < w_hi) {
             int dummy = 0;
-            const uint32_t key = score_key(a[i], dummy);
+            const uint32_t key = score_key(x[j], dummy);
             forced = i < nforced;
             const bool ranked = !st.none;
             eq = ranked && key == st.vstar;
@@ -603,9 +643,10 @@ __global__ __launch_bounds__(kChunkThreads) void split_emit_kernel(const SplitPa
         }
     };
     uint32_t eqc = 0, eqf = 0, inc = 0;
-    for (int base = w_lo; base < w_hi; base += 64) {
+#pragma unroll
+    for (int j = 0; j < per_wave / 64; ++j) {
         bool eq, in, forced;
-        classify(base + lane, eq, in, forced);
+        classify(j, eq, in, forced);
         eqc += __popcll(__ballot(eq));
         eqf += __popcll(__ballot(eq && forced));
         inc += __popcll(__ballot(in));
@@ -625,14 +666,15 @@ __global__ __launch_bounds__(kChunkThreads) void split_emit_kernel(const SplitPa
     }
     int32_t* __restrict__ out = p.idx[dir] + static_cast<size_t>(head) * cap;
     uint32_t tie_run = tb;
-    for (int base = w_lo; base < w_hi; base += 64) {
+#pragma unroll
+    for (int j = 0; j < per_wave / 64; ++j) {
         bool eq, in, forced;
-        classify(base + lane, eq, in, forced);
+        classify(j, eq, in, forced);
         const u64 eb = __ballot(eq);
         if (eq && tie_run + __popcll(eb & lt_mask) < st.ties) in = true;
         tie_run += __popcll(eb);
         const u64 sb = __ballot(in);
-        if (in) out[pos + __popcll(sb & lt_mask)] = base + lane;
+        if (in) out[pos + __popcll(sb & lt_mask)] = w_lo + 64 * j + lane;
         pos += __popcll(sb);
     }
 }
@@ -675,6 +717,13 @@ SplitLayout split_layout(int heads, int64_t n) {
 __global__ void zero_status_kernel(int32_t* status, int heads) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < heads) status[i] = 0;
+}
+
+void launch_select(const SelParams& p, int heads, const int32_t* redo, hipStream_t st) {
+    const dim3 grid(heads, 2), block(kSelThreads);
+    if (p.n <= kSelRegs[0] * kSelThreads) hipLaunchKernelGGL(select_kernel<kSelRegs[0]>, grid, block, 0, st, p, redo);
+    else if (p.n <= kSelRegs[1] * kSelThreads) hipLaunchKernelGGL(select_kernel<kSelRegs[1]>, grid, block, 0, st, p, redo);
+    else hipLaunchKernelGGL(select_kernel<0>, grid, block, 0, st, p, redo);
 }
 
 }  // namespace
@@ -751,7 +800,7 @@ int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, c
         VS_LAUNCH_CHECK();
         hipLaunchKernelGGL(split_emit_kernel, grid, dim3(kChunkThreads), 0, st, q);
         VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(select_kernel, dim3(heads, 2), dim3(kSelThreads), 0, st, p, static_cast<const int32_t*>(q.redo));
+        launch_select(p, heads, q.redo, st);
         VS_LAUNCH_CHECK();
         return VS_OK;
     }
@@ -759,7 +808,7 @@ int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, c
         hipLaunchKernelGGL(zero_status_kernel, dim3((heads + 255) / 256), dim3(256), 0, st, status, heads);
         VS_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(select_kernel, dim3(heads, 2), dim3(kSelThreads), 0, st, p, static_cast<const int32_t*>(nullptr));
+    launch_select(p, heads, nullptr, st);
     VS_LAUNCH_CHECK();
     return VS_OK;
 }
