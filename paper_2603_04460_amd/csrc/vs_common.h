@@ -12,8 +12,10 @@ void set_hip_error(hipError_t e);
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// The indexer's workspace starts with W_U split into two bf16 matrices [d_h, 256] (k contiguous): hi at byte 0, lo here.
-// The distillation step reads them from the forward pass's workspace.
+// vs_index_score; keep_split: also leaves W_U, split into two bf16 matrices [d_h, 256] (k contiguous), in the workspace: hi at
+// byte 0, lo at indexer_split_lo_offset.  The distillation step reads them there.
+int index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t n, const vs_indexer_t* w, float* a_v, float* a_s,
+                void* ws, size_t ws_bytes, void* stream, bool keep_split);
 inline size_t indexer_split_lo_offset(int d_h) { return round_up(static_cast<size_t>(d_h) * 256 * 2, 256); }
 
 // Per-device one-time set-up (kernel attributes, device facts) for entry points that may be called from several

@@ -47,22 +47,13 @@ constexpr size_t kVecOff = kXBufs * kXBytes;                            // b_U, 
 constexpr size_t kRedOff = kVecOff + 3 * kUnitsPerWg * 4;          // two parities x wavefronts x tokens x (v, s)
 constexpr size_t kSmemBytes = kRedOff + 2 * kWaves * kTokTile * 8;
 
-__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return static_cast<uint16_t>(u >> 16);
-}
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// W_U [256, d_h] fp32 -> hi, lo [d_h, 256] bf16 (k contiguous): w ~= hi + lo
-__global__ void split_weights_kernel(const float* __restrict__ W_U, int d_h, uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;   // over d_h * 256, u fastest for coalesced reads
-    if (i >= d_h * 256) return;
-    const int u = i % d_h, k = i / d_h;
-    const float w = W_U[static_cast<size_t>(k) * d_h + u];
-    const uint16_t h = f32_to_bf16_rne(w);
-    const float rem = w - __uint_as_float(static_cast<uint32_t>(h) << 16);
-    hi[static_cast<size_t>(u) * 256 + k] = h;
-    lo[static_cast<size_t>(u) * 256 + k] = f32_to_bf16_rne(rem);
+// two fp32 values -> bf16 (nearest even), the first in the low half
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    const f32x2 two = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane L's piece lands at lds_base + 16 L (lds_base is
@@ -111,8 +102,9 @@ struct IndexerParams {
     const uint16_t* kx;
     const uint16_t* vx;
     int heads, n, d_h;
-    const uint16_t* w_hi;
-    const uint16_t* w_lo;
+    const float* W_U;               // [256, d_h]
+    uint16_t* w_hi;                 // null, or where the split W_U is left: [d_h, 256] bf16 (k contiguous), w ~= hi + lo
+    uint16_t* w_lo;
     const float* b_U;
     const float* W_V;
     const float* W_S;
@@ -154,16 +146,6 @@ __global__ __launch_bounds__(kThreads) void indexer_logits_kernel(const IndexerP
         sWV[i] = ok ? p.W_V[u_base + i] : 0.f;
         sWS[i] = ok ? p.W_S[u_base + i] : 0.f;
     }
-    // W_U^T fragments of this wavefront's 32 units: A operand, lane = unit row, features 16 kk + 8 hh .. + 7
-    bf16x8 whi[16], wlo[16];
-    if (active) {
-        const size_t row = static_cast<size_t>(u_base + 32 * wave + col) * 256 + 8 * hh;
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            whi[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.w_hi + row + 16 * kk));
-            wlo[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p.w_lo + row + 16 * kk));
-        }
-    }
     float* const out_v = p.out_v + static_cast<size_t>(slice) * p.slice_stride;
     float* const out_s = p.out_s + static_cast<size_t>(slice) * p.slice_stride;
 
@@ -189,6 +171,35 @@ __global__ __launch_bounds__(kThreads) void indexer_logits_kernel(const IndexerP
     long long tile = tile_lane;
     const long long stride = p.lanes;
     if (tile < total_tiles) load_tile(tile, 0);
+    // W_U^T fragments of this wavefront's 32 units: A operand, lane = unit row, features 16 kk + 8 hh .. + 7; split into two bf16
+    // terms here (a kernel of its own, whose 2-byte stores lay 512 bytes apart, took 5 us per call)
+    bf16x8 whi[16], wlo[16];
+    if (active) {
+        const int unit = u_base + 32 * wave + col;
+        const float* const src = p.W_U + static_cast<size_t>(8 * hh) * p.d_h + unit;
+#pragma unroll
+        for (int kk = 0; kk < 16; ++kk) {
+            float w[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[j] = src[static_cast<size_t>(16 * kk + j) * p.d_h];
+            uint32_t h[4], l[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                h[j] = pack_bf16(w[2 * j], w[2 * j + 1]);
+                l[j] = pack_bf16(w[2 * j] - __uint_as_float(h[j] << 16), w[2 * j + 1] - __uint_as_float(h[j] & 0xffff0000u));
+            }
+            whi[kk] = __builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3]));
+            wlo[kk] = __builtin_bit_cast(bf16x8, make_uint4(l[0], l[1], l[2], l[3]));
+        }
+        if (p.w_hi && tile_lane == 0) {
+            const size_t row = static_cast<size_t>(unit) * 256 + 8 * hh;
+#pragma unroll
+            for (int kk = 0; kk < 16; ++kk) {
+                *reinterpret_cast<uint4*>(p.w_hi + row + 16 * kk) = __builtin_bit_cast(uint4, whi[kk]);
+                *reinterpret_cast<uint4*>(p.w_lo + row + 16 * kk) = __builtin_bit_cast(uint4, wlo[kk]);
+            }
+        }
+    }
     __builtin_amdgcn_s_waitcnt(0x0F70);                      // the first tile (and the weight fragments) have arrived
     __syncthreads();
     const int sw16 = (col & 15) << 4;                        // byte swizzle of this lane's token rows
@@ -488,6 +499,13 @@ size_t vs_index_score_workspace(int kv_heads, int64_t n, int d_h) {
 
 int vs_index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t n, const vs_indexer_t* w, float* a_v,
                    float* a_s, void* ws, size_t ws_bytes, void* stream) {
+    return vs::index_score(k_bf16, v_bf16, kv_heads, n, w, a_v, a_s, ws, ws_bytes, stream, false);
+}
+
+}  // extern "C"
+
+int vs::index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t n, const vs_indexer_t* w, float* a_v,
+                    float* a_s, void* ws, size_t ws_bytes, void* stream, bool keep_split) {
     if (!k_bf16 || !v_bf16 || !w || !a_v || !a_s) return VS_ERR_INVALID_ARG;
     if (!w->W_U || !w->b_U || !w->W_V || !w->W_S) return VS_ERR_INVALID_ARG;
     if (!vs::aligned16(k_bf16) || !vs::aligned16(v_bf16)) return VS_ERR_INVALID_ARG;
@@ -498,9 +516,6 @@ int vs_index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t
     if (!ws || ws_bytes < lay.total) return VS_ERR_WORKSPACE;
     if (!vs::aligned16(ws)) return VS_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    uint16_t* hi = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(ws) + lay.hi_off);
-    uint16_t* lo = reinterpret_cast<uint16_t*>(static_cast<unsigned char*>(ws) + lay.lo_off);
-
     static vs::PerDeviceOnce once;
     static int cus_of[vs::kMaxDevices];
     int dev = 0;
@@ -515,8 +530,6 @@ int vs_index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t
         return VS_OK;
     });
     if (rc_once != VS_OK) return rc_once;
-    hipLaunchKernelGGL(split_weights_kernel, dim3((w->d_h * 256 + 255) / 256), dim3(256), 0, st, w->W_U, w->d_h, hi, lo);
-    VS_LAUNCH_CHECK();
     unsigned char* base = static_cast<unsigned char*>(ws);
     float2* part = reinterpret_cast<float2*>(base + lay.part_off);
     IndexerParams p{};
@@ -525,8 +538,9 @@ int vs_index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t
     p.heads = kv_heads;
     p.n = static_cast<int>(n);
     p.d_h = w->d_h;
-    p.w_hi = hi;
-    p.w_lo = lo;
+    p.W_U = w->W_U;
+    p.w_hi = keep_split ? reinterpret_cast<uint16_t*>(base + lay.hi_off) : nullptr;
+    p.w_lo = keep_split ? reinterpret_cast<uint16_t*>(base + lay.lo_off) : nullptr;
     p.b_U = w->b_U;
     p.W_V = w->W_V;
     p.W_S = w->W_S;
@@ -569,5 +583,3 @@ int vs_index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t
     VS_LAUNCH_CHECK();
     return VS_OK;
 }
-
-}  // extern "C"

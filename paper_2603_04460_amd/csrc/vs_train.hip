@@ -521,8 +521,8 @@ int vs_index_train_step(const void* k_bf16, const void* v_bf16, int kv_heads, in
     float* g_s = reinterpret_cast<float*>(base + lay.gs_off);
     double* kl = reinterpret_cast<double*>(base + lay.kl_off);
 
-    // 1. forward (the inference kernels); its workspace starts with the split W_U, which the backward pass reads again
-    int rc = vs_index_score(k_bf16, v_bf16, kv_heads, n, w, p_v, p_s, base + lay.fwd_off, lay.fwd_bytes, stream);
+    // 1. forward (the inference kernels); it leaves the split W_U in its workspace for the backward pass
+    int rc = vs::index_score(k_bf16, v_bf16, kv_heads, n, w, p_v, p_s, base + lay.fwd_off, lay.fwd_bytes, stream, true);
     if (rc != VS_OK) return rc;
     const uint16_t* hi = reinterpret_cast<const uint16_t*>(base + lay.fwd_off);
     const uint16_t* lo = reinterpret_cast<const uint16_t*>(base + lay.fwd_off + vs::indexer_split_lo_offset(w->d_h));
