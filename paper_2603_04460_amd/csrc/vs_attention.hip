@@ -864,11 +864,14 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     p.group = q_heads / kv_heads;
     p.index_per_q = (index_heads == q_heads && q_heads != kv_heads) ? 1 : 0;
     p.hc = heads_per_workgroup(p.group, p.index_per_q != 0);
-    // Few row blocks and one query head per workgroup: the kernel that splits the keys of a row block over wavefronts.  One head,
-    // n = 16384 (128 units): 94 us here, 58 there; 32 heads with lists of their own, n = 4096 (1024 units): 243 here, 292
-    // there.  With several query heads in a workgroup a unit is 32 rows and this kernel has enough of them (8 KV heads,
-    // n = 1024: 52 us here, 74 there).
-    const bool few_rows = p.hc == 1 && static_cast<int64_t>(q_heads) * ((nq + 127) / 128) <= kShortUnits;
+    // Few row blocks: the kernel that splits the keys of a row block over wavefronts.
+    // One query head per workgroup (units of 128 rows): one head, n = 16384 (128 units) 94 us here, 58 there; 32 heads with lists of
+    // their own, n = 4096 (1024 units) 243 here, 292 there.
+    // Several query heads per workgroup (units of 32 or 64 rows): only a short chunk of a long sequence.  8 KV heads, 32768 keys,
+    // 256 rows (64 units) 72 us here, 56 there, 512 rows 78 and 76; whole sequences of 200 or 500 rows, whose units are
+    // few and small, 20 and 26 here, 25 and 42 there.
+    const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((nq * p.hc + 127) / 128);
+    const bool few_rows = p.hc == 1 ? units <= kShortUnits : units <= kShortUnits / 2 && n >= 8 * nq;
     if (few_rows) p.hc = vs::short_heads(p.hc);
     p.gran = slash_granularity;
     p.n = static_cast<int>(n);

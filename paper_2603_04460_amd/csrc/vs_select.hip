@@ -75,15 +75,17 @@ struct Pick {
     bool none;
 };
 
-// Keys of one lane.  J > 0: the problem has at most J * kSelThreads scores; every lane reads its J keys once and keeps them in
-// registers through all passes (five sweeps over memory with one load in flight each were half of the kernel's time at
-// n = 4096).  J == 0: any length, scores are read again in every pass.
-constexpr int kSelRegs[2] = {4, 16};           // the J that are built (32 do not fit the registers of 16 wavefronts)
+constexpr int kStageMax = 24576;               // keys that fit in LDS beside the histogram (96 KB + 49 KB)
+constexpr int kBatch = 4;                      // loads in flight per lane
 
+// STAGED: the problem's keys are read once, into LDS, and every pass sweeps that copy.  Otherwise (longer problems) the scores are
+// read again in every pass.  (Keys in registers were slower except at full ranges: their sweeps have to be unrolled, and a kernel
+// that runs once on 16 compute units waits for every new line of its code.)
 // redo: null, or per problem (head * 2 + dir) non-zero where this kernel has work
-template <int J>
+template <bool STAGED>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, const int32_t* redo) {
     __shared__ SelShared sh;
+    extern __shared__ uint32_t staged[];
     const int head = blockIdx.x, dir = blockIdx.y;
     if (redo && redo[head * 2 + dir] == 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -96,28 +98,25 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
     // each wavefront owns a contiguous range of scores
     const int per_wave = ((n + kWaves - 1) / kWaves + 63) & ~63;
     const int w_lo = min(wave * per_wave, n), w_hi = min(w_lo + per_wave, n);
-    uint32_t keys[J > 0 ? J : 1];
-    if constexpr (J > 0) {
-        float x[J];
+    if constexpr (STAGED) {
+        for (int base = tid; base < n; base += kBatch * kSelThreads) {
+            float x[kBatch];
 #pragma unroll
-        for (int j = 0; j < J; ++j) x[j] = w_lo + 64 * j < w_hi ? a[min(w_lo + 64 * j + lane, n - 1)] : 0.f;
+            for (int j = 0; j < kBatch; ++j) x[j] = a[min(base + j * kSelThreads, n - 1)];
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            int bits = 0;
-            keys[j] = score_key(x[j], bits);
-            if (w_lo + 64 * j + lane < w_hi) st |= bits;
+            for (int j = 0; j < kBatch; ++j)
+                if (base + j * kSelThreads < n) staged[base + j * kSelThreads] = score_key(x[j], st);
         }
+        __syncthreads();
     }
     // f(index, key, exists) for the lane's scores in ascending order, all lanes of the wavefront together
     auto each = [&](auto f) __attribute__((always_inline)) {
-        if constexpr (J > 0) {
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int i = w_lo + 64 * j + lane;
-                if (w_lo + 64 * j < w_hi) f(i, keys[j], i < w_hi);
+        if constexpr (STAGED) {
+            for (int base = w_lo; base < w_hi; base += 64) {
+                const int i = base + lane;
+                f(i, staged[min(i, n - 1)], i < w_hi);
             }
         } else {
-            constexpr int kBatch = 4;                        // loads in flight
             for (int base = w_lo; base < w_hi; base += 64 * kBatch) {
                 float x[kBatch];
 #pragma unroll
@@ -274,7 +273,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
     int32_t* __restrict__ out = p.idx[dir] + static_cast<size_t>(head) * cap;
 
     bool skip_forced = false;
-    // (one call of descend in the program: its sweeps over the register keys are unrolled)
+    // (one call of descend in the program: code is fetched once per call)
     for (int attempt = 0; attempt < 2; ++attempt) {
         const Pick pk = descend(by_count, skip_forced, 0, krem, by_count ? -1.0 : p.tau[dir], attempt == 0);
         // sweep 1: per wavefront, the ties, the ties among the forced entries, and the entries that are in whatever the
@@ -719,11 +718,19 @@ __global__ void zero_status_kernel(int32_t* status, int heads) {
     if (i < heads) status[i] = 0;
 }
 
-void launch_select(const SelParams& p, int heads, const int32_t* redo, hipStream_t st) {
+int launch_select(const SelParams& p, int heads, const int32_t* redo, hipStream_t st) {
+    static vs::PerDeviceOnce once;
+    const int rc = once.run(nullptr, [](int) -> int {
+        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   kStageMax * 4));
+        return VS_OK;
+    });
+    if (rc != VS_OK) return rc;
     const dim3 grid(heads, 2), block(kSelThreads);
-    if (p.n <= kSelRegs[0] * kSelThreads) hipLaunchKernelGGL(select_kernel<kSelRegs[0]>, grid, block, 0, st, p, redo);
-    else if (p.n <= kSelRegs[1] * kSelThreads) hipLaunchKernelGGL(select_kernel<kSelRegs[1]>, grid, block, 0, st, p, redo);
-    else hipLaunchKernelGGL(select_kernel<0>, grid, block, 0, st, p, redo);
+    if (p.n <= kStageMax) hipLaunchKernelGGL(select_kernel<true>, grid, block, static_cast<size_t>(p.n) * 4, st, p, redo);
+    else hipLaunchKernelGGL(select_kernel<false>, grid, block, 0, st, p, redo);
+    VS_LAUNCH_CHECK();
+    return VS_OK;
 }
 
 }  // namespace
@@ -800,17 +807,13 @@ int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, c
         VS_LAUNCH_CHECK();
         hipLaunchKernelGGL(split_emit_kernel, grid, dim3(kChunkThreads), 0, st, q);
         VS_LAUNCH_CHECK();
-        launch_select(p, heads, q.redo, st);
-        VS_LAUNCH_CHECK();
-        return VS_OK;
+        return launch_select(p, heads, q.redo, st);
     }
     if (status) {
         hipLaunchKernelGGL(zero_status_kernel, dim3((heads + 255) / 256), dim3(256), 0, st, status, heads);
         VS_LAUNCH_CHECK();
     }
-    launch_select(p, heads, nullptr, st);
-    VS_LAUNCH_CHECK();
-    return VS_OK;
+    return launch_select(p, heads, nullptr, st);
 }
 
 }  // extern "C"

@@ -75,3 +75,23 @@ def test_dense_both_sides_of_the_line(n_q):
     rows = synth.sample_rows(9, n_q, 40, 40, 40)
     ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:], kb, vb, pos0=pos0)
     check_attention(o, lse, ref_o[:, rows], ref_lse[:, rows], rows=rows)
+
+
+@pytest.mark.parametrize("hq,hk,n,n_q", [(32, 8, 2051, 256), (8, 2, 700, 33), (4, 2, 513, 1)])
+def test_sparse_short_chunk_of_a_group(hq, hk, n, n_q):
+    """Several query heads per workgroup: chunks of at most 64 units against at least 8 times as many keys."""
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(800 + n, hq, hk, n)
+    pos0 = n - n_q
+    iv, cv = lists([rng.choice(n, size=n // 10, replace=False) for _ in range(hk)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=60, replace=False)])) for _ in range(hk)])
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    qc = q[:, pos0:].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, hk, n), dtype=torch.uint8, device="cuda")
+    vs.sparse_prefill(qc, k, v, f(iv), f(cv), f(is_), f(cs), o, lse, ws, pos0=pos0)
+    torch.cuda.synchronize()
+    rows = np.arange(pos0, n)
+    ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, rows=rows)
+    check_attention(o, lse, ref_o, ref_lse)
