@@ -881,10 +881,11 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     // One query head per workgroup (units of 128 rows): one head, n = 16384 (128 units) 94 us here, 58 there; 32 heads with lists of
     // their own, n = 4096 (1024 units) 243 here, 292 there.
     // Several query heads per workgroup (units of 32 or 64 rows): only a short chunk of a long sequence.  8 KV heads, 32768 keys,
-    // 256 rows (64 units) 72 us here, 56 there, 512 rows 78 and 76; whole sequences of 200 or 500 rows, whose units are
-    // few and small, 20 and 26 here, 25 and 42 there.
+    // 256 rows (64 units) 72 us here, 56 there, 512 rows 78 and 76; 2 KV heads, 1024 rows (64 units) of 4096 keys 43 and 40.
+    // Where a unit has few tiles the merging costs more than it saves: 8 KV heads, 256 rows of 1024 keys 27 here, 31
+    // there; whole sequences of 200 or 500 rows 20 and 26 here, 25 and 42 there.
     const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((nq * p.hc + 127) / 128);
-    const bool few_rows = p.hc == 1 ? units <= kShortUnits : units <= kShortUnits / 2 && n >= 8 * nq;
+    const bool few_rows = p.hc == 1 ? units <= kShortUnits : units <= kShortUnits / 2 && n >= 4 * nq && n >= 2048;
     if (few_rows) p.hc = vs::short_heads(p.hc);
     p.gran = slash_granularity;
     p.n = static_cast<int>(n);
