@@ -75,6 +75,7 @@ struct SweepParams {
     const uint32_t* sbit;           // recall only; per index head: bit (o + 64) set iff offset o selected
     const uint32_t* vbit;           // recall only; per index head: bit j set iff column j selected
     int sw, vw, index_per_q;
+    int parts;                      // column sweep: workgroups that share the streamed rows of one group of resident rows
 };
 
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
@@ -94,7 +95,8 @@ __device__ __forceinline__ float row_move(float x) {
 }
 
 // COLUMNS == false: row sweep (resident queries, streamed keys).  COLUMNS == true: column sweep.
-template <bool COLUMNS, bool RECALL>
+// PARTS: p.parts workgroups share the streamed rows of a group (a form of its own: the long sweeps lose 2 % with it).
+template <bool COLUMNS, bool RECALL, bool PARTS = false>
 __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams p) {
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
     float* const norm_ring = reinterpret_cast<float*>(smem + kNormOff);
@@ -107,10 +109,11 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     const int n = p.n;
     const float NEG_INF = -INFINITY;
 
-    // ---- which 256 resident rows of which query head; longest sweeps first ----
+    // ---- which 256 resident rows of which query head (and which part of the streamed rows); longest sweeps first ----
     const int h = blockIdx.x % p.q_heads;
     const int ngroups = (n + kGroupRows - 1) / kGroupRows;
-    const int grp = COLUMNS ? blockIdx.x / p.q_heads : ngroups - 1 - blockIdx.x / p.q_heads;
+    const int unit = blockIdx.x / p.q_heads;
+    const int grp = COLUMNS ? (PARTS ? unit / p.parts : unit) : ngroups - 1 - unit;
     const int g = h / p.group;
     const int r0_wg = kGroupRows * grp;
     const int my_r0 = r0_wg + 64 * wave;                     // rows my_r0 .. + 31 (block 0) and my_r0 + 32 .. + 63 (block 1)
@@ -128,8 +131,18 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     }
 
     // ---- streamed tiles: keys 0 .. last resident row (rows), queries first resident row .. n-1 (columns) ----
-    const int t_begin = COLUMNS ? r0_wg >> 5 : 0;
-    const int t_end = COLUMNS ? (n + 31) >> 5 : (min(r0_wg + kGroupRows, n) + 31) >> 5;
+    int t_begin = COLUMNS ? r0_wg >> 5 : 0;
+    int t_end = COLUMNS ? (n + 31) >> 5 : (min(r0_wg + kGroupRows, n) + 31) >> 5;
+    int o_begin = 0;                                         // offset of the first streamed row to the first resident one
+    if (PARTS) {
+        // whole stages per part, as equal as they come; sums over the parts are made with the output's atomics
+        const int part = unit % p.parts, stages = (t_end - t_begin + 1) >> 1;
+        const int t0 = t_begin;
+        t_begin = t0 + 2 * static_cast<int>(static_cast<long long>(stages) * part / p.parts);
+        t_end = min(t_end, t0 + 2 * static_cast<int>(static_cast<long long>(stages) * (part + 1) / p.parts));
+        if (t_begin >= t_end) return;
+        o_begin = 32 * (t_begin - t0);
+    }
     const int nstages = (t_end - t_begin + 1) >> 1;
 
     if (COLUMNS) {
@@ -190,6 +203,10 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     const bool kh = (lane & 16) != 0;
     float d1_prev = 0.f;                                     // kh = 1: d1 of the previous tile's lanes of kh = 0
     uint64_t win_prev = 0ull;                                // block 0's window of the previous tile = block 1's of this one
+    if (PARTS && RECALL && t_begin > my_b0) {
+        const uint32_t* const at = sbit + (t_begin - my_b0);
+        win_prev = uniform64(((static_cast<uint64_t>(at[1]) << 32) | at[0]) >> 1);
+    }
 
     // diagonals of one 32 x 32 set of entries; base: first row - first key
     auto diagonals = [&](const f32x16& x, int base) __attribute__((always_inline)) {
@@ -335,7 +352,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         if (COLUMNS && st > 0) {
             // offsets below 64 st - 255 can no longer be touched: flush the 64 that became final with the last stage, 16 per
             // wavefront; a row of 16 lanes adds two rings
-            const int o = 64 * (st - 1) - (kGroupRows - 1) + 16 * wave + (lane & 15);
+            const int o = o_begin + 64 * (st - 1) - (kGroupRows - 1) + 16 * wave + (lane & 15);
             float* const at = diag + 2 * kDiagPitch * (lane >> 4) + (o & (kDiagRing - 1));
             float v = at[0] + at[kDiagPitch];
             at[0] = at[kDiagPitch] = 0.f;
@@ -368,7 +385,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             if (row < n && hh == 0) p.lse2[static_cast<size_t>(h) * n + row] = m2 + __log2f(l2);
         }
     } else {
-        if (my_r0 < n) {
+        if (my_r0 < n && (!PARTS || my_b0 < t_end)) {
             // block 0's entries of the last tile have no partner; what they leave in d1_prev has no next tile
             const int base = 32 * (t_end - 1) - my_r0;
             diagonals(pend, base);
@@ -378,7 +395,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         // what is still in the ring: the last 319 offsets the workgroup touched
         const int out_head = p.reduce_group ? g : h;
         for (int i = tid; i < kGroupRows + 64; i += kThreads) {
-            const int o = 64 * (nstages - 1) - (kGroupRows - 1) + i;
+            const int o = o_begin + 64 * (nstages - 1) - (kGroupRows - 1) + i;
             if (o >= 0 && o < n) {
                 float v = 0.f;
 #pragma unroll
@@ -391,7 +408,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             const float cs = half_swap_sum(col_sum[b]);
             const int key = my_r0 + 32 * b + qi;
             if (key < n && hh == 0) {
-                if (p.reduce_group) unsafeAtomicAdd(p.a_v + static_cast<size_t>(out_head) * n + key, cs);
+                if (PARTS || p.reduce_group) unsafeAtomicAdd(p.a_v + static_cast<size_t>(out_head) * n + key, cs);
                 else p.a_v[static_cast<size_t>(out_head) * n + key] = cs;
             }
         }
@@ -465,6 +482,7 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     unsigned char* base = static_cast<unsigned char*>(ws);
 
     SweepParams p{};
+    p.parts = 1;
     p.q = static_cast<const uint16_t*>(q);
     p.k = static_cast<const uint16_t*>(k);
     p.lse2 = reinterpret_cast<float*>(base + w.lse_off);
@@ -508,8 +526,21 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
         hipLaunchKernelGGL((vs_sweep_kernel<false, false>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
         VS_LAUNCH_CHECK();
     }
-    if (want_recall) hipLaunchKernelGGL((vs_sweep_kernel<true, true>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
-    else hipLaunchKernelGGL((vs_sweep_kernel<true, false>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
+    // Few groups of resident keys (a quarter of the 512 workgroups that run at once): their streamed queries are shared out over
+    // several workgroups of at least eight stages (16 tiles).  One head, n = 16000 809 -> 455 us for the call, 8 heads, n = 4000
+    // 222 -> 160, 32 heads, n = 1000 75 -> 60; at 256 and 512 groups the call was 2 and 5 % slower.
+    const int64_t max_parts = ((n + 63) / 64 + 7) / 8;
+    int64_t parts = blocks <= 128 ? 1024 / blocks : 1;
+    if (parts > max_parts) parts = max_parts;
+    p.parts = static_cast<int>(parts);
+    const dim3 grid(static_cast<unsigned>(blocks * parts));
+    if (parts > 1) {
+        if (want_recall) hipLaunchKernelGGL((vs_sweep_kernel<true, true, true>), grid, dim3(kThreads), 0, st, p);
+        else hipLaunchKernelGGL((vs_sweep_kernel<true, false, true>), grid, dim3(kThreads), 0, st, p);
+    } else {
+        if (want_recall) hipLaunchKernelGGL((vs_sweep_kernel<true, true>), grid, dim3(kThreads), 0, st, p);
+        else hipLaunchKernelGGL((vs_sweep_kernel<true, false>), grid, dim3(kThreads), 0, st, p);
+    }
     VS_LAUNCH_CHECK();
     return VS_OK;
 }
