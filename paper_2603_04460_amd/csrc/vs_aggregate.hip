@@ -96,7 +96,8 @@ __device__ __forceinline__ float row_move(float x) {
 
 // COLUMNS == false: row sweep (resident queries, streamed keys).  COLUMNS == true: column sweep.
 // PARTS: p.parts workgroups share the streamed rows of a group (a form of its own: the long sweeps lose 2 % with it).
-template <bool COLUMNS, bool RECALL, bool PARTS = false>
+// NB: resident blocks per wavefront; 1 (row sweep only) gives twice the workgroups of half the length when they are few.
+template <bool COLUMNS, bool RECALL, bool PARTS = false, int NB = 2>
 __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams p) {
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
     float* const norm_ring = reinterpret_cast<float*>(smem + kNormOff);
@@ -111,20 +112,22 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 
     // ---- which 256 resident rows of which query head (and which part of the streamed rows); longest sweeps first ----
     const int h = blockIdx.x % p.q_heads;
-    const int ngroups = (n + kGroupRows - 1) / kGroupRows;
+    static_assert(NB == 2 || !COLUMNS, "the diagonal sums need both blocks");
+    constexpr int kRows = 32 * NB * kWaves;                  // resident rows of this workgroup
+    const int ngroups = (n + kRows - 1) / kRows;
     const int unit = blockIdx.x / p.q_heads;
     const int grp = COLUMNS ? (PARTS ? unit / p.parts : unit) : ngroups - 1 - unit;
     const int g = h / p.group;
-    const int r0_wg = kGroupRows * grp;
-    const int my_r0 = r0_wg + 64 * wave;                     // rows my_r0 .. + 31 (block 0) and my_r0 + 32 .. + 63 (block 1)
+    const int r0_wg = kRows * grp;
+    const int my_r0 = r0_wg + 32 * NB * wave;                // rows my_r0 .. + 31 (block 0) and my_r0 + 32 .. + 63 (block 1)
     const int my_b0 = my_r0 >> 5;
     const uint16_t* __restrict__ res_base = COLUMNS ? p.k + static_cast<size_t>(g) * n * kD : p.q + static_cast<size_t>(h) * n * kD;
     const uint16_t* __restrict__ str_base = COLUMNS ? p.q + static_cast<size_t>(h) * n * kD : p.k + static_cast<size_t>(g) * n * kD;
 
     // ---- resident fragments: B operand; lane holds resident row qi, d = 16 kk + 8 hh .. +7 ----
-    bf16x8 rf[2][8];
+    bf16x8 rf[NB][8];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
+    for (int b = 0; b < NB; ++b) {
         const uint16_t* src = res_base + static_cast<size_t>(min(my_r0 + 32 * b + qi, n - 1)) * kD + 8 * hh;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) rf[b][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * kk));
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 
     // ---- streamed tiles: keys 0 .. last resident row (rows), queries first resident row .. n-1 (columns) ----
     int t_begin = COLUMNS ? r0_wg >> 5 : 0;
-    int t_end = COLUMNS ? (n + 31) >> 5 : (min(r0_wg + kGroupRows, n) + 31) >> 5;
+    int t_end = COLUMNS ? (n + 31) >> 5 : (min(r0_wg + kRows, n) + 31) >> 5;
     int o_begin = 0;                                         // offset of the first streamed row to the first resident one
     if (PARTS) {
         // whole stages per part, as equal as they come; sums over the parts are made with the output's atomics
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     auto tile = [&](int t, int slot, uint32_t w0, uint32_t w1, auto masked_tag) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         const unsigned char* const at = smem + slot * kTileBytes;
-        f32x16 acc[2];
+        f32x16 acc[NB];
         {
             bf16x8 af[8];
 #pragma unroll
@@ -243,14 +246,14 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
                 acc[0] = mfma32(af[kk], rf[0][kk], kk == 0 ? zero : acc[0]);
-                acc[1] = mfma32(af[kk], rf[1][kk], kk == 0 ? zero : acc[1]);
+                if constexpr (NB == 2) acc[1] = mfma32(af[kk], rf[1][kk], kk == 0 ? zero : acc[1]);
             }
         }
         const int s0 = 32 * t;                               // first streamed row of the tile
         if constexpr (!COLUMNS) {
             // keys s0 .. s0+31 against queries: causal where key <= query
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+            for (int b = 0; b < NB; ++b) {
                 f32x16& x = acc[b];
                 if constexpr (MASKED) {
                     const int lim = my_r0 + 32 * b + qi - s0 - 16 * hh;   // element e is causal iff e <= lim
@@ -328,7 +331,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     };
     auto tile_any = [&](int t, int slot, uint32_t w0, uint32_t w1) __attribute__((always_inline)) {
         // live if any of its entries is causal for one of the two blocks
-        const bool live = t < t_end && my_r0 < n && (COLUMNS ? t >= my_b0 : t <= my_b0 + 1);
+        const bool live = t < t_end && my_r0 < n && (COLUMNS ? t >= my_b0 : t <= my_b0 + NB - 1);
         if (!live) return;
         if (COLUMNS ? t <= my_b0 + 1 : t >= my_b0) tile(t, slot, w0, w1, std::true_type{});
         else tile(t, slot, w0, w1, std::false_type{});
@@ -371,7 +374,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     // ---- results ----
     if constexpr (!COLUMNS) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
+        for (int b = 0; b < NB; ++b) {
             // the two halves of the wavefront hold disjoint keys of the same query: merge (max, sum) pairs
             const auto mo = __builtin_amdgcn_permlane32_swap(__float_as_uint(m_run[b]), __float_as_uint(m_run[b]), false, false);
             const auto lo = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run[b]), __float_as_uint(l_run[b]), false, false);
@@ -523,7 +526,13 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     p.lse = lse ? lse : p.lse2;
     p.lse_scale = lse ? 1.4426950408889634f : 1.f;
     if (!lse) {
-        hipLaunchKernelGGL((vs_sweep_kernel<false, false>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
+        // few groups (see below): one block per wavefront; one head, n = 16000 421 -> 294 us for the call, 8 heads, n = 4000 161 -> 130
+        if (blocks <= 128) {
+            const int64_t halves = static_cast<int64_t>(q_heads) * ((n + kGroupRows / 2 - 1) / (kGroupRows / 2));
+            hipLaunchKernelGGL((vs_sweep_kernel<false, false, false, 1>), dim3(static_cast<unsigned>(halves)), dim3(kThreads), 0, st, p);
+        } else {
+            hipLaunchKernelGGL((vs_sweep_kernel<false, false>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
+        }
         VS_LAUNCH_CHECK();
     }
     // Few groups of resident keys (a quarter of the 512 workgroups that run at once): their streamed queries are shared out over

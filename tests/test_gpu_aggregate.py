@@ -89,6 +89,21 @@ def test_aggregate_tile_edges(n):
     assert np.abs(rec - ref_r).max() <= RECALL_ABS, (rec, ref_r)
 
 
+@pytest.mark.parametrize("hq,hk,n", [(32, 8, 1057), (16, 4, 2085)])
+def test_aggregate_many_groups(hq, hk, n):
+    """More than 128 groups of 256 resident rows: two blocks per wavefront in the row sweep, one workgroup per group in the
+    column sweep (fewer groups take the forms that share a group out)."""
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(520 + n, hq, hk, n, local=True)
+    iv, cv = lists([rng.choice(n, 40, replace=False) for _ in range(hk)])
+    is_, cs = lists([np.unique(np.concatenate([np.arange(20), rng.choice(n, 30, replace=False)])) for _ in range(hk)])
+    a_v, a_s, rec = _run(q, k, hq, mask=(iv, cv, is_, cs))
+    ref_v, ref_s, ref_r = _oracle(qb, kb, hq // hk, mask=(iv, cv, is_, cs))
+    _close(a_v, ref_v)
+    _close(a_s, ref_s)
+    assert np.abs(rec - ref_r).max() <= RECALL_ABS, (rec, ref_r)
+
+
 def test_aggregate_8192_one_head_elementwise():
     """n = 8192, one head: 32 resident-key workgroups, 128 streamed stages each, the 512-entry diagonal ring wraps 16
     times and every flush window is compared, element by element, together with the recall of a mask."""
