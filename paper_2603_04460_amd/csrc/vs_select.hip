@@ -75,17 +75,9 @@ struct Pick {
     bool none;
 };
 
-constexpr int kStageMax = 24576;               // keys that fit in LDS beside the histogram (96 KB + 49 KB)
-constexpr int kBatch = 4;                      // loads in flight per lane
-
-// STAGED: the problem's keys are read once, into LDS, and every pass sweeps that copy.  Otherwise (longer problems) the scores are
-// read again in every pass.  (Keys in registers were slower except at full ranges: their sweeps have to be unrolled, and a kernel
-// that runs once on 16 compute units waits for every new line of its code.)
 // redo: null, or per problem (head * 2 + dir) non-zero where this kernel has work
-template <bool STAGED>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, const int32_t* redo) {
     __shared__ SelShared sh;
-    extern __shared__ uint32_t staged[];
     const int head = blockIdx.x, dir = blockIdx.y;
     if (redo && redo[head * 2 + dir] == 0) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -95,44 +87,6 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
     const int cap = p.cap[dir];
     int st = 0;
     if (tid == 0) sh.status = 0;
-    // each wavefront owns a contiguous range of scores
-    const int per_wave = ((n + kWaves - 1) / kWaves + 63) & ~63;
-    const int w_lo = min(wave * per_wave, n), w_hi = min(w_lo + per_wave, n);
-    if constexpr (STAGED) {
-        for (int base = tid; base < n; base += kBatch * kSelThreads) {
-            float x[kBatch];
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j) x[j] = a[min(base + j * kSelThreads, n - 1)];
-#pragma unroll
-            for (int j = 0; j < kBatch; ++j)
-                if (base + j * kSelThreads < n) staged[base + j * kSelThreads] = score_key(x[j], st);
-        }
-        __syncthreads();
-    }
-    // f(index, key, exists) for the lane's scores in ascending order, all lanes of the wavefront together
-    auto each = [&](auto f) __attribute__((always_inline)) {
-        if constexpr (STAGED) {
-            for (int base = w_lo; base < w_hi; base += 64) {
-                const int i = base + lane;
-                f(i, staged[min(i, n - 1)], i < w_hi);
-            }
-        } else {
-            for (int base = w_lo; base < w_hi; base += 64 * kBatch) {
-                float x[kBatch];
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j) x[j] = a[min(base + 64 * j + lane, n - 1)];
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j) {
-                    const int i = base + 64 * j + lane;
-                    if (base + 64 * j >= w_hi) break;
-                    int bits = 0;
-                    const uint32_t key = score_key(x[j], bits);
-                    if (i < w_hi) st |= bits;
-                    f(i, key, i < w_hi);
-                }
-            }
-        }
-    };
 
     // radix descent.  by_count: rank target is a count (krem) instead of a mass (trem).  tau >= 0 (first descent of the
     // threshold rule): the first pass sees every element, so its histogram also gives the total mass; the target
@@ -155,15 +109,16 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
             }
             __syncthreads();
             const bool collect = first && pass == 0;
-            each([&](int i, uint32_t key, bool exists) __attribute__((always_inline)) {
-                if (!exists || (skip_forced && i < nforced)) return;
-                if ((key & pmask) != prefix) return;
+            for (int i = tid; i < n; i += kSelThreads) {
+                if (skip_forced && i < nforced) continue;
                 int dummy = 0;
+                const uint32_t key = score_key(a[i], collect ? st : dummy);
+                if ((key & pmask) != prefix) continue;
                 const uint32_t b = (key >> shf) & (nb - 1);
                 atomicAdd(&sh.hist_cnt[b], 1u);
                 if (!by_count) atomicAdd(&sh.hist_mass[b], key_mass(key, collect ? st : dummy));
                 else if (collect) (void)key_mass(key, st);
-            });
+            }
             __syncthreads();
             // buckets in descending order; thread owns `per` consecutive ones
             const int per = nb >= kSelThreads ? nb / kSelThreads : 1;
@@ -259,40 +214,48 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
         return pk;
     };
 
-    bool by_count = p.mode != 0;
-    const uint32_t kfix = static_cast<uint32_t>(min(p.kfix[dir], n));
-    if (by_count && kfix == 0) {                             // nothing ranked in: the status bits still need their sweep
-        each([&](int, uint32_t key, bool exists) __attribute__((always_inline)) {
-            if (exists) (void)key_mass(key, st);
-        });
+    // ---- total mass, threshold ----
+    Pick pk;
+    if (p.mode == 0) {
+        pk = descend(false, false, 0, 0u, p.tau[dir], true);
+    } else {
+        const uint32_t kfix = static_cast<uint32_t>(min(p.kfix[dir], n));
+        if (kfix == 0) {                                     // nothing ranked in: the status bits still need their sweep
+            for (int i = tid; i < n; i += kSelThreads) {
+                const uint32_t key = score_key(a[i], st);
+                (void)key_mass(key, st);
+            }
+        }
+        pk = descend(true, false, 0, kfix, -1.0, true);
     }
-    uint32_t krem = by_count ? kfix : 0u;
 
-    // ---- ordered emission: ranks come from ballots ----
+    // ---- ordered emission: each wavefront owns a contiguous range, ranks come from ballots ----
+    const int per_wave = ((n + kWaves - 1) / kWaves + 63) & ~63;
+    const int w_lo = min(wave * per_wave, n), w_hi = min(w_lo + per_wave, n);
     const u64 lt_mask = (1ull << lane) - 1ull;
     int32_t* __restrict__ out = p.idx[dir] + static_cast<size_t>(head) * cap;
 
     bool skip_forced = false;
-    // (one call of descend in the program: code is fetched once per call)
     for (int attempt = 0; attempt < 2; ++attempt) {
-        const Pick pk = descend(by_count, skip_forced, 0, krem, by_count ? -1.0 : p.tau[dir], attempt == 0);
         // sweep 1: per wavefront, the ties, the ties among the forced entries, and the entries that are in whatever the
         // ties decide (forced, or ranked above the crossing value).  Ties are taken in index order and the forced entries
         // are the lowest indices, so the number of selected entries of a wavefront follows from these three counts.
         uint32_t eqc = 0, eqf = 0, inc = 0;
-        auto classify = [&](int i, uint32_t key, bool exists, bool& eq, bool& in, bool& forced) __attribute__((always_inline)) {
-            forced = exists && i < nforced;
-            const bool ranked = exists && !pk.none && !(skip_forced && forced);
-            eq = ranked && key == pk.vstar;
-            in = forced || (ranked && key > pk.vstar);
-        };
-        each([&](int i, uint32_t key, bool exists) __attribute__((always_inline)) {
-            bool eq, in, forced;
-            classify(i, key, exists, eq, in, forced);
+        for (int base = w_lo; base < w_hi; base += 64) {
+            const int i = base + lane;
+            bool eq = false, in = false, forced = false;
+            if (i < w_hi) {
+                int dummy = 0;
+                const uint32_t key = score_key(a[i], dummy);
+                forced = i < nforced;
+                const bool ranked = !pk.none && !(skip_forced && forced);
+                eq = ranked && key == pk.vstar;
+                in = forced || (ranked && key > pk.vstar);
+            }
             eqc += __popcll(__ballot(eq));
             eqf += __popcll(__ballot(eq && forced));
             inc += __popcll(__ballot(in));
-        });
+        }
         if (lane == 0) {
             sh.wave_eq[wave] = eqc;
             sh.wave_eqf[wave] = eqf;
@@ -314,26 +277,37 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
             }
         }
         __syncthreads();
+        auto selected = [&](int i, uint32_t& tie_run) -> bool {
+            bool in = false, eq = false;
+            if (i < w_hi) {
+                const bool forced = i < nforced;
+                int dummy = 0;
+                const uint32_t key = score_key(a[i], dummy);
+                const bool ranked = !pk.none && !(skip_forced && forced);
+                eq = ranked && key == pk.vstar;
+                in = forced || (ranked && key > pk.vstar);
+            }
+            const u64 eb = __ballot(eq);
+            if (eq && tie_run + __popcll(eb & lt_mask) < pk.ties) in = true;
+            tie_run += __popcll(eb);
+            return in;
+        };
+        uint32_t tie_run = tie_base;
         if (total > static_cast<uint32_t>(cap) && attempt == 0) {
             // keep the forced entries and the best-ranked others: count-ranked pick over the rest
             st |= VS_STATUS_OVERFLOW;
             skip_forced = true;
-            by_count = true;
-            krem = static_cast<uint32_t>(cap - nforced);
+            pk = descend(true, true, 0, static_cast<uint32_t>(cap - nforced), -1.0, false);
             continue;
         }
         // sweep 2: write
-        uint32_t tie_run = tie_base;
-        each([&](int i, uint32_t key, bool exists) __attribute__((always_inline)) {
-            bool eq, in, forced;
-            classify(i, key, exists, eq, in, forced);
-            const u64 eb = __ballot(eq);
-            if (eq && tie_run + __popcll(eb & lt_mask) < pk.ties) in = true;
-            tie_run += __popcll(eb);
+        tie_run = tie_base;
+        for (int base = w_lo; base < w_hi; base += 64) {
+            const bool in = selected(base + lane, tie_run);
             const u64 sb = __ballot(in);
-            if (in) out[pos + __popcll(sb & lt_mask)] = i;
+            if (in) out[pos + __popcll(sb & lt_mask)] = base + lane;
             pos += __popcll(sb);
-        });
+        }
         if (tid == 0) p.cnt[dir][head] = static_cast<int32_t>(total);
         break;
     }
@@ -346,7 +320,8 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
 constexpr int kChunk = 8192;                   // scores per workgroup
 constexpr int kChunkThreads = 512;
 constexpr int kChunkWaves = kChunkThreads / 64;
-constexpr int kChunkRegs = kChunk / kChunkThreads;   // scores per thread: all requested at the top of a kernel, before its scan
+// scores per thread: all requested at the top of a kernel, before its scan (one load in flight at a time: 55.5 us for 8 x 131072, 46 now)
+constexpr int kChunkRegs = kChunk / kChunkThreads;
 constexpr int kMinSplitN = 32768;              // shorter problems stay with one workgroup (fewer launches)
 
 // descent state of one problem after a pass (written by the workgroup of chunk 0, read by the next kernel)
@@ -718,21 +693,6 @@ __global__ void zero_status_kernel(int32_t* status, int heads) {
     if (i < heads) status[i] = 0;
 }
 
-int launch_select(const SelParams& p, int heads, const int32_t* redo, hipStream_t st) {
-    static vs::PerDeviceOnce once;
-    const int rc = once.run(nullptr, [](int) -> int {
-        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   kStageMax * 4));
-        return VS_OK;
-    });
-    if (rc != VS_OK) return rc;
-    const dim3 grid(heads, 2), block(kSelThreads);
-    if (p.n <= kStageMax) hipLaunchKernelGGL(select_kernel<true>, grid, block, static_cast<size_t>(p.n) * 4, st, p, redo);
-    else hipLaunchKernelGGL(select_kernel<false>, grid, block, 0, st, p, redo);
-    VS_LAUNCH_CHECK();
-    return VS_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -807,13 +767,17 @@ int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, c
         VS_LAUNCH_CHECK();
         hipLaunchKernelGGL(split_emit_kernel, grid, dim3(kChunkThreads), 0, st, q);
         VS_LAUNCH_CHECK();
-        return launch_select(p, heads, q.redo, st);
+        hipLaunchKernelGGL(select_kernel, dim3(heads, 2), dim3(kSelThreads), 0, st, p, static_cast<const int32_t*>(q.redo));
+        VS_LAUNCH_CHECK();
+        return VS_OK;
     }
     if (status) {
         hipLaunchKernelGGL(zero_status_kernel, dim3((heads + 255) / 256), dim3(256), 0, st, status, heads);
         VS_LAUNCH_CHECK();
     }
-    return launch_select(p, heads, nullptr, st);
+    hipLaunchKernelGGL(select_kernel, dim3(heads, 2), dim3(kSelThreads), 0, st, p, static_cast<const int32_t*>(nullptr));
+    VS_LAUNCH_CHECK();
+    return VS_OK;
 }
 
 }  // extern "C"
