@@ -12,8 +12,9 @@
 //      gradients, rounded to two bf16 terms, are already the B operand of the second contraction
 //      dW_U^T[c, u] = sum_t X[t, c] dpre[t, u], whose A operand X^T comes from LDS through the transposing read.
 //      Every workgroup owns 128 hidden units (one 32-unit slice per wavefront, W_U fragments and the dW_U^T sums resident
-//      in registers: one wavefront per SIMD) and a strided set of 32-token blocks; its partial sums go to the workspace
-//      and a last kernel adds them up in a fixed order (no float atomics: the step is deterministic).
+//      in registers: one wavefront per SIMD) and a strided set of 32-token blocks.  Its partial sums, in fp32 over at most
+//      1/256 of the blocks (or eight) whatever the width, go to the workspace and a last kernel adds them up in fp64, in a
+//      fixed order (no float atomics: the step is deterministic).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -37,6 +38,8 @@ constexpr int kTokTile = 32;
 constexpr int kXPitch = 512;                   // bytes per token row of the X tile in LDS (K then V, bf16)
 constexpr int kXTile = kTokTile * kXPitch;
 constexpr int kXBufs = 4;                      // tiles of blocks i - 1 (dW_U), i, i + 1 (U) and i + 2 (in flight)
+constexpr int kPartials = 256;                 // an fp32 partial sum is over at most 1 / kPartials of the blocks,
+constexpr int kPartBlocks = 8;                 // or over this many where that is more
 constexpr int kKlThreads = 256;
 constexpr int kKlBlock = 1024;                 // tokens per partial KL sum
 
@@ -122,9 +125,11 @@ struct TrainParams {
     const float* W_S;
     const float* g_v;
     const float* g_s;
-    float* part_wu;                 // [chunks][256][d_h]
-    float* part_vec;                // [chunks][3][d_h]: dW_V, dW_S, db_U
-    int chunks;
+    float* part_wu;                 // [partials][256][d_h]
+    float* part_vec;                // [partials][3][d_h]: dW_V, dW_S, db_U
+    int chunks;                     // workgroups per 128 hidden units
+    int stride;                     // partial sum c is over blocks c, c + stride, ..; a multiple of chunks
+    int partials;                   // those with a block: workgroup w makes w, w + chunks, .., one after the other
 };
 
 // 16 bytes per lane from global memory straight into LDS: lane L's piece lands at lds_base + 16 L (lds_base is
@@ -188,15 +193,22 @@ __global__ __launch_bounds__(kThreads, 1) void train_backward_kernel(const Train
         for (int e = 0; e < 16; ++e) dwu[cb][e] = 0.f;
     float s_wv[4] = {0.f, 0.f, 0.f, 0.f}, s_ws[4] = {0.f, 0.f, 0.f, 0.f}, s_bu[4] = {0.f, 0.f, 0.f, 0.f};
 
+    auto half_sum = [](float x) -> float {
+        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
     const uint32_t blocks_per_head = (n + kTokTile - 1) / kTokTile;
     const uint32_t total_blocks = static_cast<uint32_t>(p.heads) * blocks_per_head;              // < 2^31
     const int nsteps = static_cast<int>((total_blocks - chunk + p.chunks - 1) / p.chunks);       // blocks of this workgroup (>= 1)
+    uint32_t next_blk = chunk, next_part = chunk;            // block that load_block() takes next, and its partial sum
 
     // ---- staging: a wavefront instruction deposits two token rows; wavefront w moves rows 8 w .. 8 w + 7 of a tile ----
     auto load_block = [&](int i, float& greg) __attribute__((always_inline)) {
         greg = 0.f;
         if (i >= nsteps) return;
-        const uint32_t blk = chunk + static_cast<uint32_t>(i) * p.chunks;
+        const uint32_t blk = next_blk;
+        next_blk += p.stride;
+        if (next_blk >= total_blocks) next_blk = next_part += p.chunks;
         const int head = static_cast<int>(blk / blocks_per_head);
         const int tok0 = static_cast<int>(blk - static_cast<uint32_t>(head) * blocks_per_head) * kTokTile;
 #pragma unroll
@@ -265,11 +277,15 @@ __global__ __launch_bounds__(kThreads, 1) void train_backward_kernel(const Train
 #pragma unroll
     for (int e = 0; e < 8; ++e) dhi[e] = dlo[e] = 0u;
 
+    // blocks of partial sum c (< partials)
+    auto blocks_of = [&](int c) __attribute__((always_inline)) -> int { return static_cast<int>((total_blocks - 1 - c) / p.stride) + 1; };
+
     constexpr int kActStages = ACT == 0 ? 7 : 16;
     constexpr int kStages = kActStages + 9;
     constexpr int kPieces = 4 * kStages;
     constexpr float kL = -1.4426950408889634f;
 #define VS_PIN(x) asm volatile("" : "+v"(x))
+    int part = chunk, last = blocks_of(chunk);               // the partial sum being made and the step at whose end its dW_U is complete
     for (int i = 0; i <= nsteps; ++i) {
         __builtin_amdgcn_s_waitcnt(0x0F70);                  // this wavefront's part of block i + 1 has arrived
         if (wave == 0) gbuf[(i + 1) & (kXBufs - 1)][hh][col] = greg;
@@ -394,31 +410,36 @@ __global__ __launch_bounds__(kThreads, 1) void train_backward_kernel(const Train
             dhi[e] = dhi_n[e];
             dlo[e] = dlo_n[e];
         }
+        // ---- partial sums that are through: dW_U now holds the blocks up to i - 1, the vectors those up to i ----
+        if (i == last) {
+            uint32_t pitch = p.d_h;
+            asm volatile("" : "+s"(pitch));                  // the 128 row addresses are made here, not kept over the steps
+            float* const pw = p.part_wu + static_cast<size_t>(part) * 256 * pitch + u;
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    pw[(32 * cb + 8 * (e >> 2) + 4 * hh + (e & 3)) * pitch] = dwu[cb][e];
+                    dwu[cb][e] = 0.f;
+                }
+            part += p.chunks;
+            if (part < p.partials) last += blocks_of(part);
+        }
+        if (i == last - 1) {                                 // (also right after the above, where the next one is a single block)
+            const float t_wv = half_sum((s_wv[0] + s_wv[1]) + (s_wv[2] + s_wv[3]));
+            const float t_ws = half_sum((s_ws[0] + s_ws[1]) + (s_ws[2] + s_ws[3]));
+            const float t_bu = half_sum((s_bu[0] + s_bu[1]) + (s_bu[2] + s_bu[3]));
+            if (hh == 0) {
+                float* const pv = p.part_vec + static_cast<size_t>(part) * 3 * p.d_h + u;
+                pv[0] = t_wv;
+                pv[p.d_h] = t_ws;
+                pv[2 * p.d_h] = t_bu;
+            }
+#pragma unroll
+            for (int c = 0; c < 4; ++c) s_wv[c] = s_ws[c] = s_bu[c] = 0.f;
+        }
     }
 #undef VS_PIN
-    if (!active) return;
-    // ---- partial sums of this workgroup ----
-    float* const pw = p.part_wu + static_cast<size_t>(chunk) * 256 * p.d_h;
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int c = 32 * cb + 8 * (e >> 2) + 4 * hh + (e & 3);
-            pw[static_cast<size_t>(c) * p.d_h + u] = dwu[cb][e];
-        }
-    auto half_sum = [](float x) -> float {
-        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    };
-    const float t_wv = half_sum((s_wv[0] + s_wv[1]) + (s_wv[2] + s_wv[3]));
-    const float t_ws = half_sum((s_ws[0] + s_ws[1]) + (s_ws[2] + s_ws[3]));
-    const float t_bu = half_sum((s_bu[0] + s_bu[1]) + (s_bu[2] + s_bu[3]));
-    if (hh == 0) {
-        float* const pv = p.part_vec + static_cast<size_t>(chunk) * 3 * p.d_h;
-        pv[u] = t_wv;
-        pv[p.d_h + u] = t_ws;
-        pv[2 * p.d_h + u] = t_bu;
-    }
 }
 
 // The gradients: sums of the workgroups' partial results in a fixed order, in fp64.  Outputs 0 .. 256 d_h - 1 are dW_U, then
@@ -430,7 +451,7 @@ struct TrainOuts {
     float* out[4];                                           // dW_U, dW_V, dW_S, db_U
 };
 __global__ __launch_bounds__(4 * kRedOut) void train_reduce_kernel(const float* __restrict__ part_wu, const float* __restrict__ part_vec,
-                                                                   int chunks, int d_h, TrainOuts o) {
+                                                                   int partials, int d_h, TrainOuts o) {
     __shared__ double red[4][kRedOut];
     const size_t nwu = static_cast<size_t>(256) * d_h, nvec = static_cast<size_t>(3) * d_h;   // both multiples of 64
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -438,7 +459,7 @@ __global__ __launch_bounds__(4 * kRedOut) void train_reduce_kernel(const float* 
     const bool vec = first >= nwu;
     const float* __restrict__ src = vec ? part_vec + (first - nwu) + lane : part_wu + first + lane;
     const size_t stride = vec ? nvec : nwu;
-    const int per = (chunks + 3) / 4, c0 = min(per * wave, chunks), c1 = min(c0 + per, chunks);
+    const int per = (partials + 3) / 4, c0 = min(per * wave, partials), c1 = min(c0 + per, partials);
     double s = 0.0;
     int c = c0;
     for (; c + 8 <= c1; c += 8) {
@@ -465,7 +486,7 @@ __global__ __launch_bounds__(4 * kRedOut) void train_reduce_kernel(const float* 
 
 struct TrainWs {
     size_t fwd_off, fwd_bytes, pv_off, ps_off, gv_off, gs_off, kl_off, pwu_off, pvec_off, total;
-    int chunks, parts;
+    int chunks, stride, partials, kl_parts;
 };
 
 bool dh_ok(int d_h) { return d_h >= 64 && d_h <= 1024 && d_h % 64 == 0; }
@@ -474,11 +495,19 @@ TrainWs train_ws_layout(int kv_heads, int64_t n, int d_h) {
     TrainWs w;
     const size_t rows = static_cast<size_t>(kv_heads) * n;
     const long long blocks = static_cast<long long>(kv_heads) * ((n + kTokTile - 1) / kTokTile);
-    // One workgroup per compute unit over all groups of 128 hidden units: a workgroup fills its compute unit, so more of
-    // them only makes more partial sums to write and add (256 d_h floats each).
+    // One workgroup per compute unit over all groups of 128 hidden units (a workgroup fills its compute unit), but partial sums
+    // of at most 1 / kPartials of the blocks, or kPartBlocks: a workgroup makes several, one after the other.  With one per
+    // workgroup the fp32 sums were 2 (d_h = 256) to 8 times (1024) as long; 8 x 16384 tokens, SiLU / 1024: error of dW_U
+    // against 64 bits 4.06e-6 (128 blocks each), 4.03e-6 now, at 394 and 456 us for the step (256 d_h floats more to write and add
+    // per partial sum); 8 x 32768, GELU / 256 245 and 256 us.  Below 8 blocks nothing is gained: 8 x 4096, SiLU / 1024 3.558e-6 and
+    // 193 us with four blocks each, 3.560e-6 and 157 us with eight (3.569e-6 with 32).
     const int chunks = 256 / ((d_h + kUnitsPerWg - 1) / kUnitsPerWg);
     w.chunks = static_cast<int>(blocks < chunks ? blocks : chunks);
-    w.parts = static_cast<int>((n + kKlBlock - 1) / kKlBlock);
+    long long want = (blocks + kPartBlocks - 1) / kPartBlocks;
+    want = want < kPartials ? want : kPartials;
+    w.stride = want > w.chunks ? static_cast<int>((want + w.chunks - 1) / w.chunks * w.chunks) : w.chunks;
+    w.partials = static_cast<int>(blocks < w.stride ? blocks : w.stride);
+    w.kl_parts = static_cast<int>((n + kKlBlock - 1) / kKlBlock);
     w.fwd_off = 0;
     w.fwd_bytes = vs::round_up(vs_index_score_workspace(kv_heads, n, d_h), 256);
     w.pv_off = w.fwd_off + w.fwd_bytes;
@@ -486,9 +515,9 @@ TrainWs train_ws_layout(int kv_heads, int64_t n, int d_h) {
     w.gv_off = w.ps_off + vs::round_up(rows * 4, 256);
     w.gs_off = w.gv_off + vs::round_up(rows * 4, 256);
     w.kl_off = w.gs_off + vs::round_up(rows * 4, 256);
-    w.pwu_off = w.kl_off + vs::round_up(static_cast<size_t>(kv_heads) * 2 * w.parts * 8, 256);
-    w.pvec_off = w.pwu_off + vs::round_up(static_cast<size_t>(w.chunks) * 256 * d_h * 4, 256);
-    w.total = w.pvec_off + vs::round_up(static_cast<size_t>(w.chunks) * 3 * d_h * 4, 256);
+    w.pwu_off = w.kl_off + vs::round_up(static_cast<size_t>(kv_heads) * 2 * w.kl_parts * 8, 256);
+    w.pvec_off = w.pwu_off + vs::round_up(static_cast<size_t>(w.partials) * 256 * d_h * 4, 256);
+    w.total = w.pvec_off + vs::round_up(static_cast<size_t>(w.partials) * 3 * d_h * 4, 256);
     return w;
 }
 
@@ -527,7 +556,7 @@ int vs_index_train_step(const void* k_bf16, const void* v_bf16, int kv_heads, in
     const uint16_t* hi = reinterpret_cast<const uint16_t*>(base + lay.fwd_off);
     const uint16_t* lo = reinterpret_cast<const uint16_t*>(base + lay.fwd_off + vs::indexer_split_lo_offset(w->d_h));
     // 2. loss and logit gradients
-    const dim3 kl_grid(lay.parts, kv_heads, 2);
+    const dim3 kl_grid(lay.kl_parts, kv_heads, 2);
     hipLaunchKernelGGL(train_kl_kernel, kl_grid, dim3(kKlThreads), 0, st, p_v, p_s, t_v, t_s, static_cast<int>(n), eps, kl);
     VS_LAUNCH_CHECK();
     hipLaunchKernelGGL(train_grad_kernel, kl_grid, dim3(kKlThreads), 0, st, p_v, p_s, t_v, t_s, static_cast<int>(n), kv_heads, eps, kl,
@@ -550,13 +579,15 @@ int vs_index_train_step(const void* k_bf16, const void* v_bf16, int kv_heads, in
     p.part_wu = reinterpret_cast<float*>(base + lay.pwu_off);
     p.part_vec = reinterpret_cast<float*>(base + lay.pvec_off);
     p.chunks = lay.chunks;
+    p.stride = lay.stride;
+    p.partials = lay.partials;
     const dim3 grid(lay.chunks, (w->d_h + kUnitsPerWg - 1) / kUnitsPerWg);
     if (w->act == 0) hipLaunchKernelGGL(train_backward_kernel<0>, grid, dim3(kThreads), 0, st, p);
     else hipLaunchKernelGGL(train_backward_kernel<1>, grid, dim3(kThreads), 0, st, p);
     VS_LAUNCH_CHECK();
     const TrainOuts outs{{dW_U, dW_V, dW_S, db_U}};
     hipLaunchKernelGGL(train_reduce_kernel, dim3(static_cast<unsigned>(259 * w->d_h / kRedOut)), dim3(4 * kRedOut), 0, st, p.part_wu,
-                       p.part_vec, lay.chunks, w->d_h, outs);
+                       p.part_vec, lay.partials, w->d_h, outs);
     VS_LAUNCH_CHECK();
     return VS_OK;
 }

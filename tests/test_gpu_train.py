@@ -79,6 +79,31 @@ def test_train_pipeline_over_several_blocks(hk, n, d_h, act):
         _check(got, want, name)
 
 
+@pytest.mark.parametrize("d_h,wide,act,n", [
+    (128, 256, 1, 32 * 900 + 7),                             # 2 x 901 blocks, one and two partial sums per workgroup
+    (512, 1024, 0, 32 * 1000 + 1),                           # the same, four and eight partial sums per workgroup
+])
+def test_train_sums_do_not_depend_on_the_width(d_h, wide, act, n):
+    """The fp32 sums of a gradient entry run over 1/256 of the 32-token blocks (here seven or eight; fp64 adds them up)
+    whatever the width of the layer.  Units with zero down-projections change neither the scores nor the other units' gradients, so a layer
+    widened by such units must give the narrow layer's gradients bit for bit."""
+    hk = 2
+    rng = np.random.default_rng(n)
+    _, k, v = synth.qkv(270 + n, 1, hk, n, local_structure=True)
+    k, v = k.cuda(), v.cuda()
+    W_U, b_U, W_V, W_S = synth.indexer_weights(n, wide, act, gain=4.0)
+    W_V[d_h:] = 0.0
+    W_S[d_h:] = 0.0
+    t_v, t_s = _targets(rng, hk, n)
+    narrow = [np.ascontiguousarray(W_U[:, :d_h]), b_U[:d_h].copy(), W_V[:d_h].copy(), W_S[:d_h].copy()]
+    loss, grads = _gpu_step(k, v, narrow, act, t_v, t_s)
+    loss_w, grads_w = _gpu_step(k, v, [W_U, b_U, W_V, W_S], act, t_v, t_s)
+    assert loss_w == loss
+    for got, want, name in zip(grads_w, grads, ("dW_U", "db_U", "dW_V", "dW_S")):
+        assert np.array_equal(got[..., :d_h], want), name
+    assert not grads_w[0][:, d_h:].any() and not grads_w[1][d_h:].any()
+
+
 def test_train_step_on_aggregated_attention_targets_and_descent():
     """Targets from vs_aggregate (the distillation targets of the paper, here of synthetic Q / K); the step is
     deterministic, and a small move against the gradient lowers the loss."""
