@@ -31,6 +31,7 @@ __device__ __forceinline__ uint16_t f64_to_bf16(double x) {
 
 constexpr int kThreads = 256;
 constexpr int kPositions = kThreads / 16;      // per workgroup
+constexpr int kSmallPositions = kThreads / 64; // the same, one plane per thread
 constexpr int kBatch = 4;                      // heads whose loads are in flight together
 
 // bf16 pair of two fp32 values (nearest even), a in the low half
@@ -126,6 +127,52 @@ __global__ __launch_bounds__(kThreads) void rope_kernel(uint16_t* x, int heads, 
     }
 }
 
+// The same with one plane per thread, 64 threads a row: a quarter of the angles in a thread's way, which is what the time of a
+// small call consists of.  The first heads are requested before the angle is evaluated.
+template <int PAIRING>
+__global__ __launch_bounds__(kThreads) void rope_small_kernel(uint16_t* x, int heads, int heads_per_group, long long n, long long pos0,
+                                                              double theta_base) {
+    const int plane = threadIdx.x & 63;
+    const long long t = static_cast<long long>(blockIdx.x) * kSmallPositions + (threadIdx.x >> 6);
+    if (t >= n) return;
+    const int h0 = blockIdx.y * heads_per_group, h1 = min(h0 + heads_per_group, heads);
+    uint32_t a[kBatch], b[kBatch];
+    auto load = [&](int h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            if (h + j >= h1) break;
+            const uint16_t* row = x + (static_cast<long long>(h + j) * n + t) * 128;
+            if (PAIRING == 0) {
+                const uint32_t w = *reinterpret_cast<const uint32_t*>(row + 2 * plane);
+                a[j] = w & 0xffffu;
+                b[j] = w >> 16;
+            } else {
+                a[j] = row[plane];
+                b[j] = row[plane + 64];
+            }
+        }
+    };
+    load(h0);
+    double c, s;
+    sincos(static_cast<double>(pos0 + t) * pow(theta_base, -2.0 * plane / 128.0), &s, &c);
+    const float cf = static_cast<float>(c), sf = static_cast<float>(s);
+    for (int h = h0; h < h1; h += kBatch) {
+        if (h > h0) load(h);
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) {
+            if (h + j >= h1) break;
+            rotate(a[j], b[j], c, s, cf, sf);
+            uint16_t* row = x + (static_cast<long long>(h + j) * n + t) * 128;
+            if (PAIRING == 0) {
+                *reinterpret_cast<uint32_t*>(row + 2 * plane) = a[j] | (b[j] << 16);
+            } else {
+                row[plane] = static_cast<uint16_t>(a[j]);
+                row[plane + 64] = static_cast<uint16_t>(b[j]);
+            }
+        }
+    }
+}
+
 }  // namespace
 
 extern "C" int vs_rope_apply(void* x_bf16, int heads, int64_t n, int64_t pos0, double theta_base, int pairing,
@@ -134,23 +181,24 @@ extern "C" int vs_rope_apply(void* x_bf16, int heads, int64_t n, int64_t pos0, d
     if (!(theta_base > 1.0) || !isfinite(theta_base)) return VS_ERR_INVALID_ARG;
     if (pairing != 0 && pairing != 1) return VS_ERR_INVALID_ARG;
     if (n > VS_MAX_SEQ) return VS_ERR_UNSUPPORTED;
-    // Short sequences: the heads are shared out so that there are about four workgroups per compute unit; every group evaluates
-    // the angles again (a few microseconds), whole batches of heads stay together.
-    const unsigned blocks = static_cast<unsigned>((n + kPositions - 1) / kPositions);
+    // Few angles: one plane per thread.  1 head x 1000 positions 4.3 us with four planes, 3.1 with one, 8 x 1000 6.5 and 4.6, 8 x 2000
+    // 6.8 and 5.9, 16 x 1500 7.8 and 7.2; on the other side 1 x 4096 4.5 and 4.7, 4 x 6000 7.9 and 8.0, 8 x 3500 8.1 and 8.2,
+    // 32 x 2000 11.7 and 12.4 (wider accesses, a quarter of the requests).
+    // Short sequences: the heads are shared out over up to four workgroups per compute unit (three with one plane); every group
+    // evaluates the angles again, whole batches of heads stay together.
     const int batches = (heads + kBatch - 1) / kBatch;
-    int groups = blocks < 1024 ? static_cast<int>((1024 + blocks - 1) / blocks) : 1;
+    const bool small = n <= (heads == 1 ? 3072 : 4096) && n * batches <= 6144;
+    const int positions = small ? kSmallPositions : kPositions;
+    const unsigned blocks = static_cast<unsigned>((n + positions - 1) / positions);
+    int groups = small ? static_cast<int>(768 / blocks) : blocks < 1024 ? static_cast<int>((1024 + blocks - 1) / blocks) : 1;
+    if (groups < 1) groups = 1;
     if (groups > batches) groups = batches;
     const int per_group = (batches + groups - 1) / groups * kBatch;
     groups = (heads + per_group - 1) / per_group;
     const dim3 grid(blocks, static_cast<unsigned>(groups));
-    uint16_t* x = static_cast<uint16_t*>(x_bf16);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (pairing == 0)
-        hipLaunchKernelGGL(rope_kernel<0>, grid, dim3(kThreads), 0, st, x, heads, per_group, static_cast<long long>(n),
-                           static_cast<long long>(pos0), theta_base);
-    else
-        hipLaunchKernelGGL(rope_kernel<1>, grid, dim3(kThreads), 0, st, x, heads, per_group, static_cast<long long>(n),
-                           static_cast<long long>(pos0), theta_base);
+    auto* const kernel = small ? (pairing == 0 ? rope_small_kernel<0> : rope_small_kernel<1>) : (pairing == 0 ? rope_kernel<0> : rope_kernel<1>);
+    hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, static_cast<hipStream_t>(stream), static_cast<uint16_t*>(x_bf16), heads, per_group,
+                       static_cast<long long>(n), static_cast<long long>(pos0), theta_base);
     VS_LAUNCH_CHECK();
     return VS_OK;
 }

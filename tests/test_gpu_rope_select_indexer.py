@@ -45,6 +45,27 @@ def test_rope_all_magnitudes(heads, n, pairing):
     assert np.abs(diff).max() <= 1 and (diff != 0).mean() < 1e-4
 
 
+@pytest.mark.parametrize("heads,n,few,pairing", [(1, 3073, None, 0), (3, 4097, None, 1), (5, 3073, 2, 1), (33, 700, 3, 0), (16, 1537, 5, 1), (9, 2049, 8, 0)])
+def test_rope_many_rows(heads, n, few, pairing):
+    """Calls of more than 4096 positions (one head: 3072) or 6144 rows of angles (positions x batches of four heads) keep four planes per
+    thread, smaller ones take the kernel with one: against the oracle as above, and the first heads by themselves, a small
+    call, bit for bit the same."""
+    assert n > (3072 if heads == 1 else 4096) or n * ((heads + 3) // 4) > 6144
+    g = torch.Generator().manual_seed(heads * 100 + n)
+    x = torch.randn(heads, n, 128, generator=g) * 2.0 ** torch.randint(-120, 120, (heads, n, 1), generator=g)
+    x[:, ::4] = torch.randn(heads, (n + 3) // 4, 128, generator=g)
+    x[:, 1::4, ::2] = x[:, 1::4, 1::2]
+    x = x.to(torch.bfloat16)
+    got = synth.to_bits(vs.rope_apply(x.cuda(), 70001, 1e6, pairing))
+    ref = oracle.rope_bf16(synth.to_bits(x), 70001, 1e6, pairing)
+    diff = got.astype(np.int32) - ref.astype(np.int32)
+    assert np.abs(diff).max() <= 1 and (diff != 0).mean() < 1e-4
+    if few:
+        assert n * ((few + 3) // 4) <= 6144
+        small = synth.to_bits(vs.rope_apply(x[:few].cuda(), 70001, 1e6, pairing))
+        assert np.array_equal(small, got[:few])
+
+
 def test_rope_special_values():
     """A NaN or an infinity makes its own plane non-finite and nothing else."""
     x = torch.ones(3, 20, 128, dtype=torch.bfloat16)
