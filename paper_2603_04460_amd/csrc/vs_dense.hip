@@ -443,10 +443,16 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
     p.scale = scale;
     p.c = scale * 1.4426950408889634f;
     p.tile_counter = nullptr;
-    // Workgroups for at most half of the compute units: split the keys of a row block over wavefronts instead.  32 / 8 heads
-    // against 32768 keys: 1000 rows (128 workgroups) 760 us here, 657 there; 2000 rows (256) 1084 here, twice the 657 there.
+    // Workgroups for at most half of the compute units: split the keys of a row block over wavefronts instead.  At 128 workgroups:
+    // 128 heads x 200 15.8 us here, 14.5 there, 64 x 500 23.0 and 18.0, 32 x 1024 34.8 and 23.1, 32 / 8 x 1024 32.0 and 21.6,
+    // 4 / 2 x 8192 187 and 94.  Beyond, long sequences still gain (152: 32 / 8 x 1200 35.9 and 30.7; 192: 24 x 2048 56.6 and 48.2),
+    // short ones and long contexts lose (160: 160 x 200 16.5 and 20.0, 80 x 500 23.6 and 24.3; 152: 32 / 8, 1200 rows of 8192 keys
+    // 191 and 211; 240: 64 / 16 x 900 33.8 and 37.5).
+    // A wavefront that has one or two tiles in all stays here: one head (1, 8, 32 of them) x 64 6.0 to 6.3 us here, 6.7 to 6.9 there
+    // (x 65 8.0 and 6.7), two heads of a group x 32 6.1 and 6.6 (x 64 7.2 and 6.7); four heads of a group x 32 7.3 and 6.8.
     const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((n_q * p.hc + 255) / 256);
-    if (units <= kShortUnits) {
+    const bool few_tiles = p.hc <= 2 && n_kv * p.hc <= 64;
+    if (units <= kShortUnits && !few_tiles) {
         p.hc = vs::short_heads(p.hc);
         return vs::launch_short_dense(p, static_cast<hipStream_t>(stream));
     }

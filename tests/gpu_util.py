@@ -1,10 +1,15 @@
 """Helpers shared by the GPU parity tests: marshalling between numpy bit patterns and device tensors and
 thin wrappers that call the library through its C ABI binding."""
+import os
+import re
+
 import numpy as np
 import torch
 
 import paper_2603_04460_amd as vs
 import synth
+
+CSRC = os.path.join(os.path.dirname(os.path.abspath(vs.__file__)), "csrc")
 
 ATTN_ATOL = 2e-2      # max-abs on bf16 attention outputs (fp32 accumulation), the bar of the benchmark spec
 SCORE_RTOL = 1e-3     # indexer scores, relative
@@ -27,6 +32,23 @@ def make_qkv(seed, hq, hkv, n, theta=1e6, local=False, rope=True):
         vs.rope_apply(k, 0, theta)
     torch.cuda.synchronize()
     return (q, k, v), (synth.to_bits(q), synth.to_bits(k), synth.to_bits(v))
+
+
+def _heads_per_workgroup(hq, hk, per_q=False):
+    group = hq // hk
+    return 1 if per_q else 4 if group % 4 == 0 else 2 if group % 2 == 0 else 1
+
+
+def _short_units(source):
+    """The line of the rule, as the source has it."""
+    return int(re.search(r"constexpr int kShortUnits = (\d+);", open(os.path.join(CSRC, source)).read()).group(1))
+
+
+def dense_is_short(hq, hk, n_q, n):
+    """Does a dense call take the kernel that splits the keys of a row block (vs_short.hip)?"""
+    hc = _heads_per_workgroup(hq, hk)
+    few_tiles = hc <= 2 and n * hc <= 64
+    return hk * (hq // hk // hc) * -(-n_q * hc // 256) <= _short_units("vs_dense.hip") and not few_tiles
 
 
 def run_sparse(q, k, v, idx_v, cnt_v, idx_s, cnt_s, want_lse=True, granularity=None):

@@ -8,7 +8,7 @@ import torch
 import oracle
 import paper_2603_04460_amd as vs
 import synth
-from gpu_util import make_qkv, lists, run_sparse, run_dense, check_attention, check_key_set
+from gpu_util import make_qkv, lists, run_sparse, run_dense, check_attention, check_key_set, dense_is_short
 
 pytestmark = pytest.mark.gpu
 
@@ -94,4 +94,19 @@ def test_sparse_short_chunk_of_a_group(hq, hk, n, n_q):
     torch.cuda.synchronize()
     rows = np.arange(pos0, n)
     ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, rows=rows)
+    check_attention(o, lse, ref_o, ref_lse)
+
+
+@pytest.mark.parametrize("hq,hk,n_q,n", [(1, 1, 65, 65), (3, 3, 1, 97), (2, 1, 33, 33), (4, 1, 31, 31), (8, 8, 32, 96), (3, 3, 33, 64), (2, 1, 32, 32)])
+def test_dense_few_keys(hq, hk, n_q, n):
+    """Both sides of the line of 64 keys for one query head per workgroup and 32 for two."""
+    assert dense_is_short(hq, hk, n_q, n) == (n not in (64, 32))
+    (q, k, v), (qb, kb, vb) = make_qkv(1400 + n, hq, hk, n)
+    pos0 = n - n_q
+    qc = q[:, pos0:].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, k, v, o, lse, pos0=pos0)
+    torch.cuda.synchronize()
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:], kb, vb, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse)
