@@ -51,6 +51,15 @@ def dense_is_short(hq, hk, n_q, n):
     return hk * (hq // hk // hc) * -(-n_q * hc // 256) <= _short_units("vs_dense.hip") and not few_tiles
 
 
+def sparse_is_short(hq, hk, n_q, n, capacity, per_q=False):
+    """The same of a sparse call; capacity: of a column list and an offset list together."""
+    hc = _heads_per_workgroup(hq, hk, per_q)
+    units, line = hk * (hq // hk // hc) * -(-n_q * hc // 128), _short_units("vs_attention.hip")
+    if hc == 1:
+        return units <= line
+    return units <= line // 2 and n >= 4 * n_q and n >= 2048 and capacity >= 10 * (units - (28 if hc == 4 else 44))
+
+
 def run_sparse(q, k, v, idx_v, cnt_v, idx_s, cnt_s, want_lse=True, granularity=None):
     hq, n, _ = q.shape
     hk = k.shape[0]

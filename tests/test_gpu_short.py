@@ -1,6 +1,7 @@
 """GPU parity of the attention kernel for launches with few row blocks (vs_short.hip: the keys of a row block split over four
-wavefronts): sparse calls of up to 128 four-block units with one query head per workgroup, dense calls of up to 128
-workgroups.  Bars as everywhere: exact kept-key sets (gpu_util.check_key_set), 2e-2 on bf16 outputs, 2e-3 on the LSE."""
+wavefronts) on both sides of the rules that choose it: sparse calls of up to 128 four-block units with one query head per
+workgroup, short chunks of long sequences, dense calls of up to 128 workgroups.  gpu_util states the rules once more, with
+the lines read from the sources, so that a case whose kernel changes is noticed.  Bars as everywhere: exact kept-key sets (gpu_util.check_key_set), 2e-2 on bf16 outputs, 2e-3 on the LSE."""
 import numpy as np
 import pytest
 import torch
@@ -8,7 +9,8 @@ import torch
 import oracle
 import paper_2603_04460_amd as vs
 import synth
-from gpu_util import make_qkv, lists, run_sparse, run_dense, check_attention, check_key_set, dense_is_short
+from gpu_util import (make_qkv, lists, run_sparse, run_dense, check_attention, check_key_set, dense_is_short,
+                      sparse_is_short)
 
 pytestmark = pytest.mark.gpu
 
@@ -75,11 +77,13 @@ def test_dense_both_sides_of_the_line(n_q):
     rows = synth.sample_rows(9, n_q, 40, 40, 40)
     ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:], kb, vb, pos0=pos0)
     check_attention(o, lse, ref_o[:, rows], ref_lse[:, rows], rows=rows)
+    assert dense_is_short(hq, hk, n_q, n) == (n_q == 1024)
 
 
 @pytest.mark.parametrize("hq,hk,n,n_q", [(32, 8, 2051, 256), (8, 2, 700, 33), (4, 2, 513, 1)])
 def test_sparse_short_chunk_of_a_group(hq, hk, n, n_q):
-    """Several query heads per workgroup: chunks of at most 64 units against at least 8 times as many keys."""
+    """Several query heads per workgroup: chunks that stay with vs_attention.hip, because the lists are short for 64 units or the
+    keys are few."""
     rng = np.random.default_rng(n)
     (q, k, v), (qb, kb, vb) = make_qkv(800 + n, hq, hk, n)
     pos0 = n - n_q
@@ -94,6 +98,34 @@ def test_sparse_short_chunk_of_a_group(hq, hk, n, n_q):
     torch.cuda.synchronize()
     rows = np.arange(pos0, n)
     ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, rows=rows)
+    check_attention(o, lse, ref_o, ref_lse)
+    assert not sparse_is_short(hq, hk, n_q, n, iv.shape[1] + is_.shape[1])
+
+
+@pytest.mark.parametrize("hq,hk,n,n_q,gran", [
+    (32, 8, 2400, 256, None),                                # 64 units, the most
+    (8, 2, 2100, 33, None),                                  # more than one row block, the second of one row
+    (4, 2, 2049, 1, None),                                   # two heads a group, one row
+    (6, 3, 2500, 300, None),
+    (8, 2, 2176, 64, 32),                                    # tile-granular
+    (4, 2, 2143, 31, 32),
+])
+def test_sparse_short_chunk_edges(hq, hk, n, n_q, gran):
+    """Chunks of at most 64 units against at least 2048 keys and 4 times as many as rows, with long lists, take this kernel."""
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(850 + n, hq, hk, n)
+    pos0 = n - n_q
+    iv, cv = lists([rng.choice(n, size=n // 4, replace=False) for _ in range(hk)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=60, replace=False)])) for _ in range(hk)])
+    assert sparse_is_short(hq, hk, n_q, n, iv.shape[1] + is_.shape[1])
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    qc = q[:, pos0:].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, hk, n), dtype=torch.uint8, device="cuda")
+    vs.sparse_prefill(qc, k, v, f(iv), f(cv), f(is_), f(cs), o, lse, ws, slash_granularity=gran, pos0=pos0)
+    torch.cuda.synchronize()
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:], kb, vb, iv, cv, is_, cs, granularity=gran or 1, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse)
 
 
