@@ -105,8 +105,8 @@ def test_aggregate_many_groups(hq, hk, n):
 
 
 def test_aggregate_8192_one_head_elementwise():
-    """n = 8192, one head: 32 resident-key workgroups, 128 streamed stages each, the 512-entry diagonal ring wraps 16
-    times and every flush window is compared, element by element, together with the recall of a mask."""
+    """n = 8192, one head: 32 groups of resident keys, the streamed rows of each shared out over 16 workgroups (up to 8 stages
+    each); every element is compared, together with the recall of a mask."""
     hq, hk, n = 1, 1, 8192
     rng = np.random.default_rng(8192)
     (q, k, v), (qb, kb, vb) = make_qkv(8192, hq, hk, n, local=True)
@@ -118,6 +118,24 @@ def test_aggregate_8192_one_head_elementwise():
     ref_v, ref_s, ref_r = _oracle(qb, kb, 1, mask=(iv, cv, is_, cs))
     _close(a_v, ref_v)
     _close(a_s, ref_s)
+    assert np.abs(rec - ref_r).max() <= RECALL_ABS, (rec, ref_r)
+
+
+def test_aggregate_8192_five_heads_elementwise():
+    """The same with five query heads (the same one five times, so that the oracle runs once): 160 groups, one workgroup per
+    group in the column sweep, 128 streamed stages for the longest; the 512-entry diagonal rings wrap 16 times and every
+    flush window is compared."""
+    hq, hk, n = 5, 1, 8192
+    rng = np.random.default_rng(8192)
+    (q, k, v), (qb, kb, vb) = make_qkv(8192, 1, hk, n, local=True)
+    sv = [np.concatenate([[0, 1, 2, 3], rng.choice(np.arange(4, n), 200, replace=False)])]
+    ss = [np.concatenate([np.arange(64), np.arange(3000, 3040), rng.choice(np.arange(64, n), 30, replace=False)])]
+    iv, cv = lists(sv)
+    is_, cs = lists(ss)
+    a_v, a_s, rec = _run(q.expand(hq, n, 128).contiguous(), k, hq, mask=(iv, cv, is_, cs))
+    ref_v, ref_s, ref_r = _oracle(qb, kb, 1, mask=(iv, cv, is_, cs))
+    _close(a_v, np.broadcast_to(ref_v, (hq, n)))
+    _close(a_s, np.broadcast_to(ref_s, (hq, n)))
     assert np.abs(rec - ref_r).max() <= RECALL_ABS, (rec, ref_r)
 
 

@@ -142,3 +142,69 @@ def test_dense_few_keys(hq, hk, n_q, n):
     torch.cuda.synchronize()
     ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:], kb, vb, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse)
+
+
+# ---- beyond the lines: the kernels that give a row block to one wavefront ----
+@pytest.mark.parametrize("hq,hk,n", [(48, 48, 700), (80, 40, 500), (48, 48, 641), (72, 36, 1025), (64, 16, 513)])
+def test_dense_long_form(hq, hk, n):
+    """vs_dense.hip with one, two and four query heads per workgroup, ragged last tiles; many heads keep n small."""
+    assert not dense_is_short(hq, hk, n, n)
+    (q, k, v), (qb, kb, vb) = make_qkv(1000 + n, hq, hk, n)
+    o, lse = run_dense(q, k, v)
+    ref_o, ref_lse = oracle.dense_attention(qb, kb, vb)
+    check_attention(o, lse, ref_o, ref_lse)
+
+
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q", [(48, 48, 800, 133, 640), (80, 40, 700, 45, 500), (64, 16, 900, 77, 600)])
+def test_dense_long_form_chunk(hq, hk, n, pos0, n_q):
+    assert not dense_is_short(hq, hk, n_q, n)
+    (q, k, v), (qb, kb, vb) = make_qkv(1100 + n, hq, hk, n)
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, k, v, o, lse, pos0=pos0)
+    torch.cuda.synchronize()
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse)
+
+
+@pytest.mark.parametrize("hq,hk,n,per_q,gran", [
+    (48, 48, 333, False, None), (48, 48, 333, False, 32),    # one head a workgroup: tiles of 128 rows, the last of 77
+    (40, 40, 511, False, None),                              # more work queues than one layer has
+    (48, 12, 300, True, None), (48, 12, 300, True, 32),      # one list per query head
+    (160, 80, 150, False, None),                             # 80 work queues: claims look at 64 of them at a time
+    (136, 68, 100, False, 32),
+])
+def test_sparse_long_form(hq, hk, n, per_q, gran):
+    """vs_attention.hip: values against the oracle and exact kept-key sets."""
+    rng = np.random.default_rng(n + hq)
+    (q, k, v), (qb, kb, vb) = make_qkv(1200 + n + hq, hq, hk, n)
+    heads = hq if per_q else hk
+    iv, cv = lists([rng.choice(n, size=int(rng.integers(1, n // 4)), replace=False) for _ in range(heads)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=int(rng.integers(1, n // 8)), replace=False)]))
+                     for _ in range(heads)])
+    assert not sparse_is_short(hq, hk, n, n, iv.shape[1] + is_.shape[1], per_q)
+    o, lse, _ = run_sparse(q, k, v, iv, cv, is_, cs, granularity=gran)
+    ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, granularity=gran or 1)
+    check_attention(o, lse, ref_o, ref_lse)
+    check_key_set(k, iv, cv, is_, cs, hq, np.arange(n), granularity=gran)
+
+
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q,per_q,gran", [(48, 48, 500, 77, 300, False, None), (48, 12, 400, 45, 333, True, None),
+                                                         (48, 48, 500, 160, 301, False, 32)])
+def test_sparse_long_form_chunk(hq, hk, n, pos0, n_q, per_q, gran):
+    rng = np.random.default_rng(n + pos0)
+    (q, k, v), (qb, kb, vb) = make_qkv(1300 + n, hq, hk, n)
+    heads = hq if per_q else hk
+    iv, cv = lists([rng.choice(n, size=n // 9, replace=False) for _ in range(heads)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=n // 14, replace=False)])) for _ in range(heads)])
+    assert not sparse_is_short(hq, hk, n_q, n, iv.shape[1] + is_.shape[1], per_q)
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, heads, n), dtype=torch.uint8, device="cuda")
+    vs.sparse_prefill(qc, k, v, f(iv), f(cv), f(is_), f(cs), o, lse, ws, slash_granularity=gran, pos0=pos0)
+    torch.cuda.synchronize()
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:pos0 + n_q], kb, vb, iv, cv, is_, cs, granularity=gran or 1, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse)
