@@ -87,63 +87,55 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     // large workgroups (measured with 160 KB / 512 threads: 23 % of the kernel at 128k).  There is
     // one queue of units per KV head.  A workgroup starts in the queue of head (its XCD number) % kv_heads, so an XCD's
     // L2 mostly sees one head's K / V, and moves on to the next queue when its own is empty, so that heads with a
-    // larger budget do not become the critical path.  Every wavefront leaves the loop at the same point.  (Without
-    // counters: one workgroup per unit, heads rotated over the XCDs.)
-    int bid = blockIdx.x;
-    int queue = 0;
+    // larger budget do not become the critical path.  Every wavefront leaves the loop at the same point.
     // statistics of this workgroup over all its units, added to the workspace counters once, at the end: one atomic per
     // unit on the same three words from every workgroup of the chip serialises in the memory system (measured: a floor
     // of 75 ns per unit of work, 2.4 ms at 128k, whatever the unit's size)
     unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
     const int units_per_head = p.work_total / p.kv_heads;
-    if (p.work_counter) {
-        queue = static_cast<int>(__builtin_amdgcn_s_getreg((20) | (0 << 6) | (3 << 11)) & 0xf) % p.kv_heads;   // XCC_ID
-        bid = -1;
-    }
+    int queue = static_cast<int>(__builtin_amdgcn_s_getreg((20) | (0 << 6) | (3 << 11)) & 0xf) % p.kv_heads;   // XCC_ID
     for (;;) {
-    if (p.work_counter) {
-        __syncthreads();                                     // LDS and the slots below are free again
-        if (threadIdx.x < 64) {
-            // wavefront 0: the own queue first; when it is empty, look at all counters with one load and try only queues that
-            // have units left (a stale value costs one vain attempt).  Every workgroup that walked all queues with atomics at
-            // the end, on counters in one cache line, was 4096 atomics of ~12 ns in a row: the larger part of a small call.
-            const int ln = threadIdx.x;
-            int q = queue, unit = -1;
-            auto claim = [&](int which) -> int {
-                int u = 0;
-                if (ln == 0) u = static_cast<int>(atomicAdd(p.work_counter + which * p.work_stride, 1u));
-                return __builtin_amdgcn_readfirstlane(u);
-            };
-            int u = claim(q);
-            if (u < units_per_head) unit = u;
-            for (int base = 0; unit < 0 && base < p.kv_heads; base += 64) {
-                // head (queue + 1 + base + lane) modulo the number of heads
-                const int off = base + ln;
-                const int head = (queue + 1 + off) % p.kv_heads;
-                const bool some = off < p.kv_heads - 1 &&
-                                  static_cast<int>(__hip_atomic_load(p.work_counter + head * p.work_stride, __ATOMIC_RELAXED,
-                                                                     __HIP_MEMORY_SCOPE_AGENT)) < units_per_head;
-                uint64_t left = __ballot(some);
-                while (left != 0ull && unit < 0) {
-                    const int l = __builtin_ctzll(left);
-                    left &= left - 1;
-                    q = (queue + 1 + base + l) % p.kv_heads;
-                    u = claim(q);
-                    if (u < units_per_head) unit = u;
-                }
-            }
-            if (ln == 0) {
-                wtot[31] = unit;
-                wtot[30] = q;
+    __syncthreads();                                         // LDS and the slots below are free again
+    if (threadIdx.x < 64) {
+        // wavefront 0: the own queue first; when it is empty, look at all counters with one load and try only queues that
+        // have units left (a stale value costs one vain attempt).  Every workgroup that walked all queues with atomics at
+        // the end, on counters in one cache line, was 4096 atomics of ~12 ns in a row: the larger part of a small call.
+        const int ln = threadIdx.x;
+        int q = queue, claimed = -1;
+        auto claim = [&](int which) -> int {
+            int u = 0;
+            if (ln == 0) u = static_cast<int>(atomicAdd(p.work_counter + which * p.work_stride, 1u));
+            return __builtin_amdgcn_readfirstlane(u);
+        };
+        int u = claim(q);
+        if (u < units_per_head) claimed = u;
+        for (int base = 0; claimed < 0 && base < p.kv_heads; base += 64) {
+            // head (queue + 1 + base + lane) modulo the number of heads
+            const int off = base + ln;
+            const int head = (queue + 1 + off) % p.kv_heads;
+            const bool some = off < p.kv_heads - 1 &&
+                              static_cast<int>(__hip_atomic_load(p.work_counter + head * p.work_stride, __ATOMIC_RELAXED,
+                                                                 __HIP_MEMORY_SCOPE_AGENT)) < units_per_head;
+            uint64_t left = __ballot(some);
+            while (left != 0ull && claimed < 0) {
+                const int l = __builtin_ctzll(left);
+                left &= left - 1;
+                q = (queue + 1 + base + l) % p.kv_heads;
+                u = claim(q);
+                if (u < units_per_head) claimed = u;
             }
         }
-        __syncthreads();
-        queue = __builtin_amdgcn_readfirstlane(wtot[30]);
-        const int unit = __builtin_amdgcn_readfirstlane(wtot[31]);
-        if (unit < 0) break;
-        bid = unit * p.kv_heads;                             // rest = unit; the head comes from the queue
+        if (ln == 0) {
+            wtot[31] = claimed;
+            wtot[30] = q;
+        }
     }
-    if (bid >= p.work_total) break;
+    __syncthreads();
+    int none = 0;
+    asm volatile("" : "+v"(none));                           // (the address of the slots, kept over the units, was spilled)
+    queue = __builtin_amdgcn_readfirstlane(wtot[30 + none]);
+    const int unit = __builtin_amdgcn_readfirstlane(wtot[31 + none]);
+    if (unit < 0) break;
     // The thread number is made opaque once per unit: every per-thread constant below is then recomputed per unit
     // instead of being carried (and spilled) across the register-hungry loops of the previous unit.
     int tid = threadIdx.x;
@@ -151,11 +143,10 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qi = lane & 31, hh = lane >> 5;
-    const int rest = bid / p.kv_heads;
-    const int g = p.work_counter ? queue : (bid + rest) % p.kv_heads;
+    const int g = queue;
     const int hchunks = p.group / p.hc;
-    const int hchunk = rest % hchunks;
-    const int tile = p.tiles - 1 - rest / hchunks;          // longest tiles first
+    const int hchunk = unit % hchunks;
+    const int tile = p.tiles - 1 - unit / hchunks;          // longest tiles first
     const int BQ = 32 * kWaves / p.hc;
     const int nsub = BQ >> 5;
     const int i0 = p.pos0 + tile * BQ;                      // positions are absolute; the tile grid starts at the chunk
@@ -646,7 +637,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         if (row < n_pos && p.lse && hh == 0)
             p.lse[static_cast<size_t>(my_head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_run * p.scale + __logf(l_tot) : NEG_INF;
     }
-    if (!p.work_counter) break;
     }
     if (p.tile_counter && (threadIdx.x & 63) == 0 && tiles_done) atomicAdd(p.tile_counter, static_cast<unsigned long long>(tiles_done));
     if (p.tile_counter && threadIdx.x == 0) {
@@ -854,8 +844,7 @@ int launch_attention(AttnParams& p, hipStream_t stream) {
     const long long blocks = static_cast<long long>(p.kv_heads) * (p.group / p.hc) * p.tiles;
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
     p.work_total = static_cast<int>(blocks);
-    long long launch = blocks;
-    if (p.work_counter) launch = blocks < 2 * info.cus ? blocks : 2 * info.cus;   // two workgroups per compute unit
+    const long long launch = blocks < 2 * info.cus ? blocks : 2 * info.cus;   // two workgroups per compute unit
     hipLaunchKernelGGL(vs_attention_kernel, dim3(static_cast<unsigned>(launch)), dim3(kThreads), kLdsBytes, stream, p);
     VS_LAUNCH_CHECK();
     return VS_OK;

@@ -37,7 +37,7 @@ struct AttnParams {
     int nq32;                       // entries per head of ndiag and ncol32
     const int32_t* vfirst;          // per head: position of the first non-negative entry of the column list
     unsigned long long* tile_counter;
-    unsigned int* work_counter;     // persistent launch: next unit of every KV head's queue (zero at launch); null: one unit per workgroup
+    unsigned int* work_counter;     // persistent launch: next unit of every KV head's queue (zero at launch)
     int work_stride;                // counters of consecutive KV heads are this many words apart
     int work_total;                 // units of work (query tiles x KV heads x head chunks)
 };

@@ -410,7 +410,6 @@ int launch_dense(AttnParams& p, hipStream_t stream) {
     // to the 8 XCDs round-robin, so KV head = block % kv_heads keeps a head's K / V in one XCD's L2
     const long long blocks = static_cast<long long>(p.kv_heads) * (p.group / p.hc) * p.tiles;
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
-    p.work_total = static_cast<int>(blocks);
     hipLaunchKernelGGL(vs_dense_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), kSmemBytes, stream, p);
     VS_LAUNCH_CHECK();
     return VS_OK;
