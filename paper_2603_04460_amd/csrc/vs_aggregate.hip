@@ -37,9 +37,6 @@
 #include <math.h>
 #include <stdint.h>
 
-#include <type_traits>
-#include <utility>
-
 #include "vs_attn_device.h"
 #include "vs_common.h"
 #include "vs_device.h"
@@ -77,16 +74,6 @@ struct SweepParams {
     int sw, vw, index_per_q;
     int parts;                      // column sweep: workgroups that share the streamed rows of one group of resident rows
 };
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
-template <int... I, typename F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
-}
 
 // x moved down by S lanes (row_shl) or up by S lanes (row_shr) inside every row of 16 lanes; lanes without a source get 0
 template <int CTRL>

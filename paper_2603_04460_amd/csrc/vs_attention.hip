@@ -188,8 +188,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     const int st_row = tid >> 4;
     // thread (wavefront w, lane L) fills piece L of groups w and w + 4 of a tile: rows 4w + L/16 (= st_row) and 16 more;
     // which 16-byte chunk of the row that piece holds follows from the rotations above
-    typedef const __attribute__((address_space(1))) void* gptr_t;
-    typedef __attribute__((address_space(3))) void* lptr_t;
     const int st_rho = (lane >> 4) & 3;
     const int st_ck = 4 * ((lane >> 2) & 3) + (((lane & 3) - st_rho) & 3);          // K chunk of this piece
     const int st_cv = 4 * ((((lane >> 2) & 3) - st_rho) & 3) + (lane & 3);          // V chunk of this piece

@@ -1,6 +1,6 @@
-// Device code shared by the two attention kernels of libvsprefill (sparse vertical-slash and dense causal):
-// MFMA fragment types, the LDS tile layout that both stage K / V with, the launch parameters and the
-// mask / staging primitives.
+// Device code shared by the attention kernels of libvsprefill (sparse vertical-slash, dense causal, few row blocks) and, for the
+// tile layout, the aggregation sweeps: MFMA fragment types, the LDS tile layout that they stage K / V with, the launch
+// parameters and the mask / staging primitives.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <limits.h>
@@ -8,6 +8,7 @@
 #include <stdint.h>
 
 #include "vs_common.h"
+#include "vs_wave.h"
 
 namespace vs {
 
@@ -56,8 +57,6 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4t __attribute__((__vector_size__(4 * sizeof(__bf16))));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kD = 128;
@@ -78,11 +77,6 @@ using vs::AttnParams;
 __device__ __forceinline__ float half_swap_max(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-
-__device__ __forceinline__ float half_swap_sum(float x) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
@@ -159,17 +153,7 @@ __device__ __forceinline__ uint4 tile_record(int gran, int n_pos, int sub_i0, in
                       (live ? 1u : 0u) | (need ? 2u : 0u) | (static_cast<uint32_t>(b) << 2));
 }
 
-// 16 bytes per lane from global memory straight into LDS: lane L's piece lands at lds_base + 16 L (lds_base is
-// wave-uniform).  Written as an instruction rather than through the builtin: the compiler orders every later LDS read
-// behind a builtin load it cannot tell apart (a full vmcnt wait in the middle of the pipeline); here the kernel itself
-// waits (vmcnt) before the barrier that publishes a stage.
-__device__ __forceinline__ void lds_load16(const void* gsrc, const void* lds_base) {
-    const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
-        (const __attribute__((address_space(3))) void*)lds_base));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(base), "v"(gsrc) : "memory", "m0");
-}
-
-// the same with a wave-uniform base pointer and a 32-bit per-lane byte offset: no address arithmetic per lane
+// lds_load16 with a wave-uniform base pointer and a 32-bit per-lane byte offset: no address arithmetic per lane
 __device__ __forceinline__ void lds_load16s(uint32_t voff, const void* sbase, const void* lds_base) {
     const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (const __attribute__((address_space(3))) void*)lds_base));

@@ -22,9 +22,6 @@
 #include <math.h>
 #include <stdint.h>
 
-#include <type_traits>
-#include <utility>
-
 #include "vs_common.h"
 #include "vs_wave.h"
 
@@ -47,28 +44,6 @@ constexpr size_t kVecOff = kXBufs * kXBytes;                            // b_U, 
 constexpr size_t kRedOff = kVecOff + 3 * kUnitsPerWg * 4;          // two parities x wavefronts x tokens x (v, s)
 constexpr size_t kSmemBytes = kRedOff + 2 * kWaves * kTokTile * 8;
 
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// two fp32 values -> bf16 (nearest even), the first in the low half
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    const f32x2 two = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
-}
-
-// 16 bytes per lane from global memory straight into LDS: lane L's piece lands at lds_base + 16 L (lds_base is
-// wave-uniform).  The loads complete in the background; the kernel waits (vmcnt) before the barrier that publishes a tile.
-__device__ __forceinline__ void lds_load16(const void* gsrc, const void* lds_base) {
-    const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
-        (const __attribute__((address_space(3))) void*)lds_base));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(base), "v"(gsrc) : "memory", "m0");
-}
-
-__device__ __forceinline__ float half_swap_sum(float x) {
-    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 // GELU (erf form) = x Phi(x) with the normal distribution function written as a logistic function of an odd polynomial,
 // Phi(x) = 1 / (1 + exp(-x P(x^2))), P of degree 4 fitted (minimax over |x| <= 8, own fit) so that x Phi(x) is within
 // 3.1e-6 of the exact value everywhere; beyond the fitted range the leading coefficient keeps the argument growing with
@@ -84,18 +59,6 @@ __device__ __forceinline__ float gelu_logistic(float x) {
     p = fmaf(p, x2, kL * 0.07293742830114522f);
     p = fmaf(p, x2, kL * 1.5956563098014116f);
     return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(x * p));
-}
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>): a loop whose counter is a constant in every iteration
-// by construction (an unrolling pragma is a request; when it is not honoured, register arrays indexed by the counter go
-// to scratch memory)
-template <int... I, typename F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
 }
 
 struct IndexerParams {

@@ -14,6 +14,7 @@
 #include <stdint.h>
 
 #include "vs_common.h"
+#include "vs_wave.h"
 
 namespace {
 
@@ -33,14 +34,6 @@ constexpr int kThreads = 256;
 constexpr int kPositions = kThreads / 16;      // per workgroup
 constexpr int kSmallPositions = kThreads / 64; // the same, one plane per thread
 constexpr int kBatch = 4;                      // heads whose loads are in flight together
-
-// bf16 pair of two fp32 values (nearest even), a in the low half
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    const f32x2 two = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
-}
 
 // (a, b) -> (a c - b s, a s + b c); a, b and the results are bf16 bit patterns in the low halves
 __device__ __forceinline__ void rotate(uint32_t& a, uint32_t& b, double c, double s, float cf, float sf) {

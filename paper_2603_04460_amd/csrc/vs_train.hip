@@ -19,18 +19,14 @@
 #include <math.h>
 #include <stdint.h>
 
-#include <type_traits>
-#include <utility>
-
 #include "vs_common.h"
+#include "vs_wave.h"
 
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4t __attribute__((__vector_size__(4 * sizeof(__bf16))));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 256;
 constexpr int kUnitsPerWg = 128;               // 4 wavefronts x 32 hidden units
@@ -132,24 +128,6 @@ struct TrainParams {
     int partials;                   // those with a block: workgroup w makes w, w + chunks, .., one after the other
 };
 
-// 16 bytes per lane from global memory straight into LDS: lane L's piece lands at lds_base + 16 L (lds_base is
-// wave-uniform).  The loads complete in the background; the kernel waits (vmcnt) before the barrier that publishes a tile.
-__device__ __forceinline__ void lds_load16(const void* gsrc, const void* lds_base) {
-    const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
-        (const __attribute__((address_space(3))) void*)lds_base));
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(base), "v"(gsrc) : "memory", "m0");
-}
-
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>)
-template <int... I, typename F>
-__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) {
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-    static_for_impl(std::make_integer_sequence<int, N>{}, static_cast<F&&>(f));
-}
-
 // Matrix and vector work of a block are about equal (64 matrix instructions of 32 clocks against ~500 vector instructions
 // for the 16 tokens of a lane: GELU with its slope, the logit gradients, the split into two bf16 terms), a workgroup has
 // one wavefront per SIMD, and a wavefront issues in order: done one after the other, with the loads of a block waited for
@@ -193,10 +171,6 @@ __global__ __launch_bounds__(kThreads, 1) void train_backward_kernel(const Train
         for (int e = 0; e < 16; ++e) dwu[cb][e] = 0.f;
     float s_wv[4] = {0.f, 0.f, 0.f, 0.f}, s_ws[4] = {0.f, 0.f, 0.f, 0.f}, s_bu[4] = {0.f, 0.f, 0.f, 0.f};
 
-    auto half_sum = [](float x) -> float {
-        auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    };
     const uint32_t blocks_per_head = (n + kTokTile - 1) / kTokTile;
     const uint32_t total_blocks = static_cast<uint32_t>(p.heads) * blocks_per_head;              // < 2^31
     const int nsteps = static_cast<int>((total_blocks - chunk + p.chunks - 1) / p.chunks);       // blocks of this workgroup (>= 1)
@@ -426,9 +400,9 @@ __global__ __launch_bounds__(kThreads, 1) void train_backward_kernel(const Train
             if (part < p.partials) last += blocks_of(part);
         }
         if (i == last - 1) {                                 // (also right after the above, where the next one is a single block)
-            const float t_wv = half_sum((s_wv[0] + s_wv[1]) + (s_wv[2] + s_wv[3]));
-            const float t_ws = half_sum((s_ws[0] + s_ws[1]) + (s_ws[2] + s_ws[3]));
-            const float t_bu = half_sum((s_bu[0] + s_bu[1]) + (s_bu[2] + s_bu[3]));
+            const float t_wv = half_swap_sum((s_wv[0] + s_wv[1]) + (s_wv[2] + s_wv[3]));
+            const float t_ws = half_swap_sum((s_ws[0] + s_ws[1]) + (s_ws[2] + s_ws[3]));
+            const float t_bu = half_swap_sum((s_bu[0] + s_bu[1]) + (s_bu[2] + s_bu[3]));
             if (hh == 0) {
                 float* const pv = p.part_vec + static_cast<size_t>(part) * 3 * p.d_h + u;
                 pv[0] = t_wv;
