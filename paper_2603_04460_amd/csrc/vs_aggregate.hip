@@ -68,7 +68,7 @@ struct SweepParams {
     int q_heads, kv_heads, group, n;
     int reduce_group;               // 1: outputs are per KV head (mean over the group's query heads)
     float c;                        // scale * log2(e)
-    float log2_norm;                // log2(n) (+ log2(group) when reducing): folded into the exponent
+    float norm;                     // 1 / n (1 / (n group) when reducing), applied to the finished sums
     const uint32_t* sbit;           // recall only; per index head: bit (o + 64) set iff offset o selected
     const uint32_t* vbit;           // recall only; per index head: bit j set iff column j selected
     int sw, vw, index_per_q;
@@ -105,6 +105,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     const int unit = blockIdx.x / p.q_heads;
     const int grp = COLUMNS ? (PARTS ? unit / p.parts : unit) : ngroups - 1 - unit;
     const int g = h / p.group;
+    const int out_head = p.reduce_group ? g : h;
     const int r0_wg = kRows * grp;
     const int my_r0 = r0_wg + 32 * NB * wave;                // rows my_r0 .. + 31 (block 0) and my_r0 + 32 .. + 63 (block 1)
     const int my_b0 = my_r0 >> 5;
@@ -329,9 +330,9 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     for (int st = 0; st < nstages; ++st) {
         __builtin_amdgcn_s_waitcnt(0x0F70);                  // this wavefront's part of stage st (and the resident rows) has arrived
         if (COLUMNS && tid < 64) {
-            // 2^(c s - lse2 - log2_norm) is the entry of A / (n * heads averaged); rows that do not exist get 2^-inf
+            // 2^(c s - lse2) is the entry of A; rows that do not exist get 2^-inf
             const bool exists = 32 * (t_begin + 2 * st) + tid < n;
-            norm_ring[64 * (st & 1) + tid] = exists ? -fmaf(nreg, p.lse_scale, p.log2_norm) : NEG_INF;
+            norm_ring[64 * (st & 1) + tid] = exists ? -(nreg * p.lse_scale) : NEG_INF;
         }
         uint32_t w[3] = {0u, 0u, 0u};
         if (RECALL) {
@@ -350,7 +351,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             const unsigned low = sw[0], high = sw[1];
             v = half_swap_sum(__uint_as_float(low) + __uint_as_float(high));
             if (lane < 16 && o >= 0 && o < n && v != 0.f)
-                unsafeAtomicAdd(p.a_s + static_cast<size_t>(p.reduce_group ? g : h) * n + o, v);
+                unsafeAtomicAdd(p.a_s + static_cast<size_t>(out_head) * n + o, v * p.norm);
         }
         if (st + 1 < nstages) load_stage(st + 1);
         const int t0 = t_begin + 2 * st;
@@ -372,7 +373,10 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             if (m_a > NEG_INF) l2 += l_a * __builtin_amdgcn_exp2f(m_a - m2);
             if (m_b > NEG_INF) l2 += l_b * __builtin_amdgcn_exp2f(m_b - m2);
             const int row = my_r0 + 32 * b + qi;
-            if (row < n && hh == 0) p.lse2[static_cast<size_t>(h) * n + row] = m2 + __log2f(l2);
+            // the logarithm of the mantissa alone: it is rounded towards zero, by more the larger it is, and with a maximum that
+            // lags by up to 2^8 the sums are large (as m2 + log2(l2) every row's entries came out 1.5e-7 too large, now below 3e-8)
+            const float base = m2 + static_cast<float>(__builtin_amdgcn_frexp_expf(l2));
+            if (row < n && hh == 0) p.lse2[static_cast<size_t>(h) * n + row] = base + __log2f(__builtin_amdgcn_frexp_mantf(l2));
         }
     } else {
         if (my_r0 < n && (!PARTS || my_b0 < t_end)) {
@@ -383,19 +387,18 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         }
         __syncthreads();
         // what is still in the ring: the last 319 offsets the workgroup touched
-        const int out_head = p.reduce_group ? g : h;
         for (int i = tid; i < kGroupRows + 64; i += kThreads) {
             const int o = o_begin + 64 * (nstages - 1) - (kGroupRows - 1) + i;
             if (o >= 0 && o < n) {
                 float v = 0.f;
 #pragma unroll
                 for (int r = 0; r < kRings; ++r) v += diag[r * kDiagPitch + (o & (kDiagRing - 1))];
-                if (v != 0.f) unsafeAtomicAdd(p.a_s + static_cast<size_t>(out_head) * n + o, v);
+                if (v != 0.f) unsafeAtomicAdd(p.a_s + static_cast<size_t>(out_head) * n + o, v * p.norm);
             }
         }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const float cs = half_swap_sum(col_sum[b]);
+            const float cs = half_swap_sum(col_sum[b]) * p.norm;
             const int key = my_r0 + 32 * b + qi;
             if (key < n && hh == 0) {
                 if (PARTS || p.reduce_group) unsafeAtomicAdd(p.a_v + static_cast<size_t>(out_head) * n + key, cs);
@@ -406,7 +409,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             float r = rec_sum;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) r += __shfl_xor(r, d);
-            if (lane == 0 && r != 0.f) unsafeAtomicAdd(p.recall + out_head, r);
+            if (lane == 0 && r != 0.f) unsafeAtomicAdd(p.recall + out_head, r * p.norm);
         }
     }
 }
@@ -485,7 +488,7 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     p.n = static_cast<int>(n);
     p.reduce_group = (out_heads != q_heads) ? 1 : 0;
     p.c = scale * 1.4426950408889634f;
-    p.log2_norm = log2f(static_cast<float>(n)) + (p.reduce_group ? log2f(static_cast<float>(p.group)) : 0.f);
+    p.norm = static_cast<float>(1.0 / (static_cast<double>(n) * (p.reduce_group ? p.group : 1)));
     p.index_per_q = (want_recall && index_heads == q_heads && q_heads != kv_heads) ? 1 : 0;
 
     const size_t out_count = static_cast<size_t>(out_heads) * n;

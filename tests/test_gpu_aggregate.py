@@ -139,6 +139,17 @@ def test_aggregate_8192_five_heads_elementwise():
     assert np.abs(rec - ref_r).max() <= RECALL_ABS, (rec, ref_r)
 
 
+@pytest.mark.parametrize("hq,hk,n", [(32, 8, 1057), (32, 8, 1024), (8, 2, 1000), (1, 1, 4000), (1, 1, 16000)])
+def test_aggregate_totals_in_single_precision(hq, hk, n):
+    """No systematic error: every head's vectors add up to 1 within 1.5e-7 (a row's normaliser and its entries are rounded by up
+    to 2^-20 relative, but at random, which over n rows leaves some 1e-8; the logarithm of a mantissa, rounded towards zero, is
+    off by up to 2^-24).  Forms with and without shared-out groups."""
+    (q, k, v), _ = make_qkv(540 + n, hq, hk, n, local=True)
+    a_v, a_s, _ = _run(q, k, hq)
+    assert np.abs(a_v.sum(axis=1) - 1).max() <= 1.5e-7, np.abs(a_v.sum(axis=1) - 1).max()
+    assert np.abs(a_s.sum(axis=1) - 1).max() <= 1.5e-7, np.abs(a_s.sum(axis=1) - 1).max()
+
+
 def test_aggregate_group_mean_and_given_lse():
     """out_heads = kv_heads gives the mean over the group's query heads; passing the normalisers of the dense attention
     call instead of recomputing them gives the same vectors."""
