@@ -69,6 +69,9 @@ struct SweepParams {
     int reduce_group;               // 1: outputs are per KV head (mean over the group's query heads)
     float c;                        // scale * log2(e)
     float norm;                     // 1 / n (1 / (n group) when reducing), applied to the finished sums
+    double* recall_acc;             // PARTS: per output head, the recall's sum and the workgroups that have added to it (zero at launch)
+    unsigned int* recall_count;
+    unsigned int recall_shares;     // PARTS: workgroups per output head
     const uint32_t* sbit;           // recall only; per index head: bit (o + 64) set iff offset o selected
     const uint32_t* vbit;           // recall only; per index head: bit j set iff column j selected
     int sw, vw, index_per_q;
@@ -79,6 +82,16 @@ struct SweepParams {
 template <int CTRL>
 __device__ __forceinline__ float row_move(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, true));
+}
+
+// One workgroup's share of a recall, one thread.  The shares of the shared-out form are many (up to 1024 for a single head: 4096
+// float atomics of its wavefronts were off by 9e-7 at n = 16000), so they are added in fp64; who adds the last writes the recall.
+__device__ __forceinline__ void add_recall_share(const SweepParams& p, int out_head, float share) {
+    unsafeAtomicAdd(p.recall_acc + out_head, static_cast<double>(share));
+    const unsigned int before = __hip_atomic_fetch_add(p.recall_count + out_head, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    if (before + 1u == p.recall_shares)
+        p.recall[out_head] = static_cast<float>(__hip_atomic_load(p.recall_acc + out_head, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) *
+                                                static_cast<double>(p.norm));
 }
 
 // COLUMNS == false: row sweep (resident queries, streamed keys).  COLUMNS == true: column sweep.
@@ -131,7 +144,10 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         const int t0 = t_begin;
         t_begin = t0 + 2 * static_cast<int>(static_cast<long long>(stages) * part / p.parts);
         t_end = min(t_end, t0 + 2 * static_cast<int>(static_cast<long long>(stages) * (part + 1) / p.parts));
-        if (t_begin >= t_end) return;
+        if (t_begin >= t_end) {
+            if (RECALL && tid == 0) add_recall_share(p, out_head, 0.f);
+            return;
+        }
         o_begin = 32 * (t_begin - t0);
     }
     const int nstages = (t_end - t_begin + 1) >> 1;
@@ -409,7 +425,13 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             float r = rec_sum;
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) r += __shfl_xor(r, d);
-            if (lane == 0 && r != 0.f) unsafeAtomicAdd(p.recall + out_head, r * p.norm);
+            if constexpr (PARTS) {
+                if (lane == 0) norm_ring[wave] = r;          // (idle since the barrier above)
+                __syncthreads();
+                if (tid == 0) add_recall_share(p, out_head, (norm_ring[0] + norm_ring[1]) + (norm_ring[2] + norm_ring[3]));
+            } else {
+                if (lane == 0 && r != 0.f) unsafeAtomicAdd(p.recall + out_head, r * p.norm);
+            }
         }
     }
 }
@@ -426,7 +448,7 @@ __global__ void clear_kernel(float* a_v, float* a_s, size_t count, float* recall
 }
 
 struct AggWs {
-    size_t lse_off, sbit_off, vbit_off, total;
+    size_t lse_off, sbit_off, vbit_off, acc_off, count_off, total;
     int sw, vw;
 };
 
@@ -437,7 +459,10 @@ AggWs agg_ws_layout(int q_heads, int index_heads, int64_t n) {
     w.lse_off = 0;
     w.sbit_off = vs::round_up(static_cast<size_t>(q_heads) * n * 4, 256);
     w.vbit_off = w.sbit_off + static_cast<size_t>(index_heads) * w.sw * 4;
-    w.total = vs::round_up(w.vbit_off + static_cast<size_t>(index_heads) * w.vw * 4, 256);
+    // (recall wanted: fp64 sums and arrival counts, cleared with the bitmaps)
+    w.acc_off = vs::round_up(w.vbit_off + static_cast<size_t>(index_heads) * w.vw * 4, 8);
+    w.count_off = w.acc_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 8 : 0);
+    w.total = vs::round_up(w.count_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 4 : 0), 256);
     return w;
 }
 
@@ -532,6 +557,11 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     int64_t parts = blocks <= 128 ? 1024 / blocks : 1;
     if (parts > max_parts) parts = max_parts;
     p.parts = static_cast<int>(parts);
+    if (want_recall) {
+        p.recall_acc = reinterpret_cast<double*>(base + w.acc_off);
+        p.recall_count = reinterpret_cast<unsigned int*>(base + w.count_off);
+        p.recall_shares = static_cast<unsigned int>(blocks / q_heads * parts * (p.reduce_group ? p.group : 1));
+    }
     const dim3 grid(static_cast<unsigned>(blocks * parts));
     if (parts > 1) {
         if (want_recall) hipLaunchKernelGGL((vs_sweep_kernel<true, true, true>), grid, dim3(kThreads), 0, st, p);

@@ -150,6 +150,30 @@ def test_aggregate_totals_in_single_precision(hq, hk, n):
     assert np.abs(a_s.sum(axis=1) - 1).max() <= 1.5e-7, np.abs(a_s.sum(axis=1) - 1).max()
 
 
+@pytest.mark.parametrize("hq,hk,n", [(32, 8, 1057), (32, 8, 1024), (8, 2, 1000), (1, 1, 4000), (1, 1, 16000)])
+def test_recall_in_single_precision(hq, hk, n):
+    """The recall is within 4e-7 of the sum in 64 bits (its shares are single-precision sums over up to 64 tiles, 2^-24 each at
+    random), with and without shared-out groups."""
+    (q, k, v), _ = make_qkv(540 + n, hq, hk, n, local=True)
+    rng = np.random.default_rng(n)
+    iv, cv = lists([rng.choice(n, 60, replace=False) for _ in range(hk)])
+    is_, cs = lists([np.unique(np.concatenate([np.arange(20), rng.choice(n, 30, replace=False)])) for _ in range(hk)])
+    _, _, rec = _run(q, k, hq, mask=(iv, cv, is_, cs))
+    j = torch.arange(n, device="cuda")
+    for h in (0, hq - 1):
+        g = h // (hq // hk)
+        col = torch.zeros(n, dtype=torch.bool, device="cuda")
+        off = torch.zeros_like(col)
+        col[torch.from_numpy(iv[g, :cv[g]]).cuda().long()] = True
+        off[torch.from_numpy(is_[g, :cs[g]]).cuda().long()] = True
+        kt, total = k[g].double().t().contiguous(), 0.0
+        for a in range(0, n, 1000):
+            o = j[a:a + 1000].unsqueeze(1) - j.unsqueeze(0)
+            x = (q[h, a:a + 1000].double() @ kt).mul_(128 ** -0.5).masked_fill_(o < 0, -float("inf"))
+            total += torch.softmax(x, 1)[(o >= 0) & (col.unsqueeze(0) | off[o.clamp(min=0)])].sum().item()
+        assert abs(rec[h] - total / n) <= 4e-7 * total / n, (rec[h], total / n, rec[h] * n / total - 1)
+
+
 def test_aggregate_group_mean_and_given_lse():
     """out_heads = kv_heads gives the mean over the group's query heads; passing the normalisers of the dense attention
     call instead of recomputing them gives the same vectors."""
