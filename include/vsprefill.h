@@ -176,7 +176,9 @@ int vs_sparse_prefill_tiled(const void* q, const void* k, const void* v, int q_h
  *
  * Batches: a batch of B sequences of equal length is B * q_heads query heads and B * kv_heads KV heads in the same
  * layout ([B, heads, n, 128] contiguous), with one index list per (sequence, index head); every call of this library
- * accepts that directly because head h always reads KV head h / (q_heads / kv_heads).
+ * accepts that directly because head h always reads KV head h / (q_heads / kv_heads).  Which kernel runs a call follows from
+ * its sizes (heads, rows, keys, list capacities), so the last bits of a head's result may differ between a call on one
+ * sequence and the same heads inside a batch; the same attention call always gives the same bits.
  */
 int vs_sparse_prefill_chunk(const void* q, const void* k, const void* v, int q_heads, int kv_heads, int64_t n_q,
                             int64_t n_kv, int64_t pos0, float scale, const int32_t* idx_v, const int32_t* cnt_v,
@@ -262,7 +264,8 @@ size_t vs_index_train_workspace(int kv_heads, int64_t n, int d_h);
  *   loss        [1] fp32 out (device);  dW_U [256, d_h], db_U, dW_V, dW_S [d_h] fp32 out (device, overwritten)
  * Arithmetic: the inference kernels for the forward; fp64 sums for the loss; the hidden activations are recomputed on
  * the matrix cores (W_U as two bf16 terms), pre-activation gradients enter the second contraction as two bf16 terms,
- * fp32 accumulation per workgroup and a fixed-order fp64 reduction over workgroups: the step is deterministic.
+ * fp32 partial sums over at most 1/256 of the tokens (or 256 tokens) that are added in fp64 in a fixed order: the step is
+ * deterministic.
  */
 int vs_index_train_step(const void* k_bf16, const void* v_bf16, int kv_heads, int64_t n, const vs_indexer_t* w,
                         const float* t_v, const float* t_s, float eps, float* loss, float* dW_U, float* db_U,

@@ -11,7 +11,7 @@
 // against 16 streamed rows, so the reduction over the streamed index is in-lane:
 //   row sweep:    resident = queries, streamed = keys 0 .. diagonal  -> per-lane online max / sum over keys
 //   column sweep: resident = keys,    streamed = queries diagonal .. n-1 -> per-lane sum over queries = column sum, kept
-//                 in a register for the whole sweep and written once.
+//                 in a register for the whole sweep; one store (one atomic where several workgroups or heads share a column).
 // Two workgroups share a compute unit, so that one wavefront's matrix instructions run under the other's vector work.
 // What bounds both sweeps is the vector work per score: scale and subtract, exponential (a quarter of the rate), add; the
 // column sweep also adds every probability to its diagonal.
@@ -551,8 +551,9 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
         VS_LAUNCH_CHECK();
     }
     // Few groups of resident keys (a quarter of the 512 workgroups that run at once): their streamed queries are shared out over
-    // several workgroups of at least eight stages (16 tiles).  One head, n = 16000 809 -> 455 us for the call, 8 heads, n = 4000
-    // 222 -> 160, 32 heads, n = 1000 75 -> 60; at 256 and 512 groups the call was 2 and 5 % slower.
+    // several workgroups of at least eight stages (16 tiles).  One head, n = 16000 809 -> 421 us for the call (the row sweep still
+    // with two blocks per wavefront), 8 heads, n = 4000 222 -> 161, 32 heads, n = 1000 75 -> 60; at 256 and 512 groups the call was
+    // 2 and 5 % slower.
     const int64_t max_parts = ((n + 63) / 64 + 7) / 8;
     int64_t parts = blocks <= 128 ? 1024 / blocks : 1;
     if (parts > max_parts) parts = max_parts;

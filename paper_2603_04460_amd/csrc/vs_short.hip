@@ -8,11 +8,11 @@
 // row block (maximum, sum, O) meet in LDS and every wavefront finishes a quarter of the 128 channels.  Arithmetic, tile
 // layout, records and gather lists are those of vs_attention.hip.
 //
-// Measured (8 KV / 32 query heads unless stated): dense, 500 rows against 32768 keys 727 -> 361 us; 1024 x 1024 32 -> 22 us; one
-// head, 16384 x 16384 364 -> 139 us; sparse, one head, n = 4096, 68 scattered columns and 190 offsets 106 -> 48 us.  A step (four
-// tiles, 64 KB staged) takes 1.07 us while few workgroups run: the chain barrier - fragment reads - scores - softmax - P V of
-// a single tile per wavefront; with a workgroup on every compute unit 1.46 us: only two row blocks use a staged tile, and
-// the L2 then delivers 11 TB/s.
+// Measured (8 KV / 32 query heads unless stated): dense, 500 rows against 32768 keys 728 -> 357 us; 1024 x 1024 32 -> 22 us; one
+// head, 16384 x 16384 364 -> 139 us; sparse, one head, n = 4096, 68 scattered columns and 190 offsets 111 -> 51 us with the
+// preparation.  A step (four tiles, 64 KB staged) takes 1.07 us while few workgroups run: the chain barrier - fragment reads -
+// scores - softmax - P V of a single tile per wavefront; with a workgroup on every compute unit 1.46 us: only two row blocks
+// use a staged tile, and the L2 then delivers 11 TB/s.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <math.h>

@@ -419,7 +419,7 @@ __global__ __launch_bounds__(kThreads, 1) void train_backward_kernel(const Train
 // The gradients: sums of the workgroups' partial results in a fixed order, in fp64.  Outputs 0 .. 256 d_h - 1 are dW_U, then
 // dW_V, dW_S, db_U.  A workgroup makes 64 outputs; its four wavefronts each add a quarter of the partials, eight loads in
 // flight (one thread per output that walks all partials waits for memory 256 times over: 62 us whatever the output's
-// size, four launches; now 7 us in one).  Bound by the memory: the partials are read once.
+// size, four launches; now 13 us in one for 64 MB).  Bound by the memory: the partials are read once.
 constexpr int kRedOut = 64;
 struct TrainOuts {
     float* out[4];                                           // dW_U, dW_V, dW_S, db_U
@@ -472,8 +472,8 @@ TrainWs train_ws_layout(int kv_heads, int64_t n, int d_h) {
     // One workgroup per compute unit over all groups of 128 hidden units (a workgroup fills its compute unit), but partial sums
     // of at most 1 / kPartials of the blocks, or kPartBlocks: a workgroup makes several, one after the other.  With one per
     // workgroup the fp32 sums were 2 (d_h = 256) to 8 times (1024) as long; 8 x 16384 tokens, SiLU / 1024: error of dW_U
-    // against 64 bits 4.06e-6 (128 blocks each), 4.03e-6 now, at 394 and 456 us for the step (256 d_h floats more to write and add
-    // per partial sum); 8 x 32768, GELU / 256 245 and 256 us.  Below 8 blocks nothing is gained: 8 x 4096, SiLU / 1024 3.558e-6 and
+    // against 64 bits 4.06e-6 (128 blocks each), 4.03e-6 now, at 394 and 456 us for the step replayed from a graph (256 d_h floats
+    // more to write and add per partial sum); 8 x 32768, GELU / 256 245 and 256 us.  Below 8 blocks nothing is gained: 8 x 4096, SiLU / 1024 3.558e-6 and
     // 193 us with four blocks each, 3.560e-6 and 157 us with eight (3.569e-6 with 32).
     const int chunks = 256 / ((d_h + kUnitsPerWg - 1) / kUnitsPerWg);
     w.chunks = static_cast<int>(blocks < chunks ? blocks : chunks);
