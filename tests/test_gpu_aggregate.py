@@ -174,6 +174,35 @@ def test_recall_in_single_precision(hq, hk, n):
         assert abs(rec[h] - total / n) <= 4e-7 * total / n, (rec[h], total / n, rec[h] * n / total - 1)
 
 
+def test_recall_repeated_on_one_workspace():
+    """Shared-out groups: the sum and the count of the workgroups' shares start at zero in every call on a workspace, whatever it
+    held, and in every replay of a captured call."""
+    hq, hk, n = 2, 1, 3000
+    (q, k, v), (qb, kb, vb) = make_qkv(77, hq, hk, n, local=True)
+    rng = np.random.default_rng(77)
+    iv, cv = lists([rng.choice(n, 60, replace=False)])
+    is_, cs = lists([np.unique(np.concatenate([np.arange(20), rng.choice(n, 30, replace=False)]))])
+    ref_v, _, ref_r = _oracle(qb, kb, hq, mask=(iv, cv, is_, cs))
+    dl = _dev_lists(iv, cv, is_, cs)
+    ws = torch.full((vs.aggregate_workspace(hq, hk, hk, n),), 0xA5, dtype=torch.uint8, device="cuda")
+    a_v, a_s = torch.empty(hq, n, device="cuda"), torch.empty(hq, n, device="cuda")
+    rec = torch.empty(hq, device="cuda")
+    run = lambda: vs.aggregate(q, k, a_v, a_s, ws, lists=dl, recall=rec)
+    for _ in range(3):
+        run()
+        assert np.abs(rec.cpu().numpy() - ref_r).max() <= 1e-6
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for _ in range(3):
+        rec.fill_(float("nan"))
+        a_v.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.abs(rec.cpu().numpy() - ref_r).max() <= 1e-6
+        _close(a_v.cpu().numpy().astype(np.float64), ref_v)
+
+
 def test_aggregate_group_mean_and_given_lse():
     """out_heads = kv_heads gives the mean over the group's query heads; passing the normalisers of the dense attention
     call instead of recomputing them gives the same vectors."""
