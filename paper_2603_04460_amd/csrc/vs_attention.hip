@@ -45,6 +45,7 @@
 #include <limits.h>
 #include <math.h>
 #include <stdint.h>
+#include <string.h>
 
 #include <mutex>
 #include <type_traits>
@@ -88,9 +89,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     // one queue of units per KV head.  A workgroup starts in the queue of head (its XCD number) % kv_heads, so an XCD's
     // L2 mostly sees one head's K / V, and moves on to the next queue when its own is empty, so that heads with a
     // larger budget do not become the critical path.  Every wavefront leaves the loop at the same point.
-    // statistics of this workgroup over all its units, added to the workspace counters once, at the end: one atomic per
-    // unit on the same three words from every workgroup of the chip serialises in the memory system (measured: a floor
-    // of 75 ns per unit of work, 2.4 ms at 128k, whatever the unit's size)
+    // statistics of this workgroup over all its units, added to the workspace counters once, at the end
     unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
     const int units_per_head = p.work_total / p.kv_heads;
     int queue = static_cast<int>(__builtin_amdgcn_s_getreg((20) | (0 << 6) | (3 << 11)) & 0xf) % p.kv_heads;   // XCC_ID
@@ -636,10 +635,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
             p.lse[static_cast<size_t>(my_head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_run * p.scale + __logf(l_tot) : NEG_INF;
     }
     }
-    if (p.tile_counter && (threadIdx.x & 63) == 0 && tiles_done) atomicAdd(p.tile_counter, static_cast<unsigned long long>(tiles_done));
-    if (p.tile_counter && threadIdx.x == 0) {
-        if (staged_gather) atomicAdd(p.tile_counter + 1, static_cast<unsigned long long>(staged_gather));
-        if (staged_block) atomicAdd(p.tile_counter + 2, static_cast<unsigned long long>(staged_block));
+    // (every wavefront has left the loop behind its barrier: words 0 .. 3 of the scratch are free)
+    if ((threadIdx.x & 63) == 0) wtot[threadIdx.x >> 6] = static_cast<int>(tiles_done);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kWaves; ++w) tiles_done += static_cast<unsigned int>(wtot[w]);
+        add_statistics(p, tiles_done, staged_gather, staged_block);
     }
 }
 
@@ -649,6 +650,9 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
 // binary search of the list per block was a chain of a dozen memory round trips).  Latency bound: n = 131072, 8 heads with
 // 180 offsets and 3300 columns each 19 us with one workgroup per head for both, 7 us now; n = 50021 9.2 -> 5.6.
 constexpr int kPrepThreads = 1024;
+// words of the workspace's head besides the three 8-byte counters: where the statistics slots are (0 slots: the counters are
+// those at the head)
+constexpr int kHeadStatOff = 8, kHeadStatSlots = 9;
 struct PrepParams {
     const int32_t* idx_v;
     const int32_t* cnt_v;
@@ -667,8 +671,11 @@ struct PrepParams {
     int32_t* ncol32;
     int nq32;
     int32_t* vfirst;
-    uint32_t* counters;             // tile counters at the head of the workspace and the work queues' counters, zeroed here
+    uint32_t* counters;             // head of the workspace and the work queues' counters, zeroed here
     int ncounters;
+    unsigned long long* stat;       // statistics slots, zeroed here; where they are is left at the head
+    int stat_slots;
+    uint32_t stat_off;
     uint32_t* queues;
     int nqueues, queue_stride;
 };
@@ -737,7 +744,9 @@ __global__ __launch_bounds__(kPrepThreads) void vs_prepare_kernel(const PrepPara
     }
     // ---- columns ----
     if (ih == 0) {
-        for (int i = tid; i < p.ncounters; i += kPrepThreads) p.counters[i] = 0u;
+        for (int i = tid; i < p.ncounters; i += kPrepThreads)
+            p.counters[i] = i == kHeadStatOff ? p.stat_off : (i == kHeadStatSlots ? static_cast<uint32_t>(p.stat_slots) : 0u);
+        for (int i = tid; i < 3 * p.stat_slots; i += kPrepThreads) p.stat[(i / 3) * vs::kStatStride + i % 3] = 0ull;
         for (int i = tid; i < p.nqueues; i += kPrepThreads) p.queues[static_cast<size_t>(i) * p.queue_stride] = 0u;
     }
     uint32_t* const negative = scan + kPrepThreads / 64;     // entries < 0, a prefix of the list
@@ -769,8 +778,8 @@ __global__ __launch_bounds__(kPrepThreads) void vs_prepare_kernel(const PrepPara
 }
 
 struct SparseWs {
-    size_t counter_off, queue_off, vbit_off, ncol_off, ndiag_off, vfirst_off, dlist_off, wlist_off, total;
-    int sw, vw, nq32, dcap, queue_stride;
+    size_t counter_off, queue_off, stat_off, vbit_off, ncol_off, ndiag_off, vfirst_off, dlist_off, wlist_off, total;
+    int sw, vw, nq32, dcap, queue_stride, stat_slots;
 };
 
 SparseWs sparse_ws_layout(int kv_heads, int index_heads, int64_t n) {
@@ -781,12 +790,17 @@ SparseWs sparse_ws_layout(int kv_heads, int index_heads, int64_t n) {
     w.vw = static_cast<int>(vs::round_up(static_cast<size_t>(nblk + 4), 4));
     w.nq32 = static_cast<int>(nblk);
     w.dcap = static_cast<int>(nblk + 4);
-    w.counter_off = 0;                                      // three 8-byte tile counters
+    w.counter_off = 0;                                      // three 8-byte tile counters, then two words (kHeadStat...)
     // Work-queue counters, one per KV head, 128 bytes apart (atomics on one cache line are served one after the other); very
     // short sequences, which have few units, get what fits.  (The area has the size of the offset bitmaps, which stay in LDS.)
     w.queue_off = vs::round_up(64 + static_cast<size_t>(kv_heads) * 4, 256);
     w.queue_stride = w.sw < 32 ? w.sw : 32;
     w.vbit_off = w.queue_off + ih * w.sw * 4;
+    // the rest of that area: statistics slots (none where it is too small: very short sequences count at the head)
+    constexpr size_t kStatBytes = vs::kStatStride * 8;
+    w.stat_off = vs::round_up(w.queue_off + static_cast<size_t>(kv_heads) * w.queue_stride * 4, kStatBytes);
+    const size_t room = w.stat_off < w.vbit_off ? (w.vbit_off - w.stat_off) / kStatBytes : 0;
+    w.stat_slots = static_cast<int>(room < vs::kMaxStatSlots ? room : vs::kMaxStatSlots);
     w.ncol_off = vs::round_up(w.vbit_off + ih * w.vw * 4, 256);
     w.ndiag_off = vs::round_up(w.ncol_off + ih * w.nq32 * 4, 256);
     w.vfirst_off = vs::round_up(w.ndiag_off + ih * w.nq32 * 4, 256);
@@ -898,7 +912,8 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     p.ncol32 = reinterpret_cast<const int32_t*>(base + w.ncol_off);
     p.nq32 = w.nq32;
     p.vfirst = reinterpret_cast<const int32_t*>(base + w.vfirst_off);
-    p.tile_counter = reinterpret_cast<unsigned long long*>(base + w.counter_off);
+    p.tile_counter = reinterpret_cast<unsigned long long*>(base + (w.stat_slots ? w.stat_off : w.counter_off));
+    p.stat_slots = w.stat_slots ? w.stat_slots : 1;
     // one queue counter per KV head (zeroed by the preparation kernel)
     p.work_counter = reinterpret_cast<unsigned int*>(base + w.queue_off);
     p.work_stride = w.queue_stride;
@@ -929,6 +944,9 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     pp.vfirst = reinterpret_cast<int32_t*>(base + w.vfirst_off);
     pp.counters = reinterpret_cast<uint32_t*>(base + w.counter_off);
     pp.ncounters = 16;
+    pp.stat = reinterpret_cast<unsigned long long*>(base + w.stat_off);
+    pp.stat_slots = w.stat_slots;
+    pp.stat_off = static_cast<uint32_t>(w.stat_off);
     pp.queues = reinterpret_cast<uint32_t*>(base + w.queue_off);
     pp.nqueues = kv_heads;
     pp.queue_stride = w.queue_stride;
@@ -1014,9 +1032,17 @@ int vs_sparse_prefill_counters(const void* ws, size_t ws_bytes, void* stream, in
     if (!ws || ws_bytes < 256 || !counters_host) return VS_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
     VS_HIP(hipStreamSynchronize(st));
-    unsigned long long c[3] = {0, 0, 0};
-    VS_HIP(hipMemcpy(c, ws, sizeof(c), hipMemcpyDeviceToHost));
-    for (int i = 0; i < 3; ++i) counters_host[i] = static_cast<int64_t>(c[i]);
+    unsigned long long head[8];
+    VS_HIP(hipMemcpy(head, ws, sizeof(head), hipMemcpyDeviceToHost));
+    for (int i = 0; i < 3; ++i) counters_host[i] = static_cast<int64_t>(head[i]);
+    uint32_t words[16];
+    memcpy(words, head, sizeof(words));
+    const size_t off = words[kHeadStatOff], slots = words[kHeadStatSlots];
+    if (slots == 0 || slots > vs::kMaxStatSlots || off + slots * vs::kStatStride * 8 > ws_bytes) return VS_OK;
+    unsigned long long c[vs::kMaxStatSlots * vs::kStatStride];
+    VS_HIP(hipMemcpy(c, static_cast<const unsigned char*>(ws) + off, slots * vs::kStatStride * 8, hipMemcpyDeviceToHost));
+    for (size_t s = 0; s < slots; ++s)
+        for (int i = 0; i < 3; ++i) counters_host[i] += static_cast<int64_t>(c[s * vs::kStatStride + i]);
     return VS_OK;
 }
 

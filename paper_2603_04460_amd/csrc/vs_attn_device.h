@@ -37,11 +37,19 @@ struct AttnParams {
     const int32_t* ncol32;          // per head and 32-row block q: number of listed columns <= 32 q + 31
     int nq32;                       // entries per head of ndiag and ncol32
     const int32_t* vfirst;          // per head: position of the first non-negative entry of the column list
-    unsigned long long* tile_counter;
+    unsigned long long* tile_counter;   // statistics: stat_slots groups of three counters, kStatStride apart
+    int stat_slots;
     unsigned int* work_counter;     // persistent launch: next unit of every KV head's queue (zero at launch)
     int work_stride;                // counters of consecutive KV heads are this many words apart
     int work_total;                 // units of work (query tiles x KV heads x head chunks)
 };
+
+// Statistics of a sparse call (executed tiles, tiles staged by gathers and as blocks): a workgroup adds its three sums once, to
+// slot blockIdx % stat_slots.  Atomics on one cache line are served one after the other, ~12 ns each, and hold up whatever else
+// goes to that memory channel: with one atomic per wavefront and counter on a single line the 3072 of a small call took longer
+// than the call (32 / 8 heads, n = 4096: work done after 35 us, kernel 66 us, now 48; the whole pipeline 113 -> 88 us).
+constexpr int kStatStride = 16;                 // 128 bytes
+constexpr int kMaxStatSlots = 64;               // 8 workgroups per slot of a full launch
 
 // Attention for launches with few row blocks (vs_short.hip); p.hc and, for the sparse form, the prepared lists must be those
 // of short_heads() / short_subblocks().
@@ -151,6 +159,13 @@ __device__ __forceinline__ uint4 tile_record(int gran, int n_pos, int sub_i0, in
     if (dlt < -31 || sub_i0 >= n_pos) live = false;          // every key lies after every row / padding rows
     return make_uint4(static_cast<uint32_t>(wz), static_cast<uint32_t>(wz >> 32), kw,
                       (live ? 1u : 0u) | (need ? 2u : 0u) | (static_cast<uint32_t>(b) << 2));
+}
+
+__device__ __forceinline__ void add_statistics(const vs::AttnParams& p, unsigned int tiles, unsigned int gather, unsigned int block) {
+    unsigned long long* const c = p.tile_counter + (blockIdx.x % p.stat_slots) * vs::kStatStride;
+    if (tiles) atomicAdd(c, static_cast<unsigned long long>(tiles));
+    if (gather) atomicAdd(c + 1, static_cast<unsigned long long>(gather));
+    if (block) atomicAdd(c + 2, static_cast<unsigned long long>(block));
 }
 
 // lds_load16 with a wave-uniform base pointer and a 32-bit per-lane byte offset: no address arithmetic per lane

@@ -36,7 +36,8 @@ constexpr size_t kGatherOff = kRecOff + (kListCap + 2 * kRecPad) * 16;
 constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4;
 constexpr size_t kPartOff = 0;                 // after the last stage: O of the 8 wavefronts, 64 registers x 64 lanes each
 constexpr size_t kStatOff = 8 * 64 * 64 * 4;   // (maximum, sum) per wavefront and lane
-static_assert(kStatOff + 8 * 64 * 8 <= kRingBytes, "partial results in the idle ring");
+constexpr size_t kDoneOff = kStatOff + 8 * 64 * 8;   // executed tiles per wavefront
+static_assert(kDoneOff + 8 * 4 <= kRingBytes, "partial results in the idle ring");
 static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % (32 * kSplits) == 0, "whole stages");
 
@@ -287,7 +288,13 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
 #pragma unroll
         for (int e = 0; e < 16; ++e) part[(wave * 64 + 16 * db + e) * 64 + lane] = oacc[db][e];
     stat[wave * 64 + lane] = make_float2(m_run, half_swap_sum(l_run));
+    unsigned int* const done = reinterpret_cast<unsigned int*>(smem + kDoneOff);
+    if (!DENSE && lane == 0) done[wave] = tiles_done;
     __syncthreads();
+    if (!DENSE && tid == 0) {
+        for (int w = 1; w < kThreads / 64; ++w) tiles_done += done[w];
+        add_statistics(p, tiles_done, staged_gather, staged_block);
+    }
     float m_tot = NEG_INF, l_tot = 0.f, f[kSplits];
 #pragma unroll
     for (int s = 0; s < kSplits; ++s) m_tot = fmaxf(m_tot, stat[(kRowBlocks * s + rb) * 64 + lane].x);
@@ -317,13 +324,6 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
     }
     if (p.lse && split == 0 && hh == 0)
         p.lse[static_cast<size_t>(my_head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_tot * p.scale + __logf(l_tot) : NEG_INF;
-    if constexpr (!DENSE) {
-        if (p.tile_counter && lane == 0 && tiles_done) atomicAdd(p.tile_counter, static_cast<unsigned long long>(tiles_done));
-        if (p.tile_counter && tid == 0) {
-            if (staged_gather) atomicAdd(p.tile_counter + 1, static_cast<unsigned long long>(staged_gather));
-            if (staged_block) atomicAdd(p.tile_counter + 2, static_cast<unsigned long long>(staged_block));
-        }
-    }
 }
 
 template <bool DENSE>

@@ -329,3 +329,22 @@ def test_key_sets_small_random():
             check_key_set(k, iv, cv, is_, cs, hq, np.arange(n), granularity=gran)
         except AssertionError as e:
             raise AssertionError("case %d: heads %d/%d n %d per_q %s g %s: %s" % (case, hq, hk, n, per_q, gran, e))
+
+
+@pytest.mark.parametrize("hq,hk,n", [(1, 1, 1), (1, 1, 700), (3, 3, 700), (8, 2, 33), (8, 2, 1500), (12, 3, 5000), (40, 40, 1300)])
+def test_tile_statistics(hq, hk, n):
+    """Executed tiles and gathered tiles of lists whose numbers are known: offset 0 and column 0, i.e. the diagonal tile and one
+    gathered tile per row block.  Sizes on both sides of the workspace's statistics slots (none below about 700 positions of one
+    head), with fewer and more workgroups than slots, on a workspace that held other counts."""
+    (q, k, v), _ = make_qkv(31, hq, hk, n, rope=False)
+    zero, one = torch.zeros((hk, 4), dtype=torch.int32, device="cuda"), torch.ones(hk, dtype=torch.int32, device="cuda")
+    ws = torch.full((vs.sparse_prefill_workspace(hq, hk, hk, n),), 0xff, dtype=torch.uint8, device="cuda")
+    o = torch.empty_like(q)
+    blocks = hq * -(-n // 32)
+    for cols in (1, 0, 1):
+        vs.sparse_prefill(q, k, v, zero, one * cols, zero, one, o, None, ws)
+        executed, gathered, staged = vs.sparse_prefill_counters(ws)
+        assert executed == blocks * (1 + cols)
+        assert vs.sparse_prefill_tiles(ws) == executed
+        assert blocks <= 4 * gathered <= 4 * blocks if cols else gathered == 0     # a workgroup has one to four row blocks
+        assert blocks <= 4 * staged
