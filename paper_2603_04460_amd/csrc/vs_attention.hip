@@ -878,22 +878,22 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     p.group = q_heads / kv_heads;
     p.index_per_q = (index_heads == q_heads && q_heads != kv_heads) ? 1 : 0;
     p.hc = heads_per_workgroup(p.group, p.index_per_q != 0);
-    // Few row blocks: the kernel that splits the keys of a row block over wavefronts.
-    // One query head per workgroup (units of 128 rows), heads x positions, columns + offsets.  At 128 units: 64 x 200, 25 + 25 48 us
-    // here, 37 there, 32 x 500, 62 + 62 39 and 41, 16 x 1000, 125 + 125 38 and 42, 8 x 2048, 256 + 256 50 and 43, 4 x 4096, 512 + 512
-    // 61 and 44, 1 x 16384, 1024 + 2048 220 and 92; beyond: 160 units 57 and 45, 43 and 49, 40 and 54, 50 and 55, 62 and 58; 256 units
-    // 60 and 71 (64 x 500), 43 and 74 (32 x 1000), 56 and 78 (16 x 2048), 62 and 82 (8 x 4096), 126 and 140 (1 x 32768).
-    // Several query heads per workgroup (units of 32 or 64 rows): only a short chunk of a long sequence, and the more units there
-    // are the longer the lists have to be for the merging to pay (as far as the host knows: their capacity).  32 / 8 heads, 8192
-    // keys, capacities of 100 / 260 / 388 / 580 / 2116 in all: 96 rows (24 units) 21 / 29 / 32 / 35 / 65 us here, 19 / 22 / 23 / 26 / 41
-    // there; 160 rows (40) 21 / 29 / 33 / 36 / 66 and 23 / 26 / 27 / 30 / 44; 256 rows (64) 22 / 30 / 33 / 37 / 66 and 29 / 31 / 32 / 36 / 50; 384 rows
-    // (96) 24 / 31 / 34 / 39 / 68 and 37 / 39 / 40 / 44 / 58.  4 / 2 heads (a unit has two row blocks of a head, not one), 2048 rows (64):
-    // 23 / 32 / 35 / 41 / 71 and 29 / 31 / 33 / 34 / 46.  Whole sequences of 200 or 500 rows 20 and 26 here, 25 and 42 there.
+    // Few row blocks: the kernels that split the keys of a row block over wavefronts (vs_short.hip).
+    // One query head per workgroup (units of 128 rows), heads x positions, columns + offsets, us here and there.  At 128 units: 64 x 200,
+    // 25 + 25 49 and 23, 32 x 500, 62 + 62 40 and 24, 16 x 1000, 125 + 125 40 and 22, 8 x 2048, 256 + 256 50 and 25, 4 x 4096, 512 + 512 62 and
+    // 30, 1 x 16384, 1024 + 2048 335 and 134; beyond, 256 units: 64 x 500 59 and 36, 16 x 2048 54 and 37, 1 x 32768, 1024 + 2048 119 and 95,
+    // 64 + 128 47 and 38, and 512 units: 1 x 65536, 512 + 512 91 and 114: the line could lie higher than where calls have been dealt so far.
+    // Several query heads per workgroup (units of 32 or 64 rows; there a workgroup per row block, vs::short_lone): only a short chunk of a
+    // long sequence, and the longer the lists the more units.  32 / 8 heads, 8192 keys, capacities of 100 / 260 / 388 / 580 / 2116 in all:
+    // 96 rows (24 units) 21 / 27 / 32 / 34 / 66 us here, 18 / 18 / 17 / 18 / 25 there; 160 rows (40) 20 / 27 / 32 / 34 / 65 and 17 / 17 / 17 / 18 / 25;
+    // 256 rows (64) 20 / 27 / 33 / 34 / 65 and 17 / 17 / 17 / 18 / 27; 384 rows (96) 21 / 27 / 32 / 34 / 66 and 21 / 25 / 26 / 28 / 45.  4 / 2 heads, 2048 rows
+    // (64): 25 / 32 / 37 / 41 / 70 and 17 / 17 / 18 / 19 / 27.  The condition on the capacities is from the time when two row blocks shared a
+    // workgroup there; it is on the safe side.  Whole sequences of 200 or 500 rows 18 and 21 here, 19 and 30 there.
     const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((nq * p.hc + 127) / 128);
     const int64_t capacity = static_cast<int64_t>(cap_v) + cap_s;
     const bool few_rows = p.hc == 1 ? units <= kShortUnits
                                     : units <= kShortUnits / 2 && n >= 4 * nq && n >= 2048 && capacity >= 10 * (units - (p.hc == 4 ? 28 : 44));
-    if (few_rows) p.hc = vs::short_heads(p.hc);
+    if (few_rows) p.hc = 1;
     p.gran = slash_granularity;
     p.n = static_cast<int>(n);
     p.nq = static_cast<int>(nq);
@@ -929,7 +929,7 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     pp.cnt_s = cnt_s;
     pp.cap_s = cap_s;
     pp.n = p.n;
-    pp.nsub = few_rows ? vs::short_subblocks(p.hc) : kWaves / p.hc;
+    pp.nsub = few_rows ? vs::short_subblocks(q_heads, nq) : kWaves / p.hc;
     pp.nblk = w.nq32;
     pp.shift = static_cast<int>(pos0 % 32);
     pp.vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);

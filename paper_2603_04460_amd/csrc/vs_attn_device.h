@@ -51,12 +51,21 @@ struct AttnParams {
 constexpr int kStatStride = 16;                 // 128 bytes
 constexpr int kMaxStatSlots = 64;               // 8 workgroups per slot of a full launch
 
-// Attention for launches with few row blocks (vs_short.hip); p.hc and, for the sparse form, the prepared lists must be those
-// of short_heads() / short_subblocks().
+// Attention for launches with few row blocks (vs_short.hip).  Dense: p.hc, the query heads of a workgroup, is short_heads(); sparse:
+// p.hc is 1 and the lists are prepared for short_subblocks().
 int launch_short_dense(AttnParams& p, hipStream_t stream);
 int launch_short_sparse(AttnParams& p, hipStream_t stream);
-inline int short_heads(int hc) { return hc >= 2 ? 2 : 1; }   // query heads a workgroup takes: its two row blocks
-inline int short_subblocks(int hc) { return 2 / short_heads(hc); }
+inline int short_heads(int hc) { return hc >= 2 ? 2 : 1; }
+// Up to 256 row blocks, one for every compute unit, a workgroup has one row block and its eight wavefronts split the keys; beyond,
+// two row blocks and four wavefronts each.  Two row blocks / one, us: dense, 1 x 8192 (256 row blocks) 74 / 45, 8 / 2 x 1024 (256)
+// 15.4 / 11.6, 8 / 2 heads, 1000 rows of 65536 keys (256) 559 / 360, 64 rows, 32 / 8 heads, of 32768 (64) 280 / 151; sparse, 1 x 8192,
+// 512 + 512 (256) 27.6 / 20.9, 4096 rows of 131072, 1024 + 1024 (128) 48 / 33, 1 x 1000 17.9 / 17.4.  Beyond, the second round of workgroups costs more
+// than the split saves: dense 8 / 2 x 4096 (1024) 52 / 64, 32 / 8 x 500 (512) 11.6 / 13.5, 32 / 8, 500 rows of 32768 (512) 317 / 367;
+// sparse 32 x 500, 62 + 62 (512) 23 / 30, 1 x 32768, 64 + 128 (1024) 38 / 51; long lists still gain (1 x 16384, 1024 + 2048 (512) 135 / 85,
+// 512 + 512 33 / 35; dense 1 x 16384 142 / 104).
+constexpr int kLoneBlocks = 256;
+inline bool short_lone(int q_heads, int64_t nq) { return static_cast<int64_t>(q_heads) * ((nq + 31) / 32) <= kLoneBlocks; }
+inline int short_subblocks(int q_heads, int64_t nq) { return short_lone(q_heads, nq) ? 1 : 2; }
 
 }  // namespace vs
 

@@ -2,17 +2,19 @@
 //
 // The kernels of vs_attention.hip and vs_dense.hip give every row block of 32 query rows to one wavefront, which walks all
 // its keys: a chunk of 500 rows is 64 workgroups on 256 compute units, each as long as the context.  Here a row block's
-// tiles are dealt to four wavefronts.  A workgroup (8 wavefronts, two per SIMD, one workgroup per compute unit) owns two row
-// blocks (two query heads of the KV group, or 64 consecutive rows of one head); a stage is four 32-key tiles, wavefront
-// (s, rb) takes tile s of the stage for row block rb; two stages live in LDS.  At the end the four partial results of a
-// row block (maximum, sum, O) meet in LDS and every wavefront finishes a quarter of the 128 channels.  Arithmetic, tile
-// layout, records and gather lists are those of vs_attention.hip.
+// tiles are dealt to several wavefronts; at the end their partial results (maximum, sum, O) meet in LDS and every wavefront
+// finishes its share of the 128 channels.  A workgroup has 8 wavefronts, two per SIMD, one workgroup per compute unit.
+// Arithmetic, tile layout, records and gather lists are those of vs_attention.hip.
+//   vs_short_kernel  two row blocks (two query heads of the KV group, or 64 consecutive rows of one head) of four wavefronts.  A
+//                    stage is four 32-key tiles, wavefront (s, rb) takes tile s of the stage for row block rb; two stages live in LDS.
+//   vs_lone_kernel   one row block of eight wavefronts, each with LDS buffers of its own (vs::short_lone, at most 256 row blocks).
 //
 // Measured (8 KV / 32 query heads unless stated): dense, 500 rows against 32768 keys 728 -> 357 us; 1024 x 1024 32 -> 22 us; one
-// head, 16384 x 16384 364 -> 139 us; sparse, one head, n = 4096, 68 scattered columns and 190 offsets 111 -> 51 us with the
-// preparation.  A step (four tiles, 64 KB staged) takes 1.07 us while few workgroups run: the chain barrier - fragment reads -
-// scores - softmax - P V of a single tile per wavefront; with a workgroup on every compute unit 1.46 us: only two row blocks
-// use a staged tile, and the L2 then delivers 11 TB/s.
+// head, 16384 x 16384 364 -> 139 us.  A step of vs_short_kernel (four tiles, 64 KB staged) takes 1.07 us while few workgroups run:
+// the chain barrier - fragment reads - scores - softmax - P V of a single tile per wavefront; with a workgroup on every compute
+// unit 1.46 us: only two row blocks use a staged tile, and the L2 then delivers 11 TB/s.
+// vs_lone_kernel: sparse, one head, n = 4096, 68 scattered columns and 190 offsets 51.7 -> 30.4 us with the preparation (111 in
+// vs_attention.hip); dense, one head, 8192 x 8192 74 -> 45 us, 64 rows, 32 / 8 heads, against 32768 keys 280 -> 151 us.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <math.h>
@@ -41,6 +43,176 @@ static_assert(kDoneOff + 8 * 4 <= kRingBytes, "partial results in the idle ring"
 static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % (32 * kSplits) == 0, "whole stages");
 
+// Fragment addresses of a lane in an LDS slot, as in vs_attention.hip.
+struct Fragments {
+    int k_off0, k_off2, v_off[4];
+    typedef __attribute__((address_space(3))) bf16x4t* lds_ptr_t;
+    __device__ __forceinline__ explicit Fragments(int lane) {
+        const int qi = lane & 31, hh = lane >> 5, li = lane & 15, dsel = (lane >> 4) & 1;
+        const int k_row = (qi >> 2) * kGroupBytes + (qi & 3) * 256;
+        k_off0 = k_row + 16 * ((hh + qi) & 3);
+        k_off2 = k_row + 16 * ((hh + qi + 2) & 3);
+        const int v_rho = (li >> 2) & 3;
+        const int v_lane = kTileBytes + hh * kGroupBytes + v_rho * 256 + 32 * dsel + 8 * (li & 3);
+#pragma unroll
+        for (int sgr = 0; sgr < 4; ++sgr) v_off[sgr] = v_lane + 64 * ((sgr + v_rho) & 3);
+    }
+    __device__ __forceinline__ void read_k(const unsigned char* at, bf16x8 (&kf)[8]) const {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk)
+            kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(at + ((kk & 1) ? k_off2 : k_off0) + 64 * (kk >> 1)));
+    }
+    __device__ __forceinline__ void read_v(const unsigned char* at, bf16x8 (&vf)[8]) const {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {                        // j = 2 db + t16: d block db, keys 16 t16 ..
+            const unsigned char* a0 = at + v_off[j >> 1] + 4 * (j & 1) * kGroupBytes;
+            const bf16x4t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0));
+            const bf16x4t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0 + 2 * kGroupBytes));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                vf[j][e] = lo[e];
+                vf[j][4 + e] = hi[e];
+            }
+        }
+    }
+};
+
+// One wavefront's share of a row block: Q, the running maximum and sum, O.
+struct RowBlock {
+    bf16x8 qf[8];
+    f32x16 oacc[4];
+    float m_run, l_run;
+
+    // Q fragments: B operand of S^T = K Q^T; lane holds query qi, d = 16 kk + 8 hh .. +7
+    __device__ __forceinline__ void init(const AttnParams& p, int head, int first, int qi, int hh) {
+        const int row = min(first + qi, p.pos0 + p.nq - 1);  // rows that do not exist are not stored
+        const uint16_t* src = p.q + (static_cast<size_t>(head) * p.nq + (row - p.pos0)) * kD + 8 * hh;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * kk));
+        m_run = -INFINITY;
+        l_run = 0.f;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
+    }
+    // Scores of a tile, two chains of matrix instructions: add() gives the sum, behind whatever the caller has put in between
+    struct Scores {
+        f32x16 a, b;
+        __device__ __forceinline__ void add() {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) a[e] += b[e];
+        }
+    };
+    __device__ __forceinline__ void scores(const bf16x8 (&kf)[8], Scores& s) const {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s.a[e] = s.b[e] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; kk += 2) {
+            s.a = mfma32(kf[kk], qf[kk], s.a);
+            s.b = mfma32(kf[kk + 1], qf[kk + 1], s.b);
+        }
+    }
+    __device__ __forceinline__ void softmax(const AttnParams& p, const f32x16& sa, bf16x8 (&pb)[2]) {
+        float mx = fmaxf(fmaxf(sa[0], sa[1]), sa[2]);
+#pragma unroll
+        for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, sa[e]), sa[e + 1]);
+        const float m_new = fmaxf(m_run, half_swap_max(fmaxf(mx, sa[15])));
+        if (__ballot((m_new - m_run) * p.c > kRescaleThreshold)) {   // false when both are -inf
+            const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * p.c);
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+            l_run *= alpha;
+            m_run = m_new;
+        }
+        const float mc = (m_run == -INFINITY) ? 0.f : m_run * p.c;
+        float lsum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            const float x0 = __builtin_amdgcn_exp2f(fmaf(sa[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(sa[e + 1], p.c, -mc));
+            lsum[0] += x0;
+            lsum[1] += x1;
+            const f32x2 two = {x0, x1};
+            const bf16x2 r = __builtin_convertvector(two, bf16x2);
+            pb[e >> 3][e & 7] = r[0];
+            pb[e >> 3][(e & 7) + 1] = r[1];
+        }
+        l_run += lsum[0] + lsum[1];
+    }
+    __device__ __forceinline__ void accumulate(const bf16x8 (&vf)[8], const bf16x8 (&pb)[2]) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int db = 0; db < 4; ++db) oacc[db] = mfma32(vf[2 * db + t], pb[t], oacc[db]);
+    }
+    // The partial results of a row block meet in LDS (every tile buffer is idle) and each of its SPLITS wavefronts
+    // (first, first + stride, ...) finishes 128 / SPLITS channels.  done: executed tiles of this wavefront; their sum over the workgroup in
+    // thread 0 afterwards (null: none).
+    template <int SPLITS>
+    __device__ __forceinline__ void merge(const AttnParams& p, unsigned char* smem, int first, int stride, int split, int head, int first_row,
+                                          unsigned int* tiles) {
+        const int tid = threadIdx.x, lane = tid & 63, qi = lane & 31, hh = lane >> 5;
+        const int wave = first + stride * split;
+        float* const part = reinterpret_cast<float*>(smem + kPartOff);
+        float2* const stat = reinterpret_cast<float2*>(smem + kStatOff);
+        unsigned int* const done = reinterpret_cast<unsigned int*>(smem + kDoneOff);
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) part[(wave * 64 + 16 * db + e) * 64 + lane] = oacc[db][e];
+        stat[wave * 64 + lane] = make_float2(m_run, half_swap_sum(l_run));
+        if (tiles && lane == 0) done[wave] = *tiles;
+        __syncthreads();
+        if (tiles && tid == 0)
+            for (int w = 1; w < kThreads / 64; ++w) *tiles += done[w];
+        float m_tot = -INFINITY, l_tot = 0.f, f[SPLITS];
+#pragma unroll
+        for (int s = 0; s < SPLITS; ++s) m_tot = fmaxf(m_tot, stat[(stride * s + first) * 64 + lane].x);
+#pragma unroll
+        for (int s = 0; s < SPLITS; ++s) {
+            const float2 x = stat[(stride * s + first) * 64 + lane];
+            f[s] = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m_tot) * p.c);
+            l_tot = fmaf(x.y, f[s], l_tot);
+        }
+        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+        const int row = first_row + qi;
+        if (row >= p.pos0 + p.nq) return;
+        constexpr int kRegs = 64 / SPLITS;                   // accumulator registers that a wavefront finishes: four are 8 bytes of a row
+        const int reg0 = kRegs * split;
+        uint16_t* const dst = p.o + (static_cast<size_t>(head) * p.nq + (row - p.pos0)) * kD + 2 * reg0 + 4 * hh;
+#pragma unroll
+        for (int a = 0; a < kRegs / 4; ++a) {
+            float x[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < SPLITS; ++s)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    x[c] = fmaf(part[((stride * s + first) * 64 + reg0 + 4 * a + c) * 64 + lane], f[s], x[c]);
+            const f32x2 x01 = {x[0] * inv, x[1] * inv}, x23 = {x[2] * inv, x[3] * inv};
+            uint2 out;
+            out.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(x01, bf16x2));
+            out.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(x23, bf16x2));
+            *reinterpret_cast<uint2*>(dst + 8 * a) = out;
+        }
+        if (p.lse && split == 0 && hh == 0)
+            p.lse[static_cast<size_t>(head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_tot * p.scale + __logf(l_tot) : -INFINITY;
+    }
+};
+
+// keep-bits (bit 27 - 8a - c of element 4a + c) of a gathered tile: column <= row; cols: the tile's columns from 4 hh on
+__device__ __forceinline__ uint32_t causal_columns(const int* cols, int row) {
+    uint32_t keep = 0u;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+        const int4 c4 = *reinterpret_cast<const int4*>(cols + 8 * a);
+        keep |= (c4.x <= row ? 1u << (27 - 8 * a) : 0u) | (c4.y <= row ? 1u << (26 - 8 * a) : 0u) |
+                (c4.z <= row ? 1u << (25 - 8 * a) : 0u) | (c4.w <= row ? 1u << (24 - 8 * a) : 0u);
+    }
+    return keep;
+}
+
 template <bool DENSE>
 __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -68,21 +240,9 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
     const uint16_t* __restrict__ kbase = p.k + static_cast<size_t>(g) * n * kD;
     const uint16_t* __restrict__ vbase = p.v + static_cast<size_t>(g) * n * kD;
 
-    // Q fragments: B operand of S^T = K Q^T; lane holds query qi, d = 16 kk + 8 hh .. +7
-    bf16x8 qf[8];
-    {
-        const int row = min(my_i0 + qi, n_pos - 1);          // rows that do not exist are not stored
-        const uint16_t* src = p.q + (static_cast<size_t>(my_head) * p.nq + (row - p.pos0)) * kD + 8 * hh;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * kk));
-    }
-    f32x16 oacc[4];
-    float m_run = NEG_INF, l_run = 0.f;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
-
+    RowBlock row_block;
+    row_block.init(p, my_head, my_i0, qi, hh);
+    const Fragments fr(lane);
     // staging: wavefront w fills group w (rows 4 w + L / 16) of the K and of the V tile of every slot of the stage
     const int st_row = tid >> 4;
     const int st_rho = (lane >> 4) & 3;
@@ -94,80 +254,21 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
         lds_load16s(off + st_bk, kbase, dst);
         lds_load16s(off + st_bv, vbase, dst + kTileBytes);
     };
-    // fragment addresses as in vs_attention.hip
-    const int li = lane & 15, dsel = (lane >> 4) & 1;
-    const int k_row = (qi >> 2) * kGroupBytes + (qi & 3) * 256;
-    const int k_off0 = k_row + 16 * ((hh + qi) & 3), k_off2 = k_row + 16 * ((hh + qi + 2) & 3);
-    const int v_rho = (li >> 2) & 3;
-    const int v_lane = kTileBytes + hh * kGroupBytes + v_rho * 256 + 32 * dsel + 8 * (li & 3);
-    int v_off[4];
-#pragma unroll
-    for (int sgr = 0; sgr < 4; ++sgr) v_off[sgr] = v_lane + 64 * ((sgr + v_rho) & 3);
-    typedef __attribute__((address_space(3))) bf16x4t* lds_ptr_t;
-
     // One tile for this wavefront: slot in LDS; need: mask with the keep-bits (bit 27 - 8a - c of element 4a + c) that keep() gives.
     auto compute = [&](int slot, bool need, auto keep) __attribute__((always_inline)) {
         const unsigned char* const at = kvbuf + slot * kSlotBytes;
-        bf16x8 kf[8], vf[8];
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk)
-            kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(at + ((kk & 1) ? k_off2 : k_off0) + 64 * (kk >> 1)));
+        bf16x8 kf[8], vf[8], pb[2];
+        RowBlock::Scores sc;
+        fr.read_k(at, kf);
         __builtin_amdgcn_sched_barrier(0);
-        f32x16 sa, sb;                                       // two chains of matrix instructions
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sa[e] = sb[e] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < 8; kk += 2) {
-            sa = mfma32(kf[kk], qf[kk], sa);
-            sb = mfma32(kf[kk + 1], qf[kk + 1], sb);
-        }
+        row_block.scores(kf, sc);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {                        // j = 2 db + t16: d block db, keys 16 t16 ..
-            const unsigned char* a0 = at + v_off[j >> 1] + 4 * (j & 1) * kGroupBytes;
-            const bf16x4t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0));
-            const bf16x4t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0 + 2 * kGroupBytes));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                vf[j][e] = lo[e];
-                vf[j][4 + e] = hi[e];
-            }
-        }
+        fr.read_v(at, vf);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sa[e] += sb[e];
-        if (need) mask_elements<0>(sa, keep(), __float_as_uint(NEG_INF));
-        float mx = fmaxf(fmaxf(sa[0], sa[1]), sa[2]);
-#pragma unroll
-        for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, sa[e]), sa[e + 1]);
-        const float m_new = fmaxf(m_run, half_swap_max(fmaxf(mx, sa[15])));
-        if (__ballot((m_new - m_run) * p.c > kRescaleThreshold)) {   // false when both are -inf
-            const float alpha = (m_new == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * p.c);
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
-            l_run *= alpha;
-            m_run = m_new;
-        }
-        const float mc = (m_run == NEG_INF) ? 0.f : m_run * p.c;
-        bf16x8 pb[2];
-        float lsum[2] = {0.f, 0.f};
-#pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-            const float x0 = __builtin_amdgcn_exp2f(fmaf(sa[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(sa[e + 1], p.c, -mc));
-            lsum[0] += x0;
-            lsum[1] += x1;
-            const f32x2 two = {x0, x1};
-            const bf16x2 r = __builtin_convertvector(two, bf16x2);
-            pb[e >> 3][e & 7] = r[0];
-            pb[e >> 3][(e & 7) + 1] = r[1];
-        }
-        l_run += lsum[0] + lsum[1];
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int db = 0; db < 4; ++db) oacc[db] = mfma32(vf[2 * db + t], pb[t], oacc[db]);
+        sc.add();
+        if (need) mask_elements<0>(sc.a, keep(), __float_as_uint(NEG_INF));
+        row_block.softmax(p, sc.a, pb);
+        row_block.accumulate(vf, pb);
     };
     // Pipeline over the stages of one phase: load(st, buf) requests the four tiles of stage st; step(st, slot) computes this
     // wavefront's tile of stage st.  One barrier per step publishes stage st and frees the buffer of stage st - 1.
@@ -265,83 +366,191 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
                     const int cmin = __builtin_amdgcn_readfirstlane(cols[0]), cmax = __builtin_amdgcn_readfirstlane(cols[31]);
                     if (!my_rows || cmin > my_i0 + 31) return;               // ascending, INT_MAX padding
                     ++tiles_done;
-                    compute(slot, cmax > my_i0, [&]() __attribute__((always_inline)) {
-                        uint32_t keep = 0u;                  // column <= row
-#pragma unroll
-                        for (int a = 0; a < 4; ++a) {
-                            const int4 c4 = *reinterpret_cast<const int4*>(cols + 8 * a + 4 * hh);
-                            const int row = my_i0 + qi;
-                            keep |= (c4.x <= row ? 1u << (27 - 8 * a) : 0u) | (c4.y <= row ? 1u << (26 - 8 * a) : 0u) |
-                                    (c4.z <= row ? 1u << (25 - 8 * a) : 0u) | (c4.w <= row ? 1u << (24 - 8 * a) : 0u);
-                        }
-                        return keep;
-                    });
+                    compute(slot, cmax > my_i0, [&]() __attribute__((always_inline)) { return causal_columns(cols + 4 * hh, my_i0 + qi); });
                 });
         }
     }
 
-    // ---- the four partial results of a row block meet (the ring is idle: every phase ends with a barrier) ----
-    float* const part = reinterpret_cast<float*>(smem + kPartOff);
-    float2* const stat = reinterpret_cast<float2*>(smem + kStatOff);
+    // (the ring is idle: every phase ends with a barrier)
+    row_block.merge<kSplits>(p, smem, rb, kRowBlocks, split, my_head, my_i0, DENSE ? nullptr : &tiles_done);
+    if (!DENSE && tid == 0) add_statistics(p, tiles_done, staged_gather, staged_block);
+}
+
+// ---- one row block per workgroup ----
+// Launches that do not even fill the chip with row blocks: every wavefront takes every eighth tile of the one row block, through a
+// K and a V buffer of its own that it fills itself.  No barrier in the tile loop and no second buffer: the K buffer is refilled
+// (tile t + 8) as soon as the K fragments of tile t are in registers, the V buffer likewise, so a load has the rest of the step to
+// arrive, and a wavefront that waits leaves the SIMD to the other one.
+constexpr int kLone = kThreads / 64;           // wavefronts = tiles in flight
+constexpr size_t kLoneRing = kLone * kSlotBytes;
+constexpr size_t kLoneRecOff = kLoneRing;
+constexpr size_t kLoneGatherOff = kLoneRecOff + (kListCap + 1) * 16;
+constexpr size_t kLoneLds = kLoneGatherOff + kGatherCap * 4;
+static_assert(kDoneOff + 8 * 4 <= kLoneRing, "partial results in the idle buffers");
+static_assert(kLoneLds <= 160 * 1024, "one workgroup per compute unit");
+static_assert(kGatherCap % 32 == 0, "whole tiles");
+
+template <bool DENSE>
+__global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    uint4* const list_rec = reinterpret_cast<uint4*>(smem + kLoneRecOff);
+    int* const glist = reinterpret_cast<int*>(smem + kLoneGatherOff);
+    const float NEG_INF = -INFINITY;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qi = lane & 31, hh = lane >> 5;
+    const int rest = blockIdx.x / p.kv_heads, g = blockIdx.x % p.kv_heads;
+    const int my_head = g * p.group + rest % p.group;
+    const int my_i0 = p.pos0 + 32 * (p.tiles - 1 - rest / p.group);          // longest row blocks first
+    const int n = p.n, n_pos = p.pos0 + p.nq;
+    const int i_last = min(my_i0 + 32, n_pos) - 1;
+    const uint16_t* __restrict__ kbase = p.k + static_cast<size_t>(g) * n * kD;
+    const uint16_t* __restrict__ vbase = p.v + static_cast<size_t>(g) * n * kD;
+    unsigned char* const slot = smem + wave * kSlotBytes;
+
+    RowBlock rb;
+    rb.init(p, my_head, my_i0, qi, hh);
+    const Fragments fr(lane);
+    // staging: this wavefront fills all eight groups of its tile, lane L the piece of row 4 grp + L / 16
+    const int st_rho = (lane >> 4) & 3;
+    const uint32_t st_bk = static_cast<uint32_t>(16 * (4 * ((lane >> 2) & 3) + (((lane & 3) - st_rho) & 3)));
+    const uint32_t st_bv = static_cast<uint32_t>(16 * (4 * ((((lane >> 2) & 3) - st_rho) & 3) + (lane & 3)));
+    uint32_t off[8];                                         // byte offsets of the rows of the tile that is loaded next
+    auto load = [&](uint32_t piece, const uint16_t* base, unsigned char* dst) __attribute__((always_inline)) {
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+        for (int grp = 0; grp < 8; ++grp) lds_load16s(off[grp] + piece, base, dst + grp * kGroupBytes);
+    };
+    auto block_rows = [&](int b) __attribute__((always_inline)) {            // rows that do not exist are masked
 #pragma unroll
-        for (int e = 0; e < 16; ++e) part[(wave * 64 + 16 * db + e) * 64 + lane] = oacc[db][e];
-    stat[wave * 64 + lane] = make_float2(m_run, half_swap_sum(l_run));
-    unsigned int* const done = reinterpret_cast<unsigned int*>(smem + kDoneOff);
-    if (!DENSE && lane == 0) done[wave] = tiles_done;
-    __syncthreads();
-    if (!DENSE && tid == 0) {
-        for (int w = 1; w < kThreads / 64; ++w) tiles_done += done[w];
-        add_statistics(p, tiles_done, staged_gather, staged_block);
+        for (int grp = 0; grp < 8; ++grp) off[grp] = static_cast<uint32_t>(min(32 * b + 4 * grp + st_rho, n - 1)) << 8;
+    };
+    // Tiles [0, ntiles) of a round, this wavefront's every eighth: rows(t) sets off; need(t): 0 skip, 1 keep whole, 2 masked with
+    // the keep-bits of keep(t)
+    auto run = [&](int ntiles, auto rows, auto need, auto keep) __attribute__((always_inline)) {
+        int t = wave;
+        if (t >= ntiles) return;
+        rows(t);
+        load(st_bk, kbase, slot);
+        load(st_bv, vbase, slot + kTileBytes);
+        for (; t < ntiles; t += kLone) {
+            const bool more = t + kLone < ntiles;
+            const int kind = need(t);
+            if (more) rows(t + kLone);
+            asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // K of tile t (its V is younger)
+            bf16x8 kf[8], vf[8], pb[2];
+            fr.read_k(slot, kf);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (more) load(st_bk, kbase, slot);
+            __builtin_amdgcn_sched_barrier(0);
+            RowBlock::Scores sc;
+            rb.scores(kf, sc);
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // V of tile t
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            fr.read_v(slot, vf);
+            __builtin_amdgcn_sched_barrier(0);
+            sc.add();
+            if (kind == 2) mask_elements<0>(sc.a, keep(t), __float_as_uint(NEG_INF));
+            if (kind) rb.softmax(p, sc.a, pb);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            if (more) load(st_bv, vbase, slot + kTileBytes);
+            __builtin_amdgcn_sched_barrier(0);
+            if (kind) rb.accumulate(vf, pb);
+        }
+    };
+    unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
+    if constexpr (DENSE) {
+        auto dlt = [&](int t) { return my_i0 - 32 * t; };    // offset of (row 0, key 0)
+        run(
+            i_last / 32 + 1, block_rows, [&](int t) __attribute__((always_inline)) { return dlt(t) < -31 ? 0 : dlt(t) < 31 ? 2 : 1; },
+            [&](int t) __attribute__((always_inline)) {
+                const uint64_t w = (kAll63 << (31 - dlt(t))) & kAll63;       // offsets >= 0
+                return static_cast<uint32_t>(w >> (qi + 4 - 4 * hh));
+            });
+    } else {
+        const int ih = p.index_per_q ? my_head : g;
+        const uint32_t* __restrict__ vbit = p.vbit + static_cast<size_t>(ih) * p.vw;
+        const int32_t* __restrict__ iv = p.idx_v + static_cast<size_t>(ih) * p.cap_v;
+        const int32_t* __restrict__ dl = p.dlist + static_cast<size_t>(ih) * p.dcap;
+        const unsigned long long* __restrict__ wl = p.wlist + static_cast<size_t>(ih) * p.dcap * 4;
+        const int qb0 = my_i0 >> 5;
+        const int ndiag = p.ndiag[static_cast<size_t>(ih) * p.nq32 + qb0];
+        const int ncand = p.ncol32[static_cast<size_t>(ih) * p.nq32 + (i_last >> 5)];
+        int cursor = min(p.vfirst[ih], ncand);
+        // rounds of up to kListCap listed blocks and kGatherCap columns; the gathered tiles follow the block tiles
+        for (int rbase = 0; rbase < ndiag || cursor < ncand; rbase += kListCap) {
+            const int nb = max(0, min(kListCap, ndiag - rbase)), count = min(ncand - cursor, kGatherCap);
+            const int ng = (count + 31) >> 5;
+            for (int t = tid; t < nb; t += kThreads) {
+                const int b = qb0 - dl[rbase + t];
+                list_rec[t] = tile_record(p.gran, n_pos, my_i0, b, wl[static_cast<size_t>(rbase + t) * 4], vbit[b]);
+            }
+            for (int t = tid; t < 32 * ng; t += kThreads) glist[t] = t < count ? iv[cursor + t] : INT_MAX;
+            cursor += count;
+            staged_block += static_cast<unsigned int>(nb);
+            staged_gather += static_cast<unsigned int>(ng);
+            __syncthreads();
+            run(
+                nb + ng,
+                [&](int t) __attribute__((always_inline)) {
+                    if (t < nb) {
+                        block_rows(static_cast<int>(__builtin_amdgcn_readfirstlane(list_rec[t].w) >> 2));
+                    } else {
+#pragma unroll
+                        for (int grp = 0; grp < 8; ++grp)
+                            off[grp] = static_cast<uint32_t>(min(glist[32 * (t - nb) + 4 * grp + st_rho], n - 1)) << 8;
+                    }
+                },
+                [&](int t) __attribute__((always_inline)) {
+                    int kind;
+                    if (t < nb) {
+                        const uint32_t fl = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(list_rec[t].w));
+                        kind = fl & 1u ? ((fl & 2u) ? 2 : 1) : 0;
+                    } else {
+                        kind = __builtin_amdgcn_readfirstlane(glist[32 * (t - nb) + 31]) > my_i0 ? 2 : 1;   // ascending, INT_MAX padding
+                    }
+                    tiles_done += kind ? 1u : 0u;
+                    return kind;
+                },
+                [&](int t) __attribute__((always_inline)) {
+                    if (t < nb) {
+                        const uint4 r = list_rec[t];         // one broadcast read
+                        const uint64_t wz = (static_cast<uint64_t>(r.y) << 32) | r.x;
+                        return static_cast<uint32_t>(wz >> (qi + 4 - 4 * hh)) & (__builtin_bitreverse32(r.z) >> (4 - 4 * hh));
+                    }
+                    return causal_columns(glist + 32 * (t - nb) + 4 * hh, my_i0 + qi);
+                });
+            __syncthreads();                                 // the lists are reused
+        }
     }
-    float m_tot = NEG_INF, l_tot = 0.f, f[kSplits];
-#pragma unroll
-    for (int s = 0; s < kSplits; ++s) m_tot = fmaxf(m_tot, stat[(kRowBlocks * s + rb) * 64 + lane].x);
-#pragma unroll
-    for (int s = 0; s < kSplits; ++s) {
-        const float2 x = stat[(kRowBlocks * s + rb) * 64 + lane];
-        f[s] = x.x == NEG_INF ? 0.f : __builtin_amdgcn_exp2f((x.x - m_tot) * p.c);
-        l_tot = fmaf(x.y, f[s], l_tot);
-    }
-    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-    const int row = my_i0 + qi;
-    if (row >= n_pos) return;
-    uint16_t* const dst = p.o + (static_cast<size_t>(my_head) * p.nq + (row - p.pos0)) * kD + 32 * split + 4 * hh;
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        float x[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < kSplits; ++s)
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                x[c] = fmaf(part[((kRowBlocks * s + rb) * 64 + 16 * split + 4 * a + c) * 64 + lane], f[s], x[c]);
-        const f32x2 x01 = {x[0] * inv, x[1] * inv}, x23 = {x[2] * inv, x[3] * inv};
-        uint2 out;
-        out.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(x01, bf16x2));
-        out.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(x23, bf16x2));
-        *reinterpret_cast<uint2*>(dst + 8 * a) = out;
-    }
-    if (p.lse && split == 0 && hh == 0)
-        p.lse[static_cast<size_t>(my_head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_tot * p.scale + __logf(l_tot) : NEG_INF;
+    __syncthreads();                                         // every buffer is idle: the partial results take their place
+    rb.merge<kLone>(p, smem, 0, 1, wave, my_head, my_i0, DENSE ? nullptr : &tiles_done);
+    if (!DENSE && tid == 0) add_statistics(p, tiles_done, staged_gather, staged_block);
 }
 
 template <bool DENSE>
 int launch_short(AttnParams& p, hipStream_t stream) {
     static vs::PerDeviceOnce once;
-    const size_t lds = DENSE ? kRingBytes : kSparseLds;
-    const int rc = once.run(nullptr, [lds](int) -> int {
+    const size_t lds = DENSE ? kRingBytes : kSparseLds, lone_lds = DENSE ? kLoneRing : kLoneLds;
+    const int rc = once.run(nullptr, [lds, lone_lds](int) -> int {
         VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vs_short_kernel<DENSE>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    static_cast<int>(lds)));
+        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vs_lone_kernel<DENSE>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   static_cast<int>(lone_lds)));
         return VS_OK;
     });
     if (rc != VS_OK) return rc;
-    const int BQ = 32 * (kRowBlocks / p.hc);
+    const bool lone = vs::short_lone(p.q_heads, p.nq);
+    if (lone) p.hc = 1;
+    const int BQ = lone ? 32 : 32 * (kRowBlocks / p.hc);
     p.tiles = (p.nq + BQ - 1) / BQ;
     // KV head = block % kv_heads: workgroups are dealt to the 8 XCDs round-robin, so a head's K / V stay in one XCD's L2
     const long long blocks = static_cast<long long>(p.kv_heads) * (p.group / p.hc) * p.tiles;
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(vs_short_kernel<DENSE>, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, stream, p);
+    const dim3 grid(static_cast<unsigned>(blocks)), threads(kThreads);
+    if (lone) hipLaunchKernelGGL(vs_lone_kernel<DENSE>, grid, threads, lone_lds, stream, p);
+    else hipLaunchKernelGGL(vs_short_kernel<DENSE>, grid, threads, lds, stream, p);
     VS_LAUNCH_CHECK();
     return VS_OK;
 }

@@ -208,3 +208,58 @@ def test_sparse_long_form_chunk(hq, hk, n, pos0, n_q, per_q, gran):
     torch.cuda.synchronize()
     ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:pos0 + n_q], kb, vb, iv, cv, is_, cs, granularity=gran or 1, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse)
+
+
+@pytest.mark.parametrize("hq,hk,n,per_q,gran", [
+    (8, 8, 1055, False, None),                               # 264 row blocks: two to a workgroup, the last one alone and ragged
+    (9, 3, 900, False, 32),                                  # a group of three
+    (16, 4, 545, True, None),                                # a mask per query head
+])
+def test_sparse_two_row_blocks(hq, hk, n, per_q, gran):
+    """More than 256 row blocks, at most 128 units: two row blocks share a workgroup; few and many tiles per wavefront."""
+    assert 256 < hq * -(-n // 32) <= 512
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(1500 + n, hq, hk, n)
+    ih = hq if per_q else hk
+    iv, cv = lists([rng.choice(n, size=3 + 40 * (h % 2), replace=False) for h in range(ih)], cap=60)
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=2 + 30 * (h % 3), replace=False)])) for h in range(ih)], cap=70)
+    assert sparse_is_short(hq, hk, n, n, 130, per_q)
+    rows = synth.sample_rows(4, n, 40, 40, 60)
+    if not per_q:
+        check_key_set(k, iv, cv, is_, cs, hq, rows, granularity=gran)
+    o, lse, _ = run_sparse(q, k, v, iv, cv, is_, cs, granularity=gran)
+    ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, rows=rows, granularity=gran or 1)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+@pytest.mark.parametrize("hq,hk,n", [(8, 2, 1056), (8, 2, 1024), (9, 9, 929), (6, 6, 1342)])
+def test_dense_around_the_line_of_row_blocks(hq, hk, n):
+    """256 row blocks (one to a workgroup) and a few more (two: two heads, or 64 rows of one head)."""
+    assert dense_is_short(hq, hk, n, n) and abs(hq * -(-n // 32) - 256) <= 14
+    (q, k, v), (qb, kb, vb) = make_qkv(1600 + n, hq, hk, n)
+    o, lse = run_dense(q, k, v)
+    rows = synth.sample_rows(5, n, 40, 40, 60)
+    ref_o, ref_lse = oracle.dense_attention(qb, kb, vb, rows=rows)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+@pytest.mark.parametrize("hq,hk,n,n_q,gran", [(1, 1, 16384, 333, None), (2, 2, 16416, 96, 32), (4, 1, 9000, 70, None)])
+def test_sparse_lone_row_blocks_several_rounds(hq, hk, n, n_q, gran):
+    """One row block per workgroup: more than 256 listed key blocks and more than 2432 columns, i.e. several rounds of either list,
+    whichever ends first; chunks that start inside a block."""
+    assert hq * -(-n_q // 32) <= 256
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(1700 + hq, hq, hk, n)
+    pos0 = n - n_q
+    iv, cv = lists([rng.choice(n, size=5000 if h == 0 else 40, replace=False) for h in range(hk)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=1500 if hq < 4 else 20, replace=False)])) for _ in range(hk)])
+    assert sparse_is_short(hq, hk, n_q, n, iv.shape[1] + is_.shape[1])
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    qc = q[:, pos0:].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, hk, n), dtype=torch.uint8, device="cuda")
+    vs.sparse_prefill(qc, k, v, f(iv), f(cv), f(is_), f(cs), o, lse, ws, slash_granularity=gran, pos0=pos0)
+    torch.cuda.synchronize()
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:], kb, vb, iv, cv, is_, cs, granularity=gran or 1, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse)
