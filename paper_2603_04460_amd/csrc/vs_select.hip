@@ -1,30 +1,46 @@
 // Budget rule and TopK (Sec. "Adaptive Sparse Index Selection": k_d is the fewest top-ranked scores
-// whose mass reaches tau_d, I_d = TopK(A_d, k_d)), one workgroup per (head, direction).
+// whose mass reaches tau_d, I_d = TopK(A_d, k_d)).
 //
-// Non-negative fp32 scores order like their bit patterns, so the k-th ranked score is found by a
-// most-significant-digit radix descent (12 + 12 + 8 bits) over LDS histograms that carry, per
-// bucket, the element count and the INTEGER mass floor(score * 2^40).  Integer masses make every
-// partial sum exact and order-independent, so the threshold crossing is the same whatever order
-// the wavefronts add in.  Ties at the crossing value are taken in ascending index order.  The
-// selected set, united with the forced leading indices, is then written in ascending order by
-// three coalesced sweeps that use wave ballots for ranks (no atomics on the output path).
+// Non-negative fp32 scores order like their bit patterns, so the k-th ranked score is found by a most-significant-digit radix
+// descent.  A bucket of a pass carries ONE 64-bit weight: the INTEGER mass floor(score * 2^40), or the element count for the fixed
+// budget and for the capacity.  Integer weights make every partial sum exact and independent of the order, so the threshold
+// crossing is the same however the work is split.  The first digit is cut where the scores are, keys >> 19 (16 buckets per octave up
+// to 1.9375, everything above in the last one): its crossing bucket usually holds less than a percent of the scores.  Those, the
+// candidates, are put aside in index order and the remaining digits (10 bits each) only look at them.  Ties at the crossing value
+// are taken in ascending index order.  The selected set, united with the forced leading indices, is then written in ascending order
+// from ballots and counts (no atomics on the output path).
 //
-// Long sequences with a workspace: the same descent split over many workgroups (one per 8192-score chunk of a problem),
-// one kernel per radix pass.  A chunk's histogram is built in LDS and added to the problem's histogram in the workspace
-// with integer atomics (exact, so the sums do not depend on the order); every workgroup of the next kernel scans that
-// histogram for the crossing bucket.  The emission gets its chunk's position from the per-chunk counts of a sweep of
-// its own.  A problem whose selection exceeds the capacity is redone by the single-workgroup kernel.
+// Bound by latency: a few dependent steps, each a round trip to memory or a barrier, and by the instructions of 16 wavefronts on
+// one compute unit, so one wavefront does the scans and the others wait for it.
+//
+// Short problems: one workgroup per (head, direction), select_kernel; up to 8192 scores stay in registers, candidates in LDS.
+// Long ones with a workspace: one workgroup per chunk (8192 scores, at most 16 chunks) and three kernels after one that clears: the
+// histogram of the first digit, added to the problem's in the workspace with integer atomics; the chunk's candidates, appended to
+// the problem's list, and the histogram of their next digit; the last digits, by every workgroup on the problem's candidates, and the
+// emission of its chunk.  (A workgroup that arrives last and finds the crossing value for all saves nothing: making the list visible to
+// it and the others' waiting took 10 us.)  Scores so crowded that the list (a quarter of the scores) does not hold the crossing bucket
+// are read again instead.  A problem whose selection exceeds the capacity is redone by the workgroup of its first chunk.
+//
+// Measured against three passes of 12, 12 and 8 bits over all scores (count and mass apart; long problems in seven kernels), 8 heads,
+// us per call: 131072 scores 48.7 -> 26.2 (32 heads 119 -> 68), 50021 46.0 -> 25.5, 32000 47.4 -> 31.2, 18763 36.5 -> 23.4, 8192
+// 24.4 -> 14.6, 4096 19.2 -> 14.6 (the kernel alone 17.7 -> 9; two launches take the host 14), 2^20 234 -> 108; 131072 equal scores 83 -> 36, within
+// 2 percent of each other 72 -> 71.  The four kernels of 8 x 131072 take 2.3 + 5.4 + 8.7 + 10.0 us.
 #include <hip/hip_runtime.h>
 #include <math.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "vs_common.h"
+#include "vs_wave.h"
 
 namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kWaves = kSelThreads / 64;
-constexpr int kMaxBuckets = 4096;
+constexpr int kTopShift = 19, kTopBuckets = 2048;             // first digit
+constexpr int kDigit = 10, kDigitBuckets = 1 << kDigit;       // digits below
+constexpr int kBatch = 8;                      // scores per lane that are requested together
+constexpr int kMinSplitN = 32768;              // shorter problems stay with one workgroup (fewer launches)
 typedef unsigned long long u64;
 
 struct SelParams {
@@ -37,277 +53,324 @@ struct SelParams {
     int kfix[2], nforced[2], cap[2];
 };
 
-struct SelShared {
-    u64 hist_mass[kMaxBuckets];
-    uint32_t hist_cnt[kMaxBuckets];
-    u64 wave_m[kWaves];
-    uint32_t wave_c[kWaves];
-    uint32_t wave_eq[kWaves], wave_eqf[kWaves], wave_in[kWaves];   // emission: ties, forced ties, entries in without a tie
-    // result of the bucket search
-    uint32_t sel_bucket, eq_c;
-    u64 above_m, eq_m;
-    uint32_t above_c;
-    int status;
-};
-
 __device__ __forceinline__ uint32_t score_key(float x, int& st) {
     if (!(x >= 0.f)) {            // NaN or negative
         st |= VS_STATUS_BAD_SCORE;
         return 0u;
     }
-    return x == 0.f ? 0u : __float_as_uint(x);
+    const uint32_t key = x == 0.f ? 0u : __float_as_uint(x);
+    if (key > 0x3f800000u) st |= VS_STATUS_SATURATED;
+    return key;
+}
+__device__ __forceinline__ uint32_t score_key(float x) {
+    int dummy = 0;
+    return score_key(x, dummy);
 }
 
-__device__ __forceinline__ u64 key_mass(uint32_t key, int& st) {
-    double xd = static_cast<double>(__uint_as_float(key));
-    if (xd > 1.0) {
-        xd = 1.0;
-        st |= VS_STATUS_SATURATED;
+// floor(min(score, 1) * 2^40) from the bits: the significand moved by the exponent
+__device__ __forceinline__ u64 key_mass(uint32_t key) {
+    key = min(key, 0x3f800000u);
+    const uint32_t down = 127u - (key >> 23);
+    return down > 63u ? 0ull : (static_cast<u64>((key & 0x7fffffu) | 0x800000u) << 17) >> down;
+}
+
+__device__ __forceinline__ uint32_t top_bucket(uint32_t key) { return min(key >> kTopShift, static_cast<uint32_t>(kTopBuckets - 1)); }
+
+// A histogram in LDS: R buckets per lane of the scanning wavefront, from the highest bucket down; neighbouring buckets, which the
+// scores crowd into, lie 65 entries apart (different banks), and the scan's reads are conflict-free.
+template <int NB>
+struct Hist {
+    static constexpr int kPerLane = NB / 64, kWords = kPerLane * 65;
+    static __device__ __forceinline__ int slot(uint32_t b) {
+        const uint32_t r = NB - 1 - b;
+        return static_cast<int>((r % kPerLane) * 65 + r / kPerLane);
     }
-    return static_cast<u64>(xd * 1099511627776.0);   // exact power-of-two scaling, truncation
+};
+constexpr int kHistWords = Hist<kTopBuckets>::kWords;
+
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_moved(T x) {
+    if constexpr (sizeof(T) == 8) {
+        const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, ROWS, 0xf, false);
+        const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(x >> 32), CTRL, ROWS, 0xf, false);
+        return (static_cast<u64>(hi) << 32) | lo;
+    } else {
+        return __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, ROWS, 0xf, false);
+    }
+}
+// inclusive sum over the lanes (row shifts, then the last lane of a row and of a half handed on); all lanes active
+template <typename T>
+__device__ __forceinline__ T wave_scan(T x) {
+    x += dpp_moved<0x111, 0xf>(x);
+    x += dpp_moved<0x112, 0xf>(x);
+    x += dpp_moved<0x114, 0xf>(x);
+    x += dpp_moved<0x118, 0xf>(x);
+    x += dpp_moved<0x142, 0xa>(x);
+    x += dpp_moved<0x143, 0xc>(x);
+    return x;
+}
+// the same with the maximum: lane 63 has that of all lanes
+__device__ __forceinline__ uint32_t wave_top(uint32_t x) {
+    x = max(x, dpp_moved<0x111, 0xf>(x));
+    x = max(x, dpp_moved<0x112, 0xf>(x));
+    x = max(x, dpp_moved<0x114, 0xf>(x));
+    x = max(x, dpp_moved<0x118, 0xf>(x));
+    x = max(x, dpp_moved<0x142, 0xa>(x));
+    return max(x, dpp_moved<0x143, 0xc>(x));
+}
+template <typename T>
+__device__ __forceinline__ T lane_value(T x, int lane) {      // lane: wave-uniform
+    const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(x), lane);
+    if constexpr (sizeof(T) == 4) return static_cast<T>(lo);
+    const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(static_cast<u64>(x) >> 32), lane);
+    return static_cast<T>((static_cast<u64>(hi) << 32) | lo);
 }
 
-// Selection state of one (head, direction): elements with key > vstar are in; of those with
-// key == vstar the first `ties` in index order are in.  none: nothing is selected by rank.
-struct Pick {
-    uint32_t vstar;
-    uint32_t ties;
-    bool none;
+// State of a problem's descent.
+struct Descent {
+    u64 target;            // weight that the elements not above the prefix still have to contribute
+    uint32_t bucket;       // crossing bucket of the last digit
+    uint32_t none, all;    // nothing / everything is in by rank
 };
 
-// redo: null, or per problem (head * 2 + dir) non-zero where this kernel has work
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, const int32_t* redo) {
-    __shared__ SelShared sh;
-    const int head = blockIdx.x, dir = blockIdx.y;
-    if (redo && redo[head * 2 + dir] == 0) return;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = p.n;
-    const float* __restrict__ a = p.a[dir] + static_cast<size_t>(head) * n;
-    const int nforced = min(p.nforced[dir], n);
-    const int cap = p.cap[dir];
-    int st = 0;
-    if (tid == 0) sh.status = 0;
-
-    // radix descent.  by_count: rank target is a count (krem) instead of a mass (trem).  tau >= 0 (first descent of the
-    // threshold rule): the first pass sees every element, so its histogram also gives the total mass; the target
-    // ceil(tau * total) is taken from it instead of from a sweep of its own.  first: the first pass also collects the
-    // status bits of the scores.
-    auto descend = [&](bool by_count, bool skip_forced, u64 trem, uint32_t krem, double tau, bool first) -> Pick {
-        Pick pk{0u, 0u, false};
-        if (tau < 0.0 && (by_count ? krem == 0 : trem == 0)) {
-            pk.none = true;
-            return pk;
-        }
-        uint32_t prefix = 0, pmask = 0;
-        const int shifts[3] = {20, 8, 0};
-        const int widths[3] = {12, 12, 8};
-        for (int pass = 0; pass < 3; ++pass) {
-            const int shf = shifts[pass], nb = 1 << widths[pass];
-            for (int b = tid; b < nb; b += kSelThreads) {
-                sh.hist_mass[b] = 0;
-                sh.hist_cnt[b] = 0;
-            }
-            __syncthreads();
-            const bool collect = first && pass == 0;
-            for (int i = tid; i < n; i += kSelThreads) {
-                if (skip_forced && i < nforced) continue;
-                int dummy = 0;
-                const uint32_t key = score_key(a[i], collect ? st : dummy);
-                if ((key & pmask) != prefix) continue;
-                const uint32_t b = (key >> shf) & (nb - 1);
-                atomicAdd(&sh.hist_cnt[b], 1u);
-                if (!by_count) atomicAdd(&sh.hist_mass[b], key_mass(key, collect ? st : dummy));
-                else if (collect) (void)key_mass(key, st);
-            }
-            __syncthreads();
-            // buckets in descending order; thread owns `per` consecutive ones
-            const int per = nb >= kSelThreads ? nb / kSelThreads : 1;
-            u64 m_loc[4] = {0, 0, 0, 0};
-            uint32_t c_loc[4] = {0, 0, 0, 0};
-            u64 msum = 0;
-            uint32_t csum = 0;
+// Called by wavefront 0: the bucket in which the running weight, from the highest bucket down, reaches the target.  tau >= 0 (first
+// digit of the threshold rule, whose histogram has every element): the target is ceil(tau * total).
+template <int NB>
+__device__ __forceinline__ void find_crossing(const u64* hist, double tau, Descent& d) {
+    constexpr int R = Hist<NB>::kPerLane;
+    const int lane = threadIdx.x & 63;
+    u64 sum = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int rb = tid * per + j;
-                if (j < per && rb < nb) {
-                    m_loc[j] = sh.hist_mass[nb - 1 - rb];
-                    c_loc[j] = sh.hist_cnt[nb - 1 - rb];
-                    msum += m_loc[j];
-                    csum += c_loc[j];
-                }
-            }
-            // exclusive prefix over threads of (mass, count)
-            u64 mi = msum;
-            uint32_t ci = csum;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const u64 my = __shfl_up(mi, d);
-                const uint32_t cy = __shfl_up(ci, d);
-                if (lane >= d) {
-                    mi += my;
-                    ci += cy;
-                }
-            }
-            if (lane == 63) {
-                sh.wave_m[wave] = mi;
-                sh.wave_c[wave] = ci;
-            }
-            __syncthreads();
-            u64 mbase = 0;
-            uint32_t cbase = 0;
-            for (int w = 0; w < wave; ++w) {
-                mbase += sh.wave_m[w];
-                cbase += sh.wave_c[w];
-            }
-            if (pass == 0 && tau >= 0.0) {
-                u64 total = 0;
-                for (int w = 0; w < kWaves; ++w) total += sh.wave_m[w];
-                trem = static_cast<u64>(ceil(tau * static_cast<double>(total)));
-                if (trem == 0) {                              // uniform: every thread sees the same total
-                    pk.none = true;
-                    __syncthreads();
-                    return pk;
-                }
-                if (trem > total) {
-                    // Totals above 2^53 are rounded when they become a double, so ceil(tau * total) can exceed the total
-                    // itself (tau = 1, more than 2^13 saturated scores): the mass is then never reached and the rule
-                    // keeps every element.  Crossing value 0 with every tie taken says exactly that.
-                    pk.vstar = 0u;
-                    pk.ties = 0xffffffffu;
-                    __syncthreads();
-                    return pk;
-                }
-            }
-            u64 mrun = mbase + mi - msum;
-            uint32_t crun = cbase + ci - csum;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int rb = tid * per + j;
-                if (j < per && rb < nb) {
-                    const bool hit = by_count ? (crun < krem && crun + c_loc[j] >= krem)
-                                              : (mrun < trem && mrun + m_loc[j] >= trem);
-                    if (hit) {
-                        sh.sel_bucket = nb - 1 - rb;
-                        sh.above_m = mrun;
-                        sh.above_c = crun;
-                        sh.eq_m = m_loc[j];
-                        sh.eq_c = c_loc[j];
-                    }
-                    mrun += m_loc[j];
-                    crun += c_loc[j];
-                }
-            }
-            __syncthreads();
-            prefix |= sh.sel_bucket << shf;
-            pmask |= static_cast<uint32_t>(nb - 1) << shf;
-            trem -= by_count ? 0 : sh.above_m;
-            krem -= by_count ? sh.above_c : 0;
-            __syncthreads();
+    for (int j = 0; j < R; ++j) sum += hist[j * 65 + lane];
+    const u64 incl = wave_scan(sum);
+    if (tau >= 0.0) {
+        const u64 total = lane_value(incl, 63);
+        d.target = static_cast<u64>(ceil(tau * static_cast<double>(total)));
+        if (d.target == 0) {
+            d.none = 1u;
+            return;
         }
-        pk.vstar = prefix;
-        if (by_count) {
-            pk.ties = krem;
-        } else {
-            const u64 wstar = sh.eq_m / sh.eq_c;               // every tie has the same mass
-            pk.ties = static_cast<uint32_t>((trem + wstar - 1) / wstar);
+        if (d.target > total) {
+            // Totals above 2^53 are rounded when they become a double, so ceil(tau * total) can exceed the total itself (tau = 1, more
+            // than 2^13 saturated scores): the mass is then never reached and the rule keeps every element.
+            d.all = 1u;
+            d.bucket = 0u;
+            return;
         }
-        return pk;
-    };
-
-    // ---- total mass, threshold ----
-    Pick pk;
-    if (p.mode == 0) {
-        pk = descend(false, false, 0, 0u, p.tau[dir], true);
-    } else {
-        const uint32_t kfix = static_cast<uint32_t>(min(p.kfix[dir], n));
-        if (kfix == 0) {                                     // nothing ranked in: the status bits still need their sweep
-            for (int i = tid; i < n; i += kSelThreads) {
-                const uint32_t key = score_key(a[i], st);
-                (void)key_mass(key, st);
-            }
-        }
-        pk = descend(true, false, 0, kfix, -1.0, true);
     }
+    const u64 hit = __ballot(incl - sum < d.target && incl >= d.target);
+    const int l = hit ? __builtin_ctzll(hit) : 63;
+    const u64 base = lane_value(incl - sum, l);
+    const u64 mine = lane < R ? hist[lane * 65 + l] : 0ull;
+    const u64 upto = base + wave_scan(mine);
+    const u64 hit2 = __ballot(lane < R && upto - mine < d.target && upto >= d.target);
+    const int j = hit2 ? __builtin_ctzll(hit2) : R - 1;
+    d.target -= lane_value(upto - mine, j);
+    d.bucket = static_cast<uint32_t>(NB - 1 - (l * R + j));
+}
 
-    // ---- ordered emission: each wavefront owns a contiguous range, ranks come from ballots ----
+// Bits of a key below its top bucket (the last bucket has everything above); key - low_end() has that many.
+__device__ __forceinline__ int bits_below(uint32_t top) { return top == kTopBuckets - 1 ? 30 : kTopShift; }
+__device__ __forceinline__ uint32_t low_end(uint32_t top) { return top << kTopShift; }
+
+// The remaining `bits` bits, kDigit at a time: each(f) calls f(candidate, valid) (candidate: key, bit 31: forced) for the candidates that
+// share the bits above (prefix).  Returns key - low; d.target is then the weight that the ties at it contribute.  All threads of
+// the workgroup.
+template <typename EACH>
+__device__ __forceinline__ uint32_t descend(u64* hist, Descent* shared, Descent& d, uint32_t low, uint32_t prefix, int bits, bool by_count,
+                                            EACH each) {
+    const int tid = threadIdx.x;
+    while (bits > 0) {
+        const int shf = bits > kDigit ? bits - kDigit : 0;
+        for (int b = tid; b < Hist<kDigitBuckets>::kWords; b += kSelThreads) hist[b] = 0ull;
+        __syncthreads();
+        each([&](uint32_t cand, bool valid) __attribute__((always_inline)) {
+            const uint32_t key = cand & 0x7fffffffu, rel = key - low;
+            if (valid && (rel >> bits) == prefix)
+                atomicAdd(&hist[Hist<kDigitBuckets>::slot((rel >> shf) & ((1u << (bits - shf)) - 1))],
+                          by_count ? 1ull : key_mass(key));
+        });
+        __syncthreads();
+        if (tid < 64) {
+            find_crossing<kDigitBuckets>(hist, -1.0, d);
+            if (tid == 0) *shared = d;
+        }
+        __syncthreads();
+        d = *shared;
+        prefix = (prefix << (bits - shf)) | d.bucket;
+        bits = shf;
+    }
+    return prefix;
+}
+
+// ties at the crossing value that are in: the fewest whose weight reaches the target (every tie has the same weight)
+__device__ __forceinline__ uint32_t ties_taken(const Descent& d, uint32_t vstar, bool by_count) {
+    if (by_count) return static_cast<uint32_t>(d.target);
+    const u64 w = key_mass(vstar);
+    return static_cast<uint32_t>((d.target + w - 1) / w);
+}
+
+// Entries of a part (a wavefront's range, a chunk) that are in whatever the ties decide, ties, forced ties; ties are taken in index
+// order and the forced entries, already counted as in, are the lowest indices: the number of selected entries follows.
+__device__ __forceinline__ uint32_t part_selected(uint32_t in, uint32_t eq, uint32_t eqf, uint32_t ties_before, uint32_t ties) {
+    const uint32_t room = ties > ties_before + eqf ? ties - ties_before - eqf : 0u;
+    return in + min(room, eq - eqf);
+}
+
+// This wavefront's scores [lo, hi) in batches of 64 * kBatch; a range of one batch is requested once and stays in registers.
+struct Range {
+    const float* a;
+    int lo, hi, have;
+    float x[kBatch];
+    __device__ __forceinline__ Range(const float* scores, int lo_, int hi_) : a(scores), lo(lo_), hi(hi_), have(-1) {
+        if (lo < hi) load(lo);
+    }
+    __device__ __forceinline__ void load(int base) {
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int j = 0; j < kBatch; ++j) x[j] = a[min(base + 64 * j + lane, hi - 1)];
+        have = base;
+    }
+    // f(index, score, valid) for all lanes of the wavefront, 64 scores at a time
+    template <typename F>
+    __device__ __forceinline__ void each(F f) {
+        const int lane = threadIdx.x & 63;
+        for (int base = lo; base < hi; base += 64 * kBatch) {
+            if (base != have) load(base);
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                const int i = base + 64 * j + lane;
+                if (base + 64 * j < hi) f(i, x[j], i < hi);
+            }
+        }
+    }
+};
+
+struct SelShared {
+    u64 hist[kHistWords];
+    Descent descent;
+    uint32_t in[kWaves], eq[kWaves], eqf[kWaves];
+    int status;
+};
+
+// Ascending output of one wavefront's range: pos and tie_run are those of its first entry.
+template <typename RANKED>
+__device__ __forceinline__ void emit(Range& r, int32_t* __restrict__ out, uint32_t pos, uint32_t tie_run, uint32_t vstar, uint32_t ties, int nforced,
+                                     RANKED ranked) {
+    const u64 lt_mask = (1ull << (threadIdx.x & 63)) - 1ull;
+    r.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+        const uint32_t key = score_key(x);
+        const bool rk = valid && ranked(i);
+        const bool eq = rk && key == vstar;
+        bool in = (valid && i < nforced) || (rk && key > vstar);
+        const u64 eb = __ballot(eq);
+        if (eq && tie_run + __popcll(eb & lt_mask) < ties) in = true;
+        tie_run += __popcll(eb);
+        const u64 sb = __ballot(in);
+        if (in) out[pos + __popcll(sb & lt_mask)] = i;
+        pos += __popcll(sb);
+    });
+}
+
+// One problem by one workgroup.  STORED: the candidates go to cand (as many entries as scores), else they are looked for among the
+// scores again.  overflowed: the selection is known to exceed the capacity.
+template <bool STORED>
+__device__ void select_problem(const SelParams& p, int head, int dir, SelShared& sh, uint32_t* cand, bool overflowed) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = p.n, nforced = min(p.nforced[dir], n), cap = p.cap[dir];
+    const u64 lt_mask = (1ull << lane) - 1ull;
     const int per_wave = ((n + kWaves - 1) / kWaves + 63) & ~63;
     const int w_lo = min(wave * per_wave, n), w_hi = min(w_lo + per_wave, n);
-    const u64 lt_mask = (1ull << lane) - 1ull;
-    int32_t* __restrict__ out = p.idx[dir] + static_cast<size_t>(head) * cap;
-
-    bool skip_forced = false;
-    for (int attempt = 0; attempt < 2; ++attempt) {
-        // sweep 1: per wavefront, the ties, the ties among the forced entries, and the entries that are in whatever the
-        // ties decide (forced, or ranked above the crossing value).  Ties are taken in index order and the forced entries
-        // are the lowest indices, so the number of selected entries of a wavefront follows from these three counts.
-        uint32_t eqc = 0, eqf = 0, inc = 0;
-        for (int base = w_lo; base < w_hi; base += 64) {
-            const int i = base + lane;
-            bool eq = false, in = false, forced = false;
-            if (i < w_hi) {
-                int dummy = 0;
-                const uint32_t key = score_key(a[i], dummy);
-                forced = i < nforced;
-                const bool ranked = !pk.none && !(skip_forced && forced);
-                eq = ranked && key == pk.vstar;
-                in = forced || (ranked && key > pk.vstar);
-            }
-            eqc += __popcll(__ballot(eq));
-            eqf += __popcll(__ballot(eq && forced));
-            inc += __popcll(__ballot(in));
+    Range range(p.a[dir] + static_cast<size_t>(head) * n, w_lo, w_hi);
+    int st = overflowed ? VS_STATUS_OVERFLOW : 0;
+    if (tid == 0) sh.status = 0;
+    bool by_count = p.mode != 0;
+    // The second attempt keeps the forced entries and fills up with the best-ranked others: a pick by count over the rest.
+    for (int attempt = overflowed ? 1 : 0; attempt < 2; ++attempt) {
+        const bool skip_forced = attempt != 0;
+        Descent d{};
+        if (skip_forced) by_count = true;
+        const bool collect = !skip_forced;                   // status bits of the scores
+        if (by_count) {
+            d.target = skip_forced ? static_cast<u64>(cap - nforced) : static_cast<u64>(min(p.kfix[dir], n));
+            d.none = d.target == 0 ? 1u : 0u;
         }
-        if (lane == 0) {
-            sh.wave_eq[wave] = eqc;
-            sh.wave_eqf[wave] = eqf;
-            sh.wave_in[wave] = inc;
+        auto ranked = [&](int i) __attribute__((always_inline)) { return !d.none && !(skip_forced && i < nforced); };
+        for (int b = tid; b < kHistWords; b += kSelThreads) sh.hist[b] = 0ull;
+        __syncthreads();
+        range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+            if (!valid) return;
+            int bits = 0;
+            const uint32_t key = score_key(x, bits);
+            if (collect) st |= bits;
+            if (ranked(i)) {
+                const u64 w = by_count ? 1ull : key_mass(key);
+                if (w) atomicAdd(&sh.hist[Hist<kTopBuckets>::slot(top_bucket(key))], w);
+            }
+        });
+        __syncthreads();
+        if (tid < 64) {
+            if (!d.none) find_crossing<kTopBuckets>(sh.hist, by_count ? -1.0 : p.tau[dir], d);
+            if (tid == 0) sh.descent = d;
         }
         __syncthreads();
-        uint32_t tie_base = 0, pos = 0, total = 0;
-        {
-            uint32_t ties_before = 0;
-            for (int w = 0; w < kWaves; ++w) {
-                const uint32_t e = sh.wave_eq[w], ef = sh.wave_eqf[w];
-                // free ties of wavefront w that are taken: its forced ties come first and are already counted as in
-                const uint32_t room = pk.ties > ties_before + ef ? pk.ties - ties_before - ef : 0u;
-                const uint32_t sel = sh.wave_in[w] + min(room, e - ef);
-                if (w < wave) pos += sel;
-                if (w == wave) tie_base = ties_before;
-                total += sel;
-                ties_before += e;
+        d = sh.descent;
+        const uint32_t top = d.bucket;
+        // candidates of this wavefront, at w_lo of cand on; entries above them and forced ones are in
+        uint32_t inc = 0, mine = 0;
+        range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+            const uint32_t key = score_key(x), b = top_bucket(key);
+            const bool forced = valid && i < nforced, rk = valid && ranked(i);
+            const bool c = rk && b == top;
+            inc += __popcll(__ballot(forced || (rk && b > top)));
+            const u64 cb = __ballot(c);
+            if (STORED && c) cand[w_lo + mine + __popcll(cb & lt_mask)] = key | (forced ? 0x80000000u : 0u);
+            mine += __popcll(cb);
+        });
+        auto each = [&](auto f) __attribute__((always_inline)) {
+            if constexpr (STORED) {
+                for (uint32_t k = 0; k < mine; k += 64) f(k + lane < mine ? cand[w_lo + k + lane] : 0u, k + lane < mine);
+            } else {
+                range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+                    const uint32_t key = score_key(x);
+                    f(key | (i < nforced ? 0x80000000u : 0u), valid && ranked(i) && top_bucket(key) == top);
+                });
             }
-        }
-        __syncthreads();
-        auto selected = [&](int i, uint32_t& tie_run) -> bool {
-            bool in = false, eq = false;
-            if (i < w_hi) {
-                const bool forced = i < nforced;
-                int dummy = 0;
-                const uint32_t key = score_key(a[i], dummy);
-                const bool ranked = !pk.none && !(skip_forced && forced);
-                eq = ranked && key == pk.vstar;
-                in = forced || (ranked && key > pk.vstar);
-            }
-            const u64 eb = __ballot(eq);
-            if (eq && tie_run + __popcll(eb & lt_mask) < pk.ties) in = true;
-            tie_run += __popcll(eb);
-            return in;
         };
-        uint32_t tie_run = tie_base;
+        uint32_t vstar = 0u, ties = 0xffffffffu;             // everything is in: crossing value 0 and every tie
+        if (d.none) ties = 0u;
+        else if (!d.all) {
+            vstar = low_end(top) + descend(sh.hist, &sh.descent, d, low_end(top), 0u, bits_below(top), by_count, each);
+            ties = ties_taken(d, vstar, by_count);
+        }
+        uint32_t eqc = 0, eqf = 0, above = 0;
+        each([&](uint32_t c, bool valid) __attribute__((always_inline)) {
+            const uint32_t key = c & 0x7fffffffu, forced = c >> 31;
+            eqc += valid && key == vstar ? 1u : 0u;
+            eqf += valid && key == vstar ? forced : 0u;
+            above += valid && key > vstar ? 1u - forced : 0u;
+        });
+        // (three counts below 2^21 each: two sums over the lanes)
+        const u64 sums = wave_scan((static_cast<u64>(eqc) << 32) | eqf);
+        const uint32_t more = wave_scan(above);
+        if (lane == 63) {
+            sh.eq[wave] = static_cast<uint32_t>(sums >> 32);
+            sh.eqf[wave] = static_cast<uint32_t>(sums);
+            sh.in[wave] = inc + more;
+        }
+        __syncthreads();
+        const uint32_t e = lane < kWaves ? sh.eq[lane] : 0u, ef = lane < kWaves ? sh.eqf[lane] : 0u, in = lane < kWaves ? sh.in[lane] : 0u;
+        const uint32_t ties_before = wave_scan(e) - e;
+        const uint32_t sel = part_selected(in, e, ef, ties_before, ties);
+        const uint32_t upto = wave_scan(sel);
+        const uint32_t total = lane_value(upto, 63);
         if (total > static_cast<uint32_t>(cap) && attempt == 0) {
-            // keep the forced entries and the best-ranked others: count-ranked pick over the rest
             st |= VS_STATUS_OVERFLOW;
-            skip_forced = true;
-            pk = descend(true, true, 0, static_cast<uint32_t>(cap - nforced), -1.0, false);
             continue;
         }
-        // sweep 2: write
-        tie_run = tie_base;
-        for (int base = w_lo; base < w_hi; base += 64) {
-            const bool in = selected(base + lane, tie_run);
-            const u64 sb = __ballot(in);
-            if (in) out[pos + __popcll(sb & lt_mask)] = base + lane;
-            pos += __popcll(sb);
-        }
+        emit(range, p.idx[dir] + static_cast<size_t>(head) * cap, lane_value(upto - sel, wave), lane_value(ties_before, wave), vstar, ties, nforced,
+             ranked);
         if (tid == 0) p.cnt[dir][head] = static_cast<int32_t>(total);
         break;
     }
@@ -316,375 +379,322 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p, 
     if (tid == 0 && p.status && sh.status) atomicOr(p.status + head, sh.status);
 }
 
+template <bool STORED>
+__global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p) {
+    __shared__ SelShared sh;
+    extern __shared__ uint32_t cand[];
+    select_problem<STORED>(p, blockIdx.x, blockIdx.y, sh, cand, false);
+}
+
 // ---- the same selection over many workgroups ----
-constexpr int kChunk = 8192;                   // scores per workgroup
-constexpr int kChunkThreads = 512;
-constexpr int kChunkWaves = kChunkThreads / 64;
-// scores per thread: all requested at the top of a kernel, before its scan (one load in flight at a time: 55.5 us for 8 x 131072, 46 now)
-constexpr int kChunkRegs = kChunk / kChunkThreads;
-constexpr int kMinSplitN = 32768;              // shorter problems stay with one workgroup (fewer launches)
+constexpr int kChunk = 8192;                   // scores per workgroup up to 131072, one batch of every wavefront; longer problems have longer
+constexpr int kMaxChunks = kWaves;             // chunks: a wavefront per chunk looks at the whole problem
+static_assert(kChunk == kSelThreads * kBatch, "one batch");
 
-// descent state of one problem after a pass (written by the workgroup of chunk 0, read by the next kernel)
-struct SelState {
-    u64 trem, eq_m;
-    uint32_t prefix, pmask, krem, eq_c;
-    uint32_t none, all, vstar, ties;
+// Workspace of one problem: histograms of the first digit and of the next one in its crossing bucket (64 lanes wide, otherwise as in
+// LDS: neighbouring buckets are 512 bytes apart, and atomics of many workgroups on one line, which are served one after the other,
+// are few) | counters | candidates
+struct ProblemWs {
+    u64 hist[kTopBuckets], next[kDigitBuckets];
+    uint32_t candidates;            // entries that the chunks have asked for; more than SplitParams::cand_cap: the list is incomplete
+    uint32_t not_least, greatest;   // maxima over the candidates: of the complement of a key, of a key
+    uint32_t pad[61];
+    uint32_t cand[1];               // SplitParams::cand_cap
 };
-
+constexpr size_t kProblemHead = offsetof(ProblemWs, cand);
+constexpr size_t kProblemBytes = 3 * 4096 * 12;              // longer sequences get a byte per score for the candidates
+struct ProblemState {
+    Descent first;                  // after the first digit
+    uint32_t pad[42];
+};
+struct ChunkInfo {
+    uint32_t in, pos, num;          // entries in without being candidates; candidates
+};
+static_assert(sizeof(Descent) == 24 && sizeof(ProblemState) == 192 && sizeof(ChunkInfo) == 12, "workspace layout");
 struct SplitParams {
     SelParams s;
-    int chunks;
-    u64* hist_m[3];                 // [problems][4096 | 4096 | 256]
-    uint32_t* hist_c[3];
-    SelState* state;                // [problems][4]
-    uint32_t* chunk_cnt;            // [problems][chunks][3]: in, ties, forced ties
-    int32_t* redo;                  // [problems]
+    int chunks, chunk_size;         // chunk_size: a multiple of kChunk
+    unsigned char* problem;
+    size_t problem_bytes;
+    uint32_t cand_cap;
+    ProblemState* state;
+    ChunkInfo* chunk;               // [problems][chunks]
+    __device__ __forceinline__ ProblemWs& ws(int pr) const { return *reinterpret_cast<ProblemWs*>(problem + problem_bytes * pr); }
 };
 
-// Where bucket b of an nb-bucket histogram (nb = R * R) sits in the workspace: transposed, so that neighbouring buckets,
-// which the scores of one problem crowd into, are R entries apart.  Atomics of many workgroups on one cache line are
-// served one after the other (~12 ns each); spread out they go to different lines.  The scan, whose thread t owns the
-// buckets 8 t .. 8 t + 7 from the top, then reads a few lines per wavefront instruction instead of 64.
-__device__ __forceinline__ int bucket_slot(int b, int nb) {
-    const int r = nb == 4096 ? 64 : 16, sh = nb == 4096 ? 6 : 4;
-    return ((b & (r - 1)) << sh) | (b >> sh);
+// This wavefront's scores of the workgroup's chunk
+__device__ __forceinline__ Range chunk_range(const SplitParams& q, int wave) {
+    const int n = q.s.n, per_wave = q.chunk_size / kWaves;
+    const int lo = min(static_cast<int>(blockIdx.x) * q.chunk_size + wave * per_wave, n);
+    return Range(q.s.a[blockIdx.z] + static_cast<size_t>(blockIdx.y) * n, lo, min(lo + per_wave, n));
 }
 
-struct ScanShared {
-    u64 wave_m[kChunkWaves];
-    uint32_t wave_c[kChunkWaves];
-    uint32_t sel_bucket, eq_c, above_c;
-    u64 above_m, eq_m;
-};
-
-// One pass of the descent on a finished histogram of nb buckets: the bucket in which the running (mass | count), taken
-// over the buckets in descending order, reaches the target.  All kChunkThreads threads call it; the arithmetic is that of
-// the single-workgroup kernel.
-__device__ __forceinline__ void scan_pass(ScanShared& sc, const u64* __restrict__ hm, const uint32_t* __restrict__ hc, int nb,
-                                          int shf, bool by_count, double tau, SelState& st) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = nb >= kChunkThreads ? nb / kChunkThreads : 1;      // 8 or 1
-    constexpr int kPer = 4096 / kChunkThreads;
-    u64 m_loc[kPer];
-    uint32_t c_loc[kPer];
-    u64 msum = 0;
-    uint32_t csum = 0;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int rb = tid * per + j;
-        m_loc[j] = 0;
-        c_loc[j] = 0;
-        if (j < per && rb < nb) {
-            m_loc[j] = hm[bucket_slot(nb - 1 - rb, nb)];
-            c_loc[j] = hc[bucket_slot(nb - 1 - rb, nb)];
-            msum += m_loc[j];
-            csum += c_loc[j];
-        }
-    }
-    u64 mi = msum;
-    uint32_t ci = csum;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const u64 my = __shfl_up(mi, d);
-        const uint32_t cy = __shfl_up(ci, d);
-        if (lane >= d) {
-            mi += my;
-            ci += cy;
-        }
-    }
-    __syncthreads();                                         // (the shared words may still be read from the previous pass)
-    if (lane == 63) {
-        sc.wave_m[wave] = mi;
-        sc.wave_c[wave] = ci;
-    }
-    __syncthreads();
-    u64 mbase = 0;
-    uint32_t cbase = 0;
-    for (int w = 0; w < wave; ++w) {
-        mbase += sc.wave_m[w];
-        cbase += sc.wave_c[w];
-    }
-    if (shf == 20 && tau >= 0.0) {
-        u64 total = 0;
-        for (int w = 0; w < kChunkWaves; ++w) total += sc.wave_m[w];
-        st.trem = static_cast<u64>(ceil(tau * static_cast<double>(total)));
-        if (st.trem == 0) {
-            st.none = 1u;
-            return;
-        }
-        if (st.trem > total) {                               // see the single-workgroup kernel: the rule keeps every element
-            st.all = 1u;
-            st.vstar = 0u;
-            st.ties = 0xffffffffu;
-            return;
-        }
-    }
-    u64 mrun = mbase + mi - msum;
-    uint32_t crun = cbase + ci - csum;
-#pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-        const int rb = tid * per + j;
-        if (j < per && rb < nb) {
-            const bool hit = by_count ? (crun < st.krem && crun + c_loc[j] >= st.krem) : (mrun < st.trem && mrun + m_loc[j] >= st.trem);
-            if (hit) {
-                sc.sel_bucket = nb - 1 - rb;
-                sc.above_m = mrun;
-                sc.above_c = crun;
-                sc.eq_m = m_loc[j];
-                sc.eq_c = c_loc[j];
-            }
-            mrun += m_loc[j];
-            crun += c_loc[j];
-        }
-    }
-    __syncthreads();
-    st.prefix |= sc.sel_bucket << shf;
-    st.pmask |= static_cast<uint32_t>(nb - 1) << shf;
-    if (by_count) st.krem -= sc.above_c;
-    else st.trem -= sc.above_m;
-    st.eq_m = sc.eq_m;
-    st.eq_c = sc.eq_c;
-}
-
-// PASS 0..2: histogram of this chunk's scores at digit PASS (after the scan of the previous digit's histogram);
-// PASS 3: scan of the last histogram, then this chunk's counts for the emission.
-template <int PASS>
-__global__ __launch_bounds__(kChunkThreads) void split_pass_kernel(const SplitParams q) {
-    __shared__ u64 h_m[PASS < 2 ? 4096 : 256];
-    __shared__ uint32_t h_c[PASS < 2 ? 4096 : 256];
-    __shared__ ScanShared sc;
-    __shared__ uint32_t cnt3[3];
+__global__ __launch_bounds__(kSelThreads) void split_hist_kernel(const SplitParams q) {
+    __shared__ u64 hist[kHistWords];
     const SelParams& p = q.s;
-    const int chunk = blockIdx.x, head = blockIdx.y, dir = blockIdx.z;
-    const int pr = head * 2 + dir;
-    const int tid = threadIdx.x;
-    const int n = p.n;
-    const float* __restrict__ a = p.a[dir] + static_cast<size_t>(head) * n;
+    const int head = blockIdx.y, dir = blockIdx.z, tid = threadIdx.x;
     const bool by_count = p.mode != 0;
-    const int lo = chunk * kChunk, hi = min(lo + kChunk, n);
-    constexpr int shifts[3] = {20, 8, 0};
-    constexpr int nbs[3] = {4096, 4096, 256};
-
-    float x[kChunkRegs];
-#pragma unroll
-    for (int j = 0; j < kChunkRegs; ++j) x[j] = a[min(lo + j * kChunkThreads + tid, n - 1)];
-    SelState st{};
-    if (PASS == 1) {
-        st.krem = static_cast<uint32_t>(min(p.kfix[dir], n));
-        if (by_count && st.krem == 0) st.none = 1u;
-        else scan_pass(sc, q.hist_m[0] + static_cast<size_t>(pr) * 4096, q.hist_c[0] + static_cast<size_t>(pr) * 4096, 4096, 20,
-                       by_count, by_count ? -1.0 : p.tau[dir], st);
-    } else if (PASS >= 2) {
-        st = q.state[pr * 4 + PASS - 1];
-        if (!st.none && !st.all) {
-            const int pp = PASS - 1;
-            scan_pass(sc, q.hist_m[pp] + static_cast<size_t>(pr) * 4096, q.hist_c[pp] + static_cast<size_t>(pr) * 4096, nbs[pp],
-                      shifts[pp], by_count, -1.0, st);
-        }
-    }
-    if (PASS == 3 && !st.none && !st.all) {
-        st.vstar = st.prefix;
-        if (by_count) {
-            st.ties = st.krem;
-        } else {
-            const u64 wstar = st.eq_m / st.eq_c;             // every tie has the same mass
-            st.ties = static_cast<uint32_t>((st.trem + wstar - 1) / wstar);
-        }
-    }
-    if (PASS >= 1 && chunk == 0 && tid == 0) q.state[pr * 4 + PASS] = st;
-
-    if constexpr (PASS < 3) {
-        if (PASS > 0 && (st.none || st.all)) return;          // uniform over the workgroup
-        constexpr int nb = nbs[PASS], shf = shifts[PASS];
-        for (int b = tid; b < nb; b += kChunkThreads) {
-            h_m[b] = 0;
-            h_c[b] = 0;
-        }
-        __syncthreads();
-        int stbits = 0, matched = 0;
-#pragma unroll
-        for (int j = 0; j < kChunkRegs; ++j) {
-            if (lo + j * kChunkThreads + tid >= hi) continue;
-            int dummy = 0;
-            const uint32_t key = score_key(x[j], PASS == 0 ? stbits : dummy);
-            if ((key & st.pmask) != st.prefix) continue;
-            matched = 1;
-            const uint32_t b = (key >> shf) & (nb - 1);
-            atomicAdd(&h_c[b], 1u);
-            if (!by_count) atomicAdd(&h_m[b], key_mass(key, PASS == 0 ? stbits : dummy));
-            else if (PASS == 0) (void)key_mass(key, stbits);
-        }
-        if (PASS == 0 && stbits && p.status) atomicOr(p.status + head, stbits);
-        if (PASS > 0 && !__syncthreads_or(matched)) return;   // nothing of this chunk under the prefix (the usual case)
-        __syncthreads();
-        u64* gm = q.hist_m[PASS] + static_cast<size_t>(pr) * 4096;
-        uint32_t* gc = q.hist_c[PASS] + static_cast<size_t>(pr) * 4096;
-        for (int b = tid; b < nb; b += kChunkThreads) {
-            const uint32_t c = h_c[b];
-            if (c) {
-                atomicAdd(&gc[bucket_slot(b, nb)], c);
-                if (!by_count) atomicAdd(&gm[bucket_slot(b, nb)], h_m[b]);
-            }
-        }
-    } else {
-        // counts of this chunk for the emission: entries that are in whatever the ties decide, ties, forced ties
-        if (tid < 3) cnt3[tid] = 0;
-        __syncthreads();
-        const int nforced = min(p.nforced[dir], n);
-        uint32_t inc = 0, eqc = 0, eqf = 0;
-#pragma unroll
-        for (int j = 0; j < kChunkRegs; ++j) {
-            const int i = lo + j * kChunkThreads + tid;
-            if (i >= hi) continue;
-            int dummy = 0;
-            const uint32_t key = score_key(x[j], dummy);
-            const bool forced = i < nforced;
-            const bool ranked = !st.none;
-            const bool eq = ranked && key == st.vstar;
-            inc += (forced || (ranked && key > st.vstar)) ? 1u : 0u;
-            eqc += eq ? 1u : 0u;
-            eqf += (eq && forced) ? 1u : 0u;
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            inc += __shfl_xor(inc, d);
-            eqc += __shfl_xor(eqc, d);
-            eqf += __shfl_xor(eqf, d);
-        }
-        if ((tid & 63) == 0) {
-            atomicAdd(&cnt3[0], inc);
-            atomicAdd(&cnt3[1], eqc);
-            atomicAdd(&cnt3[2], eqf);
-        }
-        __syncthreads();
-        if (tid < 3) q.chunk_cnt[(static_cast<size_t>(pr) * q.chunks + chunk) * 3 + tid] = cnt3[tid];
+    Range range = chunk_range(q, __builtin_amdgcn_readfirstlane(tid >> 6));
+    for (int b = tid; b < kHistWords; b += kSelThreads) hist[b] = 0ull;
+    __syncthreads();
+    int st = 0;
+    range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+        if (!valid) return;
+        const uint32_t key = score_key(x, st);
+        const u64 w = by_count ? 1ull : key_mass(key);
+        if (w) atomicAdd(&hist[Hist<kTopBuckets>::slot(top_bucket(key))], w);
+    });
+    if (st && p.status) atomicOr(p.status + head, st);
+    __syncthreads();
+    u64* const out = q.ws(head * 2 + dir).hist;
+    for (int r = tid; r < kTopBuckets; r += kSelThreads) {
+        const u64 w = hist[(r >> 6) * 65 + (r & 63)];         // both layouts have 64 lanes
+        if (w) atomicAdd(&out[r], w);
     }
 }
 
-// Ordered emission of one chunk: its first output position and its first tie rank follow from the counts of the chunks
-// before it; inside the chunk each wavefront owns a contiguous range, as in the single-workgroup kernel.
-__global__ __launch_bounds__(kChunkThreads) void split_emit_kernel(const SplitParams q) {
-    __shared__ uint32_t c_in[256], c_eq[256], c_ef[256];
-    __shared__ uint32_t w_in[kChunkWaves], w_eq[kChunkWaves], w_ef[kChunkWaves];
+// The crossing bucket of the first digit; this chunk's entries of it, and the histogram of their next digit.
+__global__ __launch_bounds__(kSelThreads) void split_pick_kernel(const SplitParams q) {
+    __shared__ u64 hist[kHistWords], next[Hist<kDigitBuckets>::kWords];
+    __shared__ Descent shared;
+    __shared__ uint32_t part[kWaves], not_least[kWaves], greatest[kWaves], base;
     const SelParams& p = q.s;
-    const int chunk = blockIdx.x, head = blockIdx.y, dir = blockIdx.z;
-    const int pr = head * 2 + dir;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n = p.n;
-    const float* __restrict__ a = p.a[dir] + static_cast<size_t>(head) * n;
+    const int chunk = blockIdx.x, head = blockIdx.y, dir = blockIdx.z, pr = head * 2 + dir;
+    const int tid = threadIdx.x, lane = tid & 63, n = p.n;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nforced = min(p.nforced[dir], n);
-    const int cap = p.cap[dir];
-    const int lo = chunk * kChunk, hi = min(lo + kChunk, n);
-    constexpr int per_wave = kChunk / kChunkWaves;
-    const int w_lo = min(lo + wave * per_wave, hi), w_hi = min(w_lo + per_wave, hi);
-    float x[per_wave / 64];
-#pragma unroll
-    for (int j = 0; j < per_wave / 64; ++j) x[j] = a[min(w_lo + 64 * j + lane, n - 1)];
-    const SelState st = q.state[pr * 4 + 3];
-    if (tid < q.chunks) {
-        const uint32_t* c = q.chunk_cnt + (static_cast<size_t>(pr) * q.chunks + tid) * 3;
-        c_in[tid] = c[0];
-        c_eq[tid] = c[1];
-        c_ef[tid] = c[2];
+    const bool by_count = p.mode != 0;
+    const u64 lt_mask = (1ull << lane) - 1ull;
+    ProblemWs& ws = q.ws(pr);
+    Range range = chunk_range(q, wave);
+    for (int r = tid; r < kTopBuckets; r += kSelThreads) hist[(r >> 6) * 65 + (r & 63)] = ws.hist[r];
+    for (int b = tid; b < Hist<kDigitBuckets>::kWords; b += kSelThreads) next[b] = 0ull;
+    __syncthreads();
+    Descent d{};
+    if (by_count) {
+        d.target = static_cast<u64>(min(p.kfix[dir], n));
+        d.none = d.target == 0 ? 1u : 0u;
+    }
+    if (tid < 64) {
+        if (!d.none) find_crossing<kTopBuckets>(hist, by_count ? -1.0 : p.tau[dir], d);
+        if (tid == 0) {
+            shared = d;
+            if (chunk == 0) q.state[pr].first = d;
+        }
     }
     __syncthreads();
-    uint32_t pos = 0, tie_base = 0, total = 0, ties_before = 0;
-    for (int c = 0; c < q.chunks; ++c) {
-        const uint32_t e = c_eq[c], ef = c_ef[c];
-        const uint32_t room = st.ties > ties_before + ef ? st.ties - ties_before - ef : 0u;
-        const uint32_t sel = c_in[c] + min(room, e - ef);
-        if (c < chunk) pos += sel;
-        if (c == chunk) tie_base = ties_before;
-        total += sel;
-        ties_before += e;
+    d = shared;
+    const uint32_t low = low_end(d.bucket);
+    const int shf = bits_below(d.bucket) - kDigit;
+    auto candidate = [&](float x, bool valid, uint32_t& key) __attribute__((always_inline)) {
+        key = score_key(x);
+        return valid && !d.none && top_bucket(key) == d.bucket;
+    };
+    uint32_t inc = 0, mine = 0, lo_key = 0u, hi_key = 0u;
+    range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+        uint32_t key;
+        const bool c = candidate(x, valid, key);
+        inc += __popcll(__ballot(valid && (i < nforced || (!d.none && top_bucket(key) > d.bucket))));
+        mine += __popcll(__ballot(c));
+        if (c) {
+            lo_key = max(lo_key, ~key);
+            hi_key = max(hi_key, key);
+            const u64 w = by_count ? 1ull : key_mass(key);
+            if (w) atomicAdd(&next[Hist<kDigitBuckets>::slot((key - low) >> shf)], w);
+        }
+    });
+    lo_key = wave_top(lo_key);
+    hi_key = wave_top(hi_key);
+    if (lane == 63) {
+        part[wave] = (inc << 16) | mine;                     // at most VS_MAX_SEQ / kMaxChunks / kWaves each
+        not_least[wave] = lo_key;
+        greatest[wave] = hi_key;
     }
-    if (total > static_cast<uint32_t>(cap)) {                // the single-workgroup kernel redoes this problem
-        if (chunk == 0 && tid == 0) q.redo[pr] = 1;
+    static_assert(VS_MAX_SEQ / kMaxChunks / kWaves < 65536, "two counts in a word");
+    __syncthreads();
+    const uint32_t pw = lane < kWaves ? part[lane] : 0u;
+    const uint32_t num = wave_scan(pw & 0xffffu), in_all = wave_scan(pw >> 16);
+    lo_key = wave_top(lane < kWaves ? not_least[lane] : 0u);
+    hi_key = wave_top(lane < kWaves ? greatest[lane] : 0u);
+    if (tid == 63) {
+        base = num ? atomicAdd(&ws.candidates, num) : 0u;
+        if (num) {
+            atomicMax(&ws.not_least, lo_key);
+            atomicMax(&ws.greatest, hi_key);
+        }
+        q.chunk[static_cast<size_t>(pr) * q.chunks + chunk] = ChunkInfo{in_all, base, num};
+    }
+    for (int r = tid; r < kDigitBuckets; r += kSelThreads) {
+        const u64 w = next[(r >> 6) * 65 + (r & 63)];
+        if (w) atomicAdd(&ws.next[r], w);
+    }
+    __syncthreads();
+    uint32_t at = base + lane_value(num - (pw & 0xffffu), wave);
+    range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+        uint32_t key;
+        const bool c = candidate(x, valid, key);
+        const u64 cb = __ballot(c);
+        const uint32_t k = at + __popcll(cb & lt_mask);
+        if (c && k < q.cand_cap) ws.cand[k] = key | (i < nforced ? 0x80000000u : 0u);
+        at += __popcll(cb);
+    });
+}
+
+// The remaining digits and the ordered emission of a chunk.  Every workgroup of a problem looks at all its candidates, a chunk of them
+// per wavefront: those above the crossing bucket of the second digit are counted, those in it (few, as a rule) kept in LDS.
+constexpr int kKept = 512;                     // per chunk
+
+__global__ __launch_bounds__(kSelThreads) void split_emit_kernel(const SplitParams q) {
+    __shared__ SelShared sh;
+    __shared__ uint32_t kept[kWaves * kKept], c_in[kMaxChunks], c_eq[kMaxChunks], c_ef[kMaxChunks];
+    const SelParams& p = q.s;
+    const int chunk = blockIdx.x, head = blockIdx.y, dir = blockIdx.z, pr = head * 2 + dir;
+    const int tid = threadIdx.x, lane = tid & 63, n = p.n;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nforced = min(p.nforced[dir], n);
+    const bool by_count = p.mode != 0;
+    const u64 lt_mask = (1ull << lane) - 1ull;
+    const ProblemWs& ws = q.ws(pr);
+    Range range = chunk_range(q, wave);
+    Descent d = q.state[pr].first;
+    const bool here = wave < q.chunks;
+    const ChunkInfo ci = here ? q.chunk[static_cast<size_t>(pr) * q.chunks + wave] : ChunkInfo{0u, 0u, 0u};
+    const uint32_t found = ws.candidates;
+    const bool stored = found <= q.cand_cap;
+    const bool one_key = !stored && ~ws.not_least == ws.greatest;      // more than the list holds, but all the same
+    const uint32_t top = d.bucket, low = low_end(top);
+    const int bits = bits_below(top) - kDigit;
+    // chunk `wave`'s candidates: from the list or, if that is incomplete, from the scores
+    auto source = [&](auto f) __attribute__((always_inline)) {
+        if (stored) {
+            for (uint32_t k = 0; k < ci.num; k += 64) f(k + lane < ci.num ? ws.cand[ci.pos + k + lane] : 0u, k + lane < ci.num);
+        } else {
+            const int lo = min(wave * q.chunk_size, n);
+            Range all(p.a[dir] + static_cast<size_t>(head) * n, lo, min(lo + q.chunk_size, n));
+            all.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+                const uint32_t key = score_key(x);
+                f(key | (i < nforced ? 0x80000000u : 0u), valid && top_bucket(key) == top);
+            });
+        }
+    };
+    uint32_t vstar = 0u, ties = 0xffffffffu;                 // everything is in: crossing value 0 and every tie
+    uint32_t eqc = 0, eqf = 0, above = 0;                    // per lane, of chunk `wave`
+    if (d.none) {
+        ties = 0u;
+    } else if (d.all || one_key) {                           // every candidate is a tie or in
+        if (one_key && !d.all) {
+            vstar = ws.greatest;
+            ties = ties_taken(d, vstar, by_count);
+        }
+        if (lane == 0) eqc = ci.num;
+        const int lo = min(wave * q.chunk_size, n);
+        Range forced(p.a[dir] + static_cast<size_t>(head) * n, lo, min(lo + q.chunk_size, nforced));
+        forced.each([&](int, float x, bool valid) __attribute__((always_inline)) { eqf += valid && top_bucket(score_key(x)) == top ? 1u : 0u; });
+    } else {
+        for (int r = tid; r < kDigitBuckets; r += kSelThreads) sh.hist[(r >> 6) * 65 + (r & 63)] = ws.next[r];
+        __syncthreads();
+        if (tid < 64) {
+            find_crossing<kDigitBuckets>(sh.hist, -1.0, d);
+            if (tid == 0) sh.descent = d;
+        }
+        __syncthreads();
+        d = sh.descent;
+        const uint32_t prefix = d.bucket;
+        uint32_t num = 0;
+        source([&](uint32_t v, bool valid) __attribute__((always_inline)) {
+            const uint32_t digit = ((v & 0x7fffffffu) - low) >> bits;
+            const bool keep = valid && digit == prefix;
+            above += valid && digit > prefix ? 1u - (v >> 31) : 0u;
+            const u64 kb = __ballot(keep);
+            const uint32_t k = num + __popcll(kb & lt_mask);
+            if (keep && k < kKept) kept[wave * kKept + k] = v;
+            num += __popcll(kb);
+        });
+        const bool fits = !__syncthreads_or(num > kKept);
+        auto each = [&](auto f) __attribute__((always_inline)) {
+            if (fits) {
+                for (uint32_t k = 0; k < num; k += 64) f(kept[wave * kKept + min(k + lane, num - 1)], k + lane < num);
+            } else {
+                source([&](uint32_t v, bool valid) __attribute__((always_inline)) { f(v, valid && ((v & 0x7fffffffu) - low) >> bits == prefix); });
+            }
+        };
+        vstar = low + descend(sh.hist, &sh.descent, d, low, prefix, bits, by_count, each);
+        ties = ties_taken(d, vstar, by_count);
+        each([&](uint32_t v, bool valid) __attribute__((always_inline)) {
+            const uint32_t key = v & 0x7fffffffu, forced = v >> 31;
+            eqc += valid && key == vstar ? 1u : 0u;
+            eqf += valid && key == vstar ? forced : 0u;
+            above += valid && key > vstar ? 1u - forced : 0u;
+        });
+    }
+    const u64 sums = wave_scan((static_cast<u64>(eqc) << 32) | eqf);
+    above = wave_scan(above);
+    if (here && lane == 63) {
+        c_eq[wave] = static_cast<uint32_t>(sums >> 32);
+        c_ef[wave] = static_cast<uint32_t>(sums);
+        c_in[wave] = ci.in + above;
+    }
+    // this wavefront's range of this chunk
+    uint32_t w_eq = 0, w_ef = 0, w_in = 0;
+    range.each([&](int i, float s, bool valid) __attribute__((always_inline)) {
+        const uint32_t key = score_key(s);
+        const bool forced = valid && i < nforced, rk = valid && !d.none;
+        const bool eq = rk && key == vstar;
+        w_eq += __popcll(__ballot(eq));
+        w_ef += __popcll(__ballot(eq && forced));
+        w_in += __popcll(__ballot(forced || (rk && key > vstar)));
+    });
+    if (lane == 0) {
+        sh.eq[wave] = w_eq;
+        sh.eqf[wave] = w_ef;
+        sh.in[wave] = w_in;
+    }
+    __syncthreads();
+    // positions: first of the chunks, then of the wavefronts inside this one
+    const bool is = lane < q.chunks;
+    uint32_t e = is ? c_eq[lane] : 0u;
+    uint32_t before = wave_scan(e) - e;
+    uint32_t sel = part_selected(is ? c_in[lane] : 0u, e, is ? c_ef[lane] : 0u, before, ties);
+    uint32_t pos = wave_scan(sel);
+    const uint32_t total = lane_value(pos, 63);
+    if (total > static_cast<uint32_t>(p.cap[dir])) {         // redone by one workgroup
+        if (chunk == 0) select_problem<false>(p, head, dir, sh, nullptr, true);
         return;
     }
     if (chunk == 0 && tid == 0) p.cnt[dir][head] = static_cast<int32_t>(total);
-    const u64 lt_mask = (1ull << lane) - 1ull;
-    auto classify = [&](int j, bool& eq, bool& in, bool& forced) __attribute__((always_inline)) {
-        eq = in = forced = false;
-        const int i = w_lo + 64 * j + lane;
-        if (i < w_hi) {
-            int dummy = 0;
-            const uint32_t key = score_key(x[j], dummy);
-            forced = i < nforced;
-            const bool ranked = !st.none;
-            eq = ranked && key == st.vstar;
-            in = forced || (ranked && key > st.vstar);
-        }
-    };
-    uint32_t eqc = 0, eqf = 0, inc = 0;
-#pragma unroll
-    for (int j = 0; j < per_wave / 64; ++j) {
-        bool eq, in, forced;
-        classify(j, eq, in, forced);
-        eqc += __popcll(__ballot(eq));
-        eqf += __popcll(__ballot(eq && forced));
-        inc += __popcll(__ballot(in));
-    }
-    if (lane == 0) {
-        w_eq[wave] = eqc;
-        w_ef[wave] = eqf;
-        w_in[wave] = inc;
-    }
-    __syncthreads();
-    uint32_t tb = tie_base;
-    for (int w = 0; w < wave; ++w) {
-        const uint32_t e = w_eq[w], ef = w_ef[w];
-        const uint32_t room = st.ties > tb + ef ? st.ties - tb - ef : 0u;
-        pos += w_in[w] + min(room, e - ef);
-        tb += e;
-    }
-    int32_t* __restrict__ out = p.idx[dir] + static_cast<size_t>(head) * cap;
-    uint32_t tie_run = tb;
-#pragma unroll
-    for (int j = 0; j < per_wave / 64; ++j) {
-        bool eq, in, forced;
-        classify(j, eq, in, forced);
-        const u64 eb = __ballot(eq);
-        if (eq && tie_run + __popcll(eb & lt_mask) < st.ties) in = true;
-        tie_run += __popcll(eb);
-        const u64 sb = __ballot(in);
-        if (in) out[pos + __popcll(sb & lt_mask)] = w_lo + 64 * j + lane;
-        pos += __popcll(sb);
-    }
+    const uint32_t chunk_before = lane_value(before, chunk), chunk_pos = lane_value(pos - sel, chunk);
+    const bool iw = lane < kWaves;
+    e = iw ? sh.eq[lane] : 0u;
+    before = chunk_before + wave_scan(e) - e;
+    sel = part_selected(iw ? sh.in[lane] : 0u, e, iw ? sh.eqf[lane] : 0u, before, ties);
+    pos = chunk_pos + wave_scan(sel) - sel;
+    emit(range, p.idx[dir] + static_cast<size_t>(head) * p.cap[dir], lane_value(pos, wave), lane_value(before, wave), vstar, ties, nforced,
+         [&](int) __attribute__((always_inline)) { return !d.none; });
 }
 
-__global__ void zero_words_kernel(uint32_t* w, size_t count, int32_t* status, int heads) {
-    const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count) w[i] = 0u;
-    if (status && i < static_cast<size_t>(heads)) status[i] = 0;
+// Histograms and counters of the problems, status words
+__global__ __launch_bounds__(kSelThreads) void clear_kernel(unsigned char* problem, size_t problem_bytes, int32_t* status) {
+    uint4* const w = reinterpret_cast<uint4*>(problem + problem_bytes * blockIdx.x);
+    for (int i = threadIdx.x; i < static_cast<int>(kProblemHead / 16); i += kSelThreads) w[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (status && threadIdx.x == 0 && (blockIdx.x & 1) == 0) status[blockIdx.x >> 1] = 0;
 }
 
 struct SplitLayout {
-    size_t hist_m[3], hist_c[3], state, chunk_cnt, redo, zero_bytes, total;
-    int chunks;
+    size_t problem_bytes, state, chunk, total;
+    int chunks, chunk_size;
 };
 
 SplitLayout split_layout(int heads, int64_t n) {
     SplitLayout w{};
     const size_t pr = static_cast<size_t>(heads) * 2;
-    w.chunks = static_cast<int>((n + kChunk - 1) / kChunk);
-    size_t off = 0;
-    for (int i = 0; i < 3; ++i) {
-        w.hist_m[i] = off;
-        off += pr * 4096 * sizeof(u64);
-    }
-    for (int i = 0; i < 3; ++i) {
-        w.hist_c[i] = off;
-        off += pr * 4096 * sizeof(uint32_t);
-    }
-    w.redo = off;
-    off = vs::round_up(off + pr * sizeof(int32_t), 256);
-    w.zero_bytes = off;                                      // everything up to here starts at zero
-    w.state = off;
-    off = vs::round_up(off + pr * 4 * sizeof(SelState), 256);
-    w.chunk_cnt = off;
-    off = vs::round_up(off + pr * w.chunks * 3 * sizeof(uint32_t), 256);
-    w.total = off;
+    const int64_t longest = static_cast<int64_t>(kChunk) * kMaxChunks;
+    w.chunk_size = kChunk * static_cast<int>((n + longest - 1) / longest);
+    w.chunks = static_cast<int>((n + w.chunk_size - 1) / w.chunk_size);
+    const size_t want = vs::round_up(kProblemHead + static_cast<size_t>(n), 256);
+    w.problem_bytes = n > 131072 ? want : kProblemBytes;    // a quarter of the scores can be candidates, of shorter ones up to all
+    w.state = vs::round_up(pr * w.problem_bytes + pr * sizeof(int32_t), 256);
+    w.chunk = vs::round_up(w.state + pr * sizeof(ProblemState), 256);
+    w.total = vs::round_up(w.chunk + pr * w.chunks * sizeof(ChunkInfo), 256);
     return w;
 }
 
@@ -745,29 +755,20 @@ int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, c
         SplitParams q{};
         q.s = p;
         q.chunks = w.chunks;
-        for (int i = 0; i < 3; ++i) {
-            q.hist_m[i] = reinterpret_cast<u64*>(base + w.hist_m[i]);
-            q.hist_c[i] = reinterpret_cast<uint32_t*>(base + w.hist_c[i]);
-        }
-        q.state = reinterpret_cast<SelState*>(base + w.state);
-        q.chunk_cnt = reinterpret_cast<uint32_t*>(base + w.chunk_cnt);
-        q.redo = reinterpret_cast<int32_t*>(base + w.redo);
-        const size_t words = w.zero_bytes / 4;                  // (more words than heads: the status words ride along)
-        hipLaunchKernelGGL(zero_words_kernel, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256), 0, st,
-                           reinterpret_cast<uint32_t*>(base), words, status, heads);
+        q.chunk_size = w.chunk_size;
+        q.problem = base;
+        q.problem_bytes = w.problem_bytes;
+        q.cand_cap = static_cast<uint32_t>((w.problem_bytes - kProblemHead) / 4);
+        q.state = reinterpret_cast<ProblemState*>(base + w.state);
+        q.chunk = reinterpret_cast<ChunkInfo*>(base + w.chunk);
+        hipLaunchKernelGGL(clear_kernel, dim3(2 * heads), dim3(kSelThreads), 0, st, q.problem, q.problem_bytes, status);
         VS_LAUNCH_CHECK();
         const dim3 grid(w.chunks, heads, 2);
-        hipLaunchKernelGGL(split_pass_kernel<0>, grid, dim3(kChunkThreads), 0, st, q);
+        hipLaunchKernelGGL(split_hist_kernel, grid, dim3(kSelThreads), 0, st, q);
         VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(split_pass_kernel<1>, grid, dim3(kChunkThreads), 0, st, q);
+        hipLaunchKernelGGL(split_pick_kernel, grid, dim3(kSelThreads), 0, st, q);
         VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(split_pass_kernel<2>, grid, dim3(kChunkThreads), 0, st, q);
-        VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(split_pass_kernel<3>, grid, dim3(kChunkThreads), 0, st, q);
-        VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(split_emit_kernel, grid, dim3(kChunkThreads), 0, st, q);
-        VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(select_kernel, dim3(heads, 2), dim3(kSelThreads), 0, st, p, static_cast<const int32_t*>(q.redo));
+        hipLaunchKernelGGL(split_emit_kernel, grid, dim3(kSelThreads), 0, st, q);
         VS_LAUNCH_CHECK();
         return VS_OK;
     }
@@ -775,7 +776,17 @@ int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, c
         hipLaunchKernelGGL(zero_status_kernel, dim3((heads + 255) / 256), dim3(256), 0, st, status, heads);
         VS_LAUNCH_CHECK();
     }
-    hipLaunchKernelGGL(select_kernel, dim3(heads, 2), dim3(kSelThreads), 0, st, p, static_cast<const int32_t*>(nullptr));
+    if (n < kMinSplitN) {
+        static vs::PerDeviceOnce once;
+        const int rc = once.run(nullptr, [](int) -> int {
+            VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&select_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, kMinSplitN * 4));
+            return VS_OK;
+        });
+        if (rc != VS_OK) return rc;
+        hipLaunchKernelGGL(select_kernel<true>, dim3(heads, 2), dim3(kSelThreads), static_cast<size_t>(n) * 4, st, p);
+    } else {
+        hipLaunchKernelGGL(select_kernel<false>, dim3(heads, 2), dim3(kSelThreads), 0, st, p);
+    }
     VS_LAUNCH_CHECK();
     return VS_OK;
 }

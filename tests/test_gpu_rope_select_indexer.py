@@ -166,6 +166,24 @@ def test_select_threshold_above_rounded_total():
     _check_select(a, a.copy(), vs.Budget(mode=0, tau_v=1.0, tau_s=1.0, n_sink=2, n_local=3, cap_v=1000, cap_s=77))
 
 
+@pytest.mark.parametrize("n", [1, 63, 8192, 8193, 32767, 40961, 131072, 140001])
+def test_select_crowded_scores(n):
+    """Scores that crowd into one bucket of the first digit: all equal, within a few percent of each other (at the longest sizes more
+    candidates than the list holds), two values, a wide spread with values above one (the last bucket has 30 bits below it);
+    both rules; registers and batches of one workgroup, ragged and many chunks."""
+    rng = np.random.default_rng(n)
+    equal = np.full(n, 1.0 / n, dtype=np.float32)
+    narrow = (equal * (1.0 + 0.04 * rng.random(n))).astype(np.float32)
+    two = np.where(rng.random(n) < 0.6, equal, np.float32(3.0 * 2.0 ** -30)).astype(np.float32)
+    wide = np.exp(rng.normal(0.0, 9.0, n)).astype(np.float32)
+    wide[rng.integers(0, n, n // 50 + 1)] = np.inf
+    a_v, a_s = np.stack([equal, narrow, wide]), np.stack([narrow, two, equal])
+    sink, local = min(4, n), min(64, n)
+    _check_select(a_v, a_s, vs.Budget(mode=0, tau_v=0.83, tau_s=0.42, n_sink=sink, n_local=local, cap_v=n, cap_s=n))
+    _check_select(a_v, a_s, vs.Budget(mode=1, k_v=n // 3 + 1, k_s=n // 2, n_sink=sink, n_local=local, cap_v=n, cap_s=n))
+    _check_select(a_v, a_s, vs.Budget(mode=0, tau_v=0.9, tau_s=0.9, n_sink=sink, n_local=local, cap_v=n // 9 + sink, cap_s=local))
+
+
 def test_select_split_over_workgroups():
     """Long problems with a workspace run the descent over one workgroup per 8192-score chunk: ties across chunk borders,
     a ragged last chunk, both rules, degenerate thresholds, bad scores, the rounded-total corner and the capacity
