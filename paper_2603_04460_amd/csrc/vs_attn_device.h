@@ -184,6 +184,60 @@ __device__ __forceinline__ void lds_load16s(uint32_t voff, const void* sbase, co
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(base), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
+// ---- row blocks whose keys are split: the partial results meet in LDS (every tile buffer is idle by then) ----
+// Eight partials: O in 64 registers x 64 lanes each, then (maximum, sum) per partial and lane.
+constexpr size_t kPartialStat = 8 * 64 * 64 * 4;
+constexpr size_t kPartialBytes = kPartialStat + 8 * 64 * 8;
+
+__device__ __forceinline__ void deposit_partial(unsigned char* smem, int which, const f32x16 (&oacc)[4], float m_run, float l_run) {
+    const int lane = threadIdx.x & 63;
+    float* const part = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) part[(which * 64 + 16 * db + e) * 64 + lane] = oacc[db][e];
+    reinterpret_cast<float2*>(smem + kPartialStat)[which * 64 + lane] = make_float2(m_run, half_swap_sum(l_run));
+}
+
+// After a barrier: of a row block's SPLITS partials (first, first + stride, ..) this wavefront finishes share `split`, 128 / SPLITS channels.
+template <int SPLITS>
+__device__ __forceinline__ void finish_partials(const AttnParams& p, const unsigned char* smem, int first, int stride, int split, int head,
+                                                int first_row) {
+    const int lane = threadIdx.x & 63, qi = lane & 31, hh = lane >> 5;
+    const float* const part = reinterpret_cast<const float*>(smem);
+    const float2* const stat = reinterpret_cast<const float2*>(smem + kPartialStat);
+    float m_tot = -INFINITY, l_tot = 0.f, f[SPLITS];
+#pragma unroll
+    for (int s = 0; s < SPLITS; ++s) m_tot = fmaxf(m_tot, stat[(stride * s + first) * 64 + lane].x);
+#pragma unroll
+    for (int s = 0; s < SPLITS; ++s) {
+        const float2 x = stat[(stride * s + first) * 64 + lane];
+        f[s] = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m_tot) * p.c);
+        l_tot = fmaf(x.y, f[s], l_tot);
+    }
+    const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    const int row = first_row + qi;
+    if (row >= p.pos0 + p.nq) return;
+    constexpr int kRegs = 64 / SPLITS;                       // accumulator registers that a wavefront finishes: four are 8 bytes of a row
+    const int reg0 = kRegs * split;
+    uint16_t* const dst = p.o + (static_cast<size_t>(head) * p.nq + (row - p.pos0)) * kD + 2 * reg0 + 4 * hh;
+#pragma unroll
+    for (int a = 0; a < kRegs / 4; ++a) {
+        float x[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < SPLITS; ++s)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = fmaf(part[((stride * s + first) * 64 + reg0 + 4 * a + c) * 64 + lane], f[s], x[c]);
+        const f32x2 x01 = {x[0] * inv, x[1] * inv}, x23 = {x[2] * inv, x[3] * inv};
+        uint2 out;
+        out.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(x01, bf16x2));
+        out.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(x23, bf16x2));
+        *reinterpret_cast<uint2*>(dst + 8 * a) = out;
+    }
+    if (p.lse && split == 0 && hh == 0)
+        p.lse[static_cast<size_t>(head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_tot * p.scale + __logf(l_tot) : -INFINITY;
+}
+
 // chunk: nq query rows at positions pos0 .. pos0 + nq - 1 against n keys
 int check_chunk(int64_t nq, int64_t n, int64_t pos0) {
     if (nq <= 0 || pos0 < 0 || pos0 + nq > n) return VS_ERR_INVALID_ARG;

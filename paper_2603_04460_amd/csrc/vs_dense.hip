@@ -33,8 +33,19 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
 constexpr size_t kSmemBytes = kSlots * kSlotBytes;
-constexpr int kShortUnits = 128;               // workgroups up to which vs_short.hip takes a call
+constexpr size_t kDuoBytes = 2 * kWaves * kSlotBytes;
+static_assert(kPartialBytes <= kDuoBytes && kDuoBytes <= 160 * 1024, "partial results in the idle buffers, one workgroup per compute unit");
+constexpr int kShortUnits = 128;               // workgroups up to which the keys of a row block are split
+constexpr int kDuoKeys = 2048;
 
+// DUO: few row blocks.  The workgroup has two row blocks, and every wavefront owns both; the keys are split over the wavefronts, which
+// take stages of two tiles in turn, each through a K and a V buffer of its own that it fills itself (no barrier): stage i of
+// wavefront w are the tiles 2 (4 i + w) and the next.  The K fragments of a stage are read in the Y slot before it, its V fragments in the X slot
+// after it, so K of the next stage is requested in the X slot and V of this one in the Y slot, between the matrix instructions, and
+// has a slot or more to arrive.  Against vs_short_kernel (one row block per wavefront, tiles shared by two wavefronts), which is bound by the
+// LDS (64 KB staged and 128 KB of fragments read for four tiles, loads alone 221 us of 322), half the fragments are read: 500 rows
+// against 32768 keys, 32 / 8 heads, 322 -> 282 us (another box 361 -> 289), 300 rows 282 -> 214, one head of 16384 143 -> 111.
+template <bool DUO>
 __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* const kvbuf = smem;
@@ -49,7 +60,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     const int hchunks = p.group / p.hc;
     const int hchunk = rest % hchunks;
     const int tile = p.tiles - 1 - rest / hchunks;          // longest tiles first
-    const int BQ = 256 / p.hc;
+    const int BQ = (DUO ? 64 : 256) / p.hc;
     const int i0 = p.pos0 + tile * BQ;                      // positions are absolute; the tile grid starts at the chunk
     const int n = p.n;                                      // keys
     const int n_pos = p.pos0 + p.nq;                        // positions that exist
@@ -59,7 +70,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     bool my_rows[2];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
-        const int w = 2 * wave + rb;
+        const int w = DUO ? rb : 2 * wave + rb;
         my_head[rb] = g * p.group + hchunk * p.hc + w % p.hc;
         my_i0[rb] = i0 + 32 * (w / p.hc);
         my_rows[rb] = my_i0[rb] < n_pos;
@@ -97,7 +108,9 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     const int st_ck = 4 * ((lane >> 2) & 3) + (((lane & 3) - st_rho) & 3);
     const int st_cv = 4 * ((((lane >> 2) & 3) - st_rho) & 3) + (lane & 3);
     const int nblk = i_last / 32 + 1;
-    const int nst = (nblk + 1) >> 1;
+    const int nst = DUO ? (nblk + 2 * kWaves - 1) / (2 * kWaves) : (nblk + 1) >> 1;
+    // first tile of a stage, in units of two
+    auto pair_of = [&](int st) __attribute__((always_inline)) { return DUO ? kWaves * st + wave : st; };
     // per-thread byte offsets of its four pieces of a stage (tile u, row half h), relative to the stage's first row
     uint32_t voff_k[2][2], voff_v[2][2];
 #pragma unroll
@@ -135,6 +148,15 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
                 lds_load16(kbase + off + st_ck * 8, dst);
                 lds_load16(vbase + off + st_cv * 8, dst + kTileBytes);
             }
+    };
+    // DUO: one group of four rows of the wavefront's own tiles, row (lane / 16) of it (rows past the end read the last one, masked);
+    // piece: 0 .. 15 of K, then of V
+    unsigned char* const own = kvbuf + wave * 2 * kSlotBytes;
+    auto load_own = [&](int st, int piece) __attribute__((always_inline)) {
+        const int v = piece >> 4, u = (piece >> 3) & 1, grp = piece & 7;
+        const uint32_t chunk = static_cast<uint32_t>(v ? st_cv : st_ck) * 16u;
+        const uint32_t at = static_cast<uint32_t>(64 * pair_of(st) + 32 * u + 4 * grp + st_rho) * 256u;
+        lds_load16s(min(at, static_cast<uint32_t>(n - 1) << 8) + chunk, v ? vbase : kbase, own + u * kSlotBytes + v * kTileBytes + grp * kGroupBytes);
     };
     const int li = lane & 15, dsel = (lane >> 4) & 1;
     const int k_row = (qi >> 2) * kGroupBytes + (qi & 3) * 256;
@@ -201,7 +223,8 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             typedef const __attribute__((address_space(3))) uint4* lds_u4_t;
             kf[u][kk] = __builtin_bit_cast(bf16x8, *(lds_u4_t)(kb[kk & 1] + u * kSlotBytes + 64 * (kk >> 1)));
         };
-        if constexpr (MR == 1) {
+        if constexpr (DUO && MR == 0 && HAS_P) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // V of stage sq - 1
+        if constexpr (!DUO && MR == 1) {
             // stage sq+1 has arrived (this wavefront's part; the barrier publishes all of it) and every wavefront
             // has left stage sq-1 behind: its buffer takes stage sq+2
             __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -213,13 +236,13 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         float mx0 = NEG_INF, mx1 = NEG_INF;
         float mxc[4];
         if constexpr (HAS_S && MASKED) {
-            mask_tile(sc[VR][0], 2 * sv, VR);
-            mask_tile(sc[VR][1], 2 * sv + 1, VR);
+            mask_tile(sc[VR][0], 2 * pair_of(sv), VR);
+            mask_tile(sc[VR][1], 2 * pair_of(sv) + 1, VR);
             VS_FENCE();
         }
         uint32_t vbase[4];                                   // V fragments of stage sq - 1
         if constexpr (MR == 0 && HAS_P) {
-            const uint32_t sbase = lds0 + 2 * ((sq + 2) % 3) * kSlotBytes;
+            const uint32_t sbase = DUO ? lds0 + wave * 2 * kSlotBytes : lds0 + 2 * ((sq + 2) % 3) * kSlotBytes;
 #pragma unroll
             for (int sgr = 0; sgr < 4; ++sgr) {
                 vbase[sgr] = sbase + v_off[sgr];
@@ -313,22 +336,38 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         };
         uint32_t kb[2];                                      // K fragments of stage sq + 1 (past the last stage: a stale slot, never used)
         if constexpr (MR == 1 && HAS_Q) {
-            const uint32_t sbase = lds0 + 2 * ((sq + 1) % 3) * kSlotBytes;
+            const uint32_t sbase = DUO ? lds0 + wave * 2 * kSlotBytes : lds0 + 2 * ((sq + 1) % 3) * kSlotBytes;
             kb[0] = sbase + k_off0;
             kb[1] = sbase + k_off2;
             asm volatile("" : "+v"(kb[0]), "+v"(kb[1]));
         }
+        // DUO: K of stage sq + 1 is requested in the X slot, V of stage sq in the Y slot; the fragments that were read from these buffers
+        // are in registers
+        constexpr bool LOADS = DUO && HAS_Q;
+        const bool next = sq + 1 < nst;
+        if constexpr (LOADS && MR == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        auto loads_upto = [&](int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+            for (int piece = 0; piece < 32; ++piece)
+                if (piece >= from && piece < to && (piece >= 16 || next)) load_own(piece >= 16 ? sq : sq + 1, piece);
+        };
 #pragma unroll
         for (int j = 6; j < 16; ++j) {                       // 10 more score products
             if constexpr (HAS_Q) qmfma(j >> 1, j & 1);
             VS_FENCE();
+            if constexpr (LOADS && MR == 0) loads_upto((j - 6) * 16 / 26, (j - 5) * 16 / 26);
+            if constexpr (LOADS && MR == 1) loads_upto(16 + (j - 6) * 16 / 10, 16 + (j - 5) * 16 / 10);
             if constexpr (HAS_S) expsteps_upto(((j - 6 + 1) * 34 + 25) / 26);
             VS_FENCE();
+        }
+        if constexpr (DUO && MR == 1 && HAS_Q) {             // K of stage sq + 1 (V of stage sq is younger)
+            if (next) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         }
 #pragma unroll
         for (int j = 0; j < 16; ++j) {                       // 16 P V products
             if constexpr (HAS_P) pmfma(j);
             VS_FENCE();
+            if constexpr (LOADS && MR == 0) loads_upto((10 + j) * 16 / 26, (11 + j) * 16 / 26);
             if constexpr (MR == 1 && HAS_Q) {
                 kread(j >> 3, j & 7, kb);
             }
@@ -344,18 +383,25 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
 #undef VS_FENCE
 
     __builtin_amdgcn_s_waitcnt(0x0F70);
-    load_stage(0);
-    if (nst > 1) load_stage(1);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
-    __syncthreads();
-    read_k(0, kf[0]);
-    read_k(1, kf[1]);
+    if constexpr (DUO) {
+#pragma unroll
+        for (int piece = 0; piece < 16; ++piece) load_own(0, piece);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
+        load_stage(0);
+        if (nst > 1) load_stage(1);
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        __syncthreads();
+    }
+    read_k(DUO ? 2 * wave : 0, kf[0]);
+    read_k(DUO ? 2 * wave + 1 : 1, kf[1]);
     using T = std::true_type;
     using F = std::false_type;
     using R0 = std::integral_constant<int, 0>;
     using R1 = std::integral_constant<int, 1>;
     // stages whose two tiles lie below the diagonal for both row blocks need no mask
-    const int nfree = (my_rows[0] && my_rows[1]) ? min(my_i0[0], my_i0[1]) / 64 : 0;
+    int nfree = (my_rows[0] && my_rows[1]) ? min(my_i0[0], my_i0[1]) / 64 : 0;
+    if constexpr (DUO) nfree = nfree > wave ? (nfree - wave - 1) / kWaves + 1 : 0;   // pairs wave, wave + 4, .. below nfree
     slot(R0{}, T{}, F{}, F{}, T{}, 0, 0);                    // X(0): scores of block 0
     slot(R1{}, T{}, F{}, T{}, T{}, 0, 0);                    // Y(0): scores of block 1; softmax of block 0
     int i = 1;
@@ -370,6 +416,15 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     slot(R0{}, F{}, T{}, T{}, T{}, nst, nst - 1);            // X(nst): P V of block 0; softmax of block 1
     slot(R1{}, F{}, T{}, F{}, T{}, nst, nst);                // Y(nst): P V of block 1
 
+    if constexpr (DUO) {
+        __syncthreads();                                     // every buffer is idle
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) deposit_partial(smem, 2 * wave + rb, oacc[rb], m_run[rb], l_run[rb]);
+        __syncthreads();
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb) finish_partials<kWaves>(p, smem, rb, 2, wave, my_head[rb], my_i0[rb]);
+        return;
+    }
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
         const float l_tot = half_swap_sum(l_run[rb]);
@@ -396,21 +451,23 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     }
 }
 
+template <bool DUO>
 int launch_dense(AttnParams& p, hipStream_t stream) {
     static vs::PerDeviceOnce once;
+    constexpr size_t lds = DUO ? kDuoBytes : kSmemBytes;
     const int rc_once = once.run(nullptr, [](int) -> int {
-        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vs_dense_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   static_cast<int>(kSmemBytes)));
+        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vs_dense_kernel<DUO>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   static_cast<int>(lds)));
         return VS_OK;
     });
     if (rc_once != VS_OK) return rc_once;
-    const int BQ = 256 / p.hc;
+    const int BQ = (DUO ? 64 : 256) / p.hc;
     p.tiles = (p.nq + BQ - 1) / BQ;
     // one workgroup per (query tile, KV head, chunk of the group's heads), longest tiles first; workgroups are dealt
     // to the 8 XCDs round-robin, so KV head = block % kv_heads keeps a head's K / V in one XCD's L2
     const long long blocks = static_cast<long long>(p.kv_heads) * (p.group / p.hc) * p.tiles;
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(vs_dense_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), kSmemBytes, stream, p);
+    hipLaunchKernelGGL(vs_dense_kernel<DUO>, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, stream, p);
     VS_LAUNCH_CHECK();
     return VS_OK;
 }
@@ -442,7 +499,8 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
     p.scale = scale;
     p.c = scale * 1.4426950408889634f;
     p.tile_counter = nullptr;
-    // Workgroups for at most half of the compute units: split the keys of a row block over wavefronts instead.  At 128 workgroups:
+    // Workgroups for at most half of the compute units: split the keys of a row block over wavefronts instead.  At 128 workgroups,
+    // vs_short_kernel there:
     // 128 heads x 200 15.8 us here, 14.5 there, 64 x 500 23.0 and 18.0, 32 x 1024 34.8 and 23.1, 32 / 8 x 1024 32.0 and 21.6,
     // 4 / 2 x 8192 187 and 94.  Beyond, long sequences still gain (152: 32 / 8 x 1200 35.9 and 30.7; 192: 24 x 2048 56.6 and 48.2),
     // short ones and long contexts lose (160: 160 x 200 16.5 and 20.0, 80 x 500 23.6 and 24.3; 152: 32 / 8, 1200 rows of 8192 keys
@@ -453,9 +511,14 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
     const bool few_tiles = p.hc <= 2 && n_kv * p.hc <= 64;
     if (units <= kShortUnits && !few_tiles) {
         p.hc = vs::short_heads(p.hc);
+        // Of these, more than 256 row blocks against at least 2048 keys: two row blocks per wavefront (DUO).  There / vs_short_kernel, us:
+        // 8 x 2048 22 / 25, 16 / 4 x 2048 33 / 33, 12 x 2600 79 / 80, 32 / 8, 500 rows of 2048 24 / 26, 1024 of 4096 73 / 80, of 32768 567 / 648;
+        // with fewer keys the fill and the larger stages cost as much: 16 / 4 x 1700 27 / 26, 24 x 1280 25 / 24, 32 / 8 x 1024 24 / 22,
+        // 128 x 200 18 / 15 (but 8 / 2 x 1500 17 / 19).
+        if (!vs::short_lone(p.q_heads, p.nq) && n_kv >= kDuoKeys) return launch_dense<true>(p, static_cast<hipStream_t>(stream));
         return vs::launch_short_dense(p, static_cast<hipStream_t>(stream));
     }
-    return launch_dense(p, static_cast<hipStream_t>(stream));
+    return launch_dense<false>(p, static_cast<hipStream_t>(stream));
 }
 
 int vs_dense_prefill(const void* q, const void* k, const void* v, int q_heads, int kv_heads, int64_t n, float scale,

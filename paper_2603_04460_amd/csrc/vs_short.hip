@@ -9,10 +9,11 @@
 //                    stage is four 32-key tiles, wavefront (s, rb) takes tile s of the stage for row block rb; two stages live in LDS.
 //   vs_lone_kernel   one row block of eight wavefronts, each with LDS buffers of its own (vs::short_lone, at most 256 row blocks).
 //
-// Measured (8 KV / 32 query heads unless stated): dense, 500 rows against 32768 keys 728 -> 357 us; 1024 x 1024 32 -> 22 us; one
-// head, 16384 x 16384 364 -> 139 us.  A step of vs_short_kernel (four tiles, 64 KB staged) takes 1.07 us while few workgroups run:
-// the chain barrier - fragment reads - scores - softmax - P V of a single tile per wavefront; with a workgroup on every compute
-// unit 1.46 us: only two row blocks use a staged tile, and the L2 then delivers 11 TB/s.
+// Long dense calls with more row blocks than that go to the two-row-block form of vs_dense.hip.
+//
+// Measured (8 KV / 32 query heads unless stated): dense, 1024 x 1024 32 -> 22 us.  A step of vs_short_kernel (four tiles, 64 KB staged)
+// takes 1.07 us while few workgroups run, 1.26 to 1.46 with one on every compute unit: the LDS (64 KB written, 128 KB of fragments
+// read) and the chain barrier - fragment reads - scores - softmax - P V of a single tile per wavefront.
 // vs_lone_kernel: sparse, one head, n = 4096, 68 scattered columns and 190 offsets 51.7 -> 30.4 us with the preparation (111 in
 // vs_attention.hip); dense, one head, 8192 x 8192 74 -> 45 us, 64 rows, 32 / 8 heads, against 32768 keys 280 -> 151 us.
 #include <hip/hip_runtime.h>
@@ -36,10 +37,7 @@ constexpr size_t kRingBytes = 2 * kSplits * kSlotBytes;
 constexpr size_t kRecOff = kRingBytes;
 constexpr size_t kGatherOff = kRecOff + (kListCap + 2 * kRecPad) * 16;
 constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4;
-constexpr size_t kPartOff = 0;                 // after the last stage: O of the 8 wavefronts, 64 registers x 64 lanes each
-constexpr size_t kStatOff = 8 * 64 * 64 * 4;   // (maximum, sum) per wavefront and lane
-constexpr size_t kDoneOff = kStatOff + 8 * 64 * 8;   // executed tiles per wavefront
-static_assert(kDoneOff + 8 * 4 <= kRingBytes, "partial results in the idle ring");
+static_assert(kPartialBytes + 8 * 4 <= kRingBytes, "partial results in the idle ring");
 static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % (32 * kSplits) == 0, "whole stages");
 
@@ -147,57 +145,18 @@ struct RowBlock {
 #pragma unroll
             for (int db = 0; db < 4; ++db) oacc[db] = mfma32(vf[2 * db + t], pb[t], oacc[db]);
     }
-    // The partial results of a row block meet in LDS (every tile buffer is idle) and each of its SPLITS wavefronts
-    // (first, first + stride, ...) finishes 128 / SPLITS channels.  done: executed tiles of this wavefront; their sum over the workgroup in
-    // thread 0 afterwards (null: none).
+    // executed tiles of this wavefront in *tiles (null: none): their sum over the workgroup in thread 0 afterwards
     template <int SPLITS>
     __device__ __forceinline__ void merge(const AttnParams& p, unsigned char* smem, int first, int stride, int split, int head, int first_row,
                                           unsigned int* tiles) {
-        const int tid = threadIdx.x, lane = tid & 63, qi = lane & 31, hh = lane >> 5;
+        unsigned int* const done = reinterpret_cast<unsigned int*>(smem + kPartialBytes);
         const int wave = first + stride * split;
-        float* const part = reinterpret_cast<float*>(smem + kPartOff);
-        float2* const stat = reinterpret_cast<float2*>(smem + kStatOff);
-        unsigned int* const done = reinterpret_cast<unsigned int*>(smem + kDoneOff);
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) part[(wave * 64 + 16 * db + e) * 64 + lane] = oacc[db][e];
-        stat[wave * 64 + lane] = make_float2(m_run, half_swap_sum(l_run));
-        if (tiles && lane == 0) done[wave] = *tiles;
+        deposit_partial(smem, wave, oacc, m_run, l_run);
+        if (tiles && (threadIdx.x & 63) == 0) done[wave] = *tiles;
         __syncthreads();
-        if (tiles && tid == 0)
+        if (tiles && threadIdx.x == 0)
             for (int w = 1; w < kThreads / 64; ++w) *tiles += done[w];
-        float m_tot = -INFINITY, l_tot = 0.f, f[SPLITS];
-#pragma unroll
-        for (int s = 0; s < SPLITS; ++s) m_tot = fmaxf(m_tot, stat[(stride * s + first) * 64 + lane].x);
-#pragma unroll
-        for (int s = 0; s < SPLITS; ++s) {
-            const float2 x = stat[(stride * s + first) * 64 + lane];
-            f[s] = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((x.x - m_tot) * p.c);
-            l_tot = fmaf(x.y, f[s], l_tot);
-        }
-        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-        const int row = first_row + qi;
-        if (row >= p.pos0 + p.nq) return;
-        constexpr int kRegs = 64 / SPLITS;                   // accumulator registers that a wavefront finishes: four are 8 bytes of a row
-        const int reg0 = kRegs * split;
-        uint16_t* const dst = p.o + (static_cast<size_t>(head) * p.nq + (row - p.pos0)) * kD + 2 * reg0 + 4 * hh;
-#pragma unroll
-        for (int a = 0; a < kRegs / 4; ++a) {
-            float x[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int s = 0; s < SPLITS; ++s)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    x[c] = fmaf(part[((stride * s + first) * 64 + reg0 + 4 * a + c) * 64 + lane], f[s], x[c]);
-            const f32x2 x01 = {x[0] * inv, x[1] * inv}, x23 = {x[2] * inv, x[3] * inv};
-            uint2 out;
-            out.x = __builtin_bit_cast(uint32_t, __builtin_convertvector(x01, bf16x2));
-            out.y = __builtin_bit_cast(uint32_t, __builtin_convertvector(x23, bf16x2));
-            *reinterpret_cast<uint2*>(dst + 8 * a) = out;
-        }
-        if (p.lse && split == 0 && hh == 0)
-            p.lse[static_cast<size_t>(head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_tot * p.scale + __logf(l_tot) : -INFINITY;
+        finish_partials<SPLITS>(p, smem, first, stride, split, head, first_row);
     }
 };
 
@@ -386,7 +345,7 @@ constexpr size_t kLoneRing = kLone * kSlotBytes;
 constexpr size_t kLoneRecOff = kLoneRing;
 constexpr size_t kLoneGatherOff = kLoneRecOff + (kListCap + 1) * 16;
 constexpr size_t kLoneLds = kLoneGatherOff + kGatherCap * 4;
-static_assert(kDoneOff + 8 * 4 <= kLoneRing, "partial results in the idle buffers");
+static_assert(kPartialBytes + 8 * 4 <= kLoneRing, "partial results in the idle buffers");
 static_assert(kLoneLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % 32 == 0, "whole tiles");
 

@@ -263,3 +263,24 @@ def test_sparse_lone_row_blocks_several_rounds(hq, hk, n, n_q, gran):
     torch.cuda.synchronize()
     ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:], kb, vb, iv, cv, is_, cs, granularity=gran or 1, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse)
+
+
+@pytest.mark.parametrize("hq,hk,n_q,n,pos0", [
+    (16, 16, 560, 2048, 0),                                  # the first rows: wavefronts without a tile of their own
+    (32, 8, 289, 2111, 1822),                                # two heads of a group, odd start, ragged last row block and last tile
+    (8, 2, 1030, 2500, 77),
+    (9, 9, 929, 4001, 3072),                                 # 64 rows of one head, the second row block missing at the end
+    (18, 9, 455, 2048, 1593),
+])
+def test_dense_two_row_blocks_per_wavefront(hq, hk, n_q, n, pos0):
+    """More than 256 row blocks, at most 128 workgroups of the long form, at least 2048 keys."""
+    assert hq * -(-n_q // 32) > 256 and dense_is_short(hq, hk, n_q, n)
+    (q, k, v), (qb, kb, vb) = make_qkv(1800 + n_q, hq, hk, n)
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, k, v, o, lse, pos0=pos0)
+    torch.cuda.synchronize()
+    rows = synth.sample_rows(7, n_q, 40, 40, 60)
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
