@@ -237,7 +237,7 @@ size_t vs_aggregate_workspace(int q_heads, int kv_heads, int index_heads, int64_
  *               scale, or NULL: then a first sweep over the scores computes them into the workspace
  *   out_heads   q_heads: one pair of vectors per query head;  kv_heads: the mean over the query heads of each KV group
  *   a_v, a_s    [out_heads, n] fp32 out.  a_v[., j] = (1/n) sum_i A[i, j];  a_s[., o] = (1/n) sum_i A[i, i - o].
- *               Each row sums to 1.  Accumulated with float atomics: the last bits depend on the order of execution.
+ *               Each row sums to 1.  Accumulated with atomics: the last bits depend on the order of execution.
  *   recall      [out_heads] fp32 out or NULL.  When given, idx_v / cnt_v / cap_v / idx_s / cnt_s / cap_s / index_heads
  *               describe the mask as for vs_sparse_prefill (element-exact rule) and
  *               recall[.] = (1/n) sum over kept (i, j), j <= i, of A[i, j].  When NULL the list arguments are ignored.

@@ -27,7 +27,7 @@
 // lanes of kh = 1.  So every offset a half wavefront meets is finished in one place, once, and is stored, without a
 // read or an atomic, to a 512-entry LDS ring that the half owns, indexed by o mod 512.  The offsets a workgroup can still touch
 // form a window of 319 consecutive values that advances by 64 per stage; the 64 that fall out of it are added over the eight
-// rings and flushed to global memory (one float atomic each) every stage.
+// rings and flushed to global memory (one atomic each) every stage.
 // (n = 16384, 32 / 8 heads with recall: 4.2 ms with one resident block per wavefront, a permutation through the LDS crossbar,
 // two adds per element and LDS float atomics; 2.2 ms with all this but the atomics, two per pair of tiles, whose rate was
 // the limit; now 1.3.  Row sweep 1.9 -> 1.05 ms.)
@@ -75,7 +75,10 @@ struct SweepParams {
     const uint32_t* sbit;           // recall only; per index head: bit (o + 64) set iff offset o selected
     const uint32_t* vbit;           // recall only; per index head: bit j set iff column j selected
     int sw, vw, index_per_q;
-    int parts;                      // column sweep: workgroups that share the streamed rows of one group of resident rows
+    int parts;                      // PARTS: workgroups that share the streamed rows of one group of resident rows
+    float2* row_part;               // row sweep with PARTS: [parts][q_heads, n] (maximum, sum) of a part's keys
+    double* acc_v;                  // column sweep with PARTS: sums of a_v and a_s, [out_heads, n] each, zero at launch
+    double* acc_s;
 };
 
 // x moved down by S lanes (row_shl) or up by S lanes (row_shr) inside every row of 16 lanes; lanes without a source get 0
@@ -94,10 +97,39 @@ __device__ __forceinline__ void add_recall_share(const SweepParams& p, int out_h
                                                 static_cast<double>(p.norm));
 }
 
+// log2 of 2^m l.  The logarithm of the mantissa alone: it is rounded towards zero, by more the larger it is, and with a maximum that
+// lags by up to 2^8 the sums are large (as m + log2(l) every row's entries came out 1.5e-7 too large, now below 3e-8).
+__device__ __forceinline__ float normaliser(float m, float l) {
+    const float base = m + static_cast<float>(__builtin_amdgcn_frexp_expf(l));
+    return base + __log2f(__builtin_amdgcn_frexp_mantf(l));
+}
+
+// The parts of the shared-out row sweep: normaliser of every row (key 0 is causal for all: the sum is positive).
+__global__ __launch_bounds__(kThreads) void combine_rows_kernel(const float2* __restrict__ part, int parts, int rows, float* __restrict__ lse2) {
+    const int row = blockIdx.x * kThreads + threadIdx.x;
+    if (row >= rows) return;
+    float m = -INFINITY;
+    for (int i = 0; i < parts; ++i) m = fmaxf(m, part[static_cast<size_t>(i) * rows + row].x);
+    float l = 0.f;
+    for (int i = 0; i < parts; ++i) {
+        const float2 x = part[static_cast<size_t>(i) * rows + row];
+        if (x.x > -INFINITY) l += x.y * __builtin_amdgcn_exp2f(x.x - m);
+    }
+    lse2[row] = normaliser(m, l);
+}
+
+// The sums of the shared-out column sweep.
+__global__ __launch_bounds__(kThreads) void finish_sums_kernel(const double* __restrict__ acc_v, const double* __restrict__ acc_s, size_t count,
+                                                               double norm, float* __restrict__ a_v, float* __restrict__ a_s) {
+    const size_t i = static_cast<size_t>(blockIdx.x) * kThreads + threadIdx.x;
+    if (i >= count) return;
+    a_v[i] = static_cast<float>(acc_v[i] * norm);
+    a_s[i] = static_cast<float>(acc_s[i] * norm);
+}
+
 // COLUMNS == false: row sweep (resident queries, streamed keys).  COLUMNS == true: column sweep.
 // PARTS: p.parts workgroups share the streamed rows of a group (a form of its own: the long sweeps lose 2 % with it).
-// NB: resident blocks per wavefront; 1 (row sweep only) gives twice the workgroups of half the length when they are few.
-template <bool COLUMNS, bool RECALL, bool PARTS = false, int NB = 2>
+template <bool COLUMNS, bool RECALL, bool PARTS = false>
 __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams p) {
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
     float* const norm_ring = reinterpret_cast<float*>(smem + kNormOff);
@@ -112,11 +144,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 
     // ---- which 256 resident rows of which query head (and which part of the streamed rows); longest sweeps first ----
     const int h = blockIdx.x % p.q_heads;
-    static_assert(NB == 2 || !COLUMNS, "the diagonal sums need both blocks");
+    constexpr int NB = 2;                                    // resident blocks per wavefront
     constexpr int kRows = 32 * NB * kWaves;                  // resident rows of this workgroup
     const int ngroups = (n + kRows - 1) / kRows;
     const int unit = blockIdx.x / p.q_heads;
-    const int grp = COLUMNS ? (PARTS ? unit / p.parts : unit) : ngroups - 1 - unit;
+    const int in_order = PARTS ? unit / p.parts : unit;
+    const int grp = COLUMNS ? in_order : ngroups - 1 - in_order;
     const int g = h / p.group;
     const int out_head = p.reduce_group ? g : h;
     const int r0_wg = kRows * grp;
@@ -146,6 +179,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         t_end = min(t_end, t0 + 2 * static_cast<int>(static_cast<long long>(stages) * (part + 1) / p.parts));
         if (t_begin >= t_end) {
             if (RECALL && tid == 0) add_recall_share(p, out_head, 0.f);
+            if (!COLUMNS && r0_wg + tid < n)
+                p.row_part[(static_cast<size_t>(part) * p.q_heads + h) * n + r0_wg + tid] = make_float2(NEG_INF, 0.f);
             return;
         }
         o_begin = 32 * (t_begin - t0);
@@ -214,6 +249,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         const uint32_t* const at = sbit + (t_begin - my_b0);
         win_prev = uniform64(((static_cast<uint64_t>(at[1]) << 32) | at[0]) >> 1);
     }
+
+    auto add_offset = [&](int o, float v) __attribute__((always_inline)) {
+        const size_t at = static_cast<size_t>(out_head) * n + o;
+        if constexpr (PARTS) unsafeAtomicAdd(p.acc_s + at, static_cast<double>(v));
+        else unsafeAtomicAdd(p.a_s + at, v * p.norm);
+    };
 
     // diagonals of one 32 x 32 set of entries; base: first row - first key
     auto diagonals = [&](const f32x16& x, int base) __attribute__((always_inline)) {
@@ -366,8 +407,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
             const unsigned low = sw[0], high = sw[1];
             v = half_swap_sum(__uint_as_float(low) + __uint_as_float(high));
-            if (lane < 16 && o >= 0 && o < n && v != 0.f)
-                unsafeAtomicAdd(p.a_s + static_cast<size_t>(out_head) * n + o, v * p.norm);
+            if (lane < 16 && o >= 0 && o < n && v != 0.f) add_offset(o, v);
         }
         if (st + 1 < nstages) load_stage(st + 1);
         const int t0 = t_begin + 2 * st;
@@ -389,10 +429,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             if (m_a > NEG_INF) l2 += l_a * __builtin_amdgcn_exp2f(m_a - m2);
             if (m_b > NEG_INF) l2 += l_b * __builtin_amdgcn_exp2f(m_b - m2);
             const int row = my_r0 + 32 * b + qi;
-            // the logarithm of the mantissa alone: it is rounded towards zero, by more the larger it is, and with a maximum that
-            // lags by up to 2^8 the sums are large (as m2 + log2(l2) every row's entries came out 1.5e-7 too large, now below 3e-8)
-            const float base = m2 + static_cast<float>(__builtin_amdgcn_frexp_expf(l2));
-            if (row < n && hh == 0) p.lse2[static_cast<size_t>(h) * n + row] = base + __log2f(__builtin_amdgcn_frexp_mantf(l2));
+            if constexpr (PARTS) {
+                if (row < n && hh == 0)
+                    p.row_part[(static_cast<size_t>(unit % p.parts) * p.q_heads + h) * n + row] = make_float2(m2, l2);
+                continue;
+            }
+            if (row < n && hh == 0) p.lse2[static_cast<size_t>(h) * n + row] = normaliser(m2, l2);
         }
     } else {
         if (my_r0 < n && (!PARTS || my_b0 < t_end)) {
@@ -409,16 +451,18 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
                 float v = 0.f;
 #pragma unroll
                 for (int r = 0; r < kRings; ++r) v += diag[r * kDiagPitch + (o & (kDiagRing - 1))];
-                if (v != 0.f) unsafeAtomicAdd(p.a_s + static_cast<size_t>(out_head) * n + o, v * p.norm);
+                if (v != 0.f) add_offset(o, v);
             }
         }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const float cs = half_swap_sum(col_sum[b]) * p.norm;
+            const float cs = half_swap_sum(col_sum[b]);
             const int key = my_r0 + 32 * b + qi;
             if (key < n && hh == 0) {
-                if (PARTS || p.reduce_group) unsafeAtomicAdd(p.a_v + static_cast<size_t>(out_head) * n + key, cs);
-                else p.a_v[static_cast<size_t>(out_head) * n + key] = cs;
+                const size_t at = static_cast<size_t>(out_head) * n + key;
+                if constexpr (PARTS) unsafeAtomicAdd(p.acc_v + at, static_cast<double>(cs));
+                else if (p.reduce_group) unsafeAtomicAdd(p.a_v + at, cs * p.norm);
+                else p.a_v[at] = cs * p.norm;
             }
         }
         if (RECALL) {
@@ -447,8 +491,22 @@ __global__ void clear_kernel(float* a_v, float* a_s, size_t count, float* recall
     if (i < words) bits[i] = 0u;
 }
 
+// Up to 1024 groups of resident rows (512 workgroups run at once, and the longest sweep is twice the average): the streamed rows of a
+// group are shared out over several workgroups, 1024 in all, or two each, of at least four stages of two tiles; their column and diagonal sums
+// are added in fp64 (as float atomics the sums of more, shorter parts were up to twice as far off).  us per call: one head, n = 4000
+// (16 groups) 73 -> 33, 16000 (63) 284 -> 127; 8 / 2 heads, n = 1500 (48) 53 -> 40, 5000 (160) 277 -> 101, 8000 (256) 425 -> 190, 16000 (504)
+// 785 -> 613; 32 / 8 heads, n = 1000 (128) 48 -> 44, 2000 (256) 125 -> 85, 4000 (512) 235 -> 199, 8192 (1024) 673 -> 643, 12000 (1504, not
+// shared) 1288.  (Before: the column sweep of up to 128 groups shared out, the row sweep in workgroups of 128 rows.)  2048 workgroups, float
+// sums: 164 at one head, n = 16000, 128 at 8 / 2 x 5000, 580 at 16000.
+int sweep_parts(int q_heads, int64_t n) {
+    const int64_t groups = static_cast<int64_t>(q_heads) * ((n + kGroupRows - 1) / kGroupRows);
+    if (groups > 1024) return 1;
+    const int64_t max_parts = ((n + 63) / 64 + 3) / 4, parts = groups > 512 ? 2 : 1024 / groups;
+    return static_cast<int>(parts < max_parts ? parts : max_parts);
+}
+
 struct AggWs {
-    size_t lse_off, sbit_off, vbit_off, acc_off, count_off, total;
+    size_t lse_off, sbit_off, vbit_off, acc_off, count_off, sums_off, clear_end, row_off, total;
     int sw, vw;
 };
 
@@ -462,7 +520,12 @@ AggWs agg_ws_layout(int q_heads, int index_heads, int64_t n) {
     // (recall wanted: fp64 sums and arrival counts, cleared with the bitmaps)
     w.acc_off = vs::round_up(w.vbit_off + static_cast<size_t>(index_heads) * w.vw * 4, 8);
     w.count_off = w.acc_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 8 : 0);
-    w.total = vs::round_up(w.count_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 4 : 0), 256);
+    w.sums_off = vs::round_up(w.count_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 4 : 0), 256);
+    const int parts = sweep_parts(q_heads, n);
+    // shared-out sweeps: fp64 sums of a_v and a_s (cleared as well), the row sweep's partial results
+    w.clear_end = w.sums_off + (parts > 1 ? vs::round_up(2 * static_cast<size_t>(q_heads) * n * sizeof(double), 256) : 0);
+    w.row_off = w.clear_end;
+    w.total = w.row_off + (parts > 1 ? vs::round_up(static_cast<size_t>(parts) * q_heads * n * sizeof(float2), 256) : 0);
     return w;
 }
 
@@ -519,10 +582,12 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     const size_t out_count = static_cast<size_t>(out_heads) * n;
     uint32_t* sbit = reinterpret_cast<uint32_t*>(base + w.sbit_off);
     uint32_t* vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);
-    const size_t words = want_recall ? (w.total - w.sbit_off) / 4 : 0;
+    const int parts = sweep_parts(q_heads, n);
+    const size_t sums_end = w.sums_off + (parts > 1 ? 2 * out_count * sizeof(double) : 0);
+    const size_t words = want_recall || parts > 1 ? (sums_end - w.sbit_off) / 4 : 0;
     const size_t most = words > out_count ? words : out_count;   // (at least one output per head: recall rides along)
-    hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>((most + 255) / 256)), dim3(256), 0, st, a_v, a_s, out_count, recall,
-                       out_heads, sbit, words);
+    hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>((most + 255) / 256)), dim3(256), 0, st, a_v, a_s, parts > 1 ? 0 : out_count,
+                       recall, out_heads, sbit, words);
     VS_LAUNCH_CHECK();
     if (want_recall) {
         hipLaunchKernelGGL(set_bits_kernel, dim3((cap_s + 255) / 256, index_heads), dim3(256), 0, st, idx_s, cnt_s, cap_s,
@@ -540,33 +605,34 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
     p.lse = lse ? lse : p.lse2;
     p.lse_scale = lse ? 1.4426950408889634f : 1.f;
+    p.parts = parts;
+    p.acc_v = reinterpret_cast<double*>(base + w.sums_off);
+    p.acc_s = p.acc_v + out_count;
+    p.row_part = reinterpret_cast<float2*>(base + w.row_off);
+    const dim3 grid(static_cast<unsigned>(blocks * parts));
     if (!lse) {
-        // few groups (see below): one block per wavefront; one head, n = 16000 421 -> 294 us for the call, 8 heads, n = 4000 161 -> 130
-        if (blocks <= 128) {
-            const int64_t halves = static_cast<int64_t>(q_heads) * ((n + kGroupRows / 2 - 1) / (kGroupRows / 2));
-            hipLaunchKernelGGL((vs_sweep_kernel<false, false, false, 1>), dim3(static_cast<unsigned>(halves)), dim3(kThreads), 0, st, p);
+        if (parts > 1) {
+            hipLaunchKernelGGL((vs_sweep_kernel<false, false, true>), grid, dim3(kThreads), 0, st, p);
+            VS_LAUNCH_CHECK();
+            const int rows = q_heads * static_cast<int>(n);  // at most 1024 groups of 256
+            hipLaunchKernelGGL(combine_rows_kernel, dim3(static_cast<unsigned>((rows + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
+                               p.row_part, parts, rows, p.lse2);
         } else {
-            hipLaunchKernelGGL((vs_sweep_kernel<false, false>), dim3(static_cast<unsigned>(blocks)), dim3(kThreads), 0, st, p);
+            hipLaunchKernelGGL((vs_sweep_kernel<false, false>), grid, dim3(kThreads), 0, st, p);
         }
         VS_LAUNCH_CHECK();
     }
-    // Few groups of resident keys (a quarter of the 512 workgroups that run at once): their streamed queries are shared out over
-    // several workgroups of at least eight stages (16 tiles).  One head, n = 16000 809 -> 421 us for the call (the row sweep still
-    // with two blocks per wavefront), 8 heads, n = 4000 222 -> 161, 32 heads, n = 1000 75 -> 60; at 256 and 512 groups the call was
-    // 2 and 5 % slower.
-    const int64_t max_parts = ((n + 63) / 64 + 7) / 8;
-    int64_t parts = blocks <= 128 ? 1024 / blocks : 1;
-    if (parts > max_parts) parts = max_parts;
-    p.parts = static_cast<int>(parts);
     if (want_recall) {
         p.recall_acc = reinterpret_cast<double*>(base + w.acc_off);
         p.recall_count = reinterpret_cast<unsigned int*>(base + w.count_off);
         p.recall_shares = static_cast<unsigned int>(blocks / q_heads * parts * (p.reduce_group ? p.group : 1));
     }
-    const dim3 grid(static_cast<unsigned>(blocks * parts));
     if (parts > 1) {
         if (want_recall) hipLaunchKernelGGL((vs_sweep_kernel<true, true, true>), grid, dim3(kThreads), 0, st, p);
         else hipLaunchKernelGGL((vs_sweep_kernel<true, false, true>), grid, dim3(kThreads), 0, st, p);
+        VS_LAUNCH_CHECK();
+        hipLaunchKernelGGL(finish_sums_kernel, dim3(static_cast<unsigned>((out_count + kThreads - 1) / kThreads)), dim3(kThreads), 0, st, p.acc_v,
+                           p.acc_s, out_count, 1.0 / (static_cast<double>(n) * (p.reduce_group ? p.group : 1)), a_v, a_s);
     } else {
         if (want_recall) hipLaunchKernelGGL((vs_sweep_kernel<true, true>), grid, dim3(kThreads), 0, st, p);
         else hipLaunchKernelGGL((vs_sweep_kernel<true, false>), grid, dim3(kThreads), 0, st, p);

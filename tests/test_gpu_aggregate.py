@@ -91,8 +91,7 @@ def test_aggregate_tile_edges(n):
 
 @pytest.mark.parametrize("hq,hk,n", [(32, 8, 1057), (16, 4, 2085)])
 def test_aggregate_many_groups(hq, hk, n):
-    """More than 128 groups of 256 resident rows: two blocks per wavefront in the row sweep, one workgroup per group in the
-    column sweep (fewer groups take the forms that share a group out)."""
+    """144 groups of 256 resident rows, several workgroups to a group."""
     rng = np.random.default_rng(n)
     (q, k, v), (qb, kb, vb) = make_qkv(520 + n, hq, hk, n, local=True)
     iv, cv = lists([rng.choice(n, 40, replace=False) for _ in range(hk)])
@@ -102,6 +101,28 @@ def test_aggregate_many_groups(hq, hk, n):
     _close(a_v, ref_v)
     _close(a_s, ref_s)
     assert np.abs(rec - ref_r).max() <= RECALL_ABS, (rec, ref_r)
+
+
+@pytest.mark.parametrize("pairs,n", [(103, 1100), (129, 900), (52, 1500), (26, 1500), (85, 1025)])
+def test_aggregate_group_sharing(pairs, n):
+    """One workgroup per group of 256 resident rows (more than 1024 groups: 206 x 5, 258 x 4), two (624; 850, with a last group of one row) and
+    three (312), with a recall, per query head and as the mean over a KV group: two query heads of one KV head, repeated."""
+    groups = 2 * pairs * -(-n // 256)
+    assert (groups > 1024) == (pairs in (103, 129)) and (512 < groups <= 1024) == (pairs in (52, 85))
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(560 + n, 2, 1, n, local=True)
+    iv, cv = lists([rng.choice(n, size=n // 10, replace=False)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=n // 20, replace=False)]))])
+    ref_v, ref_s, ref_r = _oracle(qb, kb, 2, mask=(iv, cv, is_, cs))
+    qr, kr = q.repeat(pairs, 1, 1).contiguous(), k.repeat(pairs, 1, 1).contiguous()
+    mask = (np.repeat(iv, pairs, 0), np.repeat(cv, pairs), np.repeat(is_, pairs, 0), np.repeat(cs, pairs))
+    a_v, a_s, rec = _run(qr, kr, 2 * pairs, mask=mask)
+    _close(a_v, np.tile(ref_v, (pairs, 1)))
+    _close(a_s, np.tile(ref_s, (pairs, 1)))
+    assert np.abs(rec - np.tile(ref_r, pairs)).max() <= RECALL_ABS
+    a_v, a_s, _ = _run(qr, kr, pairs)
+    _close(a_v, np.repeat(ref_v.mean(0, keepdims=True), pairs, 0))
+    _close(a_s, np.repeat(ref_s.mean(0, keepdims=True), pairs, 0))
 
 
 def test_aggregate_8192_one_head_elementwise():
@@ -122,9 +143,8 @@ def test_aggregate_8192_one_head_elementwise():
 
 
 def test_aggregate_8192_five_heads_elementwise():
-    """The same with five query heads (the same one five times, so that the oracle runs once): 160 groups, one workgroup per
-    group in the column sweep, 128 streamed stages for the longest; the 512-entry diagonal rings wrap 16 times and every
-    flush window is compared."""
+    """The same with five query heads (the same one five times, so that the oracle runs once): 160 groups, six workgroups to a
+    group, up to 22 streamed stages each; the 512-entry diagonal rings wrap and every flush window is compared."""
     hq, hk, n = 5, 1, 8192
     rng = np.random.default_rng(8192)
     (q, k, v), (qb, kb, vb) = make_qkv(8192, 1, hk, n, local=True)
