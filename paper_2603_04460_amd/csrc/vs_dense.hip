@@ -472,6 +472,21 @@ int launch_dense(AttnParams& p, hipStream_t stream) {
     return VS_OK;
 }
 
+// More workgroups of the long form than that, but about one round of them or less: the call then takes as long as its longest workgroup,
+// while the two-row-block form spreads the same work evenly, at a higher price per tile and per workgroup.  Long form: 0.93 us per tile
+// of the longest workgroup, or of the average over 256 compute units where that is more; DUO: 0.55 us per tile and row block of a SIMD and 7 us
+// per round of workgroups.  Here / there, us: 24 x 2048 (192 workgroups) 57 / 46, 16 x 4096 (256) 103 / 91, 8 / 2 x 6000 (188) 139 / 95, x 8192 (256)
+// 191 / 154, x 10000 (314) 301 / 232, 1 x 40000 (157) 1134 / 439, 32 / 8, 1500 rows of 8192 (188) 237 / 196, of 32768 927 / 776, 1100 of 32768
+// (144) 926 / 720; not: 32 / 8 x 2048 (256) 60 / 66, x 3000 (375) 84 / 108, 8 / 2 x 16000 (500) 448 / 543, 2048 rows of 8192 (256) 221 / 252.
+bool duo_is_faster(int q_heads, int64_t n_q, int64_t pos0) {
+    const int64_t blocks = (n_q + 31) / 32, last = (pos0 + n_q + 31) / 32;
+    const int64_t work = q_heads * (blocks * (last - blocks) + blocks * (blocks + 1) / 2);   // tiles x row blocks
+    const int64_t rounds = (q_heads * blocks / 2 + 255) / 256;
+    const int64_t average = work / (8 * 256);                // eight row blocks a workgroup
+    return 0.55 * static_cast<double>(work) / 1024.0 + 7.0 * static_cast<double>(rounds) <
+           0.95 * 0.93 * static_cast<double>(last > average ? last : average);
+}
+
 }  // namespace
 
 extern "C" {
@@ -517,6 +532,10 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
         // 128 x 200 18 / 15 (but 8 / 2 x 1500 17 / 19).
         if (!vs::short_lone(p.q_heads, p.nq) && n_kv >= kDuoKeys) return launch_dense<true>(p, static_cast<hipStream_t>(stream));
         return vs::launch_short_dense(p, static_cast<hipStream_t>(stream));
+    }
+    if (n_kv >= kDuoKeys && duo_is_faster(q_heads, n_q, pos0)) {
+        p.hc = vs::short_heads(p.hc);
+        return launch_dense<true>(p, static_cast<hipStream_t>(stream));
     }
     return launch_dense<false>(p, static_cast<hipStream_t>(stream));
 }

@@ -284,3 +284,21 @@ def test_dense_two_row_blocks_per_wavefront(hq, hk, n_q, n, pos0):
     rows = synth.sample_rows(7, n_q, 40, 40, 60)
     ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q", [(24, 24, 2048, 0, 2048), (8, 2, 6001, 0, 6001), (32, 8, 5000, 3700, 1290),   # evenly spread
+                                              (32, 8, 2048, 0, 2048), (32, 8, 2100, 31, 2060)])                            # long form
+def test_dense_about_one_round_of_workgroups(hq, hk, n, pos0, n_q):
+    """More than 128 workgroups of the long form, at least 2048 keys: spread over two-row-block workgroups where the longest workgroup
+    would be all that runs in the end, or not."""
+    assert not dense_is_short(hq, hk, n_q, n)
+    (q, k, v), (qb, kb, vb) = make_qkv(1900 + n, hq, hk, n)
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, k, v, o, lse, pos0=pos0 if n_q != n else None)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all() and torch.isfinite(lse).all()
+    rows = synth.sample_rows(8, n_q, 24, 24, 40)
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
