@@ -302,3 +302,33 @@ def test_dense_about_one_round_of_workgroups(hq, hk, n, pos0, n_q):
     rows = synth.sample_rows(8, n_q, 24, 24, 40)
     ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+@pytest.mark.parametrize("hq,hk,n,n_q,per_q,gran", [
+    (8, 2, 1700, 1700, False, None), (8, 2, 2048, 2048, False, 32),      # two heads of a group share a workgroup
+    (32, 8, 4101, 300, False, None),
+    (6, 3, 2431, 2431, False, None),                                     # a group of two, 456 row blocks
+    (20, 20, 1290, 1290, False, None), (8, 2, 4096, 4096, True, 32),     # one head a workgroup, 220 and 256 units
+    (8, 2, 2080, 2080, False, None), (33, 33, 1025, 1025, False, None),  # just beyond: vs_attention.hip
+])
+def test_sparse_few_row_blocks(hq, hk, n, n_q, per_q, gran):
+    """Up to 512 row blocks of grouped heads, up to 256 units of one head, at least 1000 rows or 4096 keys."""
+    rng = np.random.default_rng(n + hq)
+    (q, k, v), (qb, kb, vb) = make_qkv(2000 + n, hq, hk, n)
+    heads, pos0 = hq if per_q else hk, n - n_q
+    iv, cv = lists([rng.choice(n, size=5 + 60 * (h % 3), replace=False) for h in range(heads)], cap=130)
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=3 + 40 * (h % 2), replace=False)])) for h in range(heads)], cap=70)
+    assert sparse_is_short(hq, hk, n_q, n, 200, per_q) == ((hq, n) not in ((8, 2080), (33, 1025)))
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    qc = q[:, pos0:].contiguous()
+    o = torch.full_like(qc, float("nan"))
+    lse = torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, heads, n), dtype=torch.uint8, device="cuda")
+    vs.sparse_prefill(qc, k, v, f(iv), f(cv), f(is_), f(cs), o, lse, ws, slash_granularity=gran, pos0=pos0 if pos0 else None)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all()
+    rows = synth.sample_rows(6, n_q, 32, 40, 40)
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:], kb, vb, iv, cv, is_, cs, rows=rows, granularity=gran or 1, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+    if not per_q and not pos0:
+        check_key_set(k, iv, cv, is_, cs, hq, rows, granularity=gran)
