@@ -9,13 +9,13 @@
 //
 // Workgroups are persistent: 8 wavefronts, each keeping the W_U fragments of ITS 32 hidden units in
 // registers for the whole kernel (256 units per workgroup; wider layers are split over workgroups
-// and their partial logits added afterwards), while 128-token tiles of X stream through a double
+// and their partial logits added afterwards), while tiles of 128 or 64 tokens of X stream through a double
 // buffer in LDS, read from HBM exactly once.  Per tile every wavefront adds its units' share of the
-// two logits; the shares meet in LDS and wavefronts 0 and 1 write the logits together with the tile's
+// two logits; the shares meet in LDS and wavefronts 0 and 1 (0) write the logits together with the tile's
 // (max, sum of exp) for the softmax over all positions, which a second kernel finishes in place.
 // The wavefronts of a workgroup meet at a barrier per tile and therefore run in phase: left to
 // itself, every SIMD would alternate between a stretch of matrix instructions and a stretch of
-// activation arithmetic.  The four 32-token blocks of a tile are software-pipelined instead: the
+// activation arithmetic.  The 32-token blocks of a tile are software-pipelined instead: the
 // matrix products of block j + 1 are interleaved, instruction by instruction, with the activation
 // of block j.
 #include <hip/hip_runtime.h>
@@ -33,16 +33,16 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kUnitsPerWg = 32 * kWaves;   // 256
-constexpr int kTokTile = 128;              // tokens per step: four MFMA column blocks of 32
-constexpr int kBlocks = kTokTile / 32;
+constexpr int kMaxTile = 128;              // tokens per step: four MFMA column blocks of 32, or two
+constexpr int kMinTile = 64;
 constexpr int kXPitch = 512;               // bytes per token row in LDS: K | V in bf16; 16-byte chunk c of row r sits at chunk
                                            // position c ^ (r % 16), so that 16 consecutive rows read at one chunk hit 16 bank groups
 constexpr int kXBufs = 2;                  // token tiles: one being read, one in flight from HBM
 constexpr int kMaxDh = 1024;
-constexpr size_t kXBytes = static_cast<size_t>(kTokTile) * kXPitch;
+constexpr size_t kXBytes = static_cast<size_t>(kMaxTile) * kXPitch;
 constexpr size_t kVecOff = kXBufs * kXBytes;                            // b_U, W_V, W_S of the workgroup's units
 constexpr size_t kRedOff = kVecOff + 3 * kUnitsPerWg * 4;          // two parities x wavefronts x tokens x (v, s)
-constexpr size_t kSmemBytes = kRedOff + 2 * kWaves * kTokTile * 8;
+constexpr size_t kSmemBytes = kRedOff + 2 * kWaves * kMaxTile * 8;
 
 // GELU (erf form) = x Phi(x) with the normal distribution function written as a logistic function of an odd polynomial,
 // Phi(x) = 1 / (1 + exp(-x P(x^2))), P of degree 4 fitted (minimax over |x| <= 8, own fit) so that x Phi(x) is within
@@ -76,13 +76,14 @@ struct IndexerParams {
     float* out_s;
     size_t slice_stride;            // elements between the partial-logit arrays of consecutive slices (0: one slice)
     float2* part;                   // per (head, direction, 64-token block): (max, sum of exp) of its logits; null with several slices
-    int tiles_per_head;             // 128-token tiles
+    int tiles_per_head;             // tiles of 128 or 64 tokens
     int parts_per_head;             // 64-token statistics blocks
     int nslices, lanes;             // slices of 256 hidden units; workgroups per slice (a multiple of 8)
 };
 
-template <int ACT>
+template <int ACT, int kTokTile>
 __global__ __launch_bounds__(kThreads) void indexer_logits_kernel(const IndexerParams p) {
+    constexpr int kBlocks = kTokTile / 32;
     extern __shared__ __align__(16) unsigned char smem[];
     float* const sbU = reinterpret_cast<float*>(smem + kVecOff);
     float* const sWV = sbU + kUnitsPerWg;
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(kThreads) void indexer_logits_kernel(const IndexerP
     float* const out_v = p.out_v + static_cast<size_t>(slice) * p.slice_stride;
     float* const out_s = p.out_s + static_cast<size_t>(slice) * p.slice_stride;
 
-    // tiles of 64 tokens, never across heads; workgroup b takes tiles b, b + gridDim.x, ...
+    // tiles of tokens, never across heads; workgroup b takes tiles b, b + gridDim.x, ...
     const long long total_tiles = static_cast<long long>(p.heads) * p.tiles_per_head;
     // Staging: a wavefront instruction deposits 1 KB = two token rows; wavefront w moves rows 16 w .. 16 w + 15 of a tile
     // with eight instructions.  Lane L fills chunk position L % 32 of its row, i.e. it fetches that row's chunk
@@ -432,7 +433,7 @@ __global__ __launch_bounds__(256) void softmax_finish_kernel(float* a_v, float* 
 struct IndexerWs {
     size_t hi_off, lo_off, part_off, plog_off, total;
     size_t slice_stride;            // elements per slice of partial logits (one direction)
-    int tiles_per_head, parts_per_head, nslices;
+    int parts_per_head, nslices;
 };
 
 IndexerWs indexer_ws_layout(int kv_heads, int64_t n, int d_h) {
@@ -440,7 +441,6 @@ IndexerWs indexer_ws_layout(int kv_heads, int64_t n, int d_h) {
     w.hi_off = 0;
     w.lo_off = vs::indexer_split_lo_offset(d_h);
     w.part_off = 2 * w.lo_off;
-    w.tiles_per_head = static_cast<int>((n + kTokTile - 1) / kTokTile);
     w.parts_per_head = static_cast<int>((n + 63) / 64);
     w.nslices = (d_h + kUnitsPerWg - 1) / kUnitsPerWg;
     w.plog_off = w.part_off + vs::round_up(static_cast<size_t>(kv_heads) * 2 * w.parts_per_head * sizeof(float2), 256);
@@ -483,10 +483,11 @@ int vs::index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_
     static int cus_of[vs::kMaxDevices];
     int dev = 0;
     const int rc_once = once.run(&dev, [](int d) -> int {
-        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&indexer_logits_kernel<0>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kSmemBytes)));
-        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&indexer_logits_kernel<1>),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kSmemBytes)));
+        for (const void* kernel : {reinterpret_cast<const void*>(&indexer_logits_kernel<0, kMaxTile>),
+                                   reinterpret_cast<const void*>(&indexer_logits_kernel<0, kMinTile>),
+                                   reinterpret_cast<const void*>(&indexer_logits_kernel<1, kMaxTile>),
+                                   reinterpret_cast<const void*>(&indexer_logits_kernel<1, kMinTile>)})
+            VS_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kSmemBytes)));
         int cus = 0;
         VS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, d));
         cus_of[d] = cus > 0 ? cus : 256;
@@ -509,7 +510,6 @@ int vs::index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_
     p.W_S = w->W_S;
     p.b_V = w->b_V;
     p.b_S = w->b_S;
-    p.tiles_per_head = lay.tiles_per_head;
     p.parts_per_head = lay.parts_per_head;
     float* plog_v = reinterpret_cast<float*>(base + lay.plog_off);
     float* plog_s = plog_v + static_cast<size_t>(lay.nslices) * lay.slice_stride;
@@ -525,16 +525,26 @@ int vs::index_score(const void* k_bf16, const void* v_bf16, int kv_heads, int64_
         p.part = nullptr;
     }
     // persistent workgroups of 8 wavefronts, one per compute unit, shared out over the slices of 256 hidden units
-    const long long total_tiles = static_cast<long long>(kv_heads) * lay.tiles_per_head;
     long long lanes = (cus_of[dev] / lay.nslices) & ~7;
     if (lanes < 8) lanes = 8;
-    const long long need = (total_tiles + 7) & ~7ll;
+    auto tiles = [&](int tile) -> long long { return kv_heads * static_cast<long long>((n + tile - 1) / tile); };
+    auto rounds = [&](int tile) -> long long { return (tiles(tile) + lanes - 1) / lanes; };
+    // Tiles of 64 tokens where they fill the last round better; a round of them takes a little more than half as long.  128 / 64, us
+    // per call, 8 heads, GELU / 256: n = 1000 (one round of either) 17.3 / 13.8, 3000 (1, 2 rounds) 17.9 / 18.2, 5000 (2, 3) 24.8 / 22.2, 8192 (2, 4)
+    // 26.8 / 27.2, 10000 (3, 5) 33.4 / 31.4, 20000 (5, 10) 51.3 / 52.1; SiLU / 1024: 2 heads, n = 5000 (2, 3) 24.2 / 21.8, 8 heads, 20000 (20, 40)
+    // 150 / 155.  Same results.
+    const bool half = 53 * rounds(kMinTile) < 100 * rounds(kMaxTile);
+    const int tile = half ? kMinTile : kMaxTile;
+    const long long need = (tiles(tile) + 7) & ~7ll;
     if (lanes > need) lanes = need;
+    p.tiles_per_head = static_cast<int>((n + tile - 1) / tile);
     p.nslices = lay.nslices;
     p.lanes = static_cast<int>(lanes);
     const dim3 grid(static_cast<unsigned>(lanes * lay.nslices));
-    if (w->act == 0) hipLaunchKernelGGL(indexer_logits_kernel<0>, grid, dim3(kThreads), kSmemBytes, st, p);
-    else hipLaunchKernelGGL(indexer_logits_kernel<1>, grid, dim3(kThreads), kSmemBytes, st, p);
+    if (w->act == 0 && half) hipLaunchKernelGGL((indexer_logits_kernel<0, kMinTile>), grid, dim3(kThreads), kSmemBytes, st, p);
+    else if (w->act == 0) hipLaunchKernelGGL((indexer_logits_kernel<0, kMaxTile>), grid, dim3(kThreads), kSmemBytes, st, p);
+    else if (half) hipLaunchKernelGGL((indexer_logits_kernel<1, kMinTile>), grid, dim3(kThreads), kSmemBytes, st, p);
+    else hipLaunchKernelGGL((indexer_logits_kernel<1, kMaxTile>), grid, dim3(kThreads), kSmemBytes, st, p);
     VS_LAUNCH_CHECK();
     if (lay.nslices > 1) {
         hipLaunchKernelGGL(combine_slices_kernel, dim3(lay.parts_per_head, kv_heads, 2), dim3(64), 0, st, plog_v, plog_s,

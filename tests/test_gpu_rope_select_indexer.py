@@ -248,3 +248,21 @@ def test_indexer_scores(hk, n, d_h, act, local):
         rel = np.abs(g - r) / r
         assert rel.max() <= 1e-3, rel.max()
         np.testing.assert_allclose(g.sum(axis=1), 1.0, atol=1e-5)
+
+
+@pytest.mark.parametrize("hk,n,d_h,act,tile", [(8, 3001, 256, 1, 128), (8, 4100, 256, 1, 64), (4, 2000, 1024, 0, 128), (4, 2100, 1024, 0, 64),
+                                                (2, 65, 64, 0, 64)])
+def test_indexer_tile_sizes(hk, n, d_h, act, tile):
+    """Tiles of 64 tokens where their rounds over the 256 compute units (shared out over slices of 256 hidden units) take less than the
+    rounds of 128: one and several rounds of either, ragged last tiles."""
+    lanes = 256 // -(-d_h // 256)
+    rounds = lambda t: -(-hk * -(-n // t) // lanes)
+    assert tile == (64 if 53 * rounds(64) < 100 * rounds(128) else 128)
+    _, k, v = synth.qkv(41 + n, 1, hk, n, local_structure=False)
+    kb, vb = synth.to_bits(k), synth.to_bits(v)
+    W = synth.indexer_weights(n, d_h, act)
+    g_v, g_s = _gpu_index(kb, vb, W, act, 0.25, -1.5)
+    r_v, r_s = oracle.index_score(kb, vb, *W, 0.25, -1.5, act=act)
+    for g, r in ((g_v, r_v), (g_s, r_s)):
+        assert (np.abs(g - r) / r).max() <= 1e-3
+        np.testing.assert_allclose(g.sum(axis=1), 1.0, atol=1e-5)
