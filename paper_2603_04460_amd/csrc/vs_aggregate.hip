@@ -39,7 +39,6 @@
 
 #include "vs_attn_device.h"
 #include "vs_common.h"
-#include "vs_device.h"
 
 namespace {
 
@@ -480,15 +479,51 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     }
 }
 
-// outputs are accumulated with atomics and bitmaps with bit atomics: all of them start at zero (one launch)
-__global__ void clear_kernel(float* a_v, float* a_s, size_t count, float* recall, int heads, uint32_t* bits, size_t words) {
-    const size_t i = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < count) {
-        a_v[i] = 0.f;
-        a_s[i] = 0.f;
+// Everything a call starts from, in one launch: the bitmaps of the mask's lists (a workgroup each, built in LDS and written out whole),
+// zeroed outputs and sums.  (Clearing the bitmaps and setting their bits with global atomics were three launches: with recall, one head,
+// n = 1000 38 -> 31 us, 8 / 2 heads, n = 1500 42 -> 35, 32 / 8 heads, n = 2000 83 -> 80.)
+constexpr int kSetupThreads = 1024;
+struct SetupParams {
+    const int32_t* idx[2];          // offsets, columns
+    const int32_t* cnt[2];
+    int cap[2];
+    uint32_t* bits[2];              // per index head: words[.] words, bit e + shift[.] for every list entry e
+    int words[2], shift[2];
+    int n, index_heads;             // index_heads: 0 without a mask
+    float* a_v;                     // outputs that are accumulated in place
+    float* a_s;
+    size_t count;
+    float* recall;
+    int heads;
+    uint32_t* sums;                 // workspace words
+    size_t sum_words;
+};
+
+__global__ __launch_bounds__(kSetupThreads) void setup_kernel(const SetupParams p) {
+    extern __shared__ uint32_t bm[];
+    const int tid = threadIdx.x, block = blockIdx.x;
+    if (block < 2 * p.index_heads) {
+        const int list = block & 1, ih = block >> 1, words = p.words[list];
+        for (int w = tid; w < words; w += kSetupThreads) bm[w] = 0u;
+        __syncthreads();
+        const int m = min(p.cnt[list][ih], p.cap[list]);
+        for (int t = tid; t < m; t += kSetupThreads) {
+            const int e = p.idx[list][static_cast<size_t>(ih) * p.cap[list] + t];
+            const int bit = e + p.shift[list];
+            if (e >= 0 && e < p.n) atomicOr(&bm[bit >> 5], 1u << (bit & 31));
+        }
+        __syncthreads();
+        uint32_t* const out = p.bits[list] + static_cast<size_t>(ih) * words;
+        for (int w = tid; w < words; w += kSetupThreads) out[w] = bm[w];
+        return;
     }
-    if (recall && i < static_cast<size_t>(heads)) recall[i] = 0.f;
-    if (i < words) bits[i] = 0u;
+    const size_t i = static_cast<size_t>(block - 2 * p.index_heads) * kSetupThreads + tid;
+    if (i < p.count) {
+        p.a_v[i] = 0.f;
+        p.a_s[i] = 0.f;
+    }
+    if (p.recall && i < static_cast<size_t>(p.heads)) p.recall[i] = 0.f;
+    if (i < p.sum_words) p.sums[i] = 0u;
 }
 
 // Up to 1024 groups of resident rows (512 workgroups run at once, and the longest sweep is twice the average): the streamed rows of a
@@ -517,12 +552,12 @@ AggWs agg_ws_layout(int q_heads, int index_heads, int64_t n) {
     w.lse_off = 0;
     w.sbit_off = vs::round_up(static_cast<size_t>(q_heads) * n * 4, 256);
     w.vbit_off = w.sbit_off + static_cast<size_t>(index_heads) * w.sw * 4;
-    // (recall wanted: fp64 sums and arrival counts, cleared with the bitmaps)
+    // (recall wanted: fp64 sums and arrival counts, zeroed at the start of a call)
     w.acc_off = vs::round_up(w.vbit_off + static_cast<size_t>(index_heads) * w.vw * 4, 8);
     w.count_off = w.acc_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 8 : 0);
     w.sums_off = vs::round_up(w.count_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 4 : 0), 256);
     const int parts = sweep_parts(q_heads, n);
-    // shared-out sweeps: fp64 sums of a_v and a_s (cleared as well), the row sweep's partial results
+    // shared-out sweeps: fp64 sums of a_v and a_s (zeroed as well), the row sweep's partial results
     w.clear_end = w.sums_off + (parts > 1 ? vs::round_up(2 * static_cast<size_t>(q_heads) * n * sizeof(double), 256) : 0);
     w.row_off = w.clear_end;
     w.total = w.row_off + (parts > 1 ? vs::round_up(static_cast<size_t>(parts) * q_heads * n * sizeof(float2), 256) : 0);
@@ -580,27 +615,45 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
     p.index_per_q = (want_recall && index_heads == q_heads && q_heads != kv_heads) ? 1 : 0;
 
     const size_t out_count = static_cast<size_t>(out_heads) * n;
-    uint32_t* sbit = reinterpret_cast<uint32_t*>(base + w.sbit_off);
-    uint32_t* vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);
     const int parts = sweep_parts(q_heads, n);
-    const size_t sums_end = w.sums_off + (parts > 1 ? 2 * out_count * sizeof(double) : 0);
-    const size_t words = want_recall || parts > 1 ? (sums_end - w.sbit_off) / 4 : 0;
-    const size_t most = words > out_count ? words : out_count;   // (at least one output per head: recall rides along)
-    hipLaunchKernelGGL(clear_kernel, dim3(static_cast<unsigned>((most + 255) / 256)), dim3(256), 0, st, a_v, a_s, parts > 1 ? 0 : out_count,
-                       recall, out_heads, sbit, words);
-    VS_LAUNCH_CHECK();
+    SetupParams sp{};
+    sp.n = p.n;
     if (want_recall) {
-        hipLaunchKernelGGL(set_bits_kernel, dim3((cap_s + 255) / 256, index_heads), dim3(256), 0, st, idx_s, cnt_s, cap_s,
-                           static_cast<int>(n), sbit, w.sw, 64);
-        VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(set_bits_kernel, dim3((cap_v + 255) / 256, index_heads), dim3(256), 0, st, idx_v, cnt_v, cap_v,
-                           static_cast<int>(n), vbit, w.vw, 0);
-        VS_LAUNCH_CHECK();
-        p.sbit = sbit;
-        p.vbit = vbit;
-        p.sw = w.sw;
-        p.vw = w.vw;
+        sp.index_heads = index_heads;
+        sp.idx[0] = idx_s;
+        sp.idx[1] = idx_v;
+        sp.cnt[0] = cnt_s;
+        sp.cnt[1] = cnt_v;
+        sp.cap[0] = cap_s;
+        sp.cap[1] = cap_v;
+        sp.words[0] = p.sw = w.sw;
+        sp.words[1] = p.vw = w.vw;
+        sp.shift[0] = 64;
+        sp.bits[0] = reinterpret_cast<uint32_t*>(base + w.sbit_off);
+        sp.bits[1] = reinterpret_cast<uint32_t*>(base + w.vbit_off);
+        p.sbit = sp.bits[0];
+        p.vbit = sp.bits[1];
     }
+    sp.a_v = a_v;
+    sp.a_s = a_s;
+    sp.count = parts > 1 ? 0 : out_count;
+    sp.recall = recall;
+    sp.heads = out_heads;
+    sp.sums = reinterpret_cast<uint32_t*>(base + w.acc_off);
+    sp.sum_words = (w.sums_off + (parts > 1 ? 2 * out_count * sizeof(double) : 0) - w.acc_off) / 4;
+    size_t most = sp.count > sp.sum_words ? sp.count : sp.sum_words;
+    if (most < static_cast<size_t>(out_heads)) most = out_heads;
+    const size_t setup_lds = want_recall ? static_cast<size_t>(w.sw > w.vw ? w.sw : w.vw) * 4 : 0;
+    const size_t setup_blocks = 2 * static_cast<size_t>(index_heads) + (most + kSetupThreads - 1) / kSetupThreads;
+    if (setup_lds > 160 * 1024 || setup_blocks > 0x7fffffff) return VS_ERR_UNSUPPORTED;
+    static vs::PerDeviceOnce once;
+    const int rc = once.run(nullptr, [](int) -> int {
+        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&setup_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        return VS_OK;
+    });
+    if (rc != VS_OK) return rc;
+    hipLaunchKernelGGL(setup_kernel, dim3(static_cast<unsigned>(setup_blocks)), dim3(kSetupThreads), setup_lds, st, sp);
+    VS_LAUNCH_CHECK();
     const int64_t blocks = static_cast<int64_t>(q_heads) * ((n + kGroupRows - 1) / kGroupRows);
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
     p.lse = lse ? lse : p.lse2;

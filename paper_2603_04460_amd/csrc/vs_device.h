@@ -1,4 +1,4 @@
-// Device-side helpers shared by the attention and aggregation kernels: bitmaps built from index lists.
+// Device-side helper of the attention kernels: bitmaps of index lists.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -12,20 +12,6 @@ __device__ __forceinline__ uint64_t window64(const uint32_t* __restrict__ bm, in
     uint64_t r = ((static_cast<uint64_t>(b) << 32) | a) >> sh;
     if (sh) r |= static_cast<uint64_t>(c) << (64 - sh);
     return r;
-}
-
-// ---- index lists -> bitmaps ----
-
-// bit (e + bit_shift) of head ih's bitmap is set for every valid list entry e in [0, n)
-__global__ void set_bits_kernel(const int32_t* idx, const int32_t* cnt, int cap, int n, uint32_t* bits, int words_per_head,
-                                int bit_shift) {
-    const int ih = blockIdx.y;
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= min(cnt[ih], cap)) return;
-    const int e = idx[static_cast<size_t>(ih) * cap + t];
-    if (e < 0 || e >= n) return;
-    const int bit = e + bit_shift;
-    atomicOr(bits + static_cast<size_t>(ih) * words_per_head + (bit >> 5), 1u << (bit & 31));
 }
 
 }  // namespace
