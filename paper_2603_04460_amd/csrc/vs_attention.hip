@@ -881,24 +881,27 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     // Few row blocks: the kernels that split the keys of a row block over wavefronts (vs_short.hip; up to 256 row blocks in workgroups of
     // their own, vs::short_lone).  heads x positions, columns + offsets, us here and there.
     // One query head per workgroup (units of 128 rows).  At 128 units: 64 x 200, 25 + 25 49 and 23, 32 x 500, 62 + 62 40 and 24, 16 x 1000,
-    // 125 + 125 40 and 22, 8 x 2048, 256 + 256 50 and 25, 4 x 4096, 512 + 512 62 and 30, 1 x 16384, 1024 + 2048 335 and 134.  Up to 256 units, at
+    // 125 + 125 40 and 22, 8 x 2048, 256 + 256 50 and 25, 4 x 4096, 512 + 512 62 and 30, 1 x 16384, 1024 + 2048 335 and 134.  Up to 320 units, at
     // least 1000 rows: 32 x 1024, 64 + 128 47 and 31, 20 x 1300 43 and 29, 8 x 4096, 64 + 128 44 and 34, 512 + 512 64 and 43, 1 x 32768, 64 + 128 47 and
-    // 38, 1024 + 1024 90 and 64; beyond: 320 units 8 x 5000 48 and 48, 67 and 58, 376 2 x 24000 38 and 44, 86 and 80, 392 1 x 50000 48 and 65.
+    // 38, 1024 + 1024 90 and 64; beyond 256 units four row blocks share a workgroup: 320 units 8 x 5000 48 and 43, 67 and 52, 1 x 40000 47 and 39,
+    // 89 and 72 (376: 2 x 24000 38 and 39, 85 and 76; 392: 1 x 50000 48 and 52, 102 and 105).
     // Several query heads per workgroup (units of 32 or 64 rows).  Up to 512 row blocks and at least 1000 rows or 4096 keys: 8 / 2 x 1000,
     // 64 + 128 22 and 21, 1300 24 and 19, 2048 29 and 21, 256 + 256 35 and 24, 32 / 8 heads, 300 rows of 8192, 64 + 128 29 and 20, 500 rows of 50000,
-    // 1024 + 1024 70 and 43, 8 / 2, 1500 rows of 50000 67 and 42; beyond: 32 / 8, 700 rows of 8192 (704) 30 and 36, of 50000 72 and 76, 32 / 8 x 1000
-    // (1024) 24 and 28, 8 / 2, 2500 rows of 50000 (632) 70 and 75 (but 8 / 2 x 3000 (752) 27 and 25, 38 and 30); 32 / 8 x 500 21 and 23.
+    // 1024 + 1024 70 and 43, 8 / 2, 1500 rows of 50000 67 and 42 (32 / 8 x 500 21 and 23); up to 1024 with four row blocks in a workgroup: 8 / 2 x 3000
+    // 27 and 25, 38 and 33, 4096 28 and 25, 44 and 38, 32 / 8 x 1000 24 and 21, 700 rows of 50000 72 and 61, 1000 73 and 65; beyond: 32 / 8 x 1300 28 and 32,
+    // 1500 rows of 50000 97 and 116.
     // Smaller ones only as short chunks of longer sequences, and the longer the lists the more units: 32 / 8 heads, 8192 keys, capacities
     // of 100 / 260 / 388 / 580 / 2116 in all, 96 rows 21 / 27 / 32 / 34 / 66 us here, 18 / 18 / 17 / 18 / 25 there, 256 rows (64 units) 20 / 27 / 33 / 34 / 65 and
     // 17 / 17 / 17 / 18 / 27.  (The condition on the capacities is from the time when two row blocks shared a workgroup there; it is on the safe side.)
     const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((nq * p.hc + 127) / 128);
     const int64_t row_blocks = static_cast<int64_t>(q_heads) * ((nq + 31) / 32);
     const int64_t capacity = static_cast<int64_t>(cap_v) + cap_s;
-    const bool few_rows = p.hc == 1 ? units <= kShortUnits || (units <= 2 * kShortUnits && nq >= 1000)
-                                    : (row_blocks <= 4 * kShortUnits && (nq >= 1000 || n >= 4096)) ||
+    const bool few_rows = p.hc == 1 ? units <= kShortUnits || (units <= 5 * kShortUnits / 2 && nq >= 1000)
+                                    : (row_blocks <= 8 * kShortUnits && (nq >= 1000 || n >= 4096)) ||
                                           (units <= kShortUnits / 2 && n >= 4 * nq && n >= 2048 && capacity >= 10 * (units - (p.hc == 4 ? 28 : 44)));
-    const bool lone = few_rows && vs::short_lone(q_heads, nq);
-    if (few_rows) p.hc = lone ? 1 : vs::short_heads(p.hc);
+    // row blocks per workgroup
+    const int rows = !few_rows ? kWaves : vs::short_lone(q_heads, nq) ? 1 : (p.hc == 1 ? units <= 2 * kShortUnits : row_blocks <= 4 * kShortUnits) ? 2 : 4;
+    if (few_rows) p.hc = vs::short_heads(p.hc, rows);
     p.gran = slash_granularity;
     p.n = static_cast<int>(n);
     p.nq = static_cast<int>(nq);
@@ -934,7 +937,7 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     pp.cnt_s = cnt_s;
     pp.cap_s = cap_s;
     pp.n = p.n;
-    pp.nsub = lone ? 1 : (few_rows ? vs::short_subblocks(p.hc) : kWaves / p.hc);
+    pp.nsub = rows / p.hc;
     pp.nblk = w.nq32;
     pp.shift = static_cast<int>(pos0 % 32);
     pp.vbit = reinterpret_cast<uint32_t*>(base + w.vbit_off);
@@ -959,7 +962,7 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     if (prep_lds > 160 * 1024) return VS_ERR_UNSUPPORTED;
     hipLaunchKernelGGL(vs_prepare_kernel, dim3(index_heads, 2), dim3(kPrepThreads), prep_lds, st, pp);
     VS_LAUNCH_CHECK();
-    return few_rows ? vs::launch_short_sparse(p, st) : launch_attention(p, st);
+    return few_rows ? vs::launch_short_sparse(p, rows, st) : launch_attention(p, st);
 }
 
 }  // namespace

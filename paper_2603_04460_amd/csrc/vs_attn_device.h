@@ -51,12 +51,11 @@ struct AttnParams {
 constexpr int kStatStride = 16;                 // 128 bytes
 constexpr int kMaxStatSlots = 64;               // 8 workgroups per slot of a full launch
 
-// Attention for launches with few row blocks (vs_short.hip); p.hc, the query heads of a workgroup, is short_heads() or, in the form
-// with one row block per workgroup (short_lone), 1, and the lists of a sparse call are prepared for short_subblocks() or 1.
-int launch_short_dense(AttnParams& p, hipStream_t stream);
-int launch_short_sparse(AttnParams& p, hipStream_t stream);
-inline int short_heads(int hc) { return hc >= 2 ? 2 : 1; }      // two row blocks: two heads, or 64 rows of one
-inline int short_subblocks(int hc) { return 2 / hc; }
+// Attention for launches with few row blocks (vs_short.hip): `rows` row blocks per workgroup, 1, 2 or (sparse) 4, of p.hc =
+// short_heads() query heads; the lists of a sparse call are prepared for rows / p.hc sub-blocks.
+int launch_short_dense(AttnParams& p, int rows, hipStream_t stream);
+int launch_short_sparse(AttnParams& p, int rows, hipStream_t stream);
+inline int short_heads(int hc, int rows) { return hc < rows ? hc : rows; }
 // Up to 256 row blocks, one for every compute unit, a workgroup has one row block and its eight wavefronts split the keys; beyond,
 // two row blocks and four wavefronts each.  Two row blocks / one, us: dense, 1 x 8192 (256 row blocks) 74 / 45, 8 / 2 x 1024 (256)
 // 15.4 / 11.6, 8 / 2 heads, 1000 rows of 65536 keys (256) 559 / 360, 64 rows, 32 / 8 heads, of 32768 (64) 280 / 151; sparse, 1 x 8192,

@@ -525,16 +525,17 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
     const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((n_q * p.hc + 255) / 256);
     const bool few_tiles = p.hc <= 2 && n_kv * p.hc <= 64;
     if (units <= kShortUnits && !few_tiles) {
-        p.hc = vs::short_heads(p.hc);
+        const int rows = vs::short_lone(p.q_heads, p.nq) ? 1 : 2;
+        p.hc = vs::short_heads(p.hc, rows);
         // Of these, more than 256 row blocks against at least 2048 keys: two row blocks per wavefront (DUO).  There / vs_short_kernel, us:
         // 8 x 2048 22 / 25, 16 / 4 x 2048 33 / 33, 12 x 2600 79 / 80, 32 / 8, 500 rows of 2048 24 / 26, 1024 of 4096 73 / 80, of 32768 567 / 648;
         // with fewer keys the fill and the larger stages cost as much: 16 / 4 x 1700 27 / 26, 24 x 1280 25 / 24, 32 / 8 x 1024 24 / 22,
         // 128 x 200 18 / 15 (but 8 / 2 x 1500 17 / 19).
-        if (!vs::short_lone(p.q_heads, p.nq) && n_kv >= kDuoKeys) return launch_dense<true>(p, static_cast<hipStream_t>(stream));
-        return vs::launch_short_dense(p, static_cast<hipStream_t>(stream));
+        if (rows == 2 && n_kv >= kDuoKeys) return launch_dense<true>(p, static_cast<hipStream_t>(stream));
+        return vs::launch_short_dense(p, rows, static_cast<hipStream_t>(stream));
     }
     if (n_kv >= kDuoKeys && duo_is_faster(q_heads, n_q, pos0)) {
-        p.hc = vs::short_heads(p.hc);
+        p.hc = vs::short_heads(p.hc, 2);
         return launch_dense<true>(p, static_cast<hipStream_t>(stream));
     }
     return launch_dense<false>(p, static_cast<hipStream_t>(stream));

@@ -5,8 +5,9 @@
 // tiles are dealt to several wavefronts; at the end their partial results (maximum, sum, O) meet in LDS and every wavefront
 // finishes its share of the 128 channels.  A workgroup has 8 wavefronts, two per SIMD, one workgroup per compute unit.
 // Arithmetic, tile layout, records and gather lists are those of vs_attention.hip.
-//   vs_short_kernel  two row blocks (two query heads of the KV group, or 64 consecutive rows of one head) of four wavefronts.  A
-//                    stage is four 32-key tiles, wavefront (s, rb) takes tile s of the stage for row block rb; two stages live in LDS.
+//   vs_short_kernel  two row blocks (two query heads of the KV group, or 64 consecutive rows of one head) of four wavefronts, or four
+//                    of two.  A stage is four 32-key tiles, wavefront (s, rb) takes tile s (and s + 2) of the stage for row block
+//                    rb; two stages live in LDS.
 //   vs_lone_kernel   one row block of eight wavefronts, each with LDS buffers of its own (vs::short_lone, at most 256 row blocks).
 //
 // Long dense calls with more row blocks than that go to the two-row-block form of vs_dense.hip.
@@ -28,18 +29,17 @@
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int kRowBlocks = 2;
-constexpr int kSplits = 4;                     // wavefronts per row block = tiles per stage
+constexpr int kStage = 4;                      // tiles per stage
 constexpr int kListCap = 256;                  // block list: kListCap / nsub entries per pass
 constexpr int kGatherCap = 2432;               // gather list entries per pass
-constexpr int kRecPad = 2 * kSplits;           // dead records after the last listed block (a step looks one stage ahead)
-constexpr size_t kRingBytes = 2 * kSplits * kSlotBytes;
+constexpr int kRecPad = 2 * kStage;            // dead records after the last listed block (a step looks one stage ahead)
+constexpr size_t kRingBytes = 2 * kStage * kSlotBytes;
 constexpr size_t kRecOff = kRingBytes;
-constexpr size_t kGatherOff = kRecOff + (kListCap + 2 * kRecPad) * 16;
+constexpr size_t kGatherOff = kRecOff + (kListCap + 4 * kRecPad) * 16;
 constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4;
 static_assert(kPartialBytes + 8 * 4 <= kRingBytes, "partial results in the idle ring");
 static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
-static_assert(kGatherCap % (32 * kSplits) == 0, "whole stages");
+static_assert(kGatherCap % (32 * kStage) == 0, "whole stages");
 
 // Fragment addresses of a lane in an LDS slot, as in vs_attention.hip.
 struct Fragments {
@@ -172,8 +172,10 @@ __device__ __forceinline__ uint32_t causal_columns(const int* cols, int row) {
     return keep;
 }
 
-template <bool DENSE>
+template <bool DENSE, int kRowBlocks>
 __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) {
+    constexpr int kSplits = kThreads / 64 / kRowBlocks;      // wavefronts per row block
+    static_assert(kStage % kSplits == 0, "whole steps");
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* const kvbuf = smem;
     uint4* const list_rec = reinterpret_cast<uint4*>(smem + kRecOff);
@@ -229,16 +231,17 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
         row_block.softmax(p, sc.a, pb);
         row_block.accumulate(vf, pb);
     };
-    // Pipeline over the stages of one phase: load(st, buf) requests the four tiles of stage st; step(st, slot) computes this
-    // wavefront's tile of stage st.  One barrier per step publishes stage st and frees the buffer of stage st - 1.
+    // Pipeline over the stages of one phase: load(st, buf) requests the four tiles of stage st; step(t, slot) computes tile t, one of
+    // this wavefront's.  One barrier per stage publishes stage st and frees the buffer of stage st - 1.
     auto run_phase = [&](int ntiles, auto load, auto step) __attribute__((always_inline)) {
-        const int nst = (ntiles + kSplits - 1) / kSplits;
+        const int nst = (ntiles + kStage - 1) / kStage;
         load(0, 0);
         for (int st = 0; st < nst; ++st) {
             __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's part of stage st has arrived
             __syncthreads();
             if (st + 1 < nst) load(st + 1, (st + 1) & 1);
-            step(st, kSplits * (st & 1) + split);
+#pragma unroll
+            for (int u = split; u < kStage; u += kSplits) step(kStage * st + u, kStage * (st & 1) + u);
         }
         __syncthreads();                                     // the ring and the lists are reused
     };
@@ -250,10 +253,10 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
             nblk,
             [&](int st, int buf) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < kSplits; ++u) load_tile(32 * (kSplits * st + u) + st_row, kSplits * buf + u);
+                for (int u = 0; u < kStage; ++u) load_tile(32 * (kStage * st + u) + st_row, kStage * buf + u);
             },
-            [&](int st, int slot) __attribute__((always_inline)) {
-                const int dlt = my_i0 - 32 * (kSplits * st + split);          // offset of (row 0, key 0)
+            [&](int t, int slot) __attribute__((always_inline)) {
+                const int dlt = my_i0 - 32 * t;                               // offset of (row 0, key 0)
                 if (dlt < -31 || !my_rows) return;
                 compute(slot, dlt < 31, [&]() __attribute__((always_inline)) {
                     const uint64_t w = (kAll63 << (31 - dlt)) & kAll63;       // offsets >= 0
@@ -290,11 +293,11 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
                 count,
                 [&](int st, int buf) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int u = 0; u < kSplits; ++u)
-                        load_tile(32 * static_cast<int>(list_rec[kSplits * st + u].w >> 2) + st_row, kSplits * buf + u);
+                    for (int u = 0; u < kStage; ++u)
+                        load_tile(32 * static_cast<int>(list_rec[kStage * st + u].w >> 2) + st_row, kStage * buf + u);
                 },
-                [&](int st, int slot) __attribute__((always_inline)) {
-                    const uint4* const rec = my_rec + kSplits * st + split;
+                [&](int t, int slot) __attribute__((always_inline)) {
+                    const uint4* const rec = my_rec + t;
                     const uint32_t fl = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(rec->w));
                     if (!(fl & 1u)) return;
                     ++tiles_done;
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
         // 2. vertical part: the causal columns, gathered row by row, in rounds of kGatherCap
         while (cursor < ncand) {
             const int count = min(ncand - cursor, kGatherCap);
-            const int padded = (count + 32 * kSplits - 1) / (32 * kSplits) * (32 * kSplits);
+            const int padded = (count + 32 * kStage - 1) / (32 * kStage) * (32 * kStage);
             for (int t = tid; t < padded; t += kThreads) glist[t] = t < count ? iv[cursor + t] : INT_MAX;
             cursor += count;
             __syncthreads();
@@ -318,10 +321,10 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
                 ntiles,
                 [&](int st, int buf) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int u = 0; u < kSplits; ++u) load_tile(glist[32 * (kSplits * st + u) + st_row], kSplits * buf + u);
+                    for (int u = 0; u < kStage; ++u) load_tile(glist[32 * (kStage * st + u) + st_row], kStage * buf + u);
                 },
-                [&](int st, int slot) __attribute__((always_inline)) {
-                    const int* const cols = glist + 32 * (kSplits * st + split);
+                [&](int t, int slot) __attribute__((always_inline)) {
+                    const int* const cols = glist + 32 * t;
                     const int cmin = __builtin_amdgcn_readfirstlane(cols[0]), cmax = __builtin_amdgcn_readfirstlane(cols[31]);
                     if (!my_rows || cmin > my_i0 + 31) return;               // ascending, INT_MAX padding
                     ++tiles_done;
@@ -488,28 +491,24 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
     if (!DENSE && tid == 0) add_statistics(p, tiles_done, staged_gather, staged_block);
 }
 
-template <bool DENSE>
+template <bool DENSE, int ROWS>
 int launch_short(AttnParams& p, hipStream_t stream) {
+    constexpr size_t lds = ROWS == 1 ? (DENSE ? kLoneRing : kLoneLds) : (DENSE ? kRingBytes : kSparseLds);
+    void (*kernel)(AttnParams);
+    if constexpr (ROWS == 1) kernel = &vs_lone_kernel<DENSE>;
+    else kernel = &vs_short_kernel<DENSE, ROWS>;
     static vs::PerDeviceOnce once;
-    const size_t lds = DENSE ? kRingBytes : kSparseLds, lone_lds = DENSE ? kLoneRing : kLoneLds;
-    const int rc = once.run(nullptr, [lds, lone_lds](int) -> int {
-        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vs_short_kernel<DENSE>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   static_cast<int>(lds)));
-        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&vs_lone_kernel<DENSE>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   static_cast<int>(lone_lds)));
+    const int rc = once.run(nullptr, [kernel](int) -> int {
+        VS_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
         return VS_OK;
     });
     if (rc != VS_OK) return rc;
-    const bool lone = vs::short_lone(p.q_heads, p.nq);
-    if (lone) p.hc = 1;
-    const int BQ = lone ? 32 : 32 * (kRowBlocks / p.hc);
+    const int BQ = 32 * (ROWS / p.hc);
     p.tiles = (p.nq + BQ - 1) / BQ;
     // KV head = block % kv_heads: workgroups are dealt to the 8 XCDs round-robin, so a head's K / V stay in one XCD's L2
     const long long blocks = static_cast<long long>(p.kv_heads) * (p.group / p.hc) * p.tiles;
     if (blocks > 0x7fffffffLL) return VS_ERR_UNSUPPORTED;
-    const dim3 grid(static_cast<unsigned>(blocks)), threads(kThreads);
-    if (lone) hipLaunchKernelGGL(vs_lone_kernel<DENSE>, grid, threads, lone_lds, stream, p);
-    else hipLaunchKernelGGL(vs_short_kernel<DENSE>, grid, threads, lds, stream, p);
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, stream, p);
     VS_LAUNCH_CHECK();
     return VS_OK;
 }
@@ -517,6 +516,10 @@ int launch_short(AttnParams& p, hipStream_t stream) {
 }  // namespace
 
 namespace vs {
-int launch_short_dense(AttnParams& p, hipStream_t stream) { return launch_short<true>(p, stream); }
-int launch_short_sparse(AttnParams& p, hipStream_t stream) { return launch_short<false>(p, stream); }
+int launch_short_dense(AttnParams& p, int rows, hipStream_t stream) {
+    return rows == 1 ? launch_short<true, 1>(p, stream) : launch_short<true, 2>(p, stream);
+}
+int launch_short_sparse(AttnParams& p, int rows, hipStream_t stream) {
+    return rows == 1 ? launch_short<false, 1>(p, stream) : rows == 2 ? launch_short<false, 2>(p, stream) : launch_short<false, 4>(p, stream);
+}
 }  // namespace vs

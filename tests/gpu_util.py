@@ -56,8 +56,8 @@ def sparse_is_short(hq, hk, n_q, n, capacity, per_q=False):
     hc = _heads_per_workgroup(hq, hk, per_q)
     units, line = hk * (hq // hk // hc) * -(-n_q * hc // 128), _short_units("vs_attention.hip")
     if hc == 1:
-        return units <= line or (units <= 2 * line and n_q >= 1000)
-    if hq * -(-n_q // 32) <= 4 * line and (n_q >= 1000 or n >= 4096):
+        return units <= line or (units <= 5 * line // 2 and n_q >= 1000)
+    if hq * -(-n_q // 32) <= 8 * line and (n_q >= 1000 or n >= 4096):
         return True
     return units <= line // 2 and n >= 4 * n_q and n >= 2048 and capacity >= 10 * (units - (28 if hc == 4 else 44))
 

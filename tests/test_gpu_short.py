@@ -309,16 +309,20 @@ def test_dense_about_one_round_of_workgroups(hq, hk, n, pos0, n_q):
     (32, 8, 4101, 300, False, None),
     (6, 3, 2431, 2431, False, None),                                     # a group of two, 456 row blocks
     (20, 20, 1290, 1290, False, None), (8, 2, 4096, 4096, True, 32),     # one head a workgroup, 220 and 256 units
-    (8, 2, 2080, 2080, False, None), (33, 33, 1025, 1025, False, None),  # just beyond: vs_attention.hip
+    (8, 2, 2080, 2080, False, 32), (8, 2, 3999, 3999, False, None),      # four heads of a group, 520 and 1000 row blocks
+    (32, 8, 4101, 600, False, None), (12, 6, 1999, 1999, False, None),   # two heads of a group and 64 rows
+    (33, 33, 1025, 1025, False, None), (10, 10, 4096, 4096, False, 32),  # 128 rows of one head: 297 and 320 units
+    (8, 2, 4128, 4128, False, None), (33, 33, 1190, 1190, False, None),  # just beyond: vs_attention.hip
 ])
 def test_sparse_few_row_blocks(hq, hk, n, n_q, per_q, gran):
-    """Up to 512 row blocks of grouped heads, up to 256 units of one head, at least 1000 rows or 4096 keys."""
+    """Up to 1024 row blocks of grouped heads, up to 320 units of one head, at least 1000 rows or 4096 keys: two and four row blocks in
+    a workgroup."""
     rng = np.random.default_rng(n + hq)
     (q, k, v), (qb, kb, vb) = make_qkv(2000 + n, hq, hk, n)
     heads, pos0 = hq if per_q else hk, n - n_q
     iv, cv = lists([rng.choice(n, size=5 + 60 * (h % 3), replace=False) for h in range(heads)], cap=130)
     is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=3 + 40 * (h % 2), replace=False)])) for h in range(heads)], cap=70)
-    assert sparse_is_short(hq, hk, n_q, n, 200, per_q) == ((hq, n) not in ((8, 2080), (33, 1025)))
+    assert sparse_is_short(hq, hk, n_q, n, 200, per_q) == ((hq, n) not in ((8, 4128), (33, 1190)))
     f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
     qc = q[:, pos0:].contiguous()
     o = torch.full_like(qc, float("nan"))
