@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void combine_rows_kernel(const float2* __
     float l = 0.f;
     for (int i = 0; i < parts; ++i) {
         const float2 x = part[static_cast<size_t>(i) * rows + row];
-        if (x.x > -INFINITY) l += x.y * __builtin_amdgcn_exp2f(x.x - m);
+        l += x.y * (x.x > -INFINITY ? __builtin_amdgcn_exp2f(x.x - m) : 0.f);   // the sum of a part with nothing but NaN is NaN
     }
     lse2[row] = normaliser(m, l);
 }
@@ -425,8 +425,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             const float l_a = __uint_as_float(lo[0]), l_b = __uint_as_float(lo[1]);
             const float m2 = fmaxf(m_a, m_b);
             float l2 = 0.f;
-            if (m_a > NEG_INF) l2 += l_a * __builtin_amdgcn_exp2f(m_a - m2);
-            if (m_b > NEG_INF) l2 += l_b * __builtin_amdgcn_exp2f(m_b - m2);
+            l2 += l_a * (m_a > NEG_INF ? __builtin_amdgcn_exp2f(m_a - m2) : 0.f);   // (a NaN sum stays NaN)
+            l2 += l_b * (m_b > NEG_INF ? __builtin_amdgcn_exp2f(m_b - m2) : 0.f);
             const int row = my_r0 + 32 * b + qi;
             if constexpr (PARTS) {
                 if (row < n && hh == 0)

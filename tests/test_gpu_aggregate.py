@@ -125,6 +125,17 @@ def test_aggregate_group_sharing(pairs, n):
     _close(a_s, np.repeat(ref_s.mean(0, keepdims=True), pairs, 0))
 
 
+@pytest.mark.parametrize("n", [65, 257, 1025, 1100])
+def test_aggregate_last_key_nan(n):
+    """The last row sees one NaN key, at n = 65, 257 and 1025 the only key of its workgroup's share: its sum, and with it its entry in
+    every column and on every diagonal, is NaN whoever adds it up."""
+    (q, k, v), _ = make_qkv(570 + n, 1, 1, n, local=True)
+    k[:, -1] = float("nan")
+    a_v, a_s = torch.zeros(1, n, device="cuda"), torch.zeros(1, n, device="cuda")
+    vs.aggregate(q, k, a_v, a_s, torch.empty(vs.aggregate_workspace(1, 1, 0, n), dtype=torch.uint8, device="cuda"))
+    assert bool(a_v.isnan().all()) and bool(a_s.isnan().all())
+
+
 def test_aggregate_8192_one_head_elementwise():
     """n = 8192, one head: 32 groups of resident keys, the streamed rows of each shared out over 16 workgroups (up to 8 stages
     each); every element is compared, together with the recall of a mask."""
