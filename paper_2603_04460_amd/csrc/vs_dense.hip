@@ -149,15 +149,19 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
                 lds_load16(vbase + off + st_cv * 8, dst + kTileBytes);
             }
     };
-    // DUO: one group of four rows of the wavefront's own tiles, row (lane / 16) of it (rows past the end read the last one, masked);
-    // piece: 0 .. 15 of K, then of V
+    // DUO: one group of four rows of the wavefront's own tiles, row (lane / 16) of it; row0: first rows of the tiles; piece: 0 .. 15 of
+    // K, then of V.  Rows behind the workgroup's last are masked and read that one.
     unsigned char* const own = kvbuf + wave * 2 * kSlotBytes;
-    auto load_own = [&](int st, int piece) __attribute__((always_inline)) {
+    auto load_own = [&](int row0_0, int row0_1, int piece) __attribute__((always_inline)) {
         const int v = piece >> 4, u = (piece >> 3) & 1, grp = piece & 7;
         const uint32_t chunk = static_cast<uint32_t>(v ? st_cv : st_ck) * 16u;
-        const uint32_t at = static_cast<uint32_t>(64 * pair_of(st) + 32 * u + 4 * grp + st_rho) * 256u;
-        lds_load16s(min(at, static_cast<uint32_t>(n - 1) << 8) + chunk, v ? vbase : kbase, own + u * kSlotBytes + v * kTileBytes + grp * kGroupBytes);
+        const uint32_t at = static_cast<uint32_t>((u ? row0_1 : row0_0) + 4 * grp + st_rho) * 256u;
+        lds_load16s(min(at, static_cast<uint32_t>(i_last) << 8) + chunk, v ? vbase : kbase, own + u * kSlotBytes + v * kTileBytes + grp * kGroupBytes);
     };
+    // V of a key that is masked for every row must not be multiplied: its weight is zero, but zero times a V that is not finite is NaN.
+    // DUO: tiles behind the workgroup's last read V of the first tile instead (every row has it), and row block 0 leaves out the one
+    // tile that only row block 1 has (64 rows of one head).
+    const int second_only = DUO && p.hc == 1 ? (my_i0[0] + 31) / 32 + 1 : -1;
     const int li = lane & 15, dsel = (lane >> 4) & 1;
     const int k_row = (qi >> 2) * kGroupBytes + (qi & 3) * 256;
     const int k_off0 = k_row + 16 * ((hh + qi) & 3), k_off2 = k_row + 16 * ((hh + qi + 2) & 3);
@@ -204,8 +208,10 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
                 sc[MR][u] = mfma32(kf[u][kk], qf[MR][kk], sc[MR][u]);
             }
         };
+        const int left_out = second_only - 2 * pair_of(sq - 1);
         auto pmfma = [&](int idx) __attribute__((always_inline)) {
             const int u = idx >> 3, t = (idx >> 2) & 1, db = idx & 3;
+            if (DUO && MASKED && MR == 0 && left_out == u) return;
             oacc[MR][db] = mfma32(vf[u][2 * db + t], pb[MR][u][t], oacc[MR][db]);
         };
         // vbase[sgr] / kbase_[par]: per-lane LDS addresses of the stage, everything else is an immediate offset
@@ -346,10 +352,16 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         constexpr bool LOADS = DUO && HAS_Q;
         const bool next = sq + 1 < nst;
         if constexpr (LOADS && MR == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        const int load_pair = pair_of(MR == 0 ? sq + 1 : sq);
+        int row0[2] = {64 * load_pair, 64 * load_pair + 32};
+        if constexpr (MASKED && MR == 1) {                   // (without a mask every tile is the workgroup's)
+            row0[0] = 2 * load_pair < nblk ? row0[0] : 0;
+            row0[1] = 2 * load_pair + 1 < nblk ? row0[1] : 0;
+        }
         auto loads_upto = [&](int from, int to) __attribute__((always_inline)) {
 #pragma unroll
             for (int piece = 0; piece < 32; ++piece)
-                if (piece >= from && piece < to && (piece >= 16 || next)) load_own(piece >= 16 ? sq : sq + 1, piece);
+                if (piece >= from && piece < to && (piece >= 16 || next)) load_own(row0[0], row0[1], piece);
         };
 #pragma unroll
         for (int j = 6; j < 16; ++j) {                       // 10 more score products
@@ -385,7 +397,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     __builtin_amdgcn_s_waitcnt(0x0F70);
     if constexpr (DUO) {
 #pragma unroll
-        for (int piece = 0; piece < 16; ++piece) load_own(0, piece);
+        for (int piece = 0; piece < 16; ++piece) load_own(64 * wave, 64 * wave + 32, piece);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     } else {
         load_stage(0);

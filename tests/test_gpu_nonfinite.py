@@ -1,0 +1,56 @@
+"""Keys outside the tiles of a row block stay out of its outputs, also where their K and V are not finite (later positions of a
+sequence that went wrong there, the unfilled end of a cache): a weight of zero would turn them into NaN in a matrix product."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_04460_amd as vs
+import synth
+from gpu_util import make_qkv, check_attention, dense_is_short
+
+pytestmark = pytest.mark.gpu
+
+
+def _spoilt(k, v, bad):
+    k, v = k.clone(), v.clone()
+    k[:, bad:] = float("nan")
+    v[:, bad:] = float("nan")
+    return k, v
+
+
+def _clean_rows(pos0, n_q, bad, block):
+    """Rows of the chunk whose block of `block` rows has no key >= bad in its tiles of 32 keys."""
+    r = np.arange(n_q)
+    last = np.minimum(pos0 + (r // block + 1) * block, pos0 + n_q) - 1
+    return r[last // 32 * 32 + 31 < bad]
+
+
+def _sample(rows, count=120):
+    return rows if len(rows) <= count else np.unique(np.concatenate([rows[:8], rows[-72:], rows[::len(rows) // 40]]))
+
+
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q,bad,short", [
+    (8, 8, 2048, 0, 2048, 740, True),                        # 64 rows of a head in a workgroup: behind the workgroup's last tile
+    (8, 8, 2048, 0, 2048, 672, True),                        # the second row block's own tile
+    (32, 8, 4096, 2048, 480, 2528, True),                    # two heads of a group; a chunk with keys behind it
+    (18, 9, 2304, 1561, 455, 2016, True),
+    (24, 24, 2048, 0, 2048, 1111, False),                    # about one round of workgroups
+    (8, 2, 6001, 0, 6001, 3456, False),
+    (32, 8, 5000, 3700, 1290, 4992, False),
+])
+def test_dense_two_row_blocks_later_keys(hq, hk, n, pos0, n_q, bad, short):
+    """The dense form whose wavefronts own two row blocks and whose stages go past the last tile of either."""
+    assert dense_is_short(hq, hk, n_q, n) == short and hq * -(-n_q // 32) > 256 and n >= 2048
+    (q, k, v), (qb, kb, vb) = make_qkv(3000 + bad, hq, hk, n)
+    kx, vx = _spoilt(k, v, bad)
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o, lse = torch.empty_like(qc), torch.empty((hq, n_q), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, kx, vx, o, lse, pos0=pos0)
+    torch.cuda.synchronize()
+    clean = _clean_rows(pos0, n_q, bad, 32)
+    assert torch.isfinite(o[:, clean].float()).all() and torch.isfinite(lse[:, clean]).all()
+    assert o[:, max(bad - pos0, 0):].isnan().all()
+    rows = _sample(clean)
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
