@@ -470,7 +470,10 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
                         const uint32_t fl = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(list_rec[t].w));
                         kind = fl & 1u ? ((fl & 2u) ? 2 : 1) : 0;
                     } else {
-                        kind = __builtin_amdgcn_readfirstlane(glist[32 * (t - nb) + 31]) > my_i0 ? 2 : 1;   // ascending, INT_MAX padding
+                        // ascending, INT_MAX padding; columns behind the row block are listed where a chunk starts inside a key block
+                        const int* const cols = glist + 32 * (t - nb);
+                        const int cmin = __builtin_amdgcn_readfirstlane(cols[0]), cmax = __builtin_amdgcn_readfirstlane(cols[31]);
+                        kind = cmin > my_i0 + 31 ? 0 : cmax > my_i0 ? 2 : 1;
                     }
                     tiles_done += kind ? 1u : 0u;
                     return kind;

@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2603_04460_amd as vs
 import synth
-from gpu_util import make_qkv, check_attention, dense_is_short
+from gpu_util import make_qkv, check_attention, dense_is_short, lists
 
 pytestmark = pytest.mark.gpu
 
@@ -54,3 +54,33 @@ def test_dense_two_row_blocks_later_keys(hq, hk, n, pos0, n_q, bad, short):
     rows = _sample(clean)
     ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+def _sparse_chunk(q, k, v, iv, cv, is_, cs, pos0, n_q, gran=None):
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    hq, hk, n = q.shape[0], k.shape[0], k.shape[1]
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o, lse = torch.empty_like(qc), torch.empty((hq, n_q), dtype=torch.float32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, iv.shape[0], n), dtype=torch.uint8, device="cuda")
+    vs.sparse_prefill(qc, k, v, f(iv), f(cv), f(is_), f(cs), o, lse, ws, slash_granularity=gran, pos0=pos0)
+    torch.cuda.synchronize()
+    return o, lse, ws
+
+
+@pytest.mark.parametrize("pos0,n_q", [(1, 32), (37, 60), (31, 64)])
+def test_sparse_gathered_tile_behind_a_row_block(pos0, n_q):
+    """A chunk that starts inside a key block: the columns of that key block that lie behind the row block may fill a gathered tile of
+    their own.  It is neither multiplied nor counted."""
+    n, first = 256, pos0 + (n_q - 1) // 32 * 32
+    end = (pos0 + n_q - 1) // 32 * 32 + 31                   # last key of the key block that the last row lies in
+    cols = list(range(32)) + list(range(first + 32, end + 1))
+    (q, k, v), (qb, kb, vb) = make_qkv(3100 + pos0, 1, 1, n)
+    kx, vx = _spoilt(k, v, first + 32)
+    iv, cv = lists([cols])
+    is_, cs = lists([[n_q + 40]])                            # far offsets only: no key block reaches the spoilt keys
+    o, lse, ws = _sparse_chunk(q, kx, vx, iv, cv, is_, cs, pos0, n_q)
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:pos0 + n_q], kb, vb, iv, cv, is_, cs, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse)
+    blocks = -(-n_q // 32)
+    executed, gathered, staged = vs.sparse_prefill_counters(ws)
+    assert executed <= blocks + staged and gathered == blocks + 1
