@@ -84,3 +84,24 @@ def test_sparse_gathered_tile_behind_a_row_block(pos0, n_q):
     blocks = -(-n_q // 32)
     executed, gathered, staged = vs.sparse_prefill_counters(ws)
     assert executed <= blocks + staged and gathered == blocks + 1
+
+
+@pytest.mark.parametrize("hq,hk,n", [(1, 1, 1000), (8, 2, 1024),          # a row block to a workgroup
+                                     (8, 8, 1055), (8, 2, 3999),          # two, four
+                                     (32, 8, 1400), (64, 64, 300)])       # the kernel for many row blocks
+@pytest.mark.parametrize("cols", [1, 33, 63, 2433])
+def test_sparse_padding_of_gathered_tiles(hq, hk, n, cols):
+    """What pads the last gathered tile is not the last key of the sequence, nor any other that the row block does not have."""
+    bad = n - 40
+    cols = min(cols, bad - 3)
+    rng = np.random.default_rng(cols)
+    (q, k, v), (qb, kb, vb) = make_qkv(3200 + n, hq, hk, n)
+    kx, vx = _spoilt(k, v, bad)
+    iv, cv = lists([rng.choice(bad, cols - h % 2 if cols > 1 else cols, replace=False) for h in range(hk)])
+    is_, cs = lists([[0, 3, 200]] * hk)
+    o, lse, _ = _sparse_chunk(q, kx, vx, iv, cv, is_, cs, 0, n)
+    clean = _clean_rows(0, n, bad, 128)
+    assert torch.isfinite(o[:, clean].float()).all()
+    rows = _sample(clean)
+    ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, rows=rows)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
