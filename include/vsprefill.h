@@ -168,6 +168,7 @@ int vs_sparse_prefill_tiled(const void* q, const void* k, const void* v, int q_h
  * new query positions against all keys so far).  vs_sparse_prefill_tiled for n_q query rows that are the positions
  * pos0 .. pos0 + n_q - 1 of a sequence whose keys 0 .. n_kv - 1 are present:
  *   q, o   [q_heads, n_q, 128];  k, v  [kv_heads, n_kv, 128];  lse [q_heads, n_q];  pos0 + n_q <= n_kv
+ *   (the keys behind the chunk, pos0 + n_q .. n_kv - 1, are not read: the unfilled end of a cache may hold anything)
  * The mask speaks of absolute positions: the query at position i keeps key j iff j <= i and (j in I_v or i - j in I_s);
  * lists hold columns and offsets in [0, n_kv).  Running the chunks of a sequence one after the other gives, row for
  * row, the results of one call on the whole sequence (up to the order of summation).  pos0 may be any position for

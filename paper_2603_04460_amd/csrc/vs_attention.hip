@@ -345,16 +345,16 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                 d[1] = my_rec[2 * st + 1].w;
             }
         };
-        // rows past the sequence and tiles past the list read another row instead: their scores are masked, so the loads
-        // need no predicate
+        // rows behind the last position and tiles past the list read another row instead: their scores are masked, so the loads
+        // need no predicate (the keys behind a chunk are not read: a weight of zero times a V that is not finite is NaN)
         auto stage_rows = [&](int st, const uint32_t (&d)[2], int (&rows)[2][2]) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int r = st_row + 16 * h;
-                    if (GATHER) rows[u][h] = min(glist[32 * (2 * st + u) + r], n - 1);   // padded to a whole stage
-                    else rows[u][h] = min(static_cast<int>(d[u] >> 2) * 32 + r, n - 1);
+                    if (GATHER) rows[u][h] = min(glist[32 * (2 * st + u) + r], n_pos - 1);   // padded to a whole stage
+                    else rows[u][h] = min(static_cast<int>(d[u] >> 2) * 32 + r, n_pos - 1);
                 }
         };
         auto info = [&](int t, uint32_t d) __attribute__((always_inline)) -> TileInfo {
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) rows[u][h] = min(glist[32 * u + st_row + 16 * h], n - 1);
+                    for (int h = 0; h < 2; ++h) rows[u][h] = min(glist[32 * u + st_row + 16 * h], n_pos - 1);
                 load_stage(rows, buf1);
             }
             if constexpr (MODE != 2) {
@@ -658,7 +658,7 @@ struct PrepParams {
     const int32_t* idx_s;
     const int32_t* cnt_s;
     int cap_s;
-    int n, nsub, nblk;
+    int n, n_pos, nsub, nblk;       // n_pos: positions that exist, columns behind them are left out
     int shift;                      // pos0 % 32: row blocks start at positions 32 t + shift
     uint32_t* vbit;
     int sw, vw;                     // words of the offset bitmap (LDS only: bit (o + 64), 64-bit zero guard, zero tail), of vbit
@@ -755,13 +755,13 @@ __global__ __launch_bounds__(kPrepThreads) void vs_prepare_kernel(const PrepPara
     const int32_t* const iv = p.idx_v + static_cast<size_t>(ih) * p.cap_v;
     for (int t = tid; t < cv; t += kPrepThreads) {
         const int e = iv[t];
-        if (e >= 0 && e < p.n) atomicOr(&bm[e >> 5], 1u << (e & 31));
+        if (e >= 0 && e < p.n_pos) atomicOr(&bm[e >> 5], 1u << (e & 31));
         else if (e < 0) atomicAdd(negative, 1u);
     }
     __syncthreads();
     uint32_t* const vbit = p.vbit + static_cast<size_t>(ih) * p.vw;
     for (int w = tid; w < p.vw; w += kPrepThreads) vbit[w] = bm[w];
-    // ncol32[q] = entries of the ascending list that are <= 32 q + 31 (and < n);  vfirst = entries that are < 0
+    // ncol32[q] = entries of the ascending list that are <= 32 q + 31 (and < n_pos);  vfirst = entries that are < 0
     const int first = static_cast<int>(*negative);
     const int per = (p.nq32 + kPrepThreads - 1) / kPrepThreads;
     const int q0 = min(tid * per, p.nq32), q1 = min(q0 + per, p.nq32);
@@ -935,6 +935,7 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     pp.cnt_s = cnt_s;
     pp.cap_s = cap_s;
     pp.n = p.n;
+    pp.n_pos = p.pos0 + p.nq;
     pp.nsub = rows / p.hc;
     pp.nblk = w.nq32;
     pp.shift = static_cast<int>(pos0 % 32);

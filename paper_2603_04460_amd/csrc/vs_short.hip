@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
     const uint32_t st_bv = static_cast<uint32_t>(16 * (4 * ((((lane >> 2) & 3) - st_rho) & 3) + (lane & 3)));
     auto load_tile = [&](int row, int slot) __attribute__((always_inline)) {
         unsigned char* const dst = kvbuf + slot * kSlotBytes + wave * kGroupBytes;
-        const uint32_t off = static_cast<uint32_t>(min(row, n - 1)) << 8;      // rows that do not exist are masked
+        const uint32_t off = static_cast<uint32_t>(min(row, n_pos - 1)) << 8;  // rows behind the last position are masked, and not read
         lds_load16s(off + st_bk, kbase, dst);
         lds_load16s(off + st_bv, vbase, dst + kTileBytes);
     };
@@ -385,9 +385,9 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
 #pragma unroll
         for (int grp = 0; grp < 8; ++grp) lds_load16s(off[grp] + piece, base, dst + grp * kGroupBytes);
     };
-    auto block_rows = [&](int b) __attribute__((always_inline)) {            // rows that do not exist are masked
+    auto block_rows = [&](int b) __attribute__((always_inline)) {            // rows behind the last position are masked, and not read
 #pragma unroll
-        for (int grp = 0; grp < 8; ++grp) off[grp] = static_cast<uint32_t>(min(32 * b + 4 * grp + st_rho, n - 1)) << 8;
+        for (int grp = 0; grp < 8; ++grp) off[grp] = static_cast<uint32_t>(min(32 * b + 4 * grp + st_rho, n_pos - 1)) << 8;
     };
     // Tiles [0, ntiles) of a round, this wavefront's every eighth: rows(t) sets off; need(t): 0 skip, 1 keep whole, 2 masked with
     // the keep-bits of keep(t)
@@ -464,7 +464,7 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
                     } else {
 #pragma unroll
                         for (int grp = 0; grp < 8; ++grp)
-                            off[grp] = static_cast<uint32_t>(min(glist[32 * (t - nb) + 4 * grp + st_rho], n - 1)) << 8;
+                            off[grp] = static_cast<uint32_t>(min(glist[32 * (t - nb) + 4 * grp + st_rho], n_pos - 1)) << 8;
                     }
                 },
                 [&](int t) __attribute__((always_inline)) {

@@ -67,23 +67,22 @@ def _sparse_chunk(q, k, v, iv, cv, is_, cs, pos0, n_q, gran=None):
     return o, lse, ws
 
 
-@pytest.mark.parametrize("pos0,n_q", [(1, 32), (37, 60), (31, 64)])
-def test_sparse_gathered_tile_behind_a_row_block(pos0, n_q):
-    """A chunk that starts inside a key block: the columns of that key block that lie behind the row block may fill a gathered tile of
-    their own.  It is neither multiplied nor counted."""
-    n, first = 256, pos0 + (n_q - 1) // 32 * 32
-    end = (pos0 + n_q - 1) // 32 * 32 + 31                   # last key of the key block that the last row lies in
-    cols = list(range(32)) + list(range(first + 32, end + 1))
+@pytest.mark.parametrize("pos0", [1, 31, 37])
+def test_sparse_gathered_tile_behind_a_row_block(pos0):
+    """A chunk that starts inside a key block: the columns of that key block that lie behind the first row block, but in the chunk, may
+    fill a gathered tile of their own.  The first row block neither multiplies nor counts it (a workgroup each)."""
+    n, n_q = 256, 64
+    cols = list(range(32)) + list(range(pos0 + 32, (pos0 + 31) // 32 * 32 + 32))
     (q, k, v), (qb, kb, vb) = make_qkv(3100 + pos0, 1, 1, n)
-    kx, vx = _spoilt(k, v, first + 32)
+    kx, vx = _spoilt(k, v, pos0 + 32)
     iv, cv = lists([cols])
-    is_, cs = lists([[n_q + 40]])                            # far offsets only: no key block reaches the spoilt keys
+    is_, cs = lists([[n_q + 40]])                            # a far offset only: no key block is listed
     o, lse, ws = _sparse_chunk(q, kx, vx, iv, cv, is_, cs, pos0, n_q)
-    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:pos0 + n_q], kb, vb, iv, cv, is_, cs, pos0=pos0)
-    check_attention(o, lse, ref_o, ref_lse)
-    blocks = -(-n_q // 32)
+    rows = np.arange(32)
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:pos0 + n_q], kb, vb, iv, cv, is_, cs, rows=rows, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
     executed, gathered, staged = vs.sparse_prefill_counters(ws)
-    assert executed <= blocks + staged and gathered == blocks + 1
+    assert (executed, gathered, staged) == (3, 4, 0)
 
 
 @pytest.mark.parametrize("hq,hk,n", [(1, 1, 1000), (8, 2, 1024),          # a row block to a workgroup
@@ -104,4 +103,35 @@ def test_sparse_padding_of_gathered_tiles(hq, hk, n, cols):
     assert torch.isfinite(o[:, clean].float()).all()
     rows = _sample(clean)
     ref_o, ref_lse = oracle.sparse_attention(qb, kb, vb, iv, cv, is_, cs, rows=rows)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q,gran", [
+    (1, 1, 1000, 400, 333, None), (8, 2, 4200, 96, 77, 32),              # a row block to a workgroup
+    (8, 8, 1300, 100, 1055, None), (32, 8, 4101, 3000, 301, None),       # two
+    (8, 2, 4200, 100, 3999, None), (32, 8, 4101, 3009, 700, None),       # four
+    (32, 8, 1500, 64, 1411, 32), (32, 8, 1500, 33, 1412, None), (64, 64, 400, 0, 301, None),    # the kernel for many row blocks
+    (1, 1, 500, 2, 3, None),
+])
+def test_keys_behind_a_chunk(hq, hk, n, pos0, n_q, gran):
+    """A cache that is longer than what it holds so far: nothing behind the chunk's last position is looked at, by the sparse and by the
+    dense call."""
+    end = pos0 + n_q
+    assert end % 32 != 0 and end < n
+    rng = np.random.default_rng(n_q)
+    (q, k, v), (qb, kb, vb) = make_qkv(3300 + n_q, hq, hk, n)
+    kx, vx = _spoilt(k, v, end)
+    near = np.arange(end - 2, min(end + 40, n))              # columns on both sides of the end
+    iv, cv = lists([np.unique(np.concatenate([near, rng.choice(n, 60 + h % 2, replace=False)])) for h in range(hk)])
+    is_, cs = lists([[0, 1, 3, n // 3]] * hk)
+    o, lse, _ = _sparse_chunk(q, kx, vx, iv, cv, is_, cs, pos0, n_q, gran)
+    rows = _sample(np.arange(n_q))
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:end], kb, vb, iv, cv, is_, cs, rows=rows, pos0=pos0, granularity=gran or 1)
+    assert torch.isfinite(o.float()).all()
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+    qc = q[:, pos0:end].contiguous()
+    vs.dense_prefill(qc, kx, vx, o, lse, pos0=pos0)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o.float()).all() and torch.isfinite(lse).all()
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:end], kb, vb, rows=rows, pos0=pos0)
     check_attention(o, lse, ref_o, ref_lse, rows=rows)
