@@ -285,6 +285,8 @@ int vs_sparse_prefill_tiles(const void* ws, size_t ws_bytes, void* stream, int64
  * after synchronising `stream`: [0] executed MFMA tiles (as vs_sparse_prefill_tiles), [1] 32-key tiles staged in LDS by
  * row gathers of selected columns (each is 32 rows of K and of V, 256 bytes per row: 16 KiB), [2] 32-key tiles staged
  * as contiguous key blocks of the slash part.
+ * ws, ws_bytes: that workspace (at least 256 bytes).  VS_ERR_INVALID_ARG where it is plain that no sparse call has written it,
+ * VS_ERR_WORKSPACE for the copy of a workspace that ends before its counters.
  */
 int vs_sparse_prefill_counters(const void* ws, size_t ws_bytes, void* stream, int64_t* counters_host);
 

@@ -649,8 +649,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
 // 180 offsets and 3300 columns each 19 us with one workgroup per head for both, 7 us now; n = 50021 9.2 -> 5.6.
 constexpr int kPrepThreads = 1024;
 // words of the workspace's head besides the three 8-byte counters: where the statistics slots are (0 slots: the counters are
-// those at the head)
-constexpr int kHeadStatOff = 8, kHeadStatSlots = 9;
+// those at the head), and the address of the workspace (two words)
+constexpr int kHeadStatOff = 8, kHeadStatSlots = 9, kHeadSelf = 10;
 struct PrepParams {
     const int32_t* idx_v;
     const int32_t* cnt_v;
@@ -742,8 +742,10 @@ __global__ __launch_bounds__(kPrepThreads) void vs_prepare_kernel(const PrepPara
     }
     // ---- columns ----
     if (ih == 0) {
+        const uint64_t self = reinterpret_cast<uint64_t>(p.counters);
         for (int i = tid; i < p.ncounters; i += kPrepThreads)
-            p.counters[i] = i == kHeadStatOff ? p.stat_off : (i == kHeadStatSlots ? static_cast<uint32_t>(p.stat_slots) : 0u);
+            p.counters[i] = i == kHeadStatOff ? p.stat_off : i == kHeadStatSlots ? static_cast<uint32_t>(p.stat_slots)
+                            : i == kHeadSelf ? static_cast<uint32_t>(self) : i == kHeadSelf + 1 ? static_cast<uint32_t>(self >> 32) : 0u;
         for (int i = tid; i < 3 * p.stat_slots; i += kPrepThreads) p.stat[(i / 3) * vs::kStatStride + i % 3] = 0ull;
         for (int i = tid; i < p.nqueues; i += kPrepThreads) p.queues[static_cast<size_t>(i) * p.queue_stride] = 0u;
     }
@@ -788,7 +790,7 @@ SparseWs sparse_ws_layout(int kv_heads, int index_heads, int64_t n) {
     w.vw = static_cast<int>(vs::round_up(static_cast<size_t>(nblk + 4), 4));
     w.nq32 = static_cast<int>(nblk);
     w.dcap = static_cast<int>(nblk + 4);
-    w.counter_off = 0;                                      // three 8-byte tile counters, then two words (kHeadStat...)
+    w.counter_off = 0;                                      // three 8-byte tile counters, then four words (kHead...)
     // Work-queue counters, one per KV head, 128 bytes apart (atomics on one cache line are served one after the other); very
     // short sequences, which have few units, get what fits.  (The area has the size of the offset bitmaps, which stay in LDS.)
     w.queue_off = vs::round_up(64 + static_cast<size_t>(kv_heads) * 4, 256);
@@ -1045,7 +1047,11 @@ int vs_sparse_prefill_counters(const void* ws, size_t ws_bytes, void* stream, in
     uint32_t words[16];
     memcpy(words, head, sizeof(words));
     const size_t off = words[kHeadStatOff], slots = words[kHeadStatSlots];
-    if (slots == 0 || slots > vs::kMaxStatSlots || off + slots * vs::kStatStride * 8 > ws_bytes) return VS_OK;
+    if (slots == 0) return VS_OK;
+    if (slots > vs::kMaxStatSlots) return VS_ERR_INVALID_ARG;   // no sparse call has written this
+    // ws_bytes may name less than the call was given: the slots are in the call's workspace all the same, unless this is a copy of its head
+    const uint64_t self = words[kHeadSelf] | static_cast<uint64_t>(words[kHeadSelf + 1]) << 32;
+    if (off + slots * vs::kStatStride * 8 > ws_bytes && self != reinterpret_cast<uint64_t>(ws)) return VS_ERR_WORKSPACE;
     unsigned long long c[vs::kMaxStatSlots * vs::kStatStride];
     VS_HIP(hipMemcpy(c, static_cast<const unsigned char*>(ws) + off, slots * vs::kStatStride * 8, hipMemcpyDeviceToHost));
     for (size_t s = 0; s < slots; ++s)

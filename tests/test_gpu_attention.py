@@ -348,3 +348,23 @@ def test_tile_statistics(hq, hk, n):
         assert vs.sparse_prefill_tiles(ws) == executed
         assert blocks <= 4 * gathered <= 4 * blocks if cols else gathered == 0     # a workgroup has one to four row blocks
         assert blocks <= 4 * staged
+
+
+def test_counters_of_part_of_a_workspace():
+    """256 bytes name the workspace of the call (its counters lie further in); a whole copy has them too, a shorter one has not, and a
+    workspace that no sparse call has written is refused."""
+    hq, hk, n = 8, 2, 1500
+    (q, k, v), _ = make_qkv(32, hq, hk, n, rope=False)
+    zero, one = torch.zeros((hk, 4), dtype=torch.int32, device="cuda"), torch.ones(hk, dtype=torch.int32, device="cuda")
+    ws = torch.full((vs.sparse_prefill_workspace(hq, hk, hk, n),), 0xff, dtype=torch.uint8, device="cuda")
+    with pytest.raises(vs.VsError) as e:
+        vs.sparse_prefill_counters(ws)
+    assert e.value.code == -1
+    vs.sparse_prefill(q, k, v, zero, one, zero, one, torch.empty_like(q), None, ws)
+    want = vs.sparse_prefill_counters(ws)
+    assert want[0] == 2 * hq * -(-n // 32)
+    assert vs.sparse_prefill_counters(ws[:256]) == want and vs.sparse_prefill_tiles(ws[:256]) == want[0]
+    assert vs.sparse_prefill_counters(ws.clone()) == want
+    with pytest.raises(vs.VsError) as e:
+        vs.sparse_prefill_counters(ws[:256].clone())
+    assert e.value.code == -3
