@@ -128,7 +128,8 @@ __global__ __launch_bounds__(kThreads) void finish_sums_kernel(const double* __r
 
 // COLUMNS == false: row sweep (resident queries, streamed keys).  COLUMNS == true: column sweep.
 // PARTS: p.parts workgroups share the streamed rows of a group (a form of its own: the long sweeps lose 2 % with it).
-template <bool COLUMNS, bool RECALL, bool PARTS = false>
+// NB: resident blocks per wavefront; 1 (row sweep only) gives twice the workgroups of half the length when they are few and short.
+template <bool COLUMNS, bool RECALL, bool PARTS = false, int NB = 2>
 __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams p) {
     __shared__ __align__(16) unsigned char smem[kSmemBytes];
     float* const norm_ring = reinterpret_cast<float*>(smem + kNormOff);
@@ -143,7 +144,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 
     // ---- which 256 resident rows of which query head (and which part of the streamed rows); longest sweeps first ----
     const int h = blockIdx.x % p.q_heads;
-    constexpr int NB = 2;                                    // resident blocks per wavefront
+    static_assert(NB == 2 || !COLUMNS, "the diagonal sums need both blocks");
     constexpr int kRows = 32 * NB * kWaves;                  // resident rows of this workgroup
     const int ngroups = (n + kRows - 1) / kRows;
     const int unit = blockIdx.x / p.q_heads;
@@ -670,6 +671,12 @@ int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_
             const int rows = q_heads * static_cast<int>(n);  // at most 1024 groups of 256
             hipLaunchKernelGGL(combine_rows_kernel, dim3(static_cast<unsigned>((rows + kThreads - 1) / kThreads)), dim3(kThreads), 0, st,
                                p.row_part, parts, rows, p.lse2);
+        } else if (n <= kGroupRows && blocks <= 256) {
+            // One group per head, not shared out: workgroups of half a group, since the call lasts as long as one workgroup.  us per call, halves /
+            // whole groups: one head, n = 200 17 / 20, 256 19 / 22, 128 heads, n = 200 18 / 22, 256 heads, n = 256 21 / 24; 512 heads 34 / 34, 1024
+            // heads, n = 160 43 / 42.
+            const int64_t halves = static_cast<int64_t>(q_heads) * ((n + kGroupRows / 2 - 1) / (kGroupRows / 2));
+            hipLaunchKernelGGL((vs_sweep_kernel<false, false, false, 1>), dim3(static_cast<unsigned>(halves)), dim3(kThreads), 0, st, p);
         } else {
             hipLaunchKernelGGL((vs_sweep_kernel<false, false>), grid, dim3(kThreads), 0, st, p);
         }

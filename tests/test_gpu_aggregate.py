@@ -125,6 +125,16 @@ def test_aggregate_group_sharing(pairs, n):
     _close(a_s, np.repeat(ref_s.mean(0, keepdims=True), pairs, 0))
 
 
+@pytest.mark.parametrize("hq,hk,n", [(1, 1, 127), (3, 1, 128), (4, 2, 129), (1, 1, 200), (8, 2, 255), (3, 3, 256)])
+def test_aggregate_half_groups(hq, hk, n):
+    """Up to 256 positions of up to 256 heads: the row normalisers come from workgroups of 128 rows."""
+    (q, k, v), (qb, kb, vb) = make_qkv(580 + n, hq, hk, n, local=True)
+    ref_v, ref_s, _ = _oracle(qb, kb, hq // hk)
+    a_v, a_s, _ = _run(q, k, hq)
+    _close(a_v, ref_v)
+    _close(a_s, ref_s)
+
+
 @pytest.mark.parametrize("n", [65, 257, 1025, 1100])
 def test_aggregate_last_key_nan(n):
     """The last row sees one NaN key, at n = 65, 257 and 1025 the only key of its workgroup's share: its sum, and with it its entry in
