@@ -4,31 +4,33 @@
 // Non-negative fp32 scores order like their bit patterns, so the k-th ranked score is found by a most-significant-digit radix
 // descent.  A bucket of a pass carries ONE 64-bit weight: the INTEGER mass floor(score * 2^40), or the element count for the fixed
 // budget and for the capacity.  Integer weights make every partial sum exact and independent of the order, so the threshold
-// crossing is the same however the work is split.  The first digit is cut where the scores are, keys >> 19 (16 buckets per octave up
-// to 1.9375, everything above in the last one): its crossing bucket usually holds less than a percent of the scores.  Those, the
-// candidates, are put aside in index order and the remaining digits (10 bits each) only look at them.  Ties at the crossing value
-// are taken in ascending index order.  The selected set, united with the forced leading indices, is then written in ascending order
-// from ballots and counts (no atomics on the output path).
+// crossing is the same however the work is split.  Ties at the crossing value are taken in ascending index order.  The selected set,
+// united with the forced leading indices, is then written in ascending order from ballots and counts (no atomics on the output path).
 //
 // Bound by latency: a few dependent steps, each a round trip to memory or a barrier, and by the instructions of 16 wavefronts on
 // one compute unit, so one wavefront does the scans and the others wait for it.
 //
-// Short problems: one workgroup per (head, direction), select_kernel; up to 8192 scores stay in registers, candidates in LDS.
-// Long ones with a workspace: one workgroup per chunk (8192 scores, at most 16 chunks) and three kernels after one that clears: the
-// histogram of the first digit, added to the problem's in the workspace with integer atomics; the chunk's candidates, appended to
-// the problem's list, and the histogram of their next digit; the last digits, by every workgroup on the problem's candidates, and the
-// emission of its chunk.  (A workgroup that arrives last and finds the crossing value for all saves nothing: making the list visible to
-// it and the others' waiting took 10 us.)  Scores so crowded that the list (a quarter of the scores) does not hold the crossing bucket
-// are read again instead.  A problem whose selection exceeds the capacity is redone by the workgroup of its first chunk.
+// Short problems: one workgroup per (head, direction), select_kernel.  The first digit is cut where the scores are, keys >> 19 (16 buckets
+// per octave up to 1.9375, everything above in the last one): its crossing bucket usually holds less than a percent of the scores.
+// Those, the candidates, are put aside in index order and the remaining digits (10 bits each) only look at them.  Up to 8192 scores stay
+// in registers, candidates in LDS.
+// Long ones with a workspace: one workgroup per chunk of a problem (8192 scores up to 131072) and, after one kernel that clears, four: the histogram of
+// the first digit, that of the second in the first's crossing bucket, both added to the problem's in the workspace with integer atomics; the chunk's
+// counts of the last digit in the second's crossing bucket; the crossing value, from the counts of all chunks, and the emission.  Every pass looks at
+// a chunk's own scores only, however they crowd.  A problem whose selection exceeds the capacity is redone by the workgroup of its
+// first chunk.
 //
-// Measured against three passes of 12, 12 and 8 bits over all scores (count and mass apart; long problems in seven kernels), 8 heads,
-// us per call: 131072 scores 48.7 -> 26.2 (32 heads 119 -> 68), 50021 46.0 -> 25.5, 32000 47.4 -> 31.2, 18763 36.5 -> 23.4, 8192
-// 24.4 -> 14.6, 4096 19.2 -> 14.6 (the kernel alone 17.7 -> 9; two launches take the host 14), 2^20 234 -> 108; 131072 equal scores 83 -> 36, within
-// 2 percent of each other 72 -> 71.  The four kernels of 8 x 131072 take 2.3 + 5.4 + 8.7 + 10.0 us.
+// Measured, us per call, 8 heads.  One workgroup, against three passes of 12, 12 and 8 bits over all scores (count and mass apart): 18763 scores
+// 36.5 -> 23.4, 8192 24.4 -> 14.6, 4096 19.2 -> 14.6 (the kernel alone 17.7 -> 9; two launches take the host 14).  Many, against the same passes in
+// seven kernels / a list of the candidates in the workspace instead of the third kernel, which every workgroup then reads, or all scores where it
+// does not hold them: 131072 scores of a wide spread 49 / 27 -> 30, within 2 percent of each other 70 / 67 -> 35, equal 82 / 34 -> 25, 342475 wide
+// 89 / 49 -> 52, within 2 percent 199 / 170 -> 67; one head 342475 wide 44 / 46 -> 30, within 2 percent 66 / 161 -> 35.  The five kernels of 8 x 131072
+// take 2.4 + 5.2 + 7.8 + 5.6 + 9.4 us.
 #include <hip/hip_runtime.h>
 #include <math.h>
-#include <stddef.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "vs_common.h"
 #include "vs_wave.h"
@@ -108,15 +110,6 @@ __device__ __forceinline__ T wave_scan(T x) {
     x += dpp_moved<0x142, 0xa>(x);
     x += dpp_moved<0x143, 0xc>(x);
     return x;
-}
-// the same with the maximum: lane 63 has that of all lanes
-__device__ __forceinline__ uint32_t wave_top(uint32_t x) {
-    x = max(x, dpp_moved<0x111, 0xf>(x));
-    x = max(x, dpp_moved<0x112, 0xf>(x));
-    x = max(x, dpp_moved<0x114, 0xf>(x));
-    x = max(x, dpp_moved<0x118, 0xf>(x));
-    x = max(x, dpp_moved<0x142, 0xa>(x));
-    return max(x, dpp_moved<0x143, 0xc>(x));
 }
 template <typename T>
 __device__ __forceinline__ T lane_value(T x, int lane) {      // lane: wave-uniform
@@ -234,9 +227,20 @@ struct Range {
     // f(index, score, valid) for all lanes of the wavefront, 64 scores at a time
     template <typename F>
     __device__ __forceinline__ void each(F f) {
+        each(f, [](int, int, float) __attribute__((always_inline)) { return false; });
+    }
+    // The same, but first same(index of the first, number, score) for a batch of equal scores, which returns whether that was all:
+    // atomics of a wavefront on one LDS word are served one after the other (8 heads x 131072 equal scores 45 us per call without it).
+    template <typename F, typename G>
+    __device__ __forceinline__ void each(F f, G same) {
         const int lane = threadIdx.x & 63;
         for (int base = lo; base < hi; base += 64 * kBatch) {
             if (base != have) load(base);
+            const uint32_t first = __builtin_amdgcn_readfirstlane(__float_as_uint(x[0]));
+            bool equal = true;
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) equal &= __float_as_uint(x[j]) == first;
+            if (__all(equal) && same(base, min(hi - base, 64 * kBatch), __uint_as_float(first))) continue;
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const int i = base + 64 * j + lane;
@@ -387,39 +391,36 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelParams p) 
 }
 
 // ---- the same selection over many workgroups ----
-constexpr int kChunk = 8192;                   // scores per workgroup up to 131072, one batch of every wavefront; longer problems have longer
-constexpr int kMaxChunks = kWaves;             // chunks: a wavefront per chunk looks at the whole problem
+constexpr int kChunk = 8192;                   // scores per workgroup up to 524288, one batch of every wavefront; longer problems have longer chunks
+constexpr int kMaxChunks = 64;                 // a lane per chunk adds up the positions
 static_assert(kChunk == kSelThreads * kBatch, "one batch");
+// digits of a key: 11, 11 and 9 bits
+constexpr int kShift1 = 20, kShift2 = 9, kBuckets = 2048, kLastBuckets = 1 << kShift2;
+static_assert(kHistWords == Hist<kBuckets>::kWords, "one histogram");
 
-// Workspace of one problem: histograms of the first digit and of the next one in its crossing bucket (64 lanes wide, otherwise as in
-// LDS: neighbouring buckets are 512 bytes apart, and atomics of many workgroups on one line, which are served one after the other,
-// are few) | counters | candidates
+// Workspace of one problem.  The histograms are 64 lanes wide, otherwise as in LDS: neighbouring buckets are 512 bytes apart, and atomics
+// of many workgroups on one line, which are served one after the other, are few.
 struct ProblemWs {
-    u64 hist[kTopBuckets], next[kDigitBuckets];
-    uint32_t candidates;            // entries that the chunks have asked for; more than SplitParams::cand_cap: the list is incomplete
-    uint32_t not_least, greatest;   // maxima over the candidates: of the complement of a key, of a key
-    uint32_t pad[61];
-    uint32_t cand[1];               // SplitParams::cand_cap
+    u64 hist[kBuckets], next[kBuckets];        // first digit; second digit in the crossing bucket of the first
 };
-constexpr size_t kProblemHead = offsetof(ProblemWs, cand);
-constexpr size_t kProblemBytes = 3 * 4096 * 12;              // longer sequences get a byte per score for the candidates
 struct ProblemState {
-    Descent first;                  // after the first digit
-    uint32_t pad[42];
+    Descent first, second;                     // after these digits; second.bucket: both digits
 };
-struct ChunkInfo {
-    uint32_t in, pos, num;          // entries in without being candidates; candidates
+// What a workgroup finds in its chunk
+struct ChunkWs {
+    uint32_t in;                               // forced entries, and those above the crossing bucket of the first digit
+    uint32_t above;                            // unforced ones in that, above the crossing bucket of the second
+    uint32_t pad[62];
+    uint32_t last[kLastBuckets];               // those in that by their last digit; unforced ones also count in the high half
 };
-static_assert(sizeof(Descent) == 24 && sizeof(ProblemState) == 192 && sizeof(ChunkInfo) == 12, "workspace layout");
+constexpr int kLongestChunk = 7 * kChunk;
+static_assert(kLongestChunk < 65536 && VS_MAX_SEQ <= kMaxChunks * kLongestChunk, "two counts in a word");
 struct SplitParams {
     SelParams s;
-    int chunks, chunk_size;         // chunk_size: a multiple of kChunk
-    unsigned char* problem;
-    size_t problem_bytes;
-    uint32_t cand_cap;
+    int chunks, chunk_size;                    // chunk_size: a multiple of kChunk
+    ProblemWs* problem;
     ProblemState* state;
-    ChunkInfo* chunk;               // [problems][chunks]
-    __device__ __forceinline__ ProblemWs& ws(int pr) const { return *reinterpret_cast<ProblemWs*>(problem + problem_bytes * pr); }
+    ChunkWs* chunk;                            // [problems][chunks]
 };
 
 // This wavefront's scores of the workgroup's chunk
@@ -429,7 +430,17 @@ __device__ __forceinline__ Range chunk_range(const SplitParams& q, int wave) {
     return Range(q.s.a[blockIdx.z] + static_cast<size_t>(blockIdx.y) * n, lo, min(lo + per_wave, n));
 }
 
-__global__ __launch_bounds__(kSelThreads) void split_hist_kernel(const SplitParams q) {
+__device__ __forceinline__ void add_histogram(const u64* hist, u64* out) {
+    for (int r = threadIdx.x; r < kBuckets; r += kSelThreads) {
+        const u64 w = hist[(r >> 6) * 65 + (r & 63)];         // both layouts have 64 lanes
+        if (w) atomicAdd(&out[r], w);
+    }
+}
+__device__ __forceinline__ void load_histogram(const u64* in, u64* hist) {
+    for (int r = threadIdx.x; r < kBuckets; r += kSelThreads) hist[(r >> 6) * 65 + (r & 63)] = in[r];
+}
+
+__global__ __launch_bounds__(kSelThreads) void split_first_kernel(const SplitParams q) {
     __shared__ u64 hist[kHistWords];
     const SelParams& p = q.s;
     const int head = blockIdx.y, dir = blockIdx.z, tid = threadIdx.x;
@@ -442,41 +453,39 @@ __global__ __launch_bounds__(kSelThreads) void split_hist_kernel(const SplitPara
         if (!valid) return;
         const uint32_t key = score_key(x, st);
         const u64 w = by_count ? 1ull : key_mass(key);
-        if (w) atomicAdd(&hist[Hist<kTopBuckets>::slot(top_bucket(key))], w);
+        if (w) atomicAdd(&hist[Hist<kBuckets>::slot(key >> kShift1)], w);
+    }, [&](int, int num, float x) __attribute__((always_inline)) {
+        const uint32_t key = score_key(x, st);
+        if ((tid & 63) == 0) atomicAdd(&hist[Hist<kBuckets>::slot(key >> kShift1)], num * (by_count ? 1ull : key_mass(key)));
+        return true;
     });
     if (st && p.status) atomicOr(p.status + head, st);
     __syncthreads();
-    u64* const out = q.ws(head * 2 + dir).hist;
-    for (int r = tid; r < kTopBuckets; r += kSelThreads) {
-        const u64 w = hist[(r >> 6) * 65 + (r & 63)];         // both layouts have 64 lanes
-        if (w) atomicAdd(&out[r], w);
-    }
+    add_histogram(hist, q.problem[head * 2 + dir].hist);
 }
 
-// The crossing bucket of the first digit; this chunk's entries of it, and the histogram of their next digit.
-__global__ __launch_bounds__(kSelThreads) void split_pick_kernel(const SplitParams q) {
-    __shared__ u64 hist[kHistWords], next[Hist<kDigitBuckets>::kWords];
+// The crossing bucket of the first digit, and the histogram of the second digit in it.
+__global__ __launch_bounds__(kSelThreads) void split_second_kernel(const SplitParams q) {
+    __shared__ u64 hist[kHistWords], next[kHistWords];
     __shared__ Descent shared;
-    __shared__ uint32_t part[kWaves], not_least[kWaves], greatest[kWaves], base;
+    __shared__ uint32_t part[kWaves];
     const SelParams& p = q.s;
     const int chunk = blockIdx.x, head = blockIdx.y, dir = blockIdx.z, pr = head * 2 + dir;
-    const int tid = threadIdx.x, lane = tid & 63, n = p.n;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nforced = min(p.nforced[dir], n);
+    const int nforced = min(p.nforced[dir], p.n);
     const bool by_count = p.mode != 0;
-    const u64 lt_mask = (1ull << lane) - 1ull;
-    ProblemWs& ws = q.ws(pr);
     Range range = chunk_range(q, wave);
-    for (int r = tid; r < kTopBuckets; r += kSelThreads) hist[(r >> 6) * 65 + (r & 63)] = ws.hist[r];
-    for (int b = tid; b < Hist<kDigitBuckets>::kWords; b += kSelThreads) next[b] = 0ull;
+    load_histogram(q.problem[pr].hist, hist);
+    for (int b = tid; b < kHistWords; b += kSelThreads) next[b] = 0ull;
     __syncthreads();
     Descent d{};
     if (by_count) {
-        d.target = static_cast<u64>(min(p.kfix[dir], n));
+        d.target = static_cast<u64>(min(p.kfix[dir], p.n));
         d.none = d.target == 0 ? 1u : 0u;
     }
     if (tid < 64) {
-        if (!d.none) find_crossing<kTopBuckets>(hist, by_count ? -1.0 : p.tau[dir], d);
+        if (!d.none) find_crossing<kBuckets>(hist, by_count ? -1.0 : p.tau[dir], d);
         if (tid == 0) {
             shared = d;
             if (chunk == 0) q.state[pr].first = d;
@@ -484,155 +493,150 @@ __global__ __launch_bounds__(kSelThreads) void split_pick_kernel(const SplitPara
     }
     __syncthreads();
     d = shared;
-    const uint32_t low = low_end(d.bucket);
-    const int shf = bits_below(d.bucket) - kDigit;
-    auto candidate = [&](float x, bool valid, uint32_t& key) __attribute__((always_inline)) {
-        key = score_key(x);
-        return valid && !d.none && top_bucket(key) == d.bucket;
-    };
-    uint32_t inc = 0, mine = 0, lo_key = 0u, hi_key = 0u;
+    uint32_t inc = 0;
     range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
-        uint32_t key;
-        const bool c = candidate(x, valid, key);
-        inc += __popcll(__ballot(valid && (i < nforced || (!d.none && top_bucket(key) > d.bucket))));
-        mine += __popcll(__ballot(c));
-        if (c) {
-            lo_key = max(lo_key, ~key);
-            hi_key = max(hi_key, key);
+        const uint32_t key = score_key(x), b = key >> kShift1;
+        inc += __popcll(__ballot(valid && (i < nforced || (!d.none && b > d.bucket))));
+        if (valid && !d.none && b == d.bucket) {
             const u64 w = by_count ? 1ull : key_mass(key);
-            if (w) atomicAdd(&next[Hist<kDigitBuckets>::slot((key - low) >> shf)], w);
+            if (w) atomicAdd(&next[Hist<kBuckets>::slot((key >> kShift2) & (kBuckets - 1))], w);
         }
+    }, [&](int base, int num, float x) __attribute__((always_inline)) {
+        const uint32_t key = score_key(x), b = key >> kShift1;
+        inc += !d.none && b > d.bucket ? num : min(max(nforced - base, 0), num);
+        if (lane == 0 && !d.none && b == d.bucket)
+            atomicAdd(&next[Hist<kBuckets>::slot((key >> kShift2) & (kBuckets - 1))], num * (by_count ? 1ull : key_mass(key)));
+        return true;
     });
-    lo_key = wave_top(lo_key);
-    hi_key = wave_top(hi_key);
-    if (lane == 63) {
-        part[wave] = (inc << 16) | mine;                     // at most VS_MAX_SEQ / kMaxChunks / kWaves each
-        not_least[wave] = lo_key;
-        greatest[wave] = hi_key;
-    }
-    static_assert(VS_MAX_SEQ / kMaxChunks / kWaves < 65536, "two counts in a word");
+    if (lane == 0) part[wave] = inc;
     __syncthreads();
-    const uint32_t pw = lane < kWaves ? part[lane] : 0u;
-    const uint32_t num = wave_scan(pw & 0xffffu), in_all = wave_scan(pw >> 16);
-    lo_key = wave_top(lane < kWaves ? not_least[lane] : 0u);
-    hi_key = wave_top(lane < kWaves ? greatest[lane] : 0u);
-    if (tid == 63) {
-        base = num ? atomicAdd(&ws.candidates, num) : 0u;
-        if (num) {
-            atomicMax(&ws.not_least, lo_key);
-            atomicMax(&ws.greatest, hi_key);
-        }
-        q.chunk[static_cast<size_t>(pr) * q.chunks + chunk] = ChunkInfo{in_all, base, num};
+    if (tid < 64) {
+        inc = wave_scan(lane < kWaves ? part[lane] : 0u);
+        if (lane == 63) q.chunk[static_cast<size_t>(pr) * q.chunks + chunk].in = inc;
     }
-    for (int r = tid; r < kDigitBuckets; r += kSelThreads) {
-        const u64 w = next[(r >> 6) * 65 + (r & 63)];
-        if (w) atomicAdd(&ws.next[r], w);
-    }
-    __syncthreads();
-    uint32_t at = base + lane_value(num - (pw & 0xffffu), wave);
-    range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
-        uint32_t key;
-        const bool c = candidate(x, valid, key);
-        const u64 cb = __ballot(c);
-        const uint32_t k = at + __popcll(cb & lt_mask);
-        if (c && k < q.cand_cap) ws.cand[k] = key | (i < nforced ? 0x80000000u : 0u);
-        at += __popcll(cb);
-    });
+    add_histogram(next, q.problem[pr].next);
 }
 
-// The remaining digits and the ordered emission of a chunk.  Every workgroup of a problem looks at all its candidates, a chunk of them
-// per wavefront: those above the crossing bucket of the second digit are counted, those in it (few, as a rule) kept in LDS.
-constexpr int kKept = 512;                     // per chunk
+// The crossing bucket of the second digit, and this chunk's entries of it by their last digit.
+__global__ __launch_bounds__(kSelThreads) void split_last_kernel(const SplitParams q) {
+    __shared__ u64 hist[kHistWords];
+    __shared__ uint32_t last[kLastBuckets], part[kWaves];
+    __shared__ Descent shared;
+    const SelParams& p = q.s;
+    const int chunk = blockIdx.x, head = blockIdx.y, dir = blockIdx.z, pr = head * 2 + dir;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nforced = min(p.nforced[dir], p.n);
+    Range range = chunk_range(q, wave);
+    load_histogram(q.problem[pr].next, hist);
+    Descent d = q.state[pr].first;
+    if (d.none || d.all) return;
+    if (tid < kLastBuckets) last[tid] = 0u;
+    __syncthreads();
+    const uint32_t first = d.bucket;
+    if (tid < 64) {
+        find_crossing<kBuckets>(hist, -1.0, d);
+        d.bucket |= first << (kShift1 - kShift2);
+        if (tid == 0) {
+            shared = d;
+            if (chunk == 0) q.state[pr].second = d;
+        }
+    }
+    __syncthreads();
+    const uint32_t prefix = shared.bucket;
+    uint32_t above = 0;
+    range.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
+        const uint32_t key = score_key(x), b = key >> kShift2;
+        const bool forced = i < nforced;
+        above += __popcll(__ballot(valid && !forced && b > prefix && (key >> kShift1) == first));
+        if (valid && b == prefix) atomicAdd(&last[key & (kLastBuckets - 1)], forced ? 1u : 0x10001u);
+    }, [&](int base, int num, float x) __attribute__((always_inline)) {
+        const uint32_t key = score_key(x), b = key >> kShift2, unforced = num - min(max(nforced - base, 0), num);
+        if (b > prefix && (key >> kShift1) == first) above += unforced;
+        if (lane == 0 && b == prefix) atomicAdd(&last[key & (kLastBuckets - 1)], (unforced << 16) + num);
+        return true;
+    });
+    if (lane == 0) part[wave] = above;
+    __syncthreads();
+    ChunkWs& out = q.chunk[static_cast<size_t>(pr) * q.chunks + chunk];
+    if (tid < kLastBuckets) out.last[tid] = last[tid];
+    if (tid < 64) {
+        above = wave_scan(lane < kWaves ? part[lane] : 0u);
+        if (lane == 63) out.above = above;
+    }
+}
 
+// The crossing value and the ordered emission of a chunk.
 __global__ __launch_bounds__(kSelThreads) void split_emit_kernel(const SplitParams q) {
     __shared__ SelShared sh;
-    __shared__ uint32_t kept[kWaves * kKept], c_in[kMaxChunks], c_eq[kMaxChunks], c_ef[kMaxChunks];
+    __shared__ uint32_t c_in[kMaxChunks], c_eq[kMaxChunks], c_ef[kMaxChunks];
     const SelParams& p = q.s;
     const int chunk = blockIdx.x, head = blockIdx.y, dir = blockIdx.z, pr = head * 2 + dir;
     const int tid = threadIdx.x, lane = tid & 63, n = p.n;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nforced = min(p.nforced[dir], n);
     const bool by_count = p.mode != 0;
-    const u64 lt_mask = (1ull << lane) - 1ull;
-    const ProblemWs& ws = q.ws(pr);
+    const ChunkWs* const info = q.chunk + static_cast<size_t>(pr) * q.chunks;
     Range range = chunk_range(q, wave);
-    Descent d = q.state[pr].first;
-    const bool here = wave < q.chunks;
-    const ChunkInfo ci = here ? q.chunk[static_cast<size_t>(pr) * q.chunks + wave] : ChunkInfo{0u, 0u, 0u};
-    const uint32_t found = ws.candidates;
-    const bool stored = found <= q.cand_cap;
-    const bool one_key = !stored && ~ws.not_least == ws.greatest;      // more than the list holds, but all the same
-    const uint32_t top = d.bucket, low = low_end(top);
-    const int bits = bits_below(top) - kDigit;
-    // chunk `wave`'s candidates: from the list or, if that is incomplete, from the scores
-    auto source = [&](auto f) __attribute__((always_inline)) {
-        if (stored) {
-            for (uint32_t k = 0; k < ci.num; k += 64) f(k + lane < ci.num ? ws.cand[ci.pos + k + lane] : 0u, k + lane < ci.num);
-        } else {
-            const int lo = min(wave * q.chunk_size, n);
-            Range all(p.a[dir] + static_cast<size_t>(head) * n, lo, min(lo + q.chunk_size, n));
-            all.each([&](int i, float x, bool valid) __attribute__((always_inline)) {
-                const uint32_t key = score_key(x);
-                f(key | (i < nforced ? 0x80000000u : 0u), valid && top_bucket(key) == top);
-            });
-        }
+    // a wavefront adds up every sixteenth chunk; what it needs of the first is requested here (the words of a chunk without a last digit
+    // hold anything and are not looked at)
+    constexpr int kEntries = kLastBuckets / 64;
+    uint32_t num[kEntries], in_above = 0;
+    auto request = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kEntries; ++j) num[j] = info[c].last[64 * j + lane];
+        in_above = info[c].in + info[c].above;
     };
+    request(min(wave, q.chunks - 1));
+    const Descent second = q.state[pr].second;
+    Descent d = q.state[pr].first;
     uint32_t vstar = 0u, ties = 0xffffffffu;                 // everything is in: crossing value 0 and every tie
-    uint32_t eqc = 0, eqf = 0, above = 0;                    // per lane, of chunk `wave`
-    if (d.none) {
-        ties = 0u;
-    } else if (d.all || one_key) {                           // every candidate is a tie or in
-        if (one_key && !d.all) {
-            vstar = ws.greatest;
-            ties = ties_taken(d, vstar, by_count);
+    if (d.none || d.all) {
+        if (d.none) ties = 0u;
+        if (tid < q.chunks) {
+            c_in[tid] = d.none ? info[tid].in : static_cast<uint32_t>(min(q.chunk_size, n - tid * q.chunk_size));
+            c_eq[tid] = c_ef[tid] = 0u;
         }
-        if (lane == 0) eqc = ci.num;
-        const int lo = min(wave * q.chunk_size, n);
-        Range forced(p.a[dir] + static_cast<size_t>(head) * n, lo, min(lo + q.chunk_size, nforced));
-        forced.each([&](int, float x, bool valid) __attribute__((always_inline)) { eqf += valid && top_bucket(score_key(x)) == top ? 1u : 0u; });
     } else {
-        for (int r = tid; r < kDigitBuckets; r += kSelThreads) sh.hist[(r >> 6) * 65 + (r & 63)] = ws.next[r];
+        d = second;
+        const uint32_t low = d.bucket << kShift2;
+        // All entries of a last bucket have the same weight, so that counts are enough.
+        for (int b = tid; b < Hist<kLastBuckets>::kWords; b += kSelThreads) sh.hist[b] = 0ull;
+        __syncthreads();
+        for (int c = wave; c < q.chunks; c += kWaves) {
+            if (c != wave) request(c);
+#pragma unroll
+            for (int j = 0; j < kEntries; ++j) {
+                const uint32_t b = 64 * j + lane, all = num[j] & 0xffffu;
+                if (all) atomicAdd(&sh.hist[Hist<kLastBuckets>::slot(b)], by_count ? all : all * key_mass(low + b));
+            }
+        }
         __syncthreads();
         if (tid < 64) {
-            find_crossing<kDigitBuckets>(sh.hist, -1.0, d);
+            find_crossing<kLastBuckets>(sh.hist, -1.0, d);
             if (tid == 0) sh.descent = d;
         }
         __syncthreads();
         d = sh.descent;
-        const uint32_t prefix = d.bucket;
-        uint32_t num = 0;
-        source([&](uint32_t v, bool valid) __attribute__((always_inline)) {
-            const uint32_t digit = ((v & 0x7fffffffu) - low) >> bits;
-            const bool keep = valid && digit == prefix;
-            above += valid && digit > prefix ? 1u - (v >> 31) : 0u;
-            const u64 kb = __ballot(keep);
-            const uint32_t k = num + __popcll(kb & lt_mask);
-            if (keep && k < kKept) kept[wave * kKept + k] = v;
-            num += __popcll(kb);
-        });
-        const bool fits = !__syncthreads_or(num > kKept);
-        auto each = [&](auto f) __attribute__((always_inline)) {
-            if (fits) {
-                for (uint32_t k = 0; k < num; k += 64) f(kept[wave * kKept + min(k + lane, num - 1)], k + lane < num);
-            } else {
-                source([&](uint32_t v, bool valid) __attribute__((always_inline)) { f(v, valid && ((v & 0x7fffffffu) - low) >> bits == prefix); });
-            }
-        };
-        vstar = low + descend(sh.hist, &sh.descent, d, low, prefix, bits, by_count, each);
+        vstar = low + d.bucket;
         ties = ties_taken(d, vstar, by_count);
-        each([&](uint32_t v, bool valid) __attribute__((always_inline)) {
-            const uint32_t key = v & 0x7fffffffu, forced = v >> 31;
-            eqc += valid && key == vstar ? 1u : 0u;
-            eqf += valid && key == vstar ? forced : 0u;
-            above += valid && key > vstar ? 1u - forced : 0u;
-        });
-    }
-    const u64 sums = wave_scan((static_cast<u64>(eqc) << 32) | eqf);
-    above = wave_scan(above);
-    if (here && lane == 63) {
-        c_eq[wave] = static_cast<uint32_t>(sums >> 32);
-        c_ef[wave] = static_cast<uint32_t>(sums);
-        c_in[wave] = ci.in + above;
+        for (int c = wave; c < q.chunks; c += kWaves) {
+            if (q.chunks > kWaves) request(c);
+            uint32_t more = 0, eq = 0;
+#pragma unroll
+            for (int j = 0; j < kEntries; ++j) {
+                const uint32_t b = 64 * j + lane;
+                more += b > d.bucket ? num[j] >> 16 : 0u;
+                eq += b == d.bucket ? num[j] : 0u;
+            }
+            more = wave_scan(more);
+            eq = wave_scan(eq);
+            if (lane == 63) {
+                c_in[c] = in_above + more;
+                c_eq[c] = eq & 0xffffu;
+                c_ef[c] = (eq & 0xffffu) - (eq >> 16);
+            }
+        }
     }
     // this wavefront's range of this chunk
     uint32_t w_eq = 0, w_ef = 0, w_in = 0;
@@ -672,29 +676,39 @@ __global__ __launch_bounds__(kSelThreads) void split_emit_kernel(const SplitPara
          [&](int) __attribute__((always_inline)) { return !d.none; });
 }
 
-// Histograms and counters of the problems, status words
-__global__ __launch_bounds__(kSelThreads) void clear_kernel(unsigned char* problem, size_t problem_bytes, int32_t* status) {
-    uint4* const w = reinterpret_cast<uint4*>(problem + problem_bytes * blockIdx.x);
-    for (int i = threadIdx.x; i < static_cast<int>(kProblemHead / 16); i += kSelThreads) w[i] = make_uint4(0u, 0u, 0u, 0u);
+// Histograms of the problems, status words
+__global__ __launch_bounds__(kSelThreads) void clear_kernel(ProblemWs* problem, int32_t* status) {
+    uint4* const w = reinterpret_cast<uint4*>(problem + blockIdx.x);
+    for (int i = threadIdx.x; i < static_cast<int>(sizeof(ProblemWs) / 16); i += kSelThreads) w[i] = make_uint4(0u, 0u, 0u, 0u);
     if (status && threadIdx.x == 0 && (blockIdx.x & 1) == 0) status[blockIdx.x >> 1] = 0;
 }
 
 struct SplitLayout {
-    size_t problem_bytes, state, chunk, total;
+    size_t state, chunk, total;
     int chunks, chunk_size;
 };
 
 SplitLayout split_layout(int heads, int64_t n) {
     SplitLayout w{};
     const size_t pr = static_cast<size_t>(heads) * 2;
-    const int64_t longest = static_cast<int64_t>(kChunk) * kMaxChunks;
-    w.chunk_size = kChunk * static_cast<int>((n + longest - 1) / longest);
-    w.chunks = static_cast<int>((n + w.chunk_size - 1) / w.chunk_size);
-    const size_t want = vs::round_up(kProblemHead + static_cast<size_t>(n), 256);
-    w.problem_bytes = n > 131072 ? want : kProblemBytes;    // a quarter of the scores can be candidates, of shorter ones up to all
-    w.state = vs::round_up(pr * w.problem_bytes + pr * sizeof(int32_t), 256);
+    // Up to 131072 scores chunks of 8192.  Beyond, the length with the least work for the busiest of 256 compute units (a workgroup costs about
+    // as much as 8192 scores more), of equal ones the longest: every workgroup looks at what all chunks of its problem have found.  us per call: 8 heads x 2^20 in 19 chunks (304 workgroups) 141, 32
+    // (512) 97, 64 110; 8 x 342475 in 21 chunks (336) 59, 14 (224) 52; 32 x 342475 in 42 chunks 167, 11 (704) 129.
+    int64_t least = INT64_MAX;
+    for (int size = kChunk; size <= kLongestChunk; size += kChunk) {
+        const int64_t chunks = (n + size - 1) / size, work = (static_cast<int64_t>(pr) * chunks + 255) / 256 * (size + kChunk);
+        if (chunks > kMaxChunks || work > least) continue;
+        least = work;
+        w.chunk_size = size;
+        w.chunks = static_cast<int>(chunks);
+        if (n <= 131072) break;
+    }
+    w.state = pr * sizeof(ProblemWs);
     w.chunk = vs::round_up(w.state + pr * sizeof(ProblemState), 256);
-    w.total = vs::round_up(w.chunk + pr * w.chunks * sizeof(ChunkInfo), 256);
+    w.total = w.chunk + pr * w.chunks * sizeof(ChunkWs);
+    // never less than what the query gave when it was three histograms of 4096 entries to a problem
+    const size_t former = vs::round_up(pr * (3 * 4096 * 12 + 4), 256) + vs::round_up(pr * 192, 256) + vs::round_up(pr * ((n + kChunk - 1) / kChunk) * 12, 256);
+    if (w.total < former) w.total = former;
     return w;
 }
 
@@ -756,20 +770,16 @@ int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, c
         q.s = p;
         q.chunks = w.chunks;
         q.chunk_size = w.chunk_size;
-        q.problem = base;
-        q.problem_bytes = w.problem_bytes;
-        q.cand_cap = static_cast<uint32_t>((w.problem_bytes - kProblemHead) / 4);
+        q.problem = reinterpret_cast<ProblemWs*>(base);
         q.state = reinterpret_cast<ProblemState*>(base + w.state);
-        q.chunk = reinterpret_cast<ChunkInfo*>(base + w.chunk);
-        hipLaunchKernelGGL(clear_kernel, dim3(2 * heads), dim3(kSelThreads), 0, st, q.problem, q.problem_bytes, status);
+        q.chunk = reinterpret_cast<ChunkWs*>(base + w.chunk);
+        hipLaunchKernelGGL(clear_kernel, dim3(2 * heads), dim3(kSelThreads), 0, st, q.problem, status);
         VS_LAUNCH_CHECK();
         const dim3 grid(w.chunks, heads, 2);
-        hipLaunchKernelGGL(split_hist_kernel, grid, dim3(kSelThreads), 0, st, q);
-        VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(split_pick_kernel, grid, dim3(kSelThreads), 0, st, q);
-        VS_LAUNCH_CHECK();
-        hipLaunchKernelGGL(split_emit_kernel, grid, dim3(kSelThreads), 0, st, q);
-        VS_LAUNCH_CHECK();
+        for (void (*kernel)(SplitParams) : {&split_first_kernel, &split_second_kernel, &split_last_kernel, &split_emit_kernel}) {
+            hipLaunchKernelGGL(kernel, grid, dim3(kSelThreads), 0, st, q);
+            VS_LAUNCH_CHECK();
+        }
         return VS_OK;
     }
     if (status) {

@@ -184,6 +184,28 @@ def test_select_crowded_scores(n):
     _check_select(a_v, a_s, vs.Budget(mode=0, tau_v=0.9, tau_s=0.9, n_sink=sink, n_local=local, cap_v=n // 9 + sink, cap_s=local))
 
 
+@pytest.mark.parametrize("n", [131073, 147457, 200003, 342475, 1 << 20])
+def test_select_long_crowded_scores(n):
+    """More than 131072 scores, whose last digit comes from histograms of the chunks (up to 16, ragged): spreads from one value of the last
+    digit to several buckets of the first, ties across chunk borders and among the forced entries, zeros, scores above one at the
+    crossing; both rules, degenerate and one-off targets, the capacity fallback."""
+    rng = np.random.default_rng(n)
+    spread = lambda s: ((1.0 + s * rng.random(n)) / n).astype(np.float32)
+    ties = (rng.integers(1, 9, n) * np.float32(2.0 ** -22)).astype(np.float32)
+    ties[rng.integers(0, n, n // 3)] = 0.0
+    big = np.float32(2.0) + 4.0 * rng.random(n).astype(np.float32)
+    sink, local = 7, 8192 + 33
+    rows = [spread(2e-2), spread(1e-4), spread(3e-7), spread(1.0), ties, big]
+    for i in range(0, len(rows), 2):
+        a_v, a_s = np.stack([rows[i], rows[i + 1]]), np.stack([rows[(i + 3) % 6], rows[i]])
+        for tau in (0.9, 0.37):
+            _check_select(a_v, a_s, vs.Budget(mode=0, tau_v=tau, tau_s=1.0 - tau, n_sink=sink, n_local=local, cap_v=n, cap_s=n))
+        _check_select(a_v, a_s, vs.Budget(mode=1, k_v=n // 3, k_s=n - 1, n_sink=sink, n_local=local, cap_v=n, cap_s=n))
+    _check_select(a_v, a_s, vs.Budget(mode=1, k_v=1, k_s=n, n_sink=sink, n_local=local, cap_v=n, cap_s=n))
+    _check_select(a_v, a_s, vs.Budget(mode=0, tau_v=0.0, tau_s=1.0, n_sink=sink, n_local=local, cap_v=n, cap_s=n))
+    _check_select(a_s, a_v, vs.Budget(mode=0, tau_v=0.8, tau_s=0.8, n_sink=sink, n_local=local, cap_v=n // 5, cap_s=local + 1))
+
+
 def test_select_split_over_workgroups():
     """Long problems with a workspace run the descent over one workgroup per 8192-score chunk: ties across chunk borders,
     a ragged last chunk, both rules, degenerate thresholds, bad scores, the rounded-total corner and the capacity
