@@ -42,6 +42,7 @@
 // opens step s+1, which publishes them.  Loads are never predicated: rows that do not exist read another row, whose
 // scores are masked.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
 #include <stdint.h>
 #include <string.h>
@@ -59,13 +60,13 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kRing = 4;                       // ring of two stages of two tiles
 constexpr int kListCap = 128;                  // block list: kListCap / nsub entries per pass
 constexpr int kLdsBudget = 80 * 1024;          // per workgroup: two of them share the 160 KB of a compute unit
-// LDS: ring | tile records per (sub-block, listed block) | scratch | gather list (entries per pass) | its last tile with the padding masked
+// LDS: ring | tile records per (sub-block, listed block) | scratch | gather list (entries per pass)
 constexpr int kGatherCap = 2432;
 constexpr int kRecPad = 4;                     // dead records after a sub-block's last listed block (a step looks one stage ahead)
 constexpr size_t kListRecOff = kRing * kSlotBytes;           // 16-byte tile record per (sub-block, listed block)
 constexpr size_t kScratchOff = kListRecOff + (kListCap + 4 * kRecPad) * 16;
 constexpr size_t kGatherOff = kScratchOff + 128;
-constexpr size_t kLdsBytes = kGatherOff + (kGatherCap + 32) * 4;
+constexpr size_t kLdsBytes = kGatherOff + kGatherCap * 4;
 static_assert(kLdsBytes <= kLdsBudget, "two workgroups per compute unit");
 static_assert(kGatherCap % 64 == 0, "whole stages");
 constexpr int kShortUnits = 128;               // units of four row blocks up to which vs_short.hip takes a call
@@ -78,7 +79,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     uint4* const list_rec = reinterpret_cast<uint4*>(smem + kListRecOff);
     int* const wtot = reinterpret_cast<int*>(smem + kScratchOff);
     int* const glist = reinterpret_cast<int*>(smem + kGatherOff);
-    int* const last_tile = glist + kGatherCap;
 
     const float NEG_INF = -INFINITY;
 
@@ -294,7 +294,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     };
     auto gather_info = [&](const int* cols) __attribute__((always_inline)) -> TileInfo {
         TileInfo ti{false, false, nullptr, cols};
-        const int cmin = cols[0], cmax = cols[31];           // ascending
+        const int cmin = cols[0], cmax = cols[31];           // ascending, INT_MAX padding
         ti.live = my_rows && cmin <= my_i0 + 31;
         ti.need = cmax > my_i0;
         return ti;
@@ -329,6 +329,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     // primed: stage 0 of this phase was requested by the previous phase's last step (into the buffer it had free);
     // chain: this (block) phase is followed by a gather phase whose list is ready, so its last step requests that phase's
     // stage 0 and the pipeline does not drain between the two.
+    int last = 0;                                            // last column of the round of the gather list
     int buf = 0;                                             // buffer of the current stage; the next stage goes to the other one
     auto run_phase = [&](int ntiles, auto gather_tag, int nfull, bool primed, bool chain) __attribute__((always_inline)) {
         constexpr bool GATHER = decltype(gather_tag)::value;
@@ -353,14 +354,14 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int r = st_row + 16 * h;
-                    if (GATHER) rows[u][h] = min(glist[32 * (2 * st + u) + r], n_pos - 1);   // padded to a whole stage
+                    if (GATHER) rows[u][h] = min(glist[32 * (2 * st + u) + r], last);   // padded with INT_MAX to a whole stage
                     else rows[u][h] = min(static_cast<int>(d[u] >> 2) * 32 + r, n_pos - 1);
                 }
         };
         auto info = [&](int t, uint32_t d) __attribute__((always_inline)) -> TileInfo {
             if (GATHER) {
                 if (t >= ntiles) return TileInfo{false, false, nullptr, nullptr};
-                return gather_info(t == ntiles - 1 ? last_tile : glist + 32 * t);
+                return gather_info(glist + 32 * t);
             }
             return block_info(t, d);
         };
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) rows[u][h] = min(glist[32 * u + st_row + 16 * h], n_pos - 1);
+                    for (int h = 0; h < 2; ++h) rows[u][h] = min(glist[32 * u + st_row + 16 * h], last);
                 load_stage(rows, buf1);
             }
             if constexpr (MODE != 2) {
@@ -553,12 +554,15 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         int cursor = min(p.vfirst[ih], ncand);
         // columns before this row block's first row: every row of the block keeps them (no mask in their stages)
         const int nbefore = (my_rows && my_i0 >= 32) ? __builtin_amdgcn_readfirstlane(ncol[(my_i0 >> 5) - 1]) : 0;
-        // One round of the gather list: the next kGatherCap causal columns, copied as they are (ascending), padded to a whole
-        // stage.  Returns the number of columns; sets first to the list position of the round's start.
+        // One round of the gather list: the next kGatherCap causal columns, copied as they are (ascending), padded with
+        // INT_MAX to a whole stage.  Returns the number of columns; sets first to the list position of the round's start.
         int first = 0;
         auto gather_round = [&]() -> int {
             const int count = min(ncand - cursor, kGatherCap);
-            if (count > 0) fill_gather_list<kThreads>(tid, iv + cursor, count, (count + 63) & ~63, glist, last_tile);
+            for (int t = tid; t < count; t += kThreads) glist[t] = iv[cursor + t];
+            const int padded = (count + 63) & ~63;
+            for (int t = count + tid; t < padded; t += kThreads) glist[t] = INT_MAX;
+            last = last_column(iv + cursor, count, n_pos);
             first = cursor;
             cursor += count;
             __syncthreads();

@@ -237,14 +237,10 @@ __device__ __forceinline__ void finish_partials(const AttnParams& p, const unsig
         p.lse[static_cast<size_t>(head) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_tot * p.scale + __logf(l_tot) : -INFINITY;
 }
 
-// One round of a gather list in LDS: `count` columns from iv on, the last one repeated up to `padded`, so that what a tile loads besides
-// its columns is a row it has anyway (a weight of zero times a V that is not finite is NaN).  last_tile: the 32 entries of the last tile
-// as its mask sees them, INT_MAX behind the end.  All THREADS threads; count > 0.
-template <int THREADS>
-__device__ __forceinline__ void fill_gather_list(int tid, const int32_t* __restrict__ iv, int count, int padded, int* list, int* last_tile) {
-    for (int t = tid; t < padded; t += THREADS) list[t] = iv[min(t, count - 1)];
-    const int at = ((count - 1) & ~31) + tid;
-    if (tid < 32) last_tile[tid] = at < count ? iv[at] : INT_MAX;
+// What pads a round of the gather list (INT_MAX in LDS, masked) loads: the round's last column, a row that its tile has anyway (a weight of
+// zero times a V that is not finite is NaN).  The clamp keeps undefined lists inside the buffers.
+__device__ __forceinline__ int last_column(const int32_t* __restrict__ iv, int count, int n_pos) {
+    return count > 0 ? max(0, min(__builtin_amdgcn_readfirstlane(iv[count - 1]), n_pos - 1)) : 0;
 }
 
 // chunk: nq query rows at positions pos0 .. pos0 + nq - 1 against n keys

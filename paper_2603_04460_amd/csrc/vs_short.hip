@@ -18,6 +18,7 @@
 // vs_lone_kernel: sparse, one head, n = 4096, 68 scattered columns and 190 offsets 51.7 -> 30.4 us with the preparation (111 in
 // vs_attention.hip); dense, one head, 8192 x 8192 74 -> 45 us, 64 rows, 32 / 8 heads, against 32768 keys 280 -> 151 us.
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <math.h>
 #include <stdint.h>
 
@@ -35,7 +36,7 @@ constexpr int kRecPad = 2 * kStage;            // dead records after the last li
 constexpr size_t kRingBytes = 2 * kStage * kSlotBytes;
 constexpr size_t kRecOff = kRingBytes;
 constexpr size_t kGatherOff = kRecOff + (kListCap + 4 * kRecPad) * 16;
-constexpr size_t kSparseLds = kGatherOff + (kGatherCap + 32) * 4;
+constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4;
 static_assert(kPartialBytes + 8 * 4 <= kRingBytes, "partial results in the idle ring");
 static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % (32 * kStage) == 0, "whole stages");
@@ -179,7 +180,6 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
     unsigned char* const kvbuf = smem;
     uint4* const list_rec = reinterpret_cast<uint4*>(smem + kRecOff);
     int* const glist = reinterpret_cast<int*>(smem + kGatherOff);
-    int* const last_tile = glist + kGatherCap;
     const float NEG_INF = -INFINITY;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -312,7 +312,8 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
         while (cursor < ncand) {
             const int count = min(ncand - cursor, kGatherCap);
             const int padded = (count + 32 * kStage - 1) / (32 * kStage) * (32 * kStage);
-            fill_gather_list<kThreads>(tid, iv + cursor, count, padded, glist, last_tile);
+            for (int t = tid; t < padded; t += kThreads) glist[t] = t < count ? iv[cursor + t] : INT_MAX;
+            const int last = last_column(iv + cursor, count, n_pos);
             cursor += count;
             __syncthreads();
             const int ntiles = (count + 31) >> 5;
@@ -321,13 +322,12 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
                 ntiles,
                 [&](int st, int buf) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int u = 0; u < kStage; ++u) load_tile(glist[32 * (kStage * st + u) + st_row], kStage * buf + u);
+                    for (int u = 0; u < kStage; ++u) load_tile(min(glist[32 * (kStage * st + u) + st_row], last), kStage * buf + u);
                 },
                 [&](int t, int slot) __attribute__((always_inline)) {
-                    if (!my_rows || t >= ntiles) return;
-                    const int* const cols = t == ntiles - 1 ? last_tile : glist + 32 * t;
+                    const int* const cols = glist + 32 * t;
                     const int cmin = __builtin_amdgcn_readfirstlane(cols[0]), cmax = __builtin_amdgcn_readfirstlane(cols[31]);
-                    if (cmin > my_i0 + 31) return;                           // ascending
+                    if (!my_rows || cmin > my_i0 + 31) return;               // ascending, INT_MAX padding
                     ++tiles_done;
                     compute(slot, cmax > my_i0, [&]() __attribute__((always_inline)) { return causal_columns(cols + 4 * hh, my_i0 + qi); });
                 });
@@ -348,7 +348,7 @@ constexpr int kLone = kThreads / 64;           // wavefronts = tiles in flight
 constexpr size_t kLoneRing = kLone * kSlotBytes;
 constexpr size_t kLoneRecOff = kLoneRing;
 constexpr size_t kLoneGatherOff = kLoneRecOff + (kListCap + 1) * 16;
-constexpr size_t kLoneLds = kLoneGatherOff + (kGatherCap + 32) * 4;
+constexpr size_t kLoneLds = kLoneGatherOff + kGatherCap * 4;
 static_assert(kPartialBytes + 8 * 4 <= kLoneRing, "partial results in the idle buffers");
 static_assert(kLoneLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % 32 == 0, "whole tiles");
@@ -358,7 +358,6 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint4* const list_rec = reinterpret_cast<uint4*>(smem + kLoneRecOff);
     int* const glist = reinterpret_cast<int*>(smem + kLoneGatherOff);
-    int* const last_tile = glist + kGatherCap;
     const float NEG_INF = -INFINITY;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -450,8 +449,8 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
                 const int b = qb0 - dl[rbase + t];
                 list_rec[t] = tile_record(p.gran, n_pos, my_i0, b, wl[static_cast<size_t>(rbase + t) * 4], vbit[b]);
             }
-            if (count > 0) fill_gather_list<kThreads>(tid, iv + cursor, count, 32 * ng, glist, last_tile);
-            auto columns = [&](int t) __attribute__((always_inline)) { return t == nb + ng - 1 ? last_tile : glist + 32 * (t - nb); };
+            for (int t = tid; t < 32 * ng; t += kThreads) glist[t] = t < count ? iv[cursor + t] : INT_MAX;
+            const int last = last_column(iv + cursor, count, n_pos);
             cursor += count;
             staged_block += static_cast<unsigned int>(nb);
             staged_gather += static_cast<unsigned int>(ng);
@@ -464,7 +463,7 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
                     } else {
 #pragma unroll
                         for (int grp = 0; grp < 8; ++grp)
-                            off[grp] = static_cast<uint32_t>(min(glist[32 * (t - nb) + 4 * grp + st_rho], n_pos - 1)) << 8;
+                            off[grp] = static_cast<uint32_t>(min(glist[32 * (t - nb) + 4 * grp + st_rho], last)) << 8;
                     }
                 },
                 [&](int t) __attribute__((always_inline)) {
@@ -473,8 +472,8 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
                         const uint32_t fl = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(list_rec[t].w));
                         kind = fl & 1u ? ((fl & 2u) ? 2 : 1) : 0;
                     } else {
-                        // ascending; columns behind the row block are listed where a chunk starts inside a key block
-                        const int* const cols = columns(t);
+                        // ascending, INT_MAX padding; columns behind the row block are listed where a chunk starts inside a key block
+                        const int* const cols = glist + 32 * (t - nb);
                         const int cmin = __builtin_amdgcn_readfirstlane(cols[0]), cmax = __builtin_amdgcn_readfirstlane(cols[31]);
                         kind = cmin > my_i0 + 31 ? 0 : cmax > my_i0 ? 2 : 1;
                     }
@@ -487,7 +486,7 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
                         const uint64_t wz = (static_cast<uint64_t>(r.y) << 32) | r.x;
                         return static_cast<uint32_t>(wz >> (qi + 4 - 4 * hh)) & (__builtin_bitreverse32(r.z) >> (4 - 4 * hh));
                     }
-                    return causal_columns(columns(t) + 4 * hh, my_i0 + qi);
+                    return causal_columns(glist + 32 * (t - nb) + 4 * hh, my_i0 + qi);
                 });
             __syncthreads();                                 // the lists are reused
         }
