@@ -122,8 +122,8 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         }
     auto load_stage = [&](int st) __attribute__((always_inline)) {
         const int buf = st % 3;
-        if (2 * st + 1 < nblk && 64 * st + 63 < n_pos) {
-            // every row of the stage exists: uniform base + per-thread offset, no address arithmetic per load
+        if (64 * st + 63 <= i_last) {
+            // every row of the stage is the workgroup's: uniform base + per-thread offset, no address arithmetic per load
             const uint16_t* ks = kbase + static_cast<size_t>(64 * st) * kD;
             const uint16_t* vs_ = vbase + static_cast<size_t>(64 * st) * kD;
 #pragma unroll
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             for (int h = 0; h < 2; ++h) {
                 const int t = 2 * st + u;
                 int row = 32 * t + st_row + 16 * h;
-                if (t >= nblk || row >= n_pos) row = 0;      // masked anyway: no predicate on the load (every row has key 0)
+                if (row > i_last) row = 0;                   // masked anyway: no predicate on the load (every row has key 0)
                 unsigned char* dst = kvbuf + (2 * buf + u) * kSlotBytes + (wave + 4 * h) * kGroupBytes;
                 const size_t off = static_cast<size_t>(row) * kD;
                 lds_load16(kbase + off + st_ck * 8, dst);
