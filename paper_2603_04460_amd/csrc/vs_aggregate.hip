@@ -37,6 +37,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "vs_attn_device.h"
 #include "vs_common.h"
 
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     int t_end = COLUMNS ? (n + 31) >> 5 : (min(r0_wg + kRows, n) + 31) >> 5;
     int o_begin = 0;                                         // offset of the first streamed row to the first resident one
     if (PARTS) {
-        // whole stages per part, as equal as they come; sums over the parts are made with the output's atomics
+        // whole stages per part, as equal as they come; what the parts add up meets in the workspace
         const int part = unit % p.parts, stages = (t_end - t_begin + 1) >> 1;
         const int t0 = t_begin;
         t_begin = t0 + 2 * static_cast<int>(static_cast<long long>(stages) * part / p.parts);
@@ -237,6 +239,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     // ---- per-lane state ----
     float m_run[2] = {NEG_INF, NEG_INF}, l_run[2] = {0.f, 0.f};   // row sweep: running max (log2 domain) and sum of this lane's keys
     float col_sum[2] = {0.f, 0.f}, rec_sum = 0.f;                 // column sweep
+    double col_total[2] = {0., 0.};                               // PARTS: col_sum moves here every four stages (5e-8 off instead of 8e-8 at n = 3000, three parts)
     f32x16 pend;                                             // column sweep: block 0's entries of the previous tile
 #pragma unroll
     for (int e = 0; e < 16; ++e) pend[e] = 0.f;
@@ -413,6 +416,15 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         const int t0 = t_begin + 2 * st;
         tile_any(t0, 2 * (st & 1), w[0], w[1]);
         tile_any(t0 + 1, 2 * (st & 1) + 1, w[1], w[2]);
+        if constexpr (COLUMNS && PARTS) {
+            if ((st & 3) == 3) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    col_total[b] += static_cast<double>(col_sum[b]);
+                    col_sum[b] = 0.f;
+                }
+            }
+        }
     }
 
     // ---- results ----
@@ -456,13 +468,17 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         }
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            const float cs = half_swap_sum(col_sum[b]);
             const int key = my_r0 + 32 * b + qi;
-            if (key < n && hh == 0) {
-                const size_t at = static_cast<size_t>(out_head) * n + key;
-                if constexpr (PARTS) unsafeAtomicAdd(p.acc_v + at, static_cast<double>(cs));
-                else if (p.reduce_group) unsafeAtomicAdd(p.a_v + at, cs * p.norm);
-                else p.a_v[at] = cs * p.norm;
+            const size_t at = static_cast<size_t>(out_head) * n + key;
+            if constexpr (PARTS) {
+                // (both halves of the wavefront add)
+                if (key < n) unsafeAtomicAdd(p.acc_v + at, col_total[b] + static_cast<double>(col_sum[b]));
+            } else {
+                const float cs = half_swap_sum(col_sum[b]);
+                if (key < n && hh == 0) {
+                    if (p.reduce_group) unsafeAtomicAdd(p.a_v + at, cs * p.norm);
+                    else p.a_v[at] = cs * p.norm;
+                }
             }
         }
         if (RECALL) {
@@ -528,17 +544,19 @@ __global__ __launch_bounds__(kSetupThreads) void setup_kernel(const SetupParams 
 }
 
 // Up to 1024 groups of resident rows (512 workgroups run at once, and the longest sweep is twice the average): the streamed rows of a
-// group are shared out over several workgroups, 1024 in all, or two each, of at least four stages of two tiles; their column and diagonal sums
-// are added in fp64 (as float atomics the sums of more, shorter parts were up to twice as far off).  us per call: one head, n = 4000
-// (16 groups) 73 -> 33, 16000 (63) 284 -> 127; 8 / 2 heads, n = 1500 (48) 53 -> 40, 5000 (160) 277 -> 101, 8000 (256) 425 -> 190, 16000 (504)
-// 785 -> 613; 32 / 8 heads, n = 1000 (128) 48 -> 44, 2000 (256) 125 -> 85, 4000 (512) 235 -> 199, 8192 (1024) 673 -> 643, 12000 (1504, not
-// shared) 1288.  (Before: the column sweep of up to 128 groups shared out, the row sweep in workgroups of 128 rows.)  2048 workgroups, float
-// sums: 164 at one head, n = 16000, 128 at 8 / 2 x 5000, 580 at 16000.
+// group are shared out over several workgroups of at least four stages of two tiles; their column and diagonal sums are added in fp64 (as
+// float atomics the sums of more, shorter parts were up to twice as far off).  About 600 workgroups in all, up to 1024 where a part still has
+// sixteen stages: a part has an end of its own (up to 319 offsets and 256 columns to add, the recall's share), and the workgroups wait for
+// each other's.  us per call with recall, not shared / shared, and with how many parts: one head, n = 4000 (16 groups, 63 stages) 217 / 38 (16), 8000
+// (32, 125) 414 / 57 (16; with 32 79), 16000 (63, 250) 802 / 119 (12; 16 121); 4 heads, n = 3192 (52, 50) 178 / 54 (11; 13 57); 8 / 2 heads, n = 2867
+// (96, 45) 161 / 52 (6; 10 62), 5000 (160, 79) 270 / 98 (4; 3 118), 8000 (256, 125) 423 / 192 (4; 2 249); 32 / 8 heads, n = 1000 (128, 16) 67 / 39 (4),
+// 1500 (192, 24) 94 / 57 (3; 5 64), 4000 (512, 63) 234 / 196 (2), 8192 (1024, 128) 663 / 642 (2); 64 / 8 heads, n = 1400 (384, 22) 91 / 80 (2),
+// 2837 (768, 45) 194 / 218 (2; the fp64 sums are worth it, 7.6e-8 off instead of 1.25e-7).
 int sweep_parts(int q_heads, int64_t n) {
-    const int64_t groups = static_cast<int64_t>(q_heads) * ((n + kGroupRows - 1) / kGroupRows);
+    const int64_t groups = static_cast<int64_t>(q_heads) * ((n + kGroupRows - 1) / kGroupRows), stages = (n + 63) / 64;
     if (groups > 1024) return 1;
-    const int64_t max_parts = ((n + 63) / 64 + 3) / 4, parts = groups > 512 ? 2 : 1024 / groups;
-    return static_cast<int>(parts < max_parts ? parts : max_parts);
+    const int64_t parts = std::max<int64_t>({2, 600 / groups, std::min(1024 / groups, stages / 16)});
+    return static_cast<int>(std::min(parts, (stages + 3) / 4));
 }
 
 struct AggWs {

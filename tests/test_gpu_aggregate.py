@@ -105,8 +105,8 @@ def test_aggregate_many_groups(hq, hk, n):
 
 @pytest.mark.parametrize("pairs,n", [(103, 1100), (129, 900), (52, 1500), (26, 1500), (85, 1025)])
 def test_aggregate_group_sharing(pairs, n):
-    """One workgroup per group of 256 resident rows (more than 1024 groups: 206 x 5, 258 x 4), two (624; 850, with a last group of one row) and
-    three (312), with a recall, per query head and as the mean over a KV group: two query heads of one KV head, repeated."""
+    """One workgroup per group of 256 resident rows (more than 1024 groups: 206 x 5, 258 x 4) and two (624; 850, with a last group
+    of one row; 312), with a recall, per query head and as the mean over a KV group: two query heads of one KV head, repeated."""
     groups = 2 * pairs * -(-n // 256)
     assert (groups > 1024) == (pairs in (103, 129)) and (512 < groups <= 1024) == (pairs in (52, 85))
     rng = np.random.default_rng(n)
@@ -123,6 +123,33 @@ def test_aggregate_group_sharing(pairs, n):
     a_v, a_s, _ = _run(qr, kr, pairs)
     _close(a_v, np.repeat(ref_v.mean(0, keepdims=True), pairs, 0))
     _close(a_s, np.repeat(ref_s.mean(0, keepdims=True), pairs, 0))
+
+
+def _parts(hq, n):
+    """Workgroups that share the streamed rows of a group of 256 resident rows, as the library has it."""
+    groups, stages = hq * -(-n // 256), -(-n // 64)
+    if groups > 1024:
+        return 1
+    return min(max(2, 600 // groups, min(1024 // groups, stages // 16)), (stages + 3) // 4)
+
+
+@pytest.mark.parametrize("hq,n,parts", [(34, 4100, 2), (40, 2000, 2), (12, 2500, 5), (5, 1300, 6), (3, 6200, 8), (1, 4097, 17)])
+def test_aggregate_parts(hq, n, parts):
+    """Two workgroups to each of 578 groups, and both sides of the rule for fewer; one query head and KV head, repeated."""
+    assert parts == _parts(hq, n)
+    words = lambda index_heads: vs.aggregate_workspace(hq, hq, index_heads, n)
+    assert words(0) >= hq * n * (4 + 16 + 8 * parts)         # row normalisers, fp64 sums, a row sweep's partial results
+    assert words(0) < hq * n * (4 + 16 + 8 * parts) + 1024
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = make_qkv(590 + n, 1, 1, n, local=True)
+    iv, cv = lists([rng.choice(n, size=n // 10, replace=False)])
+    is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=n // 20, replace=False)]))])
+    ref_v, ref_s, ref_r = _oracle(qb, kb, 1, mask=(iv, cv, is_, cs))
+    qr, kr = q.repeat(hq, 1, 1).contiguous(), k.repeat(hq, 1, 1).contiguous()
+    a_v, a_s, rec = _run(qr, kr, hq, mask=(np.repeat(iv, hq, 0), np.repeat(cv, hq), np.repeat(is_, hq, 0), np.repeat(cs, hq)))
+    _close(a_v, np.repeat(ref_v, hq, 0))
+    _close(a_s, np.repeat(ref_s, hq, 0))
+    assert np.abs(rec - ref_r).max() <= RECALL_ABS
 
 
 @pytest.mark.parametrize("hq,hk,n", [(1, 1, 127), (3, 1, 128), (4, 2, 129), (1, 1, 200), (8, 2, 255), (3, 3, 256)])
@@ -147,7 +174,7 @@ def test_aggregate_last_key_nan(n):
 
 
 def test_aggregate_8192_one_head_elementwise():
-    """n = 8192, one head: 32 groups of resident keys, the streamed rows of each shared out over 16 workgroups (up to 8 stages
+    """n = 8192, one head: 32 groups of resident keys, the streamed rows of each shared out over 18 workgroups (up to 8 stages
     each); every element is compared, together with the recall of a mask."""
     hq, hk, n = 1, 1, 8192
     rng = np.random.default_rng(8192)
