@@ -896,7 +896,13 @@ int sparse_prefill_on(unsigned char* base, const SparseWs& w, const void* q, con
     // 1500 rows of 50000 97 and 116.
     // Smaller ones only as short chunks of longer sequences, and the longer the lists the more units: 32 / 8 heads, 8192 keys, capacities
     // of 100 / 260 / 388 / 580 / 2116 in all, 96 rows 21 / 27 / 32 / 34 / 66 us here, 18 / 18 / 17 / 18 / 25 there, 256 rows (64 units) 20 / 27 / 33 / 34 / 65 and
-    // 17 / 17 / 17 / 18 / 27.  (The condition on the capacities is from the time when two row blocks shared a workgroup there; it is on the safe side.)
+    // 17 / 17 / 17 / 18 / 27.
+    // Calls that these lines leave here although they would be faster there (1, 2 and 4 row blocks in a workgroup): several query heads and short
+    // lists, where the condition on the capacities is from the time when two row blocks shared a workgroup, 32 / 8 heads, 256 rows of 2048 keys, 16 +
+    // 32 25 and 15 / 18 / 22, 16 / 4 heads, 500 rows 23 and 15 / 17 / 21; 257 to 512 row blocks of less than 4096 keys, 32 / 8 heads, 500 rows of 3000 keys 26 and
+    // 25 / 20 / 23, 400 + 400 42 and 33 / 28 / 36; whole sequences of less than 1000 rows, 8 / 2 x 700, 32 + 64 21 and 18 / 16 / 19 (but 32 / 8 x 200 19 and 19 / 17 /
+    // 16); one query head, 129 to 320 units, less than 1000 rows: 40 x 500, 60 + 100 44 and 39 / 28 / 23, 64 x 640 68 and 63 / 48 / 33, 128 x 200 84 and 47 / 34 / 26,
+    // 20 x 900 37 and 29 / 26 / 28, 40 heads, 500 rows of 4096 keys, 64 + 128 70 and 39 / 41 / 37.
     const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((nq * p.hc + 127) / 128);
     const int64_t row_blocks = static_cast<int64_t>(q_heads) * ((nq + 31) / 32);
     const int64_t capacity = static_cast<int64_t>(cap_v) + cap_s;

@@ -62,6 +62,39 @@ def sparse_is_short(hq, hk, n_q, n, capacity, per_q=False):
     return units <= line // 2 and n >= 4 * n_q and n >= 2048 and capacity >= 10 * (units - (28 if hc == 4 else 44))
 
 
+def _number(source, name):
+    return int(re.search(r"constexpr int %s = (\d+);" % name, open(os.path.join(CSRC, source)).read()).group(1))
+
+
+def dense_form(hq, hk, n_q, n, pos0=0):
+    """Which dense kernel a call takes: "long", "duo" (two row blocks per wavefront, keys split), "short" (two row blocks in a workgroup) or
+    "lone" (one)."""
+    blocks, last = -(-n_q // 32), -(-(pos0 + n_q) // 32)
+    keys = _number("vs_dense.hip", "kDuoKeys")
+    if dense_is_short(hq, hk, n_q, n):
+        if hq * blocks <= _number("vs_attn_device.h", "kLoneBlocks"):
+            return "lone"
+        return "duo" if n >= keys else "short"
+    work = hq * (blocks * (last - blocks) + blocks * (blocks + 1) // 2)
+    a, b, c, d = (float(x) for x in re.search(r"return ([\d.]+) \* static_cast<double>\(work\) / 1024.0 \+ ([\d.]+) \* static_cast<double>\(rounds\) <\s+"
+                                              r"([\d.]+) \* ([\d.]+) \* static_cast<double>", open(os.path.join(CSRC, "vs_dense.hip")).read()).groups())
+    rounds = (hq * blocks // 2 + 255) // 256
+    return "duo" if n >= keys and a * work / 1024.0 + b * rounds < c * d * max(last, work // 2048) else "long"
+
+
+def sparse_rows(hq, hk, n_q, n, capacity, per_q=False):
+    """Row blocks that share a workgroup of a sparse call (four in the kernel for many row blocks, too)."""
+    if not sparse_is_short(hq, hk, n_q, n, capacity, per_q):
+        return 4
+    blocks, line = hq * -(-n_q // 32), _short_units("vs_attention.hip")
+    if blocks <= _number("vs_attn_device.h", "kLoneBlocks"):
+        return 1
+    hc = _heads_per_workgroup(hq, hk, per_q)
+    if hc == 1:
+        return 2 if hq * -(-n_q // 128) <= 2 * line else 4
+    return 2 if blocks <= 4 * line else 4
+
+
 def run_sparse(q, k, v, idx_v, cnt_v, idx_s, cnt_s, want_lse=True, granularity=None):
     hq, n, _ = q.shape
     hk = k.shape[0]

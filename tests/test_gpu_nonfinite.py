@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2603_04460_amd as vs
 import synth
-from gpu_util import make_qkv, check_attention, dense_is_short, lists
+from gpu_util import make_qkv, check_attention, dense_form, lists
 
 pytestmark = pytest.mark.gpu
 
@@ -30,18 +30,18 @@ def _sample(rows, count=120):
     return rows if len(rows) <= count else np.unique(np.concatenate([rows[:8], rows[-72:], rows[::len(rows) // 40]]))
 
 
-@pytest.mark.parametrize("hq,hk,n,pos0,n_q,bad,short", [
-    (8, 8, 2048, 0, 2048, 740, True),                        # 64 rows of a head in a workgroup: behind the workgroup's last tile
-    (8, 8, 2048, 0, 2048, 672, True),                        # the second row block's own tile
-    (32, 8, 4096, 2048, 480, 2528, True),                    # two heads of a group; a chunk with keys behind it
-    (18, 9, 2304, 1561, 455, 2016, True),
-    (24, 24, 2048, 0, 2048, 1111, False),                    # about one round of workgroups
-    (8, 2, 6001, 0, 6001, 3456, False),
-    (32, 8, 5000, 3700, 1290, 4992, False),
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q,bad", [
+    (8, 8, 2048, 0, 2048, 740),                              # 64 rows of a head in a workgroup: behind the workgroup's last tile
+    (8, 8, 2048, 0, 2048, 672),                              # the second row block's own tile
+    (32, 8, 4096, 2048, 480, 2528),                          # two heads of a group; a chunk with keys behind it
+    (18, 9, 2304, 1561, 455, 2016),
+    (24, 24, 2048, 0, 2048, 1111),                           # about one round of workgroups
+    (8, 2, 6001, 0, 6001, 3456),
+    (32, 8, 5000, 3700, 1290, 4992),
 ])
-def test_dense_two_row_blocks_later_keys(hq, hk, n, pos0, n_q, bad, short):
+def test_dense_two_row_blocks_later_keys(hq, hk, n, pos0, n_q, bad):
     """The dense form whose wavefronts own two row blocks and whose stages go past the last tile of either."""
-    assert dense_is_short(hq, hk, n_q, n) == short and hq * -(-n_q // 32) > 256 and n >= 2048
+    assert dense_form(hq, hk, n_q, n, pos0) == "duo"
     (q, k, v), (qb, kb, vb) = make_qkv(3000 + bad, hq, hk, n)
     kx, vx = _spoilt(k, v, bad)
     qc = q[:, pos0:pos0 + n_q].contiguous()

@@ -10,7 +10,7 @@ import oracle
 import paper_2603_04460_amd as vs
 import synth
 from gpu_util import (make_qkv, lists, run_sparse, run_dense, check_attention, check_key_set, dense_is_short,
-                      sparse_is_short)
+                      sparse_is_short, dense_form, sparse_rows)
 
 pytestmark = pytest.mark.gpu
 
@@ -223,7 +223,7 @@ def test_sparse_two_row_blocks(hq, hk, n, per_q, gran):
     ih = hq if per_q else hk
     iv, cv = lists([rng.choice(n, size=3 + 40 * (h % 2), replace=False) for h in range(ih)], cap=60)
     is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=2 + 30 * (h % 3), replace=False)])) for h in range(ih)], cap=70)
-    assert sparse_is_short(hq, hk, n, n, 130, per_q)
+    assert sparse_is_short(hq, hk, n, n, 130, per_q) and sparse_rows(hq, hk, n, n, 130, per_q) == 2
     rows = synth.sample_rows(4, n, 40, 40, 60)
     if not per_q:
         check_key_set(k, iv, cv, is_, cs, hq, rows, granularity=gran)
@@ -236,6 +236,7 @@ def test_sparse_two_row_blocks(hq, hk, n, per_q, gran):
 def test_dense_around_the_line_of_row_blocks(hq, hk, n):
     """256 row blocks (one to a workgroup) and a few more (two: two heads, or 64 rows of one head)."""
     assert dense_is_short(hq, hk, n, n) and abs(hq * -(-n // 32) - 256) <= 14
+    assert dense_form(hq, hk, n, n) == ("lone" if hq * -(-n // 32) <= 256 else "short")
     (q, k, v), (qb, kb, vb) = make_qkv(1600 + n, hq, hk, n)
     o, lse = run_dense(q, k, v)
     rows = synth.sample_rows(5, n, 40, 40, 60)
@@ -253,6 +254,7 @@ def test_sparse_lone_row_blocks_several_rounds(hq, hk, n, n_q, gran):
     pos0 = n - n_q
     iv, cv = lists([rng.choice(n, size=5000 if h == 0 else 40, replace=False) for h in range(hk)])
     is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=1500 if hq < 4 else 20, replace=False)])) for _ in range(hk)])
+    assert sparse_rows(hq, hk, n_q, n, iv.shape[1] + is_.shape[1]) == 1
     assert sparse_is_short(hq, hk, n_q, n, iv.shape[1] + is_.shape[1])
     f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
     qc = q[:, pos0:].contiguous()
@@ -274,7 +276,7 @@ def test_sparse_lone_row_blocks_several_rounds(hq, hk, n, n_q, gran):
 ])
 def test_dense_two_row_blocks_per_wavefront(hq, hk, n_q, n, pos0):
     """More than 256 row blocks, at most 128 workgroups of the long form, at least 2048 keys."""
-    assert hq * -(-n_q // 32) > 256 and dense_is_short(hq, hk, n_q, n)
+    assert hq * -(-n_q // 32) > 256 and dense_is_short(hq, hk, n_q, n) and dense_form(hq, hk, n_q, n, pos0) == "duo"
     (q, k, v), (qb, kb, vb) = make_qkv(1800 + n_q, hq, hk, n)
     qc = q[:, pos0:pos0 + n_q].contiguous()
     o = torch.full_like(qc, float("nan"))
@@ -292,6 +294,7 @@ def test_dense_about_one_round_of_workgroups(hq, hk, n, pos0, n_q):
     """More than 128 workgroups of the long form, at least 2048 keys: spread over two-row-block workgroups where the longest workgroup
     would be all that runs in the end, or not."""
     assert not dense_is_short(hq, hk, n_q, n)
+    assert dense_form(hq, hk, n_q, n, pos0) == ("long" if (hq, n) in ((32, 2048), (32, 2100)) else "duo")
     (q, k, v), (qb, kb, vb) = make_qkv(1900 + n, hq, hk, n)
     qc = q[:, pos0:pos0 + n_q].contiguous()
     o = torch.full_like(qc, float("nan"))
@@ -323,6 +326,9 @@ def test_sparse_few_row_blocks(hq, hk, n, n_q, per_q, gran):
     iv, cv = lists([rng.choice(n, size=5 + 60 * (h % 3), replace=False) for h in range(heads)], cap=130)
     is_, cs = lists([np.unique(np.concatenate([[0], rng.choice(n, size=3 + 40 * (h % 2), replace=False)])) for h in range(heads)], cap=70)
     assert sparse_is_short(hq, hk, n_q, n, 200, per_q) == ((hq, n) not in ((8, 4128), (33, 1190)))
+    blocks, units = hq * -(-n_q // 32), hq * -(-n_q // 128)
+    alone = per_q or hq == hk
+    assert sparse_rows(hq, hk, n_q, n, 200, per_q) == (2 if (units <= 256 if alone else blocks <= 512) else 4)
     f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
     qc = q[:, pos0:].contiguous()
     o = torch.full_like(qc, float("nan"))
@@ -336,3 +342,19 @@ def test_sparse_few_row_blocks(hq, hk, n, n_q, per_q, gran):
     check_attention(o, lse, ref_o, ref_lse, rows=rows)
     if not per_q and not pos0:
         check_key_set(k, iv, cv, is_, cs, hq, rows, granularity=gran)
+
+
+@pytest.mark.parametrize("hq,hk,n,rows", [
+    (8, 2, 1024, 1), (4, 4, 2048, 1), (8, 2, 1056, 2), (9, 9, 929, 2), (8, 8, 4096, 2), (8, 2, 2080, 4), (10, 10, 4096, 4), (33, 33, 1190, 4), (8, 2, 700, 4),
+])
+def test_sparse_workgroup_that_ran(hq, hk, n, rows):
+    """The form that ran, from what it staged: column 0 is one gathered tile per workgroup, whose row blocks are `rows`."""
+    (q, k, v), _ = make_qkv(2200 + n, hq, hk, n, rope=False)
+    zero, one = torch.zeros((hk, 4), dtype=torch.int32, device="cuda"), torch.ones(hk, dtype=torch.int32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, hk, n), dtype=torch.uint8, device="cuda")
+    vs.sparse_prefill(q, k, v, zero, one, zero, one, torch.empty_like(q), None, ws)
+    _, gathered, _ = vs.sparse_prefill_counters(ws)
+    assert sparse_rows(hq, hk, n, n, 8) == rows
+    group = hq // hk
+    hc = min(rows, 4 if group % 4 == 0 else 2 if group % 2 == 0 else 1)
+    assert gathered == hq // hc * -(-n // (32 * rows // hc))
