@@ -19,6 +19,7 @@ struct AttnParams {
     uint16_t* o;
     float* lse;
     int q_heads, kv_heads, group, hc, n, tiles, index_per_q;   // n: keys per head
+    int kv_rows;                    // vs_dense_kernel: rows of k and v per head (n: those up to the last position)
     int nq, pos0;                   // query rows per head; row r is position pos0 + r (pos0 + nq <= n)
     int gran;                       // slash granularity: 1 (element-exact) or 32 (per 32-row block)
     float scale, c;                 // c = scale * log2(e)

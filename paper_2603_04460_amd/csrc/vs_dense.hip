@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     const int tile = p.tiles - 1 - rest / hchunks;          // longest tiles first
     const int BQ = (DUO ? 64 : 256) / p.hc;
     const int i0 = p.pos0 + tile * BQ;                      // positions are absolute; the tile grid starts at the chunk
-    const int n = p.n;                                      // keys
+    const int n = p.n;                                      // keys up to the last position (those behind it are not read)
     const int n_pos = p.pos0 + p.nq;                        // positions that exist
     const int i_last = min(i0 + BQ, n_pos) - 1;
 
@@ -75,8 +75,8 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         my_i0[rb] = i0 + 32 * (w / p.hc);
         my_rows[rb] = my_i0[rb] < n_pos;
     }
-    const uint16_t* __restrict__ kbase = p.k + static_cast<size_t>(g) * n * kD;
-    const uint16_t* __restrict__ vbase = p.v + static_cast<size_t>(g) * n * kD;
+    const uint16_t* __restrict__ kbase = p.k + static_cast<size_t>(g) * p.kv_rows * kD;
+    const uint16_t* __restrict__ vbase = p.v + static_cast<size_t>(g) * p.kv_rows * kD;
 
     bf16x8 qf[2][8];
 #pragma unroll
@@ -122,8 +122,8 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         }
     auto load_stage = [&](int st) __attribute__((always_inline)) {
         const int buf = st % 3;
-        if (64 * st + 63 <= i_last) {
-            // every row of the stage is the workgroup's: uniform base + per-thread offset, no address arithmetic per load
+        if (2 * st + 1 < nblk && 64 * st + 63 < n) {
+            // every row of the stage exists: uniform base + per-thread offset, no address arithmetic per load
             const uint16_t* ks = kbase + static_cast<size_t>(64 * st) * kD;
             const uint16_t* vs_ = vbase + static_cast<size_t>(64 * st) * kD;
 #pragma unroll
@@ -142,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             for (int h = 0; h < 2; ++h) {
                 const int t = 2 * st + u;
                 int row = 32 * t + st_row + 16 * h;
-                if (row > i_last) row = 0;                   // masked anyway: no predicate on the load (every row has key 0)
+                if (t >= nblk || row >= n) row = 0;          // masked anyway: no predicate on the load (every row has key 0)
                 unsigned char* dst = kvbuf + (2 * buf + u) * kSlotBytes + (wave + 4 * h) * kGroupBytes;
                 const size_t off = static_cast<size_t>(row) * kD;
                 lds_load16(kbase + off + st_ck * 8, dst);
@@ -473,6 +473,8 @@ int launch_dense(AttnParams& p, hipStream_t stream) {
         return VS_OK;
     });
     if (rc_once != VS_OK) return rc_once;
+    p.kv_rows = p.n;
+    p.n = p.pos0 + p.nq;
     const int BQ = (DUO ? 64 : 256) / p.hc;
     p.tiles = (p.nq + BQ - 1) / BQ;
     // one workgroup per (query tile, KV head, chunk of the group's heads), longest tiles first; workgroups are dealt
