@@ -560,7 +560,7 @@ int sweep_parts(int q_heads, int64_t n) {
 }
 
 struct AggWs {
-    size_t lse_off, sbit_off, vbit_off, acc_off, count_off, sums_off, clear_end, row_off, total;
+    size_t lse_off, sbit_off, vbit_off, acc_off, count_off, sums_off, row_off, total;
     int sw, vw;
 };
 
@@ -577,8 +577,7 @@ AggWs agg_ws_layout(int q_heads, int index_heads, int64_t n) {
     w.sums_off = vs::round_up(w.count_off + (index_heads > 0 ? static_cast<size_t>(q_heads) * 4 : 0), 256);
     const int parts = sweep_parts(q_heads, n);
     // shared-out sweeps: fp64 sums of a_v and a_s (zeroed as well), the row sweep's partial results
-    w.clear_end = w.sums_off + (parts > 1 ? vs::round_up(2 * static_cast<size_t>(q_heads) * n * sizeof(double), 256) : 0);
-    w.row_off = w.clear_end;
+    w.row_off = w.sums_off + (parts > 1 ? vs::round_up(2 * static_cast<size_t>(q_heads) * n * sizeof(double), 256) : 0);
     w.total = w.row_off + (parts > 1 ? vs::round_up(static_cast<size_t>(parts) * q_heads * n * sizeof(float2), 256) : 0);
     return w;
 }

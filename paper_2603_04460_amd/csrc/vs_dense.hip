@@ -487,7 +487,8 @@ int launch_dense(AttnParams& p, hipStream_t stream) {
 }
 
 // More workgroups of the long form than that, but about one round of them or less: the call then takes as long as its longest workgroup,
-// while the two-row-block form spreads the same work evenly, at a higher price per tile and per workgroup.  Long form: 0.93 us per tile
+// while the two-row-block form spreads the same work evenly, at a higher price per tile and per workgroup.  An estimate for the whole card
+// (256 compute units at the 1.8 to 2 GHz that it holds under these kernels); a card cut into partitions would want other numbers.  Long form: 0.93 us per tile
 // of the longest workgroup, or of the average over 256 compute units where that is more; DUO: 0.55 us per tile and row block of a SIMD and 7 us
 // per round of workgroups.  Here / there, us: 24 x 2048 (192 workgroups) 57 / 46, 16 x 4096 (256) 103 / 91, 8 / 2 x 6000 (188) 139 / 95, x 8192 (256)
 // 191 / 154, x 10000 (314) 301 / 232, 1 x 40000 (157) 1134 / 439, 32 / 8, 1500 rows of 8192 (188) 237 / 196, of 32768 927 / 776, 1100 of 32768

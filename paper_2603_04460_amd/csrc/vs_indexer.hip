@@ -115,8 +115,8 @@ __global__ __launch_bounds__(kThreads) void indexer_logits_kernel(const IndexerP
 
     // tiles of tokens, never across heads; workgroup b takes tiles b, b + gridDim.x, ...
     const long long total_tiles = static_cast<long long>(p.heads) * p.tiles_per_head;
-    // Staging: a wavefront instruction deposits 1 KB = two token rows; wavefront w moves rows 16 w .. 16 w + 15 of a tile
-    // with eight instructions.  Lane L fills chunk position L % 32 of its row, i.e. it fetches that row's chunk
+    // Staging: a wavefront instruction deposits 1 KB = two token rows; wavefront w moves an eighth of a tile's rows, 16 with
+    // eight instructions or 8 with four.  Lane L fills chunk position L % 32 of its row, i.e. it fetches that row's chunk
     // (L % 32) ^ (row % 16) (chunks 0-15: K, 16-31: V).
     const int st_pos = lane & 31;
     auto load_tile = [&](long long t, int buf) __attribute__((always_inline)) {

@@ -168,8 +168,8 @@ def test_select_threshold_above_rounded_total():
 
 @pytest.mark.parametrize("n", [1, 63, 8192, 8193, 32767, 40961, 131072, 140001])
 def test_select_crowded_scores(n):
-    """Scores that crowd into one bucket of the first digit: all equal, within a few percent of each other (at the longest sizes more
-    candidates than the list holds), two values, a wide spread with values above one (the last bucket has 30 bits below it);
+    """Scores that crowd into one bucket of the first digit: all equal, within a few percent of each other, two values, a wide
+    spread with values above one (the last bucket of the single workgroup has 30 bits below it);
     both rules; registers and batches of one workgroup, ragged and many chunks."""
     rng = np.random.default_rng(n)
     equal = np.full(n, 1.0 / n, dtype=np.float32)
