@@ -244,8 +244,8 @@ size_t vs_aggregate_workspace(int q_heads, int kv_heads, int index_heads, int64_
  *               recall[.] = (1/n) sum over kept (i, j), j <= i, of A[i, j].  When NULL the list arguments are ignored.
  * Arithmetic: bf16 MFMA for Q K^T with fp32 accumulation, fp32 exponentials and sums.
  * Workspace from vs_aggregate_workspace (index_heads = 0 when no recall is wanted); errors as for the other calls.  Per query head
- * and position it is 4 bytes, and up to 1024 groups of 256 positions (q_heads x ceil(n / 256), n > 256) 20 and 8 for each of the
- * workgroups that then share a group's work: the size does not grow evenly with n, and is asked for every shape.
+ * and position a call needs 4 bytes, and up to 1024 groups of 256 positions (q_heads x ceil(n / 256), n > 256) 20 and 8 for each of
+ * the workgroups that then share a group's work, 10 MB at most; the answer for n is enough for shorter sequences of the same heads, too.
  */
 int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_t n, float scale, const float* lse,
                  int out_heads, float* a_v, float* a_s, const int32_t* idx_v, const int32_t* cnt_v, int cap_v,

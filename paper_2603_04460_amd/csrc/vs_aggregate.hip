@@ -588,7 +588,12 @@ extern "C" {
 
 size_t vs_aggregate_workspace(int q_heads, int kv_heads, int index_heads, int64_t n) {
     if (q_heads <= 0 || kv_heads <= 0 || index_heads < 0 || n <= 0 || n > VS_MAX_SEQ) return 0;
-    return agg_ws_layout(q_heads, index_heads, n).total;
+    // A workspace that is enough for n is enough for shorter sequences, also for those whose sweeps are shared out where those of n are not:
+    // the largest of them, at the lengths where the number of parts can change.
+    size_t most = agg_ws_layout(q_heads, index_heads, n).total;
+    for (int64_t m = 64; m < n && q_heads * ((m + kGroupRows - 1) / kGroupRows) <= 1024; m += 64)
+        most = std::max(most, agg_ws_layout(q_heads, index_heads, m).total);
+    return most;
 }
 
 int vs_aggregate(const void* q, const void* k, int q_heads, int kv_heads, int64_t n, float scale, const float* lse,

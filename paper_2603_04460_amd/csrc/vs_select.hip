@@ -684,7 +684,7 @@ __global__ __launch_bounds__(kSelThreads) void clear_kernel(ProblemWs* problem, 
 }
 
 struct SplitLayout {
-    size_t state, chunk, total;
+    size_t state, chunk, total, size;      // total: what a call uses; size: what the query says
     int chunks, chunk_size;
 };
 
@@ -706,9 +706,11 @@ SplitLayout split_layout(int heads, int64_t n) {
     w.state = pr * sizeof(ProblemWs);
     w.chunk = vs::round_up(w.state + pr * sizeof(ProblemState), 256);
     w.total = w.chunk + pr * w.chunks * sizeof(ChunkWs);
-    // never less than what the query gave when it was three histograms of 4096 entries to a problem
-    const size_t former = vs::round_up(pr * (3 * 4096 * 12 + 4), 256) + vs::round_up(pr * 192, 256) + vs::round_up(pr * ((n + kChunk - 1) / kChunk) * 12, 256);
-    if (w.total < former) w.total = former;
+    // The query's answer grows with n (a workspace for n does for shorter problems) and is never less than when a problem had three
+    // histograms of 4096 entries.
+    const int64_t short_chunks = (n + kChunk - 1) / kChunk;
+    const size_t former = vs::round_up(pr * (3 * 4096 * 12 + 4), 256) + vs::round_up(pr * 192, 256) + vs::round_up(pr * short_chunks * 12, 256);
+    w.size = std::max(former, w.chunk + pr * std::min<int64_t>(kMaxChunks, short_chunks) * sizeof(ChunkWs));
     return w;
 }
 
@@ -723,7 +725,7 @@ extern "C" {
 
 size_t vs_select_budget_workspace(int heads, int64_t n) {
     if (heads <= 0 || n < kMinSplitN || n > VS_MAX_SEQ) return 0;   // one workgroup per problem: everything lives in LDS
-    return split_layout(heads, n).total;
+    return split_layout(heads, n).size;
 }
 
 int vs_select_budget(const float* a_v, const float* a_s, int heads, int64_t n, const vs_budget_t* b, int32_t* idx_v,

@@ -47,6 +47,18 @@ def test_strerror_and_workspace_queries():
     assert vs.select_budget_workspace(8, 131072) == 3 * 16 * 4096 * 12 + 256 + 16 * 4 * 48 + 16 * 16 * 3 * 4
 
 
+@pytest.mark.parametrize("heads", [1, 2, 5, 8, 24, 32, 64, 300])
+def test_workspaces_for_the_longest_sequence(heads):
+    """A workspace that a program holds for its longest sequence is enough for every shorter one: no query's answer falls."""
+    lengths = sorted({n + d for n in [1 << i for i in range(21)] + [256 * (1024 // heads), 300, 600, 1300, 5000, 8448, 12000, 40000, 200000, 342475, 524289, 600000]
+                      for d in (-64, -1, 0, 1, 64, 300) if 0 < n + d <= 1 << 20})
+    for query in (lambda n: vs.aggregate_workspace(heads, heads, 0, n), lambda n: vs.aggregate_workspace(heads, heads, heads, n),
+                  lambda n: vs.select_budget_workspace(heads, n), lambda n: vs.sparse_prefill_workspace(heads, heads, heads, n),
+                  lambda n: vs.index_score_workspace(heads, n, 1024), lambda n: vs.index_train_workspace(heads, n, 256)):
+        sizes = [query(n) for n in lengths]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), [(n, s) for n, s in zip(lengths, sizes)]
+
+
 def test_host_side_argument_checks():
     L = binding._load()
     buf = (ctypes.c_char * 4096)()

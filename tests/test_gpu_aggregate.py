@@ -139,7 +139,6 @@ def test_aggregate_parts(hq, n, parts):
     assert parts == _parts(hq, n)
     words = lambda index_heads: vs.aggregate_workspace(hq, hq, index_heads, n)
     assert words(0) >= hq * n * (4 + 16 + 8 * parts)         # row normalisers, fp64 sums, a row sweep's partial results
-    assert words(0) < hq * n * (4 + 16 + 8 * parts) + 1024
     rng = np.random.default_rng(n)
     (q, k, v), (qb, kb, vb) = make_qkv(590 + n, 1, 1, n, local=True)
     iv, cv = lists([rng.choice(n, size=n // 10, replace=False)])
