@@ -184,6 +184,26 @@ __device__ __forceinline__ void lds_load16s(uint32_t voff, const void* sbase, co
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(base), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
+// ---- stages without a row maximum ----
+// Most stages of a long row block take the maximum as it stands after its first stages instead of looking for a new one: any
+// value serves as long as nothing overflows or vanishes, and the precision of P, O and the sum is relative.  Scores below it lose
+// what they lost before; scores above it make P, O and the sum larger than with a maximum that follows (where P stays below
+// 2^kRescaleThreshold).  At the end of a row block this says whether a row has left the safe range, in which case the row
+// block is computed again with a maximum in every stage.  Sums up to 2^28 (2^20 keys at the threshold) were possible before; up to
+// 2^kOutgrown the reciprocal and the logarithm are good, and O is if it is finite.  Sums that are not numbers count as outgrown.
+constexpr float kSafeSum = 268435456.f;        // 2^28
+constexpr float kOutgrownSum = 1.152921504606847e18f;   // 2^60
+__device__ __forceinline__ bool outgrown(const f32x16 (&oacc)[4], float l_run) {
+    const float l = half_swap_sum(l_run);
+    if (!__ballot(!(l <= kSafeSum))) return false;
+    float worst = 0.f;                                       // NaN as soon as an element is not finite (x - x)
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) worst += oacc[db][e] - oacc[db][e];
+    return __ballot(!(l < kOutgrownSum) || worst != 0.f) != 0ull;
+}
+
 // ---- row blocks whose keys are split: the partial results meet in LDS (every tile buffer is idle by then) ----
 // Eight partials: O in 64 registers x 64 lanes each, then (maximum, sum) per partial and lane.
 constexpr size_t kPartialStat = 8 * 64 * 64 * 4;

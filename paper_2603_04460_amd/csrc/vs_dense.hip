@@ -6,16 +6,23 @@
 // arithmetic per row block (S^T = K Q^T, joint softmax over a stage of two 32-key tiles with a lazily updated
 // maximum, O^T = V^T P^T) and the LDS tile layout are those of the sparse kernel.
 //
-// A SIMD issues about one vector instruction per 4-5 clocks whichever wavefront it comes from (an exponential
-// takes 16), while a 32x32x16 matrix instruction occupies the matrix core for 32: the softmax of a stage costs
-// more issue time than its matrix products cost matrix time, so the kernel is bound by the instruction stream
-// and is written to keep that stream short and free of waits.  With one wavefront per SIMD the overlap of the
-// softmax with the matrix core comes from inside the wavefront: the two row blocks run half a stage apart and
-// each slot is written out in issue order, matrix and vector instructions alternating.
+// One wavefront issues a vector instruction every 5 clocks (two on a SIMD every 2.5; an exponential 9, and 8.4), while a 32x32x16 matrix
+// instruction occupies the matrix core for 32 and overlaps with what fits beside it: a matrix instruction with scale, exponential,
+// sum and half a pack takes 34 clocks from one wavefront.  With one wavefront per SIMD nothing hides a wait, so the kernel is written to
+// give every matrix instruction such company and nothing in a burst: the two row blocks run half a stage apart and each slot is written
+// out in issue order, matrix and vector instructions, fragment reads and staging loads alternating.
 //   slot X(i): matrix: scores of block 0 for stage i, then P V of block 0 for stage i-1;  vector: softmax of block 1, stage i-1
 //   slot Y(i): matrix: scores of block 1 for stage i, then P V of block 1 for stage i-1;  vector: softmax of block 0, stage i
 // V fragments of stage i-1 are read at the start of X(i), K fragments of stage i+1 in Y(i) after the scores of
 // block 1; one barrier per stage, in Y(i), publishes stage i+1 and frees the buffer of stage i-1 for stage i+2.
+//
+// Stages below the diagonal take the row maximum as it stands (vs_attn_device.h, "stages without a row maximum"): the search for it was 21 of 88
+// vector instructions per tile and held the exponentials back (32 / 8 heads x 8192 487 -> 458 us, x 16384 1857 -> 1737).  Their V fragments are
+// read one behind each score product (all within the first six of them the four wavefronts asked the LDS for three times what it
+// gives) and their staging loads are issued between the score products of block 1 (all eight behind the barrier kept the matrix core
+// waiting): 458 -> 435 and 1737 -> 1642 us; the matrix core is busy 73 % of the cycles (57 % before), at 1.48 GHz instead of 1.67.
+// A row block behind the last position has no mask either: for it alone the others of its wavefront ran every stage with one
+// (32 / 8 heads x 3152, half of the last workgroup's rows missing, 104 -> 79 us, x 1500 50 -> 37, 8 / 2 x 15000 485 -> 364).
 //
 // Built with -mllvm -amdgpu-mfma-vgpr-form: score accumulators are then written to the vector registers the softmax
 // reads them from (the default puts every accumulator of a 512-register kernel in the accumulation registers and
@@ -51,7 +58,11 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     unsigned char* const kvbuf = smem;
     const float NEG_INF = -INFINITY;
     const int bid = blockIdx.x;
-    const int tid = threadIdx.x;
+    // second pass: with a maximum in every stage, where the first has outgrown the maximum of its first stages
+    bool second = false;
+    for (;;) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                            // nothing is carried from pass to pass
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qi = lane & 31, hh = lane >> 5;
@@ -92,15 +103,6 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     }
     f32x16 oacc[2][4];
     float m_run[2], l_run[2];
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-        m_run[rb] = NEG_INF;
-        l_run[rb] = 0.f;
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) oacc[rb][db][e] = 0.f;
-    }
 
     // staging: wavefront w fills groups w and w + 4 of a tile (rows 4 w + L / 16 and 16 more)
     const int st_row = tid >> 4;
@@ -120,34 +122,26 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             voff_k[u][h] = static_cast<uint32_t>(((32 * u + st_row + 16 * h) * kD + st_ck * 8) * 2);
             voff_v[u][h] = static_cast<uint32_t>(((32 * u + st_row + 16 * h) * kD + st_cv * 8) * 2);
         }
-    auto load_stage = [&](int st) __attribute__((always_inline)) {
-        const int buf = st % 3;
-        if (2 * st + 1 < nblk && 64 * st + 63 < n) {
-            // every row of the stage exists: uniform base + per-thread offset, no address arithmetic per load
-            const uint16_t* ks = kbase + static_cast<size_t>(64 * st) * kD;
-            const uint16_t* vs_ = vbase + static_cast<size_t>(64 * st) * kD;
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    unsigned char* dst = kvbuf + (2 * buf + u) * kSlotBytes + (wave + 4 * h) * kGroupBytes;
-                    lds_load16s(voff_k[u][h], ks, dst);
-                    lds_load16s(voff_v[u][h], vs_, dst + kTileBytes);
-                }
+    // piece 0 .. 7 of this thread's share of a stage: (tile u, row half h) of K, then of V; whole: every row of the stage exists
+    auto load_piece = [&](int st, int piece, bool whole) __attribute__((always_inline)) {
+        const int u = piece >> 2, h = (piece >> 1) & 1, v = piece & 1;
+        unsigned char* const dst = kvbuf + (2 * (st % 3) + u) * kSlotBytes + (wave + 4 * h) * kGroupBytes + v * kTileBytes;
+        const uint16_t* const base = v ? vbase : kbase;
+        if (whole) {
+            // uniform base + per-thread offset, no address arithmetic per load
+            lds_load16s(v ? voff_v[u][h] : voff_k[u][h], base + static_cast<size_t>(64 * st) * kD, dst);
             return;
         }
+        const int t = 2 * st + u;
+        int row = 32 * t + st_row + 16 * h;
+        if (t >= nblk || row >= n) row = 0;                  // masked anyway: no predicate on the load (every row has key 0)
+        lds_load16(base + static_cast<size_t>(row) * kD + (v ? st_cv : st_ck) * 8, dst);
+    };
+    auto whole_stage = [&](int st) __attribute__((always_inline)) { return 2 * st + 1 < nblk && 64 * st + 63 < n; };
+    auto load_stage = [&](int st) __attribute__((always_inline)) {
+        const bool whole = whole_stage(st);
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int t = 2 * st + u;
-                int row = 32 * t + st_row + 16 * h;
-                if (t >= nblk || row >= n) row = 0;          // masked anyway: no predicate on the load (every row has key 0)
-                unsigned char* dst = kvbuf + (2 * buf + u) * kSlotBytes + (wave + 4 * h) * kGroupBytes;
-                const size_t off = static_cast<size_t>(row) * kD;
-                lds_load16(kbase + off + st_ck * 8, dst);
-                lds_load16(vbase + off + st_cv * 8, dst + kTileBytes);
-            }
+        for (int piece = 0; piece < 8; ++piece) load_piece(st, piece, whole);
     };
     // DUO: one group of four rows of the wavefront's own tiles, row (lane / 16) of it; row0: first rows of the tiles; piece: 0 .. 15 of
     // K, then of V.  Rows behind the workgroup's last are masked and read that one.
@@ -185,8 +179,8 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     // causal mask of tile t for row block rb (only the tiles on and past the diagonal need it)
     auto mask_tile = [&](f32x16& acc, int t, int rb) __attribute__((always_inline)) {
         const int dlt = my_i0[rb] - 32 * t;
-        if (dlt >= 31 && my_rows[rb]) return;
-        const uint64_t w = (dlt < -31 || !my_rows[rb] || t >= nblk) ? 0ull : (dlt >= 31 ? kAll63 : ((kAll63 << (31 - dlt)) & kAll63));
+        if (dlt >= 31 || !my_rows[rb]) return;               // (a row block that does not exist is not stored: no mask, and it holds up nobody)
+        const uint64_t w = (dlt < -31 || t >= nblk) ? 0ull : ((kAll63 << (31 - dlt)) & kAll63);
         mask_elements<0>(acc, lane_keep_bits(w, w, 0u, 0u, qi + 4 - 4 * hh, 4 - 4 * hh), __float_as_uint(NEG_INF));
     };
     // One slot, written out in issue order: pieces are separated by scheduling barriers, so the matrix instructions
@@ -194,10 +188,10 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     // row block whose softmax runs.  sq: stage whose scores are computed (HAS_Q); sq - 1: stage whose P V is
     // accumulated (HAS_P); sv: stage whose scores go through the softmax (HAS_S).
 #define VS_FENCE() __builtin_amdgcn_sched_barrier(0)
-    auto slot = [&](auto mr_tag, auto has_q, auto has_p, auto has_s, auto masked, int sq, int sv) __attribute__((always_inline)) {
+    auto slot = [&](auto mr_tag, auto has_q, auto has_p, auto has_s, auto masked, auto spread, int sq, int sv) __attribute__((always_inline)) {
         constexpr int MR = decltype(mr_tag)::value, VR = 1 - MR;
         constexpr bool HAS_Q = decltype(has_q)::value, HAS_P = decltype(has_p)::value, HAS_S = decltype(has_s)::value;
-        constexpr bool MASKED = decltype(masked)::value;
+        constexpr bool MASKED = decltype(masked)::value, SPREAD = decltype(spread)::value;
         auto qmfma = [&](int kk, int u) __attribute__((always_inline)) {
             if (kk == 0) {
                 f32x16 zero;
@@ -225,6 +219,17 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
                 vf[u][j][4 + e] = hi[e];
             }
         };
+        uint32_t vbase[4];                                   // V fragments of stage sq - 1
+        if constexpr (MR == 0 && HAS_P) {
+            const uint32_t sbase = DUO ? lds0 + wave * 2 * kSlotBytes : lds0 + 2 * ((sq + 2) % 3) * kSlotBytes;
+#pragma unroll
+            for (int sgr = 0; sgr < 4; ++sgr) {
+                vbase[sgr] = sbase + v_off[sgr];
+                asm volatile("" : "+v"(vbase[sgr]));
+            }
+        }
+        // one V fragment of stage sq - 1 behind each of the 16 score products, in the order of use
+        auto vread_share = [&](int j) __attribute__((always_inline)) { vread(j >> 3, 2 * (j & 3) + ((j >> 2) & 1), vbase); };
         auto kread = [&](int u, int kk, const uint32_t (&kb)[2]) __attribute__((always_inline)) {
             typedef const __attribute__((address_space(3))) uint4* lds_u4_t;
             kf[u][kk] = __builtin_bit_cast(bf16x8, *(lds_u4_t)(kb[kk & 1] + u * kSlotBytes + 64 * (kk >> 1)));
@@ -235,72 +240,12 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             // has left stage sq-1 behind: its buffer takes stage sq+2
             __builtin_amdgcn_s_waitcnt(0x0F70);
             __syncthreads();
-            if (sq + 2 < nst) load_stage(sq + 2);
+            if (!SPREAD && sq + 2 < nst) load_stage(sq + 2);
             VS_FENCE();
         }
-        // ---- part 1: first matrix instructions | V fragments (X slot) | row maximum ----
-        float mx0 = NEG_INF, mx1 = NEG_INF;
-        float mxc[4];
-        if constexpr (HAS_S && MASKED) {
-            mask_tile(sc[VR][0], 2 * pair_of(sv), VR);
-            mask_tile(sc[VR][1], 2 * pair_of(sv) + 1, VR);
-            VS_FENCE();
-        }
-        uint32_t vbase[4];                                   // V fragments of stage sq - 1
-        if constexpr (MR == 0 && HAS_P) {
-            const uint32_t sbase = DUO ? lds0 + wave * 2 * kSlotBytes : lds0 + 2 * ((sq + 2) % 3) * kSlotBytes;
-#pragma unroll
-            for (int sgr = 0; sgr < 4; ++sgr) {
-                vbase[sgr] = sbase + v_off[sgr];
-                asm volatile("" : "+v"(vbase[sgr]));
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
-            if constexpr (HAS_Q) qmfma(j >> 1, j & 1);
-            VS_FENCE();
-            if constexpr (MR == 0 && HAS_P) {
-                // V fragments of stage sq-1: 16 fragments over 6 pieces
-#pragma unroll
-                for (int f = 3 * j; f < min(3 * j + 3, 16); ++f) vread(f >> 3, f & 7, vbase);
-            }
-            if constexpr (HAS_S) {
-                // row maximum: four independent chains (two per tile) of three-input maxima, one link of each per piece
-                if (j < 4) {
-#pragma unroll
-                    for (int ch = 0; ch < 4; ++ch) {
-                        const f32x16& a = sc[VR][ch >> 1];
-                        const int b0 = 8 * (ch & 1);
-                        if (j == 0) mxc[ch] = fmaxf(fmaxf(a[b0], a[b0 + 1]), a[b0 + 2]);
-                        if (j == 1) mxc[ch] = fmaxf(fmaxf(mxc[ch], a[b0 + 3]), a[b0 + 4]);
-                        if (j == 2) mxc[ch] = fmaxf(fmaxf(mxc[ch], a[b0 + 5]), a[b0 + 6]);
-                        if (j == 3) mxc[ch] = fmaxf(mxc[ch], a[b0 + 7]);
-                    }
-                }
-                if (j == 4) {
-                    mx0 = fmaxf(mxc[0], mxc[1]);
-                    mx1 = fmaxf(mxc[2], mxc[3]);
-                }
-            }
-            VS_FENCE();
-        }
-        if constexpr (HAS_S) {
-            const float m_new = fmaxf(m_run[VR], half_swap_max(fmaxf(mx0, mx1)));
-            if (__ballot((m_new - m_run[VR]) * p.c > kRescaleThreshold)) {
-                const float alpha = (m_new == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f((m_run[VR] - m_new) * p.c);
-#pragma unroll
-                for (int db = 0; db < 4; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) oacc[VR][db][e] *= alpha;
-                l_run[VR] *= alpha;
-                m_run[VR] = m_new;
-            }
-        }
-        // ---- part 2: remaining matrix instructions | K fragments (Y slot) | exponentials ----
-        const float mc = (!HAS_S || m_run[VR] == NEG_INF) ? 0.f : m_run[VR] * p.c;
-        float lsum = 0.f;
         // Softmax elements as a three-deep pipeline: step k scales element k, takes the exponential of element k-1 and adds
         // element k-2 to the row sum (packing a finished pair): no instruction uses the result of its predecessor.
+        float mc = 0.f, lsum = 0.f;
         float tq[3] = {0.f, 0.f, 0.f};                       // values in flight, indexed by element mod 3
         int estep = 0;
         auto expstep = [&]() __attribute__((always_inline)) {
@@ -336,10 +281,68 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
                 ++estep;
             }
         };
-        // 34 steps over the 26 matrix instructions of this part
+        // 34 steps: over the 32 matrix instructions, or (MASKED) over the 26 behind the row maximum
         auto expsteps_upto = [&](int target) __attribute__((always_inline)) {
             while (estep < target) expstep();
         };
+        auto exp_share = [&](int j) __attribute__((always_inline)) {   // behind matrix instruction j
+            if constexpr (MASKED) expsteps_upto(((j - 5) * 34 + 25) / 26);
+            else expsteps_upto(((j + 1) * 34 + 31) / 32);
+        };
+        // ---- part 1: first matrix instructions | V fragments (X slot) | row maximum (MASKED) ----
+        float mx0 = NEG_INF, mx1 = NEG_INF;
+        float mxc[4];
+        if constexpr (HAS_S && !MASKED) mc = m_run[VR] * p.c;
+        if constexpr (HAS_S && MASKED) {
+            mask_tile(sc[VR][0], 2 * pair_of(sv), VR);
+            mask_tile(sc[VR][1], 2 * pair_of(sv) + 1, VR);
+            VS_FENCE();
+        }
+#pragma unroll
+        for (int j = 0; j < 6; ++j) {
+            if constexpr (HAS_Q) qmfma(j >> 1, j & 1);
+            VS_FENCE();
+            if constexpr (MR == 0 && HAS_P) {
+                vread_share(j);
+            }
+            if constexpr (SPREAD && MR == 1) {
+                if (j & 1) load_piece(sq + 2, j >> 1, true);
+            }
+            if constexpr (HAS_S && !MASKED) exp_share(j);
+            if constexpr (HAS_S && MASKED) {
+                // row maximum: four independent chains (two per tile) of three-input maxima, one link of each per piece
+                if (j < 4) {
+#pragma unroll
+                    for (int ch = 0; ch < 4; ++ch) {
+                        const f32x16& a = sc[VR][ch >> 1];
+                        const int b0 = 8 * (ch & 1);
+                        if (j == 0) mxc[ch] = fmaxf(fmaxf(a[b0], a[b0 + 1]), a[b0 + 2]);
+                        if (j == 1) mxc[ch] = fmaxf(fmaxf(mxc[ch], a[b0 + 3]), a[b0 + 4]);
+                        if (j == 2) mxc[ch] = fmaxf(fmaxf(mxc[ch], a[b0 + 5]), a[b0 + 6]);
+                        if (j == 3) mxc[ch] = fmaxf(mxc[ch], a[b0 + 7]);
+                    }
+                }
+                if (j == 4) {
+                    mx0 = fmaxf(mxc[0], mxc[1]);
+                    mx1 = fmaxf(mxc[2], mxc[3]);
+                }
+            }
+            VS_FENCE();
+        }
+        if constexpr (HAS_S && MASKED) {
+            const float m_new = fmaxf(m_run[VR], half_swap_max(fmaxf(mx0, mx1)));
+            if (__ballot((m_new - m_run[VR]) * p.c > kRescaleThreshold)) {
+                const float alpha = (m_new == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f((m_run[VR] - m_new) * p.c);
+#pragma unroll
+                for (int db = 0; db < 4; ++db)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) oacc[VR][db][e] *= alpha;
+                l_run[VR] *= alpha;
+                m_run[VR] = m_new;
+            }
+            mc = m_run[VR] == NEG_INF ? 0.f : m_run[VR] * p.c;
+        }
+        // ---- part 2: remaining matrix instructions | K fragments (Y slot) | exponentials ----
         uint32_t kb[2];                                      // K fragments of stage sq + 1 (past the last stage: a stale slot, never used)
         if constexpr (MR == 1 && HAS_Q) {
             const uint32_t sbase = DUO ? lds0 + wave * 2 * kSlotBytes : lds0 + 2 * ((sq + 1) % 3) * kSlotBytes;
@@ -367,9 +370,13 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         for (int j = 6; j < 16; ++j) {                       // 10 more score products
             if constexpr (HAS_Q) qmfma(j >> 1, j & 1);
             VS_FENCE();
+            if constexpr (MR == 0 && HAS_P) vread_share(j);
+            if constexpr (SPREAD && MR == 1) {
+                if (j & 1) load_piece(sq + 2, j >> 1, true);
+            }
             if constexpr (LOADS && MR == 0) loads_upto((j - 6) * 16 / 26, (j - 5) * 16 / 26);
             if constexpr (LOADS && MR == 1) loads_upto(16 + (j - 6) * 16 / 10, 16 + (j - 5) * 16 / 10);
-            if constexpr (HAS_S) expsteps_upto(((j - 6 + 1) * 34 + 25) / 26);
+            if constexpr (HAS_S) exp_share(j);
             VS_FENCE();
         }
         if constexpr (DUO && MR == 1 && HAS_Q) {             // K of stage sq + 1 (V of stage sq is younger)
@@ -383,7 +390,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             if constexpr (MR == 1 && HAS_Q) {
                 kread(j >> 3, j & 7, kb);
             }
-            if constexpr (HAS_S) expsteps_upto(((10 + j + 1) * 34 + 25) / 26);
+            if constexpr (HAS_S) exp_share(16 + j);
             VS_FENCE();
         }
         if constexpr (HAS_S) {
@@ -394,7 +401,24 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     };
 #undef VS_FENCE
 
+    using T = std::true_type;
+    using F = std::false_type;
+    using R0 = std::integral_constant<int, 0>;
+    using R1 = std::integral_constant<int, 1>;
+    // stages whose two tiles lie below the diagonal for both row blocks need no mask
+    int nfree = min(my_i0[0], my_i0[1]) / 64;
+    if constexpr (DUO) nfree = nfree > wave ? (nfree - wave - 1) / kWaves + 1 : 0;   // pairs wave, wave + 4, .. below nfree
+
     __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb) {
+        m_run[rb] = NEG_INF;
+        l_run[rb] = 0.f;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) oacc[rb][db][e] = 0.f;
+    }
     if constexpr (DUO) {
 #pragma unroll
         for (int piece = 0; piece < 16; ++piece) load_own(64 * wave, 64 * wave + 32, piece);
@@ -407,26 +431,49 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     }
     read_k(DUO ? 2 * wave : 0, kf[0]);
     read_k(DUO ? 2 * wave + 1 : 1, kf[1]);
-    using T = std::true_type;
-    using F = std::false_type;
-    using R0 = std::integral_constant<int, 0>;
-    using R1 = std::integral_constant<int, 1>;
-    // stages whose two tiles lie below the diagonal for both row blocks need no mask
-    int nfree = (my_rows[0] && my_rows[1]) ? min(my_i0[0], my_i0[1]) / 64 : 0;
-    if constexpr (DUO) nfree = nfree > wave ? (nfree - wave - 1) / kWaves + 1 : 0;   // pairs wave, wave + 4, .. below nfree
-    slot(R0{}, T{}, F{}, F{}, T{}, 0, 0);                    // X(0): scores of block 0
-    slot(R1{}, T{}, F{}, T{}, T{}, 0, 0);                    // Y(0): scores of block 1; softmax of block 0
+    slot(R0{}, T{}, F{}, F{}, T{}, F{}, 0, 0);                // X(0): scores of block 0
+    slot(R1{}, T{}, F{}, T{}, T{}, F{}, 0, 0);                // Y(0): scores of block 1; softmax of block 0
     int i = 1;
-    for (; i < min(nst, nfree); ++i) {
-        slot(R0{}, T{}, T{}, T{}, F{}, i, i - 1);
-        slot(R1{}, T{}, T{}, T{}, F{}, i, i);
+    if (nst > 1) {                                       // (X(1) has the softmax of block 1 for stage 0)
+        slot(R0{}, T{}, T{}, T{}, T{}, F{}, 1, 0);
+        slot(R1{}, T{}, T{}, T{}, T{}, F{}, 1, 1);
+        i = 2;
+    }
+    // from here on without a maximum, up to the diagonal
+    const int to = second || __ballot(m_run[0] == NEG_INF || m_run[1] == NEG_INF) ? 0 : min(nst, nfree);
+    const bool optimistic = i < to;
+    using Spread = std::bool_constant<!DUO>;
+    for (; i < to && (DUO || i < nst - 3); ++i) {            // (stage i + 2 is loaded, and whole)
+        slot(R0{}, T{}, T{}, T{}, F{}, Spread{}, i, i - 1);
+        slot(R1{}, T{}, T{}, T{}, F{}, Spread{}, i, i);
+    }
+    for (; !DUO && i < to; ++i) {
+        slot(R0{}, T{}, T{}, T{}, F{}, F{}, i, i - 1);
+        slot(R1{}, T{}, T{}, T{}, F{}, F{}, i, i);
     }
     for (; i < nst; ++i) {
-        slot(R0{}, T{}, T{}, T{}, T{}, i, i - 1);
-        slot(R1{}, T{}, T{}, T{}, T{}, i, i);
+        slot(R0{}, T{}, T{}, T{}, T{}, F{}, i, i - 1);
+        slot(R1{}, T{}, T{}, T{}, T{}, F{}, i, i);
     }
-    slot(R0{}, F{}, T{}, T{}, T{}, nst, nst - 1);            // X(nst): P V of block 0; softmax of block 1
-    slot(R1{}, F{}, T{}, F{}, T{}, nst, nst);                // Y(nst): P V of block 1
+    slot(R0{}, F{}, T{}, T{}, T{}, F{}, nst, nst - 1);        // X(nst): P V of block 0; softmax of block 1
+    slot(R1{}, F{}, T{}, F{}, T{}, F{}, nst, nst);            // Y(nst): P V of block 1
+
+    bool again = optimistic && (outgrown(oacc[0], l_run[0]) || outgrown(oacc[1], l_run[1]));
+    if constexpr (!DUO) {
+        // the stages are shared: if one wavefront has to, all start again (the ring is free: every wavefront has passed
+        // the barrier of Y(nst))
+        if (nst > 3 && !second) {                        // (else no wavefront had a stage without a maximum)
+            int* const flag = reinterpret_cast<int*>(smem);
+            if (lane == 0) flag[wave] = again ? 1 : 0;
+            __syncthreads();
+            again = (flag[0] | flag[1] | flag[2] | flag[3]) != 0;
+            __syncthreads();
+        }
+    }
+    if (again) {
+        second = true;
+        continue;
+    }
 
     if constexpr (DUO) {
         __syncthreads();                                     // every buffer is idle
@@ -460,6 +507,8 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             if (p.lse && hh == 0)
                 p.lse[static_cast<size_t>(my_head[rb]) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_run[rb] * p.scale + __logf(l_tot) : NEG_INF;
         }
+    }
+    return;
     }
 }
 

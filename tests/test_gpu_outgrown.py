@@ -1,0 +1,63 @@
+"""Attention without a row maximum in most stages: scores that leave the maximum of a row block's first stages far behind.  The
+rows are then computed again with a maximum in every stage; results are as exact as those of any other row."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2603_04460_amd as vs
+import synth
+from gpu_util import bf16_to_f64, check_attention, dense_form, lists, sparse_rows
+
+pytestmark = pytest.mark.gpu
+
+SCALE = 128 ** -0.5
+
+
+def _inputs(seed, hq, hk, n, growth, big_v=0.0):
+    """The score of key n // 2 is `growth` powers of two above those before it, that of key n // 4 half as many, in every second KV head (a
+    workgroup without them sits beside one that starts again); big_v: V of key n // 2."""
+    q, k, v = synth.qkv(seed, hq, hk, n)
+    q, k, v = q.float(), k.float(), v.float()
+    q[:, :, 0] = 16.0
+    k[:, :, 0] = 0.0
+    step = growth / (16.0 * SCALE * 1.4426950408889634)
+    k[::2, n // 2, 0] = step
+    k[::2, n // 4, 0] = 0.5 * step
+    if big_v:
+        v[::2, n // 2] = big_v
+    q, k, v = (x.bfloat16() for x in (q, k, v))
+    return (q.cuda(), k.cuda(), v.cuda()), tuple(synth.to_bits(x) for x in (q, k, v))
+
+
+def _rows(n):
+    """Before, between and after the two keys, first and last rows."""
+    return np.unique(np.concatenate([np.arange(4), [n // 4 - 1, n // 4, n // 4 + 1, n // 2 - 1, n // 2, n // 2 + 1], np.arange(n // 2, n, n // 23), [n - 33, n - 2, n - 1]]))
+
+
+def _check(o, lse, ref_o, ref_lse, rows, big_v):
+    if big_v:                                                # rows that hold the large V, relative to it; the others as they are
+        large = np.abs(ref_o).max(axis=(0, 2)) > 1e3
+        got = bf16_to_f64(o)[:, rows]
+        assert np.isfinite(got).all()
+        assert np.abs(got[:, large] - ref_o[:, large]).max() <= 2e-2 * big_v
+        assert np.abs(got[:, ~large] - ref_o[:, ~large]).max() <= 2e-2
+    else:
+        check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
+# 2^20: kept as it is; 2^50: kept where O is finite; 2^100: sums out of range; 2^300: infinite
+GROWTH = [(20, 0.0), (50, 0.0), (50, 2.0 ** 90), (100, 0.0), (300, 0.0)]
+
+
+@pytest.mark.parametrize("growth,big_v", GROWTH)
+@pytest.mark.parametrize("hq,hk,n,form", [(64, 16, 1411, "long"), (160, 160, 600, "long"), (16, 4, 2050, "duo"), (1, 1, 3000, "lone"), (32, 8, 999, "short")])
+def test_dense(hq, hk, n, form, growth, big_v):
+    assert dense_form(hq, hk, n, n) == form
+    (q, k, v), (qb, kb, vb) = _inputs(4000 + n, hq, hk, n, growth, big_v)
+    o, lse = torch.empty_like(q), torch.empty((hq, n), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(q, k, v, o, lse)
+    torch.cuda.synchronize()
+    rows = _rows(n)
+    ref_o, ref_lse = oracle.dense_attention(qb, kb, vb, rows=rows)
+    _check(o, lse, ref_o, ref_lse, rows, big_v)
