@@ -36,8 +36,15 @@
 //      empty skip the tile.  A gathered tile needs a mask (column <= row) only in the one or two
 //      stages that straddle the row block's first row.
 //
+// Once every row of a row block has a maximum (after its first stage, as a rule), stages whose tiles are both live take it as it
+// stands (vs_attn_device.h, "stages without a row maximum"): the exponentials of a tile then wait for nothing but its scores and run
+// beside the next tile's score products, the V fragment reads and the staging loads likewise, one behind each matrix instruction.
+// Against a joint maximum between the score products and P V: 32 / 8 heads x 32768, 1024 + 2048 listed 1517 -> 1448 us, the 128k
+// layer 7.45 -> 7.14 ms, short lists (layers of 4096 to 46000 positions) 0 to 2 %.  The matrix core is busy 56 % of the cycles (52 %), at
+// 1.75 GHz (1.80): like the dense kernel this one runs against the chip's power.
+//
 // Staging: K / V rows go from global memory straight into LDS (global_load_lds_dwordx4: no staging registers, no LDS
-// store instructions).  Two stage buffers: the loads of stage s+1 are issued at the top of step s, after its barrier,
+// store instructions).  Two stage buffers: the loads of stage s+1 are issued in step s, after its barrier,
 // into the buffer that stage s-1 has just left; each wavefront waits for its own loads (vmcnt) before the barrier that
 // opens step s+1, which publishes them.  Loads are never predicated: rows that do not exist read another row, whose
 // scores are masked.
@@ -91,6 +98,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     // larger budget do not become the critical path.  Every wavefront leaves the loop at the same point.
     // statistics of this workgroup over all its units, added to the workspace counters once, at the end
     unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
+    unsigned int unit_tiles = 0, unit_gather = 0, unit_block = 0;     // of the unit at hand
+    if (threadIdx.x < kWaves) wtot[threadIdx.x] = 0;         // wavefront w's row block has outgrown the maximum of its first stages
     const int units_per_head = p.work_total / p.kv_heads;
     int queue = static_cast<int>(__builtin_amdgcn_s_getreg((20) | (0 << 6) | (3 << 11)) & 0xf) % p.kv_heads;   // XCC_ID
     for (;;) {
@@ -100,13 +109,14 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         // have units left (a stale value costs one vain attempt).  Every workgroup that walked all queues with atomics at
         // the end, on counters in one cache line, was 4096 atomics of ~12 ns in a row: the larger part of a small call.
         const int ln = threadIdx.x;
+        const bool again = __ballot(ln < kWaves && wtot[ln & (kWaves - 1)] != 0) != 0ull;
         int q = queue, claimed = -1;
         auto claim = [&](int which) -> int {
             int u = 0;
             if (ln == 0) u = static_cast<int>(atomicAdd(p.work_counter + which * p.work_stride, 1u));
             return __builtin_amdgcn_readfirstlane(u);
         };
-        int u = claim(q);
+        int u = again ? wtot[31] : claim(q);
         if (u < units_per_head) claimed = u;
         for (int base = 0; claimed < 0 && base < p.kv_heads; base += 64) {
             // head (queue + 1 + base + lane) modulo the number of heads
@@ -127,6 +137,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         if (ln == 0) {
             wtot[31] = claimed;
             wtot[30] = q;
+            wtot[29] = again ? 1 : 0;
         }
     }
     __syncthreads();
@@ -134,6 +145,14 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     asm volatile("" : "+v"(none));                           // (the address of the slots, kept over the units, was spilled)
     queue = __builtin_amdgcn_readfirstlane(wtot[30 + none]);
     const int unit = __builtin_amdgcn_readfirstlane(wtot[31 + none]);
+    // second: the unit of before with a maximum in every stage (the first attempt is not counted)
+    const bool second = __builtin_amdgcn_readfirstlane(wtot[29 + none]) != 0;
+    if (!second) {
+        tiles_done += unit_tiles;
+        staged_gather += unit_gather;
+        staged_block += unit_block;
+    }
+    unit_tiles = unit_gather = unit_block = 0;
     if (unit < 0) break;
     // The thread number is made opaque once per unit: every per-thread constant below is then recomputed per unit
     // instead of being carried (and spilled) across the register-hungry loops of the previous unit.
@@ -178,6 +197,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
 
     f32x16 oacc[4];
     float m_run = NEG_INF, l_run = 0.f;
+    bool settled = false;                                    // every row has a maximum, and the unit's stages may leave it as it is
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -193,16 +213,16 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     // buf: which of the two stage buffers.  The loads complete in the background (vmcnt).
     // The head's K / V base is wave-uniform; a thread adds a 32-bit byte offset: row * 256 + its chunk (n <= 2^20 rows).
     const uint32_t st_bk = static_cast<uint32_t>(st_ck * 16), st_bv = static_cast<uint32_t>(st_cv * 16);
+    auto load_piece = [&](const int (&rows)[2][2], int buf, int piece) __attribute__((always_inline)) {   // 0 .. 7: K and V of (tile, row half)
+        const int u = piece >> 2, h = (piece >> 1) & 1;
+        unsigned char* dst = kvbuf + (2 * buf + u) * kSlotBytes + (wave + kWaves * h) * kGroupBytes;
+        const uint32_t off = static_cast<uint32_t>(rows[u][h]) << 8;
+        if (piece & 1) lds_load16s(off + st_bv, vbase, dst + kTileBytes);
+        else lds_load16s(off + st_bk, kbase, dst);
+    };
     auto load_stage = [&](const int (&rows)[2][2], int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                unsigned char* dst = kvbuf + (2 * buf + u) * kSlotBytes + (wave + kWaves * h) * kGroupBytes;
-                const uint32_t off = static_cast<uint32_t>(rows[u][h]) << 8;
-                lds_load16s(off + st_bk, kbase, dst);
-                lds_load16s(off + st_bv, vbase, dst + kTileBytes);
-            }
+        for (int piece = 0; piece < 8; ++piece) load_piece(rows, buf, piece);
     };
 
     // ---- pieces of one (row block, 32-key tile) unit ----
@@ -226,19 +246,19 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     };
     // transposing LDS read: within 16 lanes, lane i addresses row i/4, 4 columns at 4 (i%4); it receives column i of
     // those 4 rows, i.e. 4 consecutive keys of one d
-    auto read_v = [&](int slot, bf16x8 (&vf)[8]) __attribute__((always_inline)) {
-        const unsigned char* va = kvbuf + slot * kSlotBytes;
+    auto read_v1 = [&](int slot, int j, bf16x8 (&vf)[8]) __attribute__((always_inline)) {   // j = 2 db + t16: d block db, keys 16 t16 ..
+        const unsigned char* a0 = kvbuf + slot * kSlotBytes + v_off[j >> 1] + 4 * (j & 1) * kGroupBytes;
+        const bf16x4t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0));
+        const bf16x4t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0 + 2 * kGroupBytes));
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {                      // j = 2 db + t16: d block db, keys 16 t16 ..
-            const unsigned char* a0 = va + v_off[j >> 1] + 4 * (j & 1) * kGroupBytes;
-            const bf16x4t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0));
-            const bf16x4t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0 + 2 * kGroupBytes));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                vf[j][e] = lo[e];
-                vf[j][4 + e] = hi[e];
-            }
+        for (int e = 0; e < 4; ++e) {
+            vf[j][e] = lo[e];
+            vf[j][4 + e] = hi[e];
         }
+    };
+    auto read_v = [&](int slot, bf16x8 (&vf)[8]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) read_v1(slot, j, vf);
     };
     auto tile_max = [&](const f32x16& acc) __attribute__((always_inline)) -> float {
         float mx = fmaxf(fmaxf(acc[0], acc[1]), acc[2]);
@@ -335,8 +355,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         constexpr bool GATHER = decltype(gather_tag)::value;
         if (ntiles == 0) return;
         const int nstages = (ntiles + 1) >> 1;
-        if (GATHER) staged_gather += static_cast<unsigned int>(ntiles);   // 32-key tiles this workgroup stages in LDS
-        else staged_block += static_cast<unsigned int>(ntiles);
+        if (GATHER) unit_gather += static_cast<unsigned int>(ntiles);   // 32-key tiles this workgroup stages in LDS
+        else unit_block += static_cast<unsigned int>(ntiles);
         // Descriptor words of the two tiles of stage st (block phase): one LDS instruction; the records are padded with dead
         // entries, so a stage past the list reads as "not live, block 0".
         auto stage_desc = [&](int st, uint32_t (&d)[2]) __attribute__((always_inline)) {
@@ -368,10 +388,10 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         // Every vector memory load issued so far (the Q fragments) is waited for here, once.  Left pending, the first
         // use of Q inside the loop would wait for "all loads", including the staging loads issued just before it.
         __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0), other counters untouched
-        int rows[2][2];
         uint32_t d0[2];
         stage_desc(0, d0);
         if (!primed) {
+            int rows[2][2];
             stage_rows(0, d0, rows);
             load_stage(rows, buf);
             __builtin_amdgcn_s_waitcnt(0x0F70);              // the barrier publishes only what has arrived
@@ -379,7 +399,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         __syncthreads();
         nfull = min(nfull, nstages);
         TileInfo a{false, false, nullptr, nullptr}, b = a;
-        if (nfull == 0) {
+        if (nfull == 0 || !settled) {
             a = info(0, d0[0]);
             b = info(1, d0[1]);
         }
@@ -390,10 +410,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                 for (int db = 0; db < 4; ++db) oacc[db] = mfma32(vf[2 * db + t], pk[t], oacc[db]);
         };
         // one step
-        // FULL: both tiles are kept whole by this row block: no tile descriptions, no masks, no tests
+        // MODE 0: both tiles are kept whole by this row block (no tile descriptions, no masks, no tests) and the maximum is settled
+        //      1: both tiles are live and the maximum is settled
+        //      2: any; looks for a new maximum
         auto step = [&](int st, auto mode_tag) __attribute__((always_inline)) {
             constexpr int MODE = decltype(mode_tag)::value;
-            constexpr bool FULL = MODE == 0;
+            constexpr bool FULL = MODE == 0, SETTLED = MODE != 2;
             if (st > 0) {
                 __builtin_amdgcn_s_waitcnt(0x0F70);          // this wavefront's part of stage st has arrived
                 __syncthreads();
@@ -409,54 +431,96 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                 nb = info(2 * st + 3, d[1]);
             }
             const bool more = st + 1 < nstages;
+            const bool loads = more || (!GATHER && chain);
+            int rows[2][2];
             if (more) {                                      // into the buffer of stage st-1, free since the barrier
                 stage_rows(st + 1, d, rows);
-                load_stage(rows, buf1);
             } else if (!GATHER && chain) {                   // first stage of the gather phase that follows
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
                     for (int h = 0; h < 2; ++h) rows[u][h] = min(glist[32 * u + st_row + 16 * h], last);
-                load_stage(rows, buf1);
             }
-            if constexpr (MODE != 2) {
-                // Both tiles live: one straight-line piece in a fixed order (the scheduling barriers keep the compiler from
-                // moving LDS reads across them: left alone it either hoists all of them, which does not fit the registers,
-                // or issues them one at a time in front of their use).  The K fragments of both tiles are read first, the
-                // two score chains are interleaved, the V fragments of both tiles are requested as soon as the K fragments
-                // are dead (they take their registers) and arrive during the softmax.
+            if (!SETTLED && loads) load_stage(rows, buf1);
+            if constexpr (SETTLED) {
+                // Without a new maximum the first tile's exponentials need nothing but its own scores: they run beside the second
+                // tile's score products, those of the second tile beside P V of the first.  Every fragment read, staging load and
+                // softmax step has its place behind a matrix instruction (scheduling barriers); V fragments take the registers of
+                // the K fragments before them.
                 bf16x8 k0[8], k1[8], v0[8], v1[8], p0[2], p1[2];
                 f32x16 s0, s1, zero;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+                unit_tiles += 2;
                 read_k(2 * buf, k0);
                 read_k(2 * buf + 1, k1);
-                tiles_done += 2;
                 __builtin_amdgcn_sched_barrier(0);
+                const float mc = m_run * p.c;
+                float lsum = 0.f;
+                // steps of a softmax as a three-deep pipeline, as in vs_dense.hip
+                float tq[3] = {0.f, 0.f, 0.f};
+                auto softmax_steps = [&](f32x16& x, bf16x8 (&pk)[2], int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int k = from; k < to; ++k) {
+                        // (the empty asm statements keep the arithmetic at this place)
+                        if (k < 16) {
+                            tq[k % 3] = fmaf(x[k], p.c, -mc);
+                            asm volatile("" : "+v"(tq[k % 3]));
+                        }
+                        if (k >= 1 && k <= 16) {
+                            tq[(k - 1) % 3] = __builtin_amdgcn_exp2f(tq[(k - 1) % 3]);
+                            asm volatile("" : "+v"(tq[(k - 1) % 3]));
+                        }
+                        if (k >= 2 && k <= 17) {
+                            const int e = k - 2;
+                            x[e] = tq[e % 3];
+                            lsum += x[e];
+                            asm volatile("" : "+v"(lsum));
+                            if (e & 1) {
+                                const f32x2 two = {x[e - 1], x[e]};
+                                uint32_t packed = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
+                                asm volatile("" : "+v"(packed));
+                                const bf16x2 r = __builtin_bit_cast(bf16x2, packed);
+                                pk[e >> 3][(e & 7) - 1] = r[0];
+                                pk[e >> 3][e & 7] = r[1];
+                            }
+                        }
+                    }
+                };
+                auto first_scores = [&](auto with_loads) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int kk = 0; kk < 8; ++kk) {
+                        s0 = mfma32(k0[kk], qf[kk], kk == 0 ? zero : s0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if constexpr (decltype(with_loads)::value) load_piece(rows, buf1, kk);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                if (loads) first_scores(std::true_type{});
+                else first_scores(std::false_type{});
 #pragma unroll
                 for (int kk = 0; kk < 8; ++kk) {
-                    s0 = mfma32(k0[kk], qf[kk], kk == 0 ? zero : s0);
                     s1 = mfma32(k1[kk], qf[kk], kk == 0 ? zero : s1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_v1(2 * buf, 2 * (kk & 3) + (kk >> 2), v0);
+                    if constexpr (!FULL) {
+                        if (kk == 0) apply_mask(s0, a, gather_tag);
+                    }
+                    if (kk > 0) softmax_steps(s0, p0, 18 * (kk - 1) / 7, 18 * kk / 7);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-                read_v(2 * buf, v0);
-                read_v(2 * buf + 1, v1);
-                __builtin_amdgcn_sched_barrier(0);
-                if constexpr (!FULL) {
-                    apply_mask(s0, a, gather_tag);
-                    apply_mask(s1, b, gather_tag);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    oacc[i & 3] = mfma32(v0[2 * (i & 3) + (i >> 2)], p0[i >> 2], oacc[i & 3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    read_v1(2 * buf + 1, 2 * (i & 3) + (i >> 2), v1);
+                    if constexpr (!FULL) {
+                        if (i == 0) apply_mask(s1, b, gather_tag);
+                    }
+                    if (i > 0) softmax_steps(s1, p1, 18 * (i - 1) / 7, 18 * i / 7);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
-                const float mx = fmaxf(tile_max(s0), tile_max(s1));
-                const float m_new = fmaxf(m_run, half_swap_max(mx));
-                if (__ballot((m_new - m_run) * p.c > kRescaleThreshold)) rescale(m_new);   // false when both are -inf
-                const float mc = (m_run == NEG_INF) ? 0.f : m_run * p.c;
-                float lsum = 0.f;
-                exp_part(s0, 0, 16, mc, lsum);
-                pack_p(s0, p0);
-                exp_part(s1, 0, 16, mc, lsum);
-                pack_p(s1, p1);
                 l_run += lsum;
-                pv(p0, v0);
                 pv(p1, v1);
             } else {
             // scores of the two tiles: defined only where the tile is live (every later use is under the same test), so
@@ -470,12 +534,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
             if (alive) read_k(2 * buf, k0);
             if (blive) read_k(2 * buf + 1, k1);
             if (alive) {
-                ++tiles_done;
+                ++unit_tiles;
 #pragma unroll
                 for (int kk = 0; kk < 8; ++kk) s0 = mfma32(k0[kk], qf[kk], kk == 0 ? zero : s0);
             }
             if (blive) {
-                ++tiles_done;
+                ++unit_tiles;
 #pragma unroll
                 for (int kk = 0; kk < 8; ++kk) s1 = mfma32(k1[kk], qf[kk], kk == 0 ? zero : s1);
             }
@@ -512,19 +576,24 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                 }
             }
             }
+            if constexpr (!SETTLED) {
+                if (!settled && !second) settled = __ballot(m_run == NEG_INF) == 0ull;
+            }
             a = na;
             b = nb;
             buf = buf1;
         };
         int st = 0;
+        for (; st < nfull && !settled; ++st) step(st, std::integral_constant<int, 2>{});
+        const int unsettled = st;
         for (; st < nfull; ++st) step(st, std::integral_constant<int, 0>{});
-        if (st > 0 && st < nstages) {
+        if (st > unsettled && st < nstages) {
             stage_desc(st, d0);
             a = info(2 * st, d0[0]);
             b = info(2 * st + 1, d0[1]);
         }
         while (st < nstages) {
-            if (a.live && b.live) {
+            if (settled && a.live && b.live) {
                 do {
                     step(st, std::integral_constant<int, 1>{});
                     ++st;
@@ -601,10 +670,16 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     }
 
     // ---- epilogue: O = O^T / l in bf16; lse = m * scale + ln(l) ----
+    // (read behind the barrier that opens the next unit; what is stored now is then stored once more)
+    const bool bad = settled && outgrown(oacc, l_run);
     // A lane holds 8-byte pieces of one output row; stored directly they would be 64 scattered pieces per instruction.
     // The row block goes through the wavefront's own 8.5 KB of the (now idle) ring instead: written as held, read back
     // 16 bytes per lane, so that 16 lanes store one whole 256-byte row and an instruction stores four rows.
     {
+        int etid = threadIdx.x;                              // (the lane's constants anew: kept over the phases they were spilled)
+        asm volatile("" : "+v"(etid));
+        const int lane = etid & 63, qi = lane & 31, hh = lane >> 5;
+        if (lane == 0) wtot[wave] = bad ? 1 : 0;
         const float l_tot = half_swap_sum(l_run);
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         constexpr int kPitch = 256 + 16;                     // row pitch in LDS: 16-byte aligned, spreads the rows over the banks

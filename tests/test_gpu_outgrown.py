@@ -61,3 +61,30 @@ def test_dense(hq, hk, n, form, growth, big_v):
     rows = _rows(n)
     ref_o, ref_lse = oracle.dense_attention(qb, kb, vb, rows=rows)
     _check(o, lse, ref_o, ref_lse, rows, big_v)
+
+
+@pytest.mark.parametrize("growth,big_v", GROWTH)
+@pytest.mark.parametrize("hq,hk,n,pos0,gran,rows_per_workgroup", [
+    (32, 8, 1411, 0, None, 4), (160, 160, 600, 0, None, 4), (32, 8, 1600, 32, 32, 4), (64, 32, 1300, 37, None, 4)])
+def test_sparse(hq, hk, n, pos0, gran, rows_per_workgroup, growth, big_v):
+    """Columns before, between and after the two keys (more than a stage of them before the first), runs of offsets and scattered ones."""
+    n_q = n - pos0
+    rng = np.random.default_rng(n)
+    (q, k, v), (qb, kb, vb) = _inputs(4100 + n, hq, hk, n, growth, big_v)
+    iv, cv = lists([np.union1d([n // 4, n // 2], rng.choice(n, 330, replace=False)) for _ in range(hk)])
+    is_, cs = lists([np.union1d(np.arange(70), rng.choice(n, 40, replace=False)) for _ in range(hk)])
+    assert sparse_rows(hq, hk, n_q, n, iv.shape[1] + is_.shape[1]) == rows_per_workgroup
+    f = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    qc = q[:, pos0:].contiguous()
+    o, lse = torch.empty_like(qc), torch.empty((hq, n_q), dtype=torch.float32, device="cuda")
+    ws = torch.empty(vs.sparse_prefill_workspace(hq, hk, hk, n), dtype=torch.uint8, device="cuda")
+    tiles = []
+    for key in (k, torch.zeros_like(k)):                     # zero scores outgrow nothing; what is executed twice counts once
+        vs.sparse_prefill(qc, key, v, f(iv), f(cv), f(is_), f(cs), o if key is k else torch.empty_like(o), lse if key is k else None, ws,
+                          slash_granularity=gran, pos0=pos0)
+        tiles.append(vs.sparse_prefill_counters(ws))
+    assert tiles[0] == tiles[1]
+    rows = _rows(n)
+    rows = rows[rows >= pos0] - pos0
+    ref_o, ref_lse = oracle.sparse_attention(qb[:, pos0:], kb, vb, iv, cv, is_, cs, rows=rows, pos0=pos0, granularity=gran or 1)
+    _check(o, lse, ref_o, ref_lse, rows, big_v)
