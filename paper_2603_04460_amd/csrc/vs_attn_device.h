@@ -184,6 +184,29 @@ __device__ __forceinline__ void lds_load16s(uint32_t voff, const void* sbase, co
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(base), "v"(voff), "s"(sbase) : "memory", "m0");
 }
 
+// The same for four rows further along a tile: the instruction's own offset moves both addresses
+template <int BYTES>
+__device__ __forceinline__ void lds_load16o(uint32_t voff, const void* sbase, const void* lds_base) {
+    const uint32_t base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
+        (const __attribute__((address_space(3))) void*)lds_base)) - BYTES;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" : : "s"(base), "v"(voff), "s"(sbase), "n"(BYTES) : "memory", "m0");
+}
+
+// A wavefront loads the 32 rows of a tile of K or V that stand one behind the other, rows: the first of them; voff: per lane, the row
+// (lane / 16) and the 16-byte chunk of the piece: no address arithmetic per load
+__device__ __forceinline__ void lds_load_tile(uint32_t voff, const uint16_t* rows, unsigned char* dst) {
+    lds_load16o<0>(voff, rows, dst);
+    lds_load16o<1024>(voff, rows, dst + kGroupBytes);
+    lds_load16o<2048>(voff, rows, dst + 2 * kGroupBytes);
+    lds_load16o<3072>(voff, rows, dst + 3 * kGroupBytes);
+    rows += 16 * kD;
+    dst += 4 * kGroupBytes;
+    lds_load16o<0>(voff, rows, dst);
+    lds_load16o<1024>(voff, rows, dst + kGroupBytes);
+    lds_load16o<2048>(voff, rows, dst + 2 * kGroupBytes);
+    lds_load16o<3072>(voff, rows, dst + 3 * kGroupBytes);
+}
+
 // ---- stages without a row maximum ----
 // Most stages of a long row block take the maximum as it stands after its first stages instead of looking for a new one: any
 // value serves as long as nothing overflows or vanishes, and the precision of P, O and the sum is relative.  Scores below it lose

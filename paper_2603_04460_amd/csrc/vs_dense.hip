@@ -42,16 +42,28 @@ constexpr int kWaves = kThreads / 64;
 constexpr size_t kSmemBytes = kSlots * kSlotBytes;
 constexpr size_t kDuoBytes = 2 * kWaves * kSlotBytes;
 static_assert(kPartialBytes <= kDuoBytes && kDuoBytes <= 160 * 1024, "partial results in the idle buffers, one workgroup per compute unit");
+// f(integral_constant<int, FROM>), .., f(integral_constant<int, TO - 1>)
+template <int FROM, int TO, class F>
+__device__ __forceinline__ void unroll(F f) {
+    if constexpr (FROM < TO) {
+        f(std::integral_constant<int, FROM>{});
+        unroll<FROM + 1, TO>(f);
+    }
+}
+
 constexpr int kShortUnits = 128;               // workgroups up to which the keys of a row block are split
 constexpr int kDuoKeys = 2048;
 
 // DUO: few row blocks.  The workgroup has two row blocks, and every wavefront owns both; the keys are split over the wavefronts, which
 // take stages of two tiles in turn, each through a K and a V buffer of its own that it fills itself (no barrier): stage i of
-// wavefront w are the tiles 2 (4 i + w) and the next.  The K fragments of a stage are read in the Y slot before it, its V fragments in the X slot
-// after it, so K of the next stage is requested in the X slot and V of this one in the Y slot, between the matrix instructions, and
-// has a slot or more to arrive.  Against vs_short_kernel (one row block per wavefront, tiles shared by two wavefronts), which is bound by the
-// LDS (64 KB staged and 128 KB of fragments read for four tiles, loads alone 221 us of 322), half the fragments are read: 500 rows
-// against 32768 keys, 32 / 8 heads, 322 -> 282 us (another box 361 -> 289), 300 rows 282 -> 214, one head of 16384 143 -> 111.
+// wavefront w are the tiles 2 (4 i + w) and the next.  The fragments of a stage are read in the slot before their use, so a buffer can be
+// filled again a whole slot before the next fragment is read from it.  Against vs_short_kernel (one row block per wavefront, tiles shared by two
+// wavefronts), which is bound by the LDS (64 KB staged and 128 KB of fragments read for four tiles), half the fragments are read: 500 rows
+// against 32768 keys, 32 / 8 heads, 322 -> 282 us, 300 rows 282 -> 214, one head of 16384 143 -> 111.
+// Bound by matrix products and loads alike: 2048 clocks each for a stage of the four wavefronts (128 KB at 64 bytes a clock).  The loads go out one
+// behind each matrix instruction, 46 of them before their data is needed (all of K in the X slot and of V in the Y slot, half a slot and
+// a little more, had to wait), without address arithmetic: 270 -> 254 us, 1128 rows of 30575 keys 652 -> 597, one head of 16001 103 -> 93; the
+// matrix core is busy 68 % of the cycles at 1.73 GHz.
 template <bool DUO>
 __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -143,14 +155,20 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
 #pragma unroll
         for (int piece = 0; piece < 8; ++piece) load_piece(st, piece, whole);
     };
-    // DUO: one group of four rows of the wavefront's own tiles, row (lane / 16) of it; row0: first rows of the tiles; piece: 0 .. 15 of
-    // K, then of V.  Rows behind the workgroup's last are masked and read that one.
+    // DUO: one group of four rows of tile u of the wavefront's own stage, row (lane / 16) of it; row0: the tile's first row.  WHOLE: the tile
+    // exists for the workgroup; otherwise rows behind the workgroup's last are masked and read that one.
     unsigned char* const own = kvbuf + wave * 2 * kSlotBytes;
-    auto load_own = [&](int row0_0, int row0_1, int piece) __attribute__((always_inline)) {
-        const int v = piece >> 4, u = (piece >> 3) & 1, grp = piece & 7;
+    auto load_own = [&](auto whole, int v, int u, auto group, int row0) __attribute__((always_inline)) {
+        constexpr int GRP = decltype(group)::value;
         const uint32_t chunk = static_cast<uint32_t>(v ? st_cv : st_ck) * 16u;
-        const uint32_t at = static_cast<uint32_t>((u ? row0_1 : row0_0) + 4 * grp + st_rho) * 256u;
-        lds_load16s(min(at, static_cast<uint32_t>(i_last) << 8) + chunk, v ? vbase : kbase, own + u * kSlotBytes + v * kTileBytes + grp * kGroupBytes);
+        unsigned char* const dst = own + u * kSlotBytes + v * kTileBytes + GRP * kGroupBytes;
+        if constexpr (decltype(whole)::value) {
+            const uint16_t* const rows = (v ? vbase : kbase) + static_cast<size_t>(row0 + 16 * (GRP / 4)) * kD;
+            lds_load16o<1024 * (GRP % 4)>(static_cast<uint32_t>(st_rho) * 256u + chunk, rows, dst);
+        } else {
+            const uint32_t at = static_cast<uint32_t>(row0 + 4 * GRP + st_rho) * 256u;
+            lds_load16s(min(at, static_cast<uint32_t>(i_last) << 8) + chunk, v ? vbase : kbase, dst);
+        }
     };
     // V of a key that is masked for every row must not be multiplied: its weight is zero, but zero times a V that is not finite is NaN.
     // DUO: tiles behind the workgroup's last read V of the first tile instead (every row has it), and row block 0 leaves out the one
@@ -234,7 +252,46 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             typedef const __attribute__((address_space(3))) uint4* lds_u4_t;
             kf[u][kk] = __builtin_bit_cast(bf16x8, *(lds_u4_t)(kb[kk & 1] + u * kSlotBytes + 64 * (kk >> 1)));
         };
-        if constexpr (DUO && MR == 0 && HAS_P) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // V of stage sq - 1
+        // DUO: what the wavefront requests for itself, a group of a tile behind each matrix instruction, as soon as the fragments that were in
+        // the buffer are in registers, which is 46 matrix instructions before the first fragment of it is read:
+        //   Y(sq - 1) 26 .. 31, X(sq) 0, 1   K of stage sq + 1, first tile      X(sq) 2 .. 9     K of stage sq + 1, second tile
+        //   X(sq) 10 .. 17                   V of stage sq, first tile          X(sq) 18 .. 25   V of stage sq, second tile
+        // (the waits count what has been requested since).  SPREAD: all these tiles exist, and are whole.
+        const bool next = SPREAD || sq + 1 < nst, after_next = SPREAD || sq + 2 < nst;
+        auto own_rows = [&](int st, int u) __attribute__((always_inline)) { return 32 * (2 * pair_of(st) + u); };
+        auto own_piece = [&](auto matrix) __attribute__((always_inline)) {
+            constexpr int JJ = decltype(matrix)::value;
+            constexpr auto whole = std::bool_constant<SPREAD>{};
+            if constexpr (DUO && HAS_Q && MR == 0) {
+                if constexpr (JJ < 2) {
+                    if (next) load_own(whole, 0, 0, std::integral_constant<int, JJ + 6>{}, own_rows(sq + 1, 0));
+                } else if constexpr (JJ < 10) {
+                    if constexpr (JJ == 2 && HAS_P) asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
+                    if constexpr (JJ == 2 && !HAS_P) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    if (next) load_own(whole, 0, 1, std::integral_constant<int, JJ - 2>{}, own_rows(sq + 1, 1));
+                } else if constexpr (JJ < 26) {
+                    constexpr int U = JJ < 18 ? 0 : 1;
+                    if constexpr (JJ == 10 && HAS_P) asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
+                    if constexpr (JJ == 18) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    int row0 = own_rows(sq, U);
+                    if constexpr (MASKED) row0 = row0 < 32 * nblk ? row0 : 0;   // (without a mask every tile is the workgroup's)
+                    load_own(whole, 1, U, std::integral_constant<int, (JJ - 10) % 8>{}, row0);
+                }
+            }
+            if constexpr (DUO && HAS_Q && MR == 1 && JJ >= 26) {
+                if constexpr (JJ == 26) asm volatile("s_waitcnt lgkmcnt(2)" ::: "memory");
+                if (after_next) load_own(whole, 0, 0, std::integral_constant<int, JJ - 26>{}, own_rows(sq + 2, 0));
+            }
+        };
+        // V of stage sq - 1, first and second tile
+        auto v_arrived = [&](int u) __attribute__((always_inline)) {
+            if constexpr (DUO && MR == 0 && HAS_P) {
+                if (HAS_Q && next) asm volatile("s_waitcnt vmcnt(14)" ::: "memory");
+                else if (u == 0) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            }
+        };
+        v_arrived(0);
         if constexpr (!DUO && MR == 1) {
             // stage sq+1 has arrived (this wavefront's part; the barrier publishes all of it) and every wavefront
             // has left stage sq-1 behind: its buffer takes stage sq+2
@@ -298,16 +355,15 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             mask_tile(sc[VR][1], 2 * pair_of(sv) + 1, VR);
             VS_FENCE();
         }
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
+        unroll<0, 6>([&](auto index) __attribute__((always_inline)) {
+            constexpr int j = decltype(index)::value;
             if constexpr (HAS_Q) qmfma(j >> 1, j & 1);
             VS_FENCE();
+            own_piece(index);
             if constexpr (MR == 0 && HAS_P) {
                 vread_share(j);
             }
-            if constexpr (SPREAD && MR == 1) {
-                if (j & 1) load_piece(sq + 2, j >> 1, true);
-            }
+            if constexpr (!DUO && SPREAD && MR == 1 && (j & 1)) load_piece(sq + 2, j >> 1, true);
             if constexpr (HAS_S && !MASKED) exp_share(j);
             if constexpr (HAS_S && MASKED) {
                 // row maximum: four independent chains (two per tile) of three-input maxima, one link of each per piece
@@ -328,7 +384,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
                 }
             }
             VS_FENCE();
-        }
+        });
         if constexpr (HAS_S && MASKED) {
             const float m_new = fmaxf(m_run[VR], half_swap_max(fmaxf(mx0, mx1)));
             if (__ballot((m_new - m_run[VR]) * p.c > kRescaleThreshold)) {
@@ -350,49 +406,32 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             kb[1] = sbase + k_off2;
             asm volatile("" : "+v"(kb[0]), "+v"(kb[1]));
         }
-        // DUO: K of stage sq + 1 is requested in the X slot, V of stage sq in the Y slot; the fragments that were read from these buffers
-        // are in registers
-        constexpr bool LOADS = DUO && HAS_Q;
-        const bool next = sq + 1 < nst;
-        if constexpr (LOADS && MR == 0) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        const int load_pair = pair_of(MR == 0 ? sq + 1 : sq);
-        int row0[2] = {64 * load_pair, 64 * load_pair + 32};
-        if constexpr (MASKED && MR == 1) {                   // (without a mask every tile is the workgroup's)
-            row0[0] = 2 * load_pair < nblk ? row0[0] : 0;
-            row0[1] = 2 * load_pair + 1 < nblk ? row0[1] : 0;
-        }
-        auto loads_upto = [&](int from, int to) __attribute__((always_inline)) {
-#pragma unroll
-            for (int piece = 0; piece < 32; ++piece)
-                if (piece >= from && piece < to && (piece >= 16 || next)) load_own(row0[0], row0[1], piece);
-        };
-#pragma unroll
-        for (int j = 6; j < 16; ++j) {                       // 10 more score products
+        unroll<6, 16>([&](auto index) __attribute__((always_inline)) {   // 10 more score products
+            constexpr int j = decltype(index)::value;
             if constexpr (HAS_Q) qmfma(j >> 1, j & 1);
             VS_FENCE();
+            if constexpr (j == 8) v_arrived(1);
+            own_piece(index);
             if constexpr (MR == 0 && HAS_P) vread_share(j);
-            if constexpr (SPREAD && MR == 1) {
-                if (j & 1) load_piece(sq + 2, j >> 1, true);
-            }
-            if constexpr (LOADS && MR == 0) loads_upto((j - 6) * 16 / 26, (j - 5) * 16 / 26);
-            if constexpr (LOADS && MR == 1) loads_upto(16 + (j - 6) * 16 / 10, 16 + (j - 5) * 16 / 10);
+            if constexpr (!DUO && SPREAD && MR == 1 && (j & 1)) load_piece(sq + 2, j >> 1, true);
             if constexpr (HAS_S) exp_share(j);
             VS_FENCE();
-        }
-        if constexpr (DUO && MR == 1 && HAS_Q) {             // K of stage sq + 1 (V of stage sq is younger)
-            if (next) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {                       // 16 P V products
+        });
+        unroll<0, 16>([&](auto index) __attribute__((always_inline)) {   // 16 P V products
+            constexpr int j = decltype(index)::value;
             if constexpr (HAS_P) pmfma(j);
             VS_FENCE();
-            if constexpr (LOADS && MR == 0) loads_upto((10 + j) * 16 / 26, (11 + j) * 16 / 26);
+            if constexpr (DUO && MR == 1 && HAS_Q) {         // K of stage sq + 1, first and second tile
+                if (j == 0 && next) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+                if (j == 8 && next) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+            }
+            own_piece(std::integral_constant<int, 16 + j>{});
             if constexpr (MR == 1 && HAS_Q) {
                 kread(j >> 3, j & 7, kb);
             }
             if constexpr (HAS_S) exp_share(16 + j);
             VS_FENCE();
-        }
+        });
         if constexpr (HAS_S) {
             expsteps_upto(34);
             l_run[VR] += lsum;
@@ -421,7 +460,8 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     }
     if constexpr (DUO) {
 #pragma unroll
-        for (int piece = 0; piece < 16; ++piece) load_own(64 * wave, 64 * wave + 32, piece);
+        for (int u = 0; u < 2; ++u)
+            unroll<0, 8>([&](auto grp) __attribute__((always_inline)) { load_own(std::false_type{}, 0, u, grp, 64 * wave + 32 * u); });
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     } else {
         load_stage(0);
@@ -431,6 +471,10 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     }
     read_k(DUO ? 2 * wave : 0, kf[0]);
     read_k(DUO ? 2 * wave + 1 : 1, kf[1]);
+    if constexpr (DUO) {                                     // as Y(-1) would
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (nst > 1) unroll<0, 6>([&](auto grp) __attribute__((always_inline)) { load_own(std::false_type{}, 0, 0, grp, 64 * (kWaves + wave)); });
+    }
     slot(R0{}, T{}, F{}, F{}, T{}, F{}, 0, 0);                // X(0): scores of block 0
     slot(R1{}, T{}, F{}, T{}, T{}, F{}, 0, 0);                // Y(0): scores of block 1; softmax of block 0
     int i = 1;
@@ -442,12 +486,11 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     // from here on without a maximum, up to the diagonal
     const int to = second || __ballot(m_run[0] == NEG_INF || m_run[1] == NEG_INF) ? 0 : min(nst, nfree);
     const bool optimistic = i < to;
-    using Spread = std::bool_constant<!DUO>;
-    for (; i < to && (DUO || i < nst - 3); ++i) {            // (stage i + 2 is loaded, and whole)
-        slot(R0{}, T{}, T{}, T{}, F{}, Spread{}, i, i - 1);
-        slot(R1{}, T{}, T{}, T{}, F{}, Spread{}, i, i);
+    for (; i < to && (DUO ? i + 2 < to : i < nst - 3); ++i) {   // (stage i + 2 is loaded, and whole)
+        slot(R0{}, T{}, T{}, T{}, F{}, T{}, i, i - 1);
+        slot(R1{}, T{}, T{}, T{}, F{}, T{}, i, i);
     }
-    for (; !DUO && i < to; ++i) {
+    for (; i < to; ++i) {
         slot(R0{}, T{}, T{}, T{}, F{}, F{}, i, i - 1);
         slot(R1{}, T{}, T{}, T{}, F{}, F{}, i, i);
     }
