@@ -15,6 +15,12 @@
 // Measured (8 KV / 32 query heads unless stated): dense, 1024 x 1024 32 -> 22 us.  A step of vs_short_kernel (four tiles, 64 KB staged)
 // takes 1.07 us while few workgroups run, 1.26 to 1.46 with one on every compute unit: the LDS (64 KB written, 128 KB of fragments
 // read) and the chain barrier - fragment reads - scores - softmax - P V of a single tile per wavefront.
+// Score products of a tile are one chain (a chain of matrix instructions runs as fast as two; two cost 16 adds).  Where it pays, tiles take the
+// row maximum as it stands once every row has one (vs_attn_device.h): sparse with two or four row blocks (32 / 8 heads, 1000 rows of 40000
+// keys 51.5 -> 49.3 us, 16384 rows of one head 102.5 -> 99.3; without 50.6 and 101.9), dense with one (8 / 2 heads, 1000 rows of 65536 keys
+// 359 -> 335).  Dense with two row blocks has too few tiles per wavefront for it (32 / 8 heads x 900 20.0 us before, 19.5 now, 20.1 with it), and a
+// sparse row block to itself is bound by its loads: 16 KB a tile at the 64 bytes a clock that a compute unit's vector memory takes, 256 clocks
+// (n = 4096, below, 30.4 with it, 28.7 without).
 // vs_lone_kernel: sparse, one head, n = 4096, 68 scattered columns and 190 offsets 51.7 -> 30.4 us with the preparation (111 in
 // vs_attention.hip); dense, one head, 8192 x 8192 74 -> 45 us, 64 rows, 32 / 8 heads, against 32768 keys 280 -> 151 us.
 #include <hip/hip_runtime.h>
@@ -36,7 +42,8 @@ constexpr int kRecPad = 2 * kStage;            // dead records after the last li
 constexpr size_t kRingBytes = 2 * kStage * kSlotBytes;
 constexpr size_t kRecOff = kRingBytes;
 constexpr size_t kGatherOff = kRecOff + (kListCap + 4 * kRecPad) * 16;
-constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4;
+constexpr size_t kFlagBytes = 64;              // behind everything else: a word per wavefront, has its row block outgrown the maximum
+constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4 + kFlagBytes;
 static_assert(kPartialBytes + 8 * 4 <= kRingBytes, "partial results in the idle ring");
 static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % (32 * kStage) == 0, "whole stages");
@@ -60,17 +67,15 @@ struct Fragments {
         for (int kk = 0; kk < 8; ++kk)
             kf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(at + ((kk & 1) ? k_off2 : k_off0) + 64 * (kk >> 1)));
     }
-    __device__ __forceinline__ void read_v(const unsigned char* at, bf16x8 (&vf)[8]) const {
+    // j = 2 db + t16: d block db, keys 16 t16 ..
+    __device__ __forceinline__ void read_v(const unsigned char* at, int j, bf16x8& vf) const {
+        const unsigned char* a0 = at + v_off[j >> 1] + 4 * (j & 1) * kGroupBytes;
+        const bf16x4t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0));
+        const bf16x4t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0 + 2 * kGroupBytes));
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {                        // j = 2 db + t16: d block db, keys 16 t16 ..
-            const unsigned char* a0 = at + v_off[j >> 1] + 4 * (j & 1) * kGroupBytes;
-            const bf16x4t lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0));
-            const bf16x4t hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr_t)(a0 + 2 * kGroupBytes));
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                vf[j][e] = lo[e];
-                vf[j][4 + e] = hi[e];
-            }
+        for (int e = 0; e < 4; ++e) {
+            vf[e] = lo[e];
+            vf[4 + e] = hi[e];
         }
     }
 };
@@ -80,42 +85,34 @@ struct RowBlock {
     bf16x8 qf[8];
     f32x16 oacc[4];
     float m_run, l_run;
+    int settled;                                             // every row has a maximum, which stays as it is (vs_attn_device.h)
+    int second;                                              // second attempt: never settled
 
     // Q fragments: B operand of S^T = K Q^T; lane holds query qi, d = 16 kk + 8 hh .. +7
-    __device__ __forceinline__ void init(const AttnParams& p, int head, int first, int qi, int hh) {
+    __device__ __forceinline__ void load_q(const AttnParams& p, int head, int first, int qi, int hh) {
         const int row = min(first + qi, p.pos0 + p.nq - 1);  // rows that do not exist are not stored
         const uint16_t* src = p.q + (static_cast<size_t>(head) * p.nq + (row - p.pos0)) * kD + 8 * hh;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * kk));
+        // (waited for here: at its first use, in the tile loop, the compiler would wait for every load in flight, in every tile)
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+    }
+    __device__ __forceinline__ void start(bool again) {
         m_run = -INFINITY;
         l_run = 0.f;
+        settled = 0;
+        second = again ? 1 : 0;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
     }
-    // Scores of a tile, two chains of matrix instructions: add() gives the sum, behind whatever the caller has put in between
-    struct Scores {
-        f32x16 a, b;
-        __device__ __forceinline__ void add() {
+    __device__ __forceinline__ bool has_outgrown() { return settled && outgrown(oacc, l_run); }
+    __device__ __forceinline__ void new_maximum(const AttnParams& p, const f32x16& s) {
+        float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) a[e] += b[e];
-        }
-    };
-    __device__ __forceinline__ void scores(const bf16x8 (&kf)[8], Scores& s) const {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) s.a[e] = s.b[e] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < 8; kk += 2) {
-            s.a = mfma32(kf[kk], qf[kk], s.a);
-            s.b = mfma32(kf[kk + 1], qf[kk + 1], s.b);
-        }
-    }
-    __device__ __forceinline__ void softmax(const AttnParams& p, const f32x16& sa, bf16x8 (&pb)[2]) {
-        float mx = fmaxf(fmaxf(sa[0], sa[1]), sa[2]);
-#pragma unroll
-        for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, sa[e]), sa[e + 1]);
-        const float m_new = fmaxf(m_run, half_swap_max(fmaxf(mx, sa[15])));
+        for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, s[e]), s[e + 1]);
+        const float m_new = fmaxf(m_run, half_swap_max(fmaxf(mx, s[15])));
         if (__ballot((m_new - m_run) * p.c > kRescaleThreshold)) {   // false when both are -inf
             const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * p.c);
 #pragma unroll
@@ -125,25 +122,52 @@ struct RowBlock {
             l_run *= alpha;
             m_run = m_new;
         }
-        const float mc = (m_run == -INFINITY) ? 0.f : m_run * p.c;
-        float lsum[2] = {0.f, 0.f};
-#pragma unroll
-        for (int e = 0; e < 16; e += 2) {
-            const float x0 = __builtin_amdgcn_exp2f(fmaf(sa[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(sa[e + 1], p.c, -mc));
-            lsum[0] += x0;
-            lsum[1] += x1;
-            const f32x2 two = {x0, x1};
-            const bf16x2 r = __builtin_convertvector(two, bf16x2);
-            pb[e >> 3][e & 7] = r[0];
-            pb[e >> 3][(e & 7) + 1] = r[1];
-        }
-        l_run += lsum[0] + lsum[1];
+        settled = !second && __ballot(m_run == -INFINITY) == 0ull ? 1 : 0;
     }
-    __device__ __forceinline__ void accumulate(const bf16x8 (&vf)[8], const bf16x8 (&pb)[2]) {
+    // A tile: its K fragments are in registers, its V (v_there() waits for it) at `at`; kind: 0 nothing of it counts, 1 whole, 2 masked with the
+    // keep-bits (bit 27 - 8a - c of element 4a + c) that keep() gives.  v_read(): the V fragments are in registers.
+    // SETTLED: the maximum stays as it is
+    template <bool SETTLED, class Keep, class Wait, class Load>
+    __device__ __forceinline__ void tile(const AttnParams& p, const bf16x8 (&kf)[8], const Fragments& fr, const unsigned char* at, int kind,
+                                         Keep keep, Wait v_there, Load v_read) {
+        f32x16 s;
+        bf16x8 vf[8], pb[2];
 #pragma unroll
-        for (int t = 0; t < 2; ++t)
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int db = 0; db < 4; ++db) oacc[db] = mfma32(vf[2 * db + t], pb[t], oacc[db]);
+        for (int kk = 0; kk < 8; ++kk) s = mfma32(kf[kk], qf[kk], s);
+        __builtin_amdgcn_sched_barrier(0);
+        v_there();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fr.read_v(at, j, vf[j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (kind == 2) mask_elements<0>(s, keep(), __float_as_uint(-INFINITY));
+        if (kind) {
+            if constexpr (!SETTLED) new_maximum(p, s);
+            const float mc = (m_run == -INFINITY) ? 0.f : m_run * p.c;
+            float lsum[2] = {0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 16; e += 2) {
+                const float x0 = __builtin_amdgcn_exp2f(fmaf(s[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(s[e + 1], p.c, -mc));
+                lsum[0] += x0;
+                lsum[1] += x1;
+                const f32x2 two = {x0, x1};
+                const bf16x2 r = __builtin_convertvector(two, bf16x2);
+                pb[e >> 3][e & 7] = r[0];
+                pb[e >> 3][(e & 7) + 1] = r[1];
+            }
+            l_run += lsum[0] + lsum[1];
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        v_read();
+        __builtin_amdgcn_sched_barrier(0);
+        if (kind) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)                      // the four d blocks in turn: consecutive products are independent
+#pragma unroll
+                for (int db = 0; db < 4; ++db) oacc[db] = mfma32(vf[2 * db + t], pb[t], oacc[db]);
+        }
     }
     // executed tiles of this wavefront in *tiles (null: none): their sum over the workgroup in thread 0 afterwards
     template <int SPLITS>
@@ -159,6 +183,18 @@ struct RowBlock {
         finish_partials<SPLITS>(p, smem, first, stride, split, head, first_row);
     }
 };
+
+// Behind the last tile of a first attempt: does any wavefront of the workgroup ask for a second?  (The stages are shared.)  The barrier
+// also leaves every buffer idle.
+__device__ __forceinline__ bool any_outgrown(RowBlock& rb, int* flags, int wave) {
+    const bool bad = rb.has_outgrown();
+    if ((threadIdx.x & 63) == 0) flags[wave] = bad ? 1 : 0;
+    __syncthreads();
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) any |= flags[w];
+    return __builtin_amdgcn_readfirstlane(any) != 0;
+}
 
 // keep-bits (bit 27 - 8a - c of element 4a + c) of a gathered tile: column <= row; cols: the tile's columns from 4 hh on
 __device__ __forceinline__ uint32_t causal_columns(const int* cols, int row) {
@@ -202,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
     const uint16_t* __restrict__ vbase = p.v + static_cast<size_t>(g) * n * kD;
 
     RowBlock row_block;
-    row_block.init(p, my_head, my_i0, qi, hh);
+    row_block.load_q(p, my_head, my_i0, qi, hh);
     const Fragments fr(lane);
     // staging: wavefront w fills group w (rows 4 w + L / 16) of the K and of the V tile of every slot of the stage
     const int st_row = tid >> 4;
@@ -215,38 +251,40 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
         lds_load16s(off + st_bk, kbase, dst);
         lds_load16s(off + st_bv, vbase, dst + kTileBytes);
     };
-    // One tile for this wavefront: slot in LDS; need: mask with the keep-bits (bit 27 - 8a - c of element 4a + c) that keep() gives.
-    auto compute = [&](int slot, bool need, auto keep) __attribute__((always_inline)) {
+    // One tile for this wavefront: slot in LDS; need: mask with the keep-bits that keep() gives.
+    auto compute = [&](auto settled, int slot, bool need, auto keep) __attribute__((always_inline)) {
         const unsigned char* const at = kvbuf + slot * kSlotBytes;
-        bf16x8 kf[8], vf[8], pb[2];
-        RowBlock::Scores sc;
+        bf16x8 kf[8];
         fr.read_k(at, kf);
-        __builtin_amdgcn_sched_barrier(0);
-        row_block.scores(kf, sc);
-        __builtin_amdgcn_sched_barrier(0);
-        fr.read_v(at, vf);
-        __builtin_amdgcn_sched_barrier(0);
-        sc.add();
-        if (need) mask_elements<0>(sc.a, keep(), __float_as_uint(NEG_INF));
-        row_block.softmax(p, sc.a, pb);
-        row_block.accumulate(vf, pb);
+        row_block.tile<decltype(settled)::value>(p, kf, fr, at, need ? 2 : 1, keep, [] {}, [] {});
     };
     // Pipeline over the stages of one phase: load(st, buf) requests the four tiles of stage st; step(t, slot) computes tile t, one of
     // this wavefront's.  One barrier per stage publishes stage st and frees the buffer of stage st - 1.
     auto run_phase = [&](int ntiles, auto load, auto step) __attribute__((always_inline)) {
         const int nst = (ntiles + kStage - 1) / kStage;
         load(0, 0);
-        for (int st = 0; st < nst; ++st) {
+        int st = 0;
+        auto stage = [&](auto settled) __attribute__((always_inline)) {
             __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0): this wavefront's part of stage st has arrived
             __syncthreads();
             if (st + 1 < nst) load(st + 1, (st + 1) & 1);
 #pragma unroll
-            for (int u = split; u < kStage; u += kSplits) step(kStage * st + u, kStage * (st & 1) + u);
+            for (int u = split; u < kStage; u += kSplits) step(settled, kStage * st + u, kStage * (st & 1) + u);
+            ++st;
+        };
+        if constexpr (DENSE) {                               // (never settled: the rule is at the top of this file)
+            while (st < nst) stage(std::false_type{});
+        } else {
+            while (st < nst && !row_block.settled) stage(std::false_type{});
+            while (st < nst) stage(std::true_type{});
         }
         __syncthreads();                                     // the ring and the lists are reused
     };
-    unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
-
+    unsigned int tiles_done, staged_gather, staged_block;
+    int* const flags = reinterpret_cast<int*>(smem + (DENSE ? kRingBytes : kSparseLds - kFlagBytes));
+    for (bool again = false;; again = true) {
+    row_block.start(again);
+    tiles_done = staged_gather = staged_block = 0;
     if constexpr (DENSE) {
         const int nblk = i_last / 32 + 1;
         run_phase(
@@ -255,10 +293,10 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
 #pragma unroll
                 for (int u = 0; u < kStage; ++u) load_tile(32 * (kStage * st + u) + st_row, kStage * buf + u);
             },
-            [&](int t, int slot) __attribute__((always_inline)) {
+            [&](auto settled, int t, int slot) __attribute__((always_inline)) {
                 const int dlt = my_i0 - 32 * t;                               // offset of (row 0, key 0)
                 if (dlt < -31 || !my_rows) return;
-                compute(slot, dlt < 31, [&]() __attribute__((always_inline)) {
+                compute(settled, slot, dlt < 31, [&]() __attribute__((always_inline)) {
                     const uint64_t w = (kAll63 << (31 - dlt)) & kAll63;       // offsets >= 0
                     return static_cast<uint32_t>(w >> (qi + 4 - 4 * hh));
                 });
@@ -296,12 +334,12 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
                     for (int u = 0; u < kStage; ++u)
                         load_tile(32 * static_cast<int>(list_rec[kStage * st + u].w >> 2) + st_row, kStage * buf + u);
                 },
-                [&](int t, int slot) __attribute__((always_inline)) {
+                [&](auto settled, int t, int slot) __attribute__((always_inline)) {
                     const uint4* const rec = my_rec + t;
                     const uint32_t fl = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(rec->w));
                     if (!(fl & 1u)) return;
                     ++tiles_done;
-                    compute(slot, (fl & 2u) != 0u, [&]() __attribute__((always_inline)) {
+                    compute(settled, slot, (fl & 2u) != 0u, [&]() __attribute__((always_inline)) {
                         const uint4 r = *rec;                // one broadcast read
                         const uint64_t wz = (static_cast<uint64_t>(r.y) << 32) | r.x;
                         return static_cast<uint32_t>(wz >> (qi + 4 - 4 * hh)) & (__builtin_bitreverse32(r.z) >> (4 - 4 * hh));
@@ -324,14 +362,16 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
 #pragma unroll
                     for (int u = 0; u < kStage; ++u) load_tile(min(glist[32 * (kStage * st + u) + st_row], last), kStage * buf + u);
                 },
-                [&](int t, int slot) __attribute__((always_inline)) {
+                [&](auto settled, int t, int slot) __attribute__((always_inline)) {
                     const int* const cols = glist + 32 * t;
                     const int cmin = __builtin_amdgcn_readfirstlane(cols[0]), cmax = __builtin_amdgcn_readfirstlane(cols[31]);
                     if (!my_rows || cmin > my_i0 + 31) return;               // ascending, INT_MAX padding
                     ++tiles_done;
-                    compute(slot, cmax > my_i0, [&]() __attribute__((always_inline)) { return causal_columns(cols + 4 * hh, my_i0 + qi); });
+                    compute(settled, slot, cmax > my_i0, [&]() __attribute__((always_inline)) { return causal_columns(cols + 4 * hh, my_i0 + qi); });
                 });
         }
+    }
+    if (DENSE || again || !any_outgrown(row_block, flags, wave)) break;
     }
 
     // (the ring is idle: every phase ends with a barrier)
@@ -348,7 +388,7 @@ constexpr int kLone = kThreads / 64;           // wavefronts = tiles in flight
 constexpr size_t kLoneRing = kLone * kSlotBytes;
 constexpr size_t kLoneRecOff = kLoneRing;
 constexpr size_t kLoneGatherOff = kLoneRecOff + (kListCap + 1) * 16;
-constexpr size_t kLoneLds = kLoneGatherOff + kGatherCap * 4;
+constexpr size_t kLoneLds = kLoneGatherOff + kGatherCap * 4 + kFlagBytes;
 static_assert(kPartialBytes + 8 * 4 <= kLoneRing, "partial results in the idle buffers");
 static_assert(kLoneLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % 32 == 0, "whole tiles");
@@ -373,22 +413,31 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
     unsigned char* const slot = smem + wave * kSlotBytes;
 
     RowBlock rb;
-    rb.init(p, my_head, my_i0, qi, hh);
+    rb.load_q(p, my_head, my_i0, qi, hh);
     const Fragments fr(lane);
     // staging: this wavefront fills all eight groups of its tile, lane L the piece of row 4 grp + L / 16
     const int st_rho = (lane >> 4) & 3;
     const uint32_t st_bk = static_cast<uint32_t>(16 * (4 * ((lane >> 2) & 3) + (((lane & 3) - st_rho) & 3)));
     const uint32_t st_bv = static_cast<uint32_t>(16 * (4 * ((((lane >> 2) & 3) - st_rho) & 3) + (lane & 3)));
-    uint32_t off[8];                                         // byte offsets of the rows of the tile that is loaded next
+    uint32_t off[8];                                         // byte offsets of the rows of the tile that is loaded next,
+    int whole = -1;                                          // or its first row, if they all exist and stand one behind the other
     auto load = [&](uint32_t piece, const uint16_t* base, unsigned char* dst) __attribute__((always_inline)) {
+        if (DENSE && whole >= 0) {
+            lds_load_tile(static_cast<uint32_t>(st_rho) * 256u + piece, base + static_cast<size_t>(whole) * kD, dst);
+            return;
+        }
 #pragma unroll
         for (int grp = 0; grp < 8; ++grp) lds_load16s(off[grp] + piece, base, dst + grp * kGroupBytes);
     };
     auto block_rows = [&](int b) __attribute__((always_inline)) {            // rows behind the last position are masked, and not read
+        if constexpr (DENSE) {
+            whole = 32 * b + 31 < n_pos ? 32 * b : -1;
+            if (whole >= 0) return;
+        }
 #pragma unroll
         for (int grp = 0; grp < 8; ++grp) off[grp] = static_cast<uint32_t>(min(32 * b + 4 * grp + st_rho, n_pos - 1)) << 8;
     };
-    // Tiles [0, ntiles) of a round, this wavefront's every eighth: rows(t) sets off; need(t): 0 skip, 1 keep whole, 2 masked with
+    // Tiles [0, ntiles) of a round, this wavefront's every eighth: rows(t) says what to load; need(t): 0 skip, 1 keep whole, 2 masked with
     // the keep-bits of keep(t)
     auto run = [&](int ntiles, auto rows, auto need, auto keep) __attribute__((always_inline)) {
         int t = wave;
@@ -396,33 +445,38 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
         rows(t);
         load(st_bk, kbase, slot);
         load(st_bv, vbase, slot + kTileBytes);
-        for (; t < ntiles; t += kLone) {
+        auto step = [&](auto settled) __attribute__((always_inline)) {
             const bool more = t + kLone < ntiles;
             const int kind = need(t);
             if (more) rows(t + kLone);
             asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); // K of tile t (its V is younger)
-            bf16x8 kf[8], vf[8], pb[2];
+            bf16x8 kf[8];
             fr.read_k(slot, kf);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             if (more) load(st_bk, kbase, slot);
-            __builtin_amdgcn_sched_barrier(0);
-            RowBlock::Scores sc;
-            rb.scores(kf, sc);
-            __builtin_amdgcn_sched_barrier(0);
-            if (more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");       // V of tile t
-            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            fr.read_v(slot, vf);
-            __builtin_amdgcn_sched_barrier(0);
-            sc.add();
-            if (kind == 2) mask_elements<0>(sc.a, keep(t), __float_as_uint(NEG_INF));
-            if (kind) rb.softmax(p, sc.a, pb);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (more) load(st_bv, vbase, slot + kTileBytes);
-            __builtin_amdgcn_sched_barrier(0);
-            if (kind) rb.accumulate(vf, pb);
+            rb.tile<decltype(settled)::value>(
+                p, kf, fr, slot, kind, [&]() __attribute__((always_inline)) { return keep(t); },
+                [&]() __attribute__((always_inline)) {       // V of tile t (K of the next is younger)
+                    if (more) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+                    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                },
+                [&]() __attribute__((always_inline)) {
+                    if (more) load(st_bv, vbase, slot + kTileBytes);
+                });
+            t += kLone;
+        };
+        if constexpr (DENSE) {
+            while (t < ntiles && !rb.settled) step(std::false_type{});
+            while (t < ntiles) step(std::true_type{});
+        } else {
+            while (t < ntiles) step(std::false_type{});
         }
     };
-    unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
+    unsigned int tiles_done, staged_gather, staged_block;
+    int* const flags = reinterpret_cast<int*>(smem + (DENSE ? kLoneRing : kLoneLds - kFlagBytes));
+    for (bool again = false;; again = true) {
+    rb.start(again);
+    tiles_done = staged_gather = staged_block = 0;
     if constexpr (DENSE) {
         auto dlt = [&](int t) { return my_i0 - 32 * t; };    // offset of (row 0, key 0)
         run(
@@ -491,14 +545,19 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
             __syncthreads();                                 // the lists are reused
         }
     }
-    __syncthreads();                                         // every buffer is idle: the partial results take their place
+    if (!DENSE || again) {
+        __syncthreads();                                     // every buffer is idle: the partial results take their place
+        break;
+    }
+    if (!any_outgrown(rb, flags, wave)) break;
+    }
     rb.merge<kLone>(p, smem, 0, 1, wave, my_head, my_i0, DENSE ? nullptr : &tiles_done);
     if (!DENSE && tid == 0) add_statistics(p, tiles_done, staged_gather, staged_block);
 }
 
 template <bool DENSE, int ROWS>
 int launch_short(AttnParams& p, hipStream_t stream) {
-    constexpr size_t lds = ROWS == 1 ? (DENSE ? kLoneRing : kLoneLds) : (DENSE ? kRingBytes : kSparseLds);
+    constexpr size_t lds = ROWS == 1 ? (DENSE ? kLoneRing + kFlagBytes : kLoneLds) : (DENSE ? kRingBytes + kFlagBytes : kSparseLds);
     void (*kernel)(AttnParams);
     if constexpr (ROWS == 1) kernel = &vs_lone_kernel<DENSE>;
     else kernel = &vs_short_kernel<DENSE, ROWS>;
