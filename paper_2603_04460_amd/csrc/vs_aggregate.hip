@@ -12,7 +12,7 @@
 //   row sweep:    resident = queries, streamed = keys 0 .. diagonal  -> per-lane online max / sum over keys
 //   column sweep: resident = keys,    streamed = queries diagonal .. n-1 -> per-lane sum over queries = column sum, kept
 //                 in a register for the whole sweep; one store (one atomic where several workgroups or heads share a column).
-// Two workgroups share a compute unit, so that one wavefront's matrix instructions run under the other's vector work.
+// Two workgroups (row sweep: three) share a compute unit, so that one wavefront's matrix instructions run under the others' vector work.
 // What bounds both sweeps is the vector work per score: scale and subtract, exponential (a quarter of the rate), add; the
 // column sweep also adds every probability to its diagonal.
 //
@@ -30,7 +30,7 @@
 // rings and flushed to global memory (one atomic each) every stage.
 // (n = 16384, 32 / 8 heads with recall: 4.2 ms with one resident block per wavefront, a permutation through the LDS crossbar,
 // two adds per element and LDS float atomics; 2.2 ms with all this but the atomics, two per pair of tiles, whose rate was
-// the limit; now 1.3.  Row sweep 1.9 -> 1.05 ms.)
+// the limit; now 1.23.  Row sweep 1.9 -> 0.96 ms.)
 // Recall: a tile that no selected offset crosses adds its column sums where the column is selected; only crossed tiles look
 // at single elements.
 #include <hip/hip_runtime.h>
@@ -55,6 +55,7 @@ constexpr int kDiagRing = 512;                 // residues of an offset ring
 constexpr int kDiagPitch = kDiagRing + 16;     // words from one ring to the next: the halves' offsets are 16 apart, their banks 32
 constexpr int kRings = 2 * kWaves;             // one per half wavefront
 constexpr int kDiagOff = kNormOff + kStages * 64 * 4;
+constexpr float kLagSum = 256.f;               // entries of a row sweep up to 2^8 above the maximum: their exponents are as exact as below it
 constexpr int kSmemBytes = kDiagOff + kRings * kDiagPitch * 4;
 
 struct SweepParams {
@@ -236,8 +237,13 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
     const int a_row = (qi >> 2) * kGroupBytes + (qi & 3) * 256;
     const int a_off0 = a_row + 16 * ((hh + qi) & 3), a_off2 = a_row + 16 * ((hh + qi + 2) & 3);
 
+    auto read_a = [&](const unsigned char* at, int kk) __attribute__((always_inline)) -> bf16x8 {
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at + ((kk & 1) ? a_off2 : a_off0) + 64 * (kk >> 1)));
+    };
+
     // ---- per-lane state ----
     float m_run[2] = {NEG_INF, NEG_INF}, l_run[2] = {0.f, 0.f};   // row sweep: running max (log2 domain) and sum of this lane's keys
+    bool settled = false;                                         // every lane has a maximum (NB blocks; stays true)
     float col_sum[2] = {0.f, 0.f}, rec_sum = 0.f;                 // column sweep
     double col_total[2] = {0., 0.};                               // PARTS: col_sum moves here every four stages (5e-8 off instead of 8e-8 at n = 3000, three parts)
     f32x16 pend;                                             // column sweep: block 0's entries of the previous tile
@@ -259,22 +265,49 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         else unsafeAtomicAdd(p.a_s + at, v * p.norm);
     };
 
-    // diagonals of one 32 x 32 set of entries; base: first row - first key
+    // diagonals of one 32 x 32 set of entries; base: first row - first key.  Two chains each for d0 and d1.  Written out: from the builtin
+    // the compiler makes 14 of the 30 moves instructions of their own.  (The wait covers the two states between a register's
+    // write and its use through a lane move.)
     auto diagonals = [&](const f32x16& x, int base) __attribute__((always_inline)) {
-        float d0[2] = {0.f, 0.f}, d1[2] = {0.f, 0.f};        // two chains each
-        static_for<16>([&](auto e_tag) __attribute__((always_inline)) {
-            constexpr int e = decltype(e_tag)::value;
-            if constexpr (e == 0) d0[0] = x[0];
-            else {
-                d0[e & 1] += row_move<0x100 + e>(x[e]);
-                d1[e & 1] += row_move<0x110 + 16 - e>(x[e]);
-            }
-        });
+        float d0[2], d1[2];
+#define VS_DIAG(d, s, m) "v_add_f32_dpp %" #d ", %" #s ", %" #d " " m " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+#define VS_DIAG_FIRST(d, s, m) "v_mov_b32_dpp %" #d ", %" #s " " m " row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %6, %4 row_shl:2 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+            VS_DIAG_FIRST(1, 5, "row_shl:1") VS_DIAG_FIRST(2, 6, "row_shr:14") VS_DIAG_FIRST(3, 5, "row_shr:15")
+            VS_DIAG(0, 8, "row_shl:4") VS_DIAG(1, 7, "row_shl:3") VS_DIAG(2, 8, "row_shr:12") VS_DIAG(3, 7, "row_shr:13")
+            VS_DIAG(0, 10, "row_shl:6") VS_DIAG(1, 9, "row_shl:5") VS_DIAG(2, 10, "row_shr:10") VS_DIAG(3, 9, "row_shr:11")
+            VS_DIAG(0, 12, "row_shl:8") VS_DIAG(1, 11, "row_shl:7") VS_DIAG(2, 12, "row_shr:8") VS_DIAG(3, 11, "row_shr:9")
+            VS_DIAG(0, 14, "row_shl:10") VS_DIAG(1, 13, "row_shl:9") VS_DIAG(2, 14, "row_shr:6") VS_DIAG(3, 13, "row_shr:7")
+            VS_DIAG(0, 16, "row_shl:12") VS_DIAG(1, 15, "row_shl:11") VS_DIAG(2, 16, "row_shr:4") VS_DIAG(3, 15, "row_shr:5")
+            VS_DIAG(0, 18, "row_shl:14") VS_DIAG(1, 17, "row_shl:13") VS_DIAG(2, 18, "row_shr:2") VS_DIAG(3, 17, "row_shr:3")
+            VS_DIAG(1, 19, "row_shl:15") VS_DIAG(3, 19, "row_shr:1")
+            : "=&v"(d0[0]), "=&v"(d0[1]), "=&v"(d1[0]), "=&v"(d1[1])
+            : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]), "v"(x[8]), "v"(x[9]), "v"(x[10]), "v"(x[11]),
+              "v"(x[12]), "v"(x[13]), "v"(x[14]), "v"(x[15]));
+#undef VS_DIAG
+#undef VS_DIAG_FIRST
         const float e1 = d1[0] + d1[1];
         const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(e1), __float_as_uint(e1), false, false);
         const unsigned low = sw[0], high = sw[1];            // the values of kh = 0 / kh = 1 in all lanes
         my_diag[(base + diag_lane) & (kDiagRing - 1)] = (d0[0] + d0[1]) + (kh ? d1_prev : __uint_as_float(high));
         d1_prev = __uint_as_float(low);
+    };
+
+    // recall of a block's entries of a tile; sum: theirs; win: the tile's offset window
+    auto add_recall = [&](const f32x16& x, float sum, uint64_t win, uint32_t col) __attribute__((always_inline)) {
+        float rsum = __uint_as_float(__float_as_uint(sum) & col);
+        if (win != 0ull) {
+            const uint32_t keep = static_cast<uint32_t>(win >> (31 - qi + 16 * hh)) | col;   // bit e: (i, j) kept
+            rsum = 0.f;
+            static_for<16>([&](auto e_tag) __attribute__((always_inline)) {
+                constexpr int e = decltype(e_tag)::value;
+                uint32_t m;                                  // the keep-bit spread over a word
+                asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(keep), "n"(e));
+                rsum += __uint_as_float(__float_as_uint(x[e]) & m);
+            });
+        }
+        rec_sum += rsum;
     };
 
     // Streamed tile t in slot `slot` against both resident blocks.  acc element e of lane (qi, hh) is (streamed row 16 hh +
@@ -286,8 +319,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         {
             bf16x8 af[8];
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk)
-                af[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(at + ((kk & 1) ? a_off2 : a_off0) + 64 * (kk >> 1)));
+            for (int kk = 0; kk < 8; ++kk) af[kk] = read_a(at, kk);
             f32x16 zero;
 #pragma unroll
             for (int e = 0; e < 16; ++e) zero[e] = 0.f;
@@ -300,6 +332,34 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         const int s0 = 32 * t;                               // first streamed row of the tile
         if constexpr (!COLUMNS) {
             // keys s0 .. s0+31 against queries: causal where key <= query
+            if constexpr (!MASKED) {
+                // The maxima as they stand, if no entry is more than 2^8 above its row's (the sums say so; not true for NaN); else the
+                // tile is taken again and moves them, each time, or entries a little above would send every tile there.  (Maximum of every tile,
+                // moved beyond 2^8: 32 / 8 heads, n = 16384 1.02 ms, 45 vector instructions beside the exponentials of a block, now 33, 0.96.  Matrix
+                // instructions issued between the exponentials, as in the column sweep: 1.00, three wavefronts share a SIMD here.)
+                if (settled) {
+                    float sum[NB][2];
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) {
+                            const float pr = __builtin_amdgcn_exp2f(fmaf(acc[b][e], p.c, -m_run[b]));
+                            sum[b][e & 1] = e < 2 ? pr : sum[b][e & 1] + pr;
+                        }
+                    float worst = 0.f;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        sum[b][0] += sum[b][1];
+                        worst += sum[b][0];
+                    }
+                    if (!__ballot(!(worst < kLagSum))) {
+#pragma unroll
+                        for (int b = 0; b < NB; ++b) l_run[b] += sum[b][0];
+                        return;
+                    }
+                }
+            }
+            settled = true;
 #pragma unroll
             for (int b = 0; b < NB; ++b) {
                 f32x16& x = acc[b];
@@ -313,8 +373,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 #pragma unroll
                 for (int e = 3; e < 15; e += 2) mt = fmaxf(fmaxf(mt, x[e]), x[e + 1]);
                 mt = fmaxf(mt, x[15]) * p.c;
-                // the maximum is only moved when it grew by more than 2^8 (false where both are -inf)
-                if (__ballot(mt - m_run[b] > kRescaleThreshold)) {
+                if (__ballot(mt > m_run[b])) {
                     const float m_new = fmaxf(m_run[b], mt);
                     l_run[b] *= m_new == NEG_INF ? 1.f : __builtin_amdgcn_exp2f(m_run[b] - m_new);
                     m_run[b] = m_new;
@@ -324,6 +383,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 #pragma unroll
                 for (int e = 0; e < 16; ++e) sum[e & 1] += __builtin_amdgcn_exp2f(fmaf(x[e], p.c, -mc));
                 l_run[b] += sum[0] + sum[1];
+                settled &= !__ballot(m_run[b] == NEG_INF);
             }
         } else {
             // queries s0 .. s0+31 against keys: causal where query >= key
@@ -343,14 +403,14 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
 #pragma unroll
             for (int b = 1; b >= 0; --b) {
                 f32x16& x = acc[b];
-                float sum[2] = {0.f, 0.f};
+                float sum[2];
                 const int lim = my_r0 + 32 * b + qi - s0 - 16 * hh;       // element e is causal iff e >= lim
 #pragma unroll
                 for (int e = 0; e < 16; ++e) {
                     float pr = __builtin_amdgcn_exp2f(fmaf(x[e], p.c, nv[e >> 2][e & 3]));
                     if (MASKED && e < lim) pr = 0.f;
                     x[e] = pr;
-                    sum[e & 1] += pr;
+                    sum[e & 1] = e < 2 ? pr : sum[e & 1] + pr;
                     if (b == 1) pend[e] += pr;
                 }
                 psum[b] = sum[0] + sum[1];
@@ -359,24 +419,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             diagonals(pend, s0 - my_r0 - 32);
             pend = acc[0];
             if (RECALL) {
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    float rsum = __uint_as_float(__float_as_uint(psum[b]) & col_keep[b]);
-                    if (win[b] != 0ull) {
-                        const uint32_t keep = static_cast<uint32_t>(win[b] >> (31 - qi + 16 * hh)) | col_keep[b];   // bit e: (i, j) kept
-                        rsum = 0.f;
-                        static_for<16>([&](auto e_tag) __attribute__((always_inline)) {
-                            constexpr int e = decltype(e_tag)::value;
-                            uint32_t m;                      // the keep-bit spread over a word
-                            asm("v_bfe_i32 %0, %1, %2, 1" : "=v"(m) : "v"(keep), "n"(e));
-                            rsum += __uint_as_float(__float_as_uint(acc[b][e]) & m);
-                        });
-                    }
-                    rec_sum += rsum;
-                }
+                add_recall(acc[0], psum[0], win[0], col_keep[0]);
+                add_recall(acc[1], psum[1], win[1], col_keep[1]);
             }
         }
     };
+
     auto tile_any = [&](int t, int slot, uint32_t w0, uint32_t w1) __attribute__((always_inline)) {
         // live if any of its entries is causal for one of the two blocks
         const bool live = t < t_end && my_r0 < n && (COLUMNS ? t >= my_b0 : t <= my_b0 + NB - 1);
@@ -384,6 +432,113 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         if (COLUMNS ? t <= my_b0 + 1 : t >= my_b0) tile(t, slot, w0, w1, std::true_type{});
         else tile(t, slot, w0, w1, std::false_type{});
     };
+
+    // ---- column sweep: stages whose two tiles are whole for both blocks ----
+    // The scores of a block are made between the vector instructions of the block before: slot (x, y) issues a matrix instruction for x,
+    // then a piece of y, in a pipeline of its own (scale element pair k - 1, exponentials of k - 2, sums of k - 3: nothing waits for its
+    // predecessor).  Two wavefronts share a SIMD, and one after the other they were in the same half of a tile too often.  Scheduling
+    // barriers keep the order; arithmetic is pinned, or the compiler moves it to its use.  (32 / 8 heads, n = 16384 with recall 1.29 -> 1.26 ms with the
+    // lane moves as operand modifiers, -> 1.23 with this.)
+#define VS_PIN(x) asm volatile("" : "+v"(x))
+    bf16x8 af[8];
+    // MM: x = scores of the resident block with fragments rfb; the fragments af are replaced by those of the tile at `next` (if not null).
+    // VV: y, scores -> entries 2^(c y + off(e)); sum: their sums, two chains; extra(k): more work for the pair k of entries
+    auto slot = [&](auto mm, auto vv, const bf16x8 (&rfb)[8], f32x16& x, const unsigned char* next, f32x16& y, auto&& off, float (&sum)[2],
+                    auto&& extra) __attribute__((always_inline)) {
+        constexpr bool MM = decltype(mm)::value, VV = decltype(vv)::value;
+        f32x16 zero;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) zero[e] = 0.f;
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<VV ? 12 : 8>([&](auto k_tag) __attribute__((always_inline)) {
+            constexpr int k = decltype(k_tag)::value;
+            if constexpr (MM && k < 8) {
+                x = mfma32(af[k], rfb[k], k == 0 ? zero : x);
+                if (next) af[k] = read_a(next, k);
+            }
+            if constexpr (VV) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    if constexpr (k >= 1 && k < 9) {
+                        float t = fmaf(y[2 * (k - 1) + i], p.c, off(2 * (k - 1) + i));
+                        VS_PIN(t);
+                        y[2 * (k - 1) + i] = t;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    if constexpr (k >= 2 && k < 10) {
+                        float t = __builtin_amdgcn_exp2f(y[2 * (k - 2) + i]);
+                        VS_PIN(t);
+                        y[2 * (k - 2) + i] = t;
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    if constexpr (k >= 3 && k < 11) {
+                        sum[i] = k == 3 ? y[2 * (k - 3) + i] : sum[i] + y[2 * (k - 3) + i];
+                        VS_PIN(sum[i]);
+                    }
+                }
+                if constexpr (k >= 3 && k < 11) extra(std::integral_constant<int, k - 3>{});
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    auto nothing = [](auto) __attribute__((always_inline)) {};
+    // Column sweep, queries of stage st, t0: its first tile; w: words of the offset bitmap
+    auto full_columns = [&](int st, int t0, const uint32_t (&w)[3]) __attribute__((always_inline)) {
+        const unsigned char* const at = smem + 2 * (st & 1) * kTileBytes;
+        const float* const nr = norm_ring + 64 * (st & 1) + 16 * hh;
+        f32x16 x0, x1;
+        f32x4 nv[4];
+        float s[2];
+        auto norms = [&](int u) __attribute__((always_inline)) {
+#pragma unroll
+            for (int a = 0; a < 4; ++a) nv[a] = *reinterpret_cast<const f32x4*>(nr + 32 * u + 4 * a);
+        };
+        auto off = [&](int e) __attribute__((always_inline)) { return nv[e >> 2][e & 3]; };
+        auto into_pend = [&](auto k_tag) __attribute__((always_inline)) {
+            constexpr int k = decltype(k_tag)::value;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                float t = pend[2 * k + i] + x1[2 * k + i];
+                VS_PIN(t);
+                pend[2 * k + i] = t;
+            }
+        };
+        auto through = [&](const f32x16& x, int b, uint64_t win) __attribute__((always_inline)) {
+            const float sum = s[0] + s[1];
+            col_sum[b] += sum;
+            if (RECALL) add_recall(x, sum, win, col_keep[b]);
+        };
+        uint64_t win[2] = {0ull, 0ull};
+        if (RECALL) {
+            win[0] = ((static_cast<uint64_t>(w[1]) << 32) | w[0]) >> 1;
+            win[1] = ((static_cast<uint64_t>(w[2]) << 32) | w[1]) >> 1;
+        }
+        norms(0);
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) af[kk] = read_a(at, kk);
+        slot(yes, no, rf[NB - 1], x1, nullptr, x1, off, s, nothing);
+        slot(yes, yes, rf[0], x0, at + kTileBytes, x1, off, s, into_pend);
+        through(x1, 1, win_prev);
+        diagonals(pend, 32 * t0 - my_r0 - 32);
+        slot(yes, yes, rf[NB - 1], x1, nullptr, x0, off, s, nothing);
+        pend = x0;
+        through(pend, 0, win[0]);
+        norms(1);
+        slot(yes, yes, rf[0], x0, nullptr, x1, off, s, into_pend);
+        through(x1, 1, win[0]);
+        diagonals(pend, 32 * t0 - my_r0);
+        slot(no, yes, rf[0], x1, nullptr, x0, off, s, nothing);
+        pend = x0;
+        through(pend, 0, win[1]);
+        win_prev = win[1];
+    };
+#undef VS_PIN
 
     // ---- pipeline: step s computes stage s; the loads of stage s + 1 are issued at its top, over stage s - 1 ----
     load_stage(0);
@@ -414,8 +569,17 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
         }
         if (st + 1 < nstages) load_stage(st + 1);
         const int t0 = t_begin + 2 * st;
-        tile_any(t0, 2 * (st & 1), w[0], w[1]);
-        tile_any(t0 + 1, 2 * (st & 1) + 1, w[1], w[2]);
+        bool done = false;
+        if constexpr (COLUMNS) {
+            if (t0 > my_b0 + 1 && t0 + 1 < t_end && my_r0 < n) {
+                full_columns(st, t0, w);
+                done = true;
+            }
+        }
+        if (!done) {
+            tile_any(t0, 2 * (st & 1), w[0], w[1]);
+            tile_any(t0 + 1, 2 * (st & 1) + 1, w[1], w[2]);
+        }
         if constexpr (COLUMNS && PARTS) {
             if ((st & 3) == 3) {
 #pragma unroll

@@ -151,6 +151,30 @@ def test_aggregate_parts(hq, n, parts):
     assert np.abs(rec - ref_r).max() <= RECALL_ABS
 
 
+@pytest.mark.parametrize("growth", [6, 12, 100, 300])
+@pytest.mark.parametrize("hq,hk,n", [(172, 43, 1473), (8, 2, 1411), (4, 4, 256)])
+def test_aggregate_growing_scores(hq, hk, n, growth):
+    """Stages without a row maximum, long form, shared out and half groups: the scores of keys n // 4 and n // 2 are 2^(growth / 2) and 2^growth
+    above those before them, in every second KV head; with the recall of columns and runs of offsets across whole stages."""
+    q, k, v = (x.float() for x in synth.qkv(900 + n, hq, hk, n))
+    q[:, :, 0] = 16.0
+    k[:, :, 0] = 0.0
+    step = growth / (16.0 * 128 ** -0.5 * 1.4426950408889634)
+    k[::2, n // 2, 0] = step
+    k[::2, n // 4, 0] = 0.5 * step
+    q, k = q.bfloat16(), k.bfloat16()
+    rng = np.random.default_rng(n)
+    mask = [*lists([np.union1d([n // 4], rng.choice(n, 20, replace=False)) for _ in range(hk)]),
+            *lists([np.union1d(np.arange(n // 3, n // 3 + 90), rng.choice(n, 9, replace=False)) for _ in range(hk)])]
+    a_v, a_s, rec = _run(q.cuda(), k.cuda(), hq, mask=mask)
+    group, heads = hq // hk, np.array([0, 1, hq // 2, hq - 1])
+    per_q = [m[heads // group] for m in mask]
+    ref_v, ref_s, ref_rec = _oracle(synth.to_bits(q)[heads], synth.to_bits(k)[heads // group], 1, mask=per_q)
+    _close(a_v[heads], ref_v)
+    _close(a_s[heads], ref_s)
+    assert np.abs(rec[heads] - ref_rec).max() <= RECALL_ABS
+
+
 @pytest.mark.parametrize("hq,hk,n", [(1, 1, 127), (3, 1, 128), (4, 2, 129), (1, 1, 200), (8, 2, 255), (3, 3, 256)])
 def test_aggregate_half_groups(hq, hk, n):
     """Up to 256 positions of up to 256 heads: the row normalisers come from workgroups of 128 rows."""
