@@ -364,8 +364,10 @@ __global__ __launch_bounds__(kThreads, 1) void train_backward_kernel(const Train
                     xd[(k + 1) & 1] = read_t(tb, (k + 1) >> 1, (k + 1) & 1);
                 }
                 acc_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xu[k & 1], whi[k], k == 0 ? bias : acc_next, 0, 0, 0);
+                VS_PIN(acc_next);
             } else if constexpr (part == 2) {
                 acc_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xu[k & 1], wlo[k], acc_next, 0, 0, 0);
+                VS_PIN(acc_next);
             } else {
                 const uint32_t* const dd = part == 1 ? dhi : dlo;
                 const uint4 b4 = make_uint4(dd[4 * (k & 1)], dd[4 * (k & 1) + 1], dd[4 * (k & 1) + 2], dd[4 * (k & 1) + 3]);
