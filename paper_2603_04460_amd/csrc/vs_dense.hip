@@ -632,7 +632,7 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
     const int64_t units = static_cast<int64_t>(kv_heads) * (p.group / p.hc) * ((n_q * p.hc + 255) / 256);
     const bool few_tiles = p.hc <= 2 && n_kv * p.hc <= 64;
     if (units <= kShortUnits && !few_tiles) {
-        const int rows = vs::short_lone(p.q_heads, p.nq) ? 1 : 2;
+        const int rows = vs::dense_lone(p.q_heads, p.nq, p.pos0) ? 1 : 2;
         p.hc = vs::short_heads(p.hc, rows);
         // Of these, more than 256 row blocks against at least 2048 keys: two row blocks per wavefront (DUO).  There / vs_short_kernel, us:
         // 8 x 2048 22 / 25, 16 / 4 x 2048 33 / 33, 12 x 2600 79 / 80, 32 / 8, 500 rows of 2048 24 / 26, 1024 of 4096 73 / 80, of 32768 567 / 648;

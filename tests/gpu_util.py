@@ -72,7 +72,10 @@ def dense_form(hq, hk, n_q, n, pos0=0):
     blocks, last = -(-n_q // 32), -(-(pos0 + n_q) // 32)
     keys = _number("vs_dense.hip", "kDuoKeys")
     if dense_is_short(hq, hk, n_q, n):
-        if hq * blocks <= _number("vs_attn_device.h", "kLoneBlocks"):
+        lone = _number("vs_attn_device.h", "kLoneBlocks")
+        if hq * blocks <= lone:
+            return "lone"
+        if hq * blocks <= 2 * lone and last >= _number("vs_attn_device.h", "kLoneTiles") and 2 * (last - lone // hq) < last:
             return "lone"
         return "duo" if n >= keys else "short"
     work = hq * (blocks * (last - blocks) + blocks * (blocks + 1) // 2)

@@ -288,6 +288,20 @@ def test_dense_two_row_blocks_per_wavefront(hq, hk, n_q, n, pos0):
     check_attention(o, lse, ref_o, ref_lse, rows=rows)
 
 
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q", [(8, 2, 1129, 0, 1129), (8, 2, 2016, 0, 2016), (3, 3, 3201, 0, 3201), (6, 6, 1603, 99, 1500), (1, 1, 8222, 0, 8222)])
+def test_dense_lone_row_blocks_second_round(hq, hk, n, pos0, n_q):
+    """More than 256 row blocks of one workgroup each: the smallest and the largest number, ragged last row blocks, a chunk."""
+    assert 256 < hq * -(-n_q // 32) <= 512 and dense_form(hq, hk, n_q, n, pos0) == "lone"
+    (q, k, v), (qb, kb, vb) = make_qkv(1700 + n, hq, hk, n)
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o, lse = torch.full_like(qc, float("nan")), torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, k, v, o, lse, pos0=pos0 if n_q != n else None)
+    torch.cuda.synchronize()
+    rows = synth.sample_rows(6, n_q, 33, 40, 60)
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
 @pytest.mark.parametrize("hq,hk,n,pos0,n_q", [(24, 24, 2048, 0, 2048), (8, 2, 6001, 0, 6001), (32, 8, 5000, 3700, 1290),   # evenly spread
                                               (32, 8, 2048, 0, 2048), (32, 8, 2100, 31, 2060)])                            # long form
 def test_dense_about_one_round_of_workgroups(hq, hk, n, pos0, n_q):
