@@ -288,6 +288,21 @@ def test_dense_two_row_blocks_per_wavefront(hq, hk, n_q, n, pos0):
     check_attention(o, lse, ref_o, ref_lse, rows=rows)
 
 
+@pytest.mark.parametrize("hq,hk,n,pos0,n_q,form", [(8, 2, 2817, 0, 2817, "short"), (32, 8, 2100, 1339, 761, "short"), (12, 6, 2049, 0, 2049, "short"),
+                                                   (8, 2, 2560, 0, 2560, "duo"), (6, 3, 3499, 0, 3499, "short")])
+def test_dense_long_keys_many_row_blocks(hq, hk, n, pos0, n_q, form):
+    """At least 2048 keys and more than 640 row blocks of grouped heads, few keys to a row: two row blocks in a workgroup."""
+    assert dense_form(hq, hk, n_q, n, pos0) == form
+    (q, k, v), (qb, kb, vb) = make_qkv(1750 + n, hq, hk, n)
+    qc = q[:, pos0:pos0 + n_q].contiguous()
+    o, lse = torch.full_like(qc, float("nan")), torch.full((hq, n_q), float("nan"), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(qc, k, v, o, lse, pos0=pos0 if n_q != n else None)
+    torch.cuda.synchronize()
+    rows = synth.sample_rows(8, n_q, 33, 40, 60)
+    ref_o, ref_lse = oracle.dense_attention(qb[:, pos0:pos0 + n_q], kb, vb, rows=rows, pos0=pos0)
+    check_attention(o, lse, ref_o, ref_lse, rows=rows)
+
+
 @pytest.mark.parametrize("hq,hk,n,pos0,n_q", [(8, 2, 1129, 0, 1129), (8, 2, 2016, 0, 2016), (3, 3, 3201, 0, 3201), (6, 6, 1603, 99, 1500), (1, 1, 8222, 0, 8222)])
 def test_dense_lone_row_blocks_second_round(hq, hk, n, pos0, n_q):
     """More than 256 row blocks of one workgroup each: the smallest and the largest number, ragged last row blocks, a chunk."""
