@@ -55,7 +55,8 @@ constexpr int kDiagRing = 512;                 // residues of an offset ring
 constexpr int kDiagPitch = kDiagRing + 16;     // words from one ring to the next: the halves' offsets are 16 apart, their banks 32
 constexpr int kRings = 2 * kWaves;             // one per half wavefront
 constexpr int kDiagOff = kNormOff + kStages * 64 * 4;
-constexpr float kLagSum = 256.f;               // entries of a row sweep up to 2^8 above the maximum: their exponents are as exact as below it
+constexpr float kLagSum = 512.f;               // entries of a row sweep up to 2^9 above the running maximum: their exponents are as exact as those below it
+constexpr float kBelowMax = 1.f;               // the running maximum stays this far below: exponents of the entries that matter are smaller, and more exact
 constexpr int kSmemBytes = kDiagOff + kRings * kDiagPitch * 4;
 
 struct SweepParams {
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
                 float mt = fmaxf(fmaxf(x[0], x[1]), x[2]);
 #pragma unroll
                 for (int e = 3; e < 15; e += 2) mt = fmaxf(fmaxf(mt, x[e]), x[e + 1]);
-                mt = fmaxf(mt, x[15]) * p.c;
+                mt = fmaf(fmaxf(mt, x[15]), p.c, -kBelowMax);
                 if (__ballot(mt > m_run[b])) {
                     const float m_new = fmaxf(m_run[b], mt);
                     l_run[b] *= m_new == NEG_INF ? 1.f : __builtin_amdgcn_exp2f(m_run[b] - m_new);
