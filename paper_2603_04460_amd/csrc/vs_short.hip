@@ -8,7 +8,8 @@
 //   vs_short_kernel  two row blocks (two query heads of the KV group, or 64 consecutive rows of one head) of four wavefronts, or four
 //                    of two.  A stage is four 32-key tiles, wavefront (s, rb) takes tile s (and s + 2) of the stage for row block
 //                    rb; two stages live in LDS.
-//   vs_lone_kernel   one row block of eight wavefronts, each with LDS buffers of its own (vs::short_lone, at most 256 row blocks).
+//   vs_lone_kernel   one row block of eight wavefronts, each with LDS buffers of its own (vs::short_lone, at most 256 row blocks; dense up
+//                    to 512, vs::dense_lone).
 //
 // Long dense calls with more row blocks than that go to the two-row-block form of vs_dense.hip.
 //

@@ -131,8 +131,9 @@ struct TrainParams {
 // Matrix and vector work of a block are about equal (64 matrix instructions of 32 clocks against ~500 vector instructions
 // for the 16 tokens of a lane: GELU with its slope, the logit gradients, the split into two bf16 terms), a workgroup has
 // one wavefront per SIMD, and a wavefront issues in order: done one after the other, with the loads of a block waited for
-// in front of it, a block took 4.7 us (8 x 32768 tokens, d_h = 256, GELU: 300 us; now 173 us, of which the issue of the ~750
-// instructions of a block is the larger part).  So the blocks are pipelined inside the wavefront: step i issues the matrix
+// in front of it, a block took 4.7 us (8 x 32768 tokens, d_h = 256, GELU: 300 us; now 158 us, of which the issue of the ~700
+// instructions of a block is the larger part; 173 while the compiler had all matrix instructions of U behind the vector instructions:
+// their accumulator is pinned after each).  So the blocks are pipelined inside the wavefront: step i issues the matrix
 // instructions of U for block i + 1 and of dW_U for block i - 1 and, after each of them, a piece of the activation of
 // block i (scheduling barriers keep the order; pure arithmetic is pinned with empty asm statements).  The X tiles come
 // straight into LDS two blocks ahead; four tile buffers.  Steps at the ends run on zeroed or stale tiles whose gradients
