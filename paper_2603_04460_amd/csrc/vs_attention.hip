@@ -98,8 +98,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     // larger budget do not become the critical path.  Every wavefront leaves the loop at the same point.
     // statistics of this workgroup over all its units, added to the workspace counters once, at the end
     unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
-    unsigned int unit_tiles = 0, unit_gather = 0, unit_block = 0;     // of the unit at hand
-    if (threadIdx.x < kWaves) wtot[threadIdx.x] = 0;         // wavefront w's row block has outgrown the maximum of its first stages
     const int units_per_head = p.work_total / p.kv_heads;
     int queue = static_cast<int>(__builtin_amdgcn_s_getreg((20) | (0 << 6) | (3 << 11)) & 0xf) % p.kv_heads;   // XCC_ID
     for (;;) {
@@ -109,14 +107,13 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         // have units left (a stale value costs one vain attempt).  Every workgroup that walked all queues with atomics at
         // the end, on counters in one cache line, was 4096 atomics of ~12 ns in a row: the larger part of a small call.
         const int ln = threadIdx.x;
-        const bool again = __ballot(ln < kWaves && wtot[ln & (kWaves - 1)] != 0) != 0ull;
         int q = queue, claimed = -1;
         auto claim = [&](int which) -> int {
             int u = 0;
             if (ln == 0) u = static_cast<int>(atomicAdd(p.work_counter + which * p.work_stride, 1u));
             return __builtin_amdgcn_readfirstlane(u);
         };
-        int u = again ? wtot[31] : claim(q);
+        int u = claim(q);
         if (u < units_per_head) claimed = u;
         for (int base = 0; claimed < 0 && base < p.kv_heads; base += 64) {
             // head (queue + 1 + base + lane) modulo the number of heads
@@ -137,7 +134,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         if (ln == 0) {
             wtot[31] = claimed;
             wtot[30] = q;
-            wtot[29] = again ? 1 : 0;
         }
     }
     __syncthreads();
@@ -145,14 +141,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     asm volatile("" : "+v"(none));                           // (the address of the slots, kept over the units, was spilled)
     queue = __builtin_amdgcn_readfirstlane(wtot[30 + none]);
     const int unit = __builtin_amdgcn_readfirstlane(wtot[31 + none]);
-    // second: the unit of before with a maximum in every stage (the first attempt is not counted)
-    const bool second = __builtin_amdgcn_readfirstlane(wtot[29 + none]) != 0;
-    if (!second) {
-        tiles_done += unit_tiles;
-        staged_gather += unit_gather;
-        staged_block += unit_block;
-    }
-    unit_tiles = unit_gather = unit_block = 0;
     if (unit < 0) break;
     // The thread number is made opaque once per unit: every per-thread constant below is then recomputed per unit
     // instead of being carried (and spilled) across the register-hungry loops of the previous unit.
@@ -197,7 +185,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
 
     f32x16 oacc[4];
     float m_run = NEG_INF, l_run = 0.f;
-    bool settled = false;                                    // every row has a maximum, and the unit's stages may leave it as it is
+    bool settled = false;                                    // every row has a maximum
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -355,8 +343,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         constexpr bool GATHER = decltype(gather_tag)::value;
         if (ntiles == 0) return;
         const int nstages = (ntiles + 1) >> 1;
-        if (GATHER) unit_gather += static_cast<unsigned int>(ntiles);   // 32-key tiles this workgroup stages in LDS
-        else unit_block += static_cast<unsigned int>(ntiles);
+        if (GATHER) staged_gather += static_cast<unsigned int>(ntiles);   // 32-key tiles this workgroup stages in LDS
+        else staged_block += static_cast<unsigned int>(ntiles);
         // Descriptor words of the two tiles of stage st (block phase): one LDS instruction; the records are padded with dead
         // entries, so a stage past the list reads as "not live, block 0".
         auto stage_desc = [&](int st, uint32_t (&d)[2]) __attribute__((always_inline)) {
@@ -451,40 +439,54 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                 f32x16 s0, s1, zero;
 #pragma unroll
                 for (int e = 0; e < 16; ++e) zero[e] = 0.f;
-                unit_tiles += 2;
+                tiles_done += 2;
                 read_k(2 * buf, k0);
                 read_k(2 * buf + 1, k1);
                 __builtin_amdgcn_sched_barrier(0);
-                const float mc = m_run * p.c;
-                float lsum = 0.f;
-                // steps of a softmax as a three-deep pipeline, as in vs_dense.hip
-                float tq[3] = {0.f, 0.f, 0.f};
-                auto softmax_steps = [&](f32x16& x, bf16x8 (&pk)[2], int from, int to) __attribute__((always_inline)) {
+                float mc = m_run * p.c, lsum = 0.f;
+                // steps of a softmax as a three-deep pipeline, as in vs_dense.hip; the scores stay as they are
+                float tq[4] = {0.f, 0.f, 0.f, 0.f};
+                auto pack_pair = [&](bf16x8 (&pk)[2], int e, float x0, float x1) __attribute__((always_inline)) {   // weights of e - 1 and e
+                    const f32x2 two = {x0, x1};
+                    uint32_t packed = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
+                    asm volatile("" : "+v"(packed));
+                    const bf16x2 r = __builtin_bit_cast(bf16x2, packed);
+                    pk[e >> 3][(e & 7) - 1] = r[0];
+                    pk[e >> 3][e & 7] = r[1];
+                };
+                auto softmax_steps = [&](const f32x16& x, bf16x8 (&pk)[2], int from, int to) __attribute__((always_inline)) {
 #pragma unroll
                     for (int k = from; k < to; ++k) {
                         // (the empty asm statements keep the arithmetic at this place)
                         if (k < 16) {
-                            tq[k % 3] = fmaf(x[k], p.c, -mc);
-                            asm volatile("" : "+v"(tq[k % 3]));
+                            tq[k & 3] = fmaf(x[k], p.c, -mc);
+                            asm volatile("" : "+v"(tq[k & 3]));
                         }
                         if (k >= 1 && k <= 16) {
-                            tq[(k - 1) % 3] = __builtin_amdgcn_exp2f(tq[(k - 1) % 3]);
-                            asm volatile("" : "+v"(tq[(k - 1) % 3]));
+                            tq[(k - 1) & 3] = __builtin_amdgcn_exp2f(tq[(k - 1) & 3]);
+                            asm volatile("" : "+v"(tq[(k - 1) & 3]));
                         }
                         if (k >= 2 && k <= 17) {
                             const int e = k - 2;
-                            x[e] = tq[e % 3];
-                            lsum += x[e];
+                            lsum += tq[e & 3];
                             asm volatile("" : "+v"(lsum));
-                            if (e & 1) {
-                                const f32x2 two = {x[e - 1], x[e]};
-                                uint32_t packed = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
-                                asm volatile("" : "+v"(packed));
-                                const bf16x2 r = __builtin_bit_cast(bf16x2, packed);
-                                pk[e >> 3][(e & 7) - 1] = r[0];
-                                pk[e >> 3][e & 7] = r[1];
-                            }
+                            if (e & 1) pack_pair(pk, e, tq[(e - 1) & 3], tq[e & 3]);
                         }
+                    }
+                };
+                // where a row of the tile with scores x may have grown; before: the stage's sum without it.  Before P V of the tile.
+                auto look_again = [&](const f32x16& x, bf16x8 (&pk)[2], float before) __attribute__((always_inline)) {
+                    const float m_old = m_run, m_new = fmaxf(m_run, half_swap_max(tile_max(x)));
+                    if (!__ballot((m_new - m_run) * p.c > kRescaleThreshold)) return;
+                    rescale(m_new);
+                    mc = m_run * p.c;
+                    lsum = before * __builtin_amdgcn_exp2f((m_old - m_run) * p.c);
+#pragma unroll
+                    for (int e = 0; e < 16; e += 2) {
+                        const float x0 = __builtin_amdgcn_exp2f(fmaf(x[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(x[e + 1], p.c, -mc));
+                        lsum += x0;
+                        lsum += x1;
+                        pack_pair(pk, e + 1, x0, x1);
                     }
                 };
                 auto first_scores = [&](auto with_loads) __attribute__((always_inline)) {
@@ -509,6 +511,8 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                     if (kk > 0) softmax_steps(s0, p0, 18 * (kk - 1) / 7, 18 * kk / 7);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                if (VS_MAY_HAVE_GROWN(lsum)) look_again(s0, p0, 0.f);
+                const float lsum0 = lsum;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
                     oacc[i & 3] = mfma32(v0[2 * (i & 3) + (i >> 2)], p0[i >> 2], oacc[i & 3]);
@@ -520,6 +524,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
                     if (i > 0) softmax_steps(s1, p1, 18 * (i - 1) / 7, 18 * i / 7);
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                if (VS_MAY_HAVE_GROWN(lsum)) look_again(s1, p1, lsum0);
                 l_run += lsum;
                 pv(p1, v1);
             } else {
@@ -534,12 +539,12 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
             if (alive) read_k(2 * buf, k0);
             if (blive) read_k(2 * buf + 1, k1);
             if (alive) {
-                ++unit_tiles;
+                ++tiles_done;
 #pragma unroll
                 for (int kk = 0; kk < 8; ++kk) s0 = mfma32(k0[kk], qf[kk], kk == 0 ? zero : s0);
             }
             if (blive) {
-                ++unit_tiles;
+                ++tiles_done;
 #pragma unroll
                 for (int kk = 0; kk < 8; ++kk) s1 = mfma32(k1[kk], qf[kk], kk == 0 ? zero : s1);
             }
@@ -577,7 +582,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
             }
             }
             if constexpr (!SETTLED) {
-                if (!settled && !second) settled = __ballot(m_run == NEG_INF) == 0ull;
+                if (!settled) settled = __ballot(m_run == NEG_INF) == 0ull;
             }
             a = na;
             b = nb;
@@ -670,8 +675,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
     }
 
     // ---- epilogue: O = O^T / l in bf16; lse = m * scale + ln(l) ----
-    // (read behind the barrier that opens the next unit; what is stored now is then stored once more)
-    const bool bad = settled && outgrown(oacc, l_run);
     // A lane holds 8-byte pieces of one output row; stored directly they would be 64 scattered pieces per instruction.
     // The row block goes through the wavefront's own 8.5 KB of the (now idle) ring instead: written as held, read back
     // 16 bytes per lane, so that 16 lanes store one whole 256-byte row and an instruction stores four rows.
@@ -679,7 +682,6 @@ __global__ __launch_bounds__(kThreads, 2) void vs_attention_kernel(const AttnPar
         int etid = threadIdx.x;                              // (the lane's constants anew: kept over the phases they were spilled)
         asm volatile("" : "+v"(etid));
         const int lane = etid & 63, qi = lane & 31, hh = lane >> 5;
-        if (lane == 0) wtot[wave] = bad ? 1 : 0;
         const float l_tot = half_swap_sum(l_run);
         const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
         constexpr int kPitch = 256 + 16;                     // row pitch in LDS: 16-byte aligned, spreads the rows over the banks

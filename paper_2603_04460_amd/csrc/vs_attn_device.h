@@ -222,23 +222,13 @@ __device__ __forceinline__ void lds_load_tile(uint32_t voff, const uint16_t* row
 
 // ---- stages without a row maximum ----
 // Most stages of a long row block take the maximum as it stands after its first stages instead of looking for a new one: any
-// value serves as long as nothing overflows or vanishes, and the precision of P, O and the sum is relative.  Scores below it lose
-// what they lost before; scores above it make P, O and the sum larger than with a maximum that follows (where P stays below
-// 2^kRescaleThreshold).  At the end of a row block this says whether a row has left the safe range, in which case the row
-// block is computed again with a maximum in every stage.  Sums up to 2^28 (2^20 keys at the threshold) were possible before; up to
-// 2^kOutgrown the reciprocal and the logarithm are good, and O is if it is finite.  Sums that are not numbers count as outgrown.
-constexpr float kSafeSum = 268435456.f;        // 2^28
-constexpr float kOutgrownSum = 1.152921504606847e18f;   // 2^60
-__device__ __forceinline__ bool outgrown(const f32x16 (&oacc)[4], float l_run) {
-    const float l = half_swap_sum(l_run);
-    if (!__ballot(!(l <= kSafeSum))) return false;
-    float worst = 0.f;                                       // NaN as soon as an element is not finite (x - x)
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) worst += oacc[db][e] - oacc[db][e];
-    return __ballot(!(l < kOutgrownSum) || worst != 0.f) != 0ull;
-}
+// value serves as long as nothing overflows or vanishes, and the precision of P, O and the sum is relative.  The sum of a lane's
+// weights in the stage says whether that held: no weight is above 2^kRescaleThreshold if the sum is not.  If it is (not true for NaN, where no
+// maximum helps) the stage looks for its maximum after all, the scores being at hand still, and if a row has grown by more than the threshold
+// it moves the maximum and weighs its scores anew, before anything has been added to O or to the sum.  So the maximum moves where it
+// would with a search in every stage, and a key whose score leaves all before it behind has a weight of exactly one.
+constexpr float kGrownSum = 256.f;             // 2^kRescaleThreshold
+#define VS_MAY_HAVE_GROWN(lane_sum) __builtin_expect(__ballot((lane_sum) > kGrownSum) != 0ull, 0)   // (a function loses the expectation)
 
 // ---- row blocks whose keys are split: the partial results meet in LDS (every tile buffer is idle by then) ----
 // Eight partials: O in 64 registers x 64 lanes each, then (maximum, sum) per partial and lane.

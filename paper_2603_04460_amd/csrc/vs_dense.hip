@@ -71,11 +71,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     unsigned char* const kvbuf = smem;
     const float NEG_INF = -INFINITY;
     const int bid = blockIdx.x;
-    // second pass: with a maximum in every stage, where the first has outgrown the maximum of its first stages
-    bool second = false;
-    for (;;) {
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));                            // nothing is carried from pass to pass
+    const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qi = lane & 31, hh = lane >> 5;
@@ -304,48 +300,46 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         // Softmax elements as a three-deep pipeline: step k scales element k, takes the exponential of element k-1 and adds
         // element k-2 to the row sum (packing a finished pair): no instruction uses the result of its predecessor.
         float mc = 0.f, lsum = 0.f;
-        float tq[3] = {0.f, 0.f, 0.f};                       // values in flight, indexed by element mod 3
+        float tq[4] = {0.f, 0.f, 0.f, 0.f};                  // values in flight, indexed by element mod 4
         int estep = 0;
+        auto pack_pair = [&](int u, int e, float x0, float x1) __attribute__((always_inline)) {   // weights of elements e - 1 and e
+            const f32x2 two = {x0, x1};
+            uint32_t packed = __builtin_bit_cast(uint32_t, __builtin_convertvector(two, bf16x2));
+            asm volatile("" : "+v"(packed));
+            const bf16x2 r = __builtin_bit_cast(bf16x2, packed);
+            pb[VR][u][e >> 3][(e & 7) - 1] = r[0];
+            pb[VR][u][e >> 3][e & 7] = r[1];
+        };
         auto expstep = [&]() __attribute__((always_inline)) {
             if constexpr (HAS_S) {
                 const int k = estep;
                 if (k < 32) {
                     float t = fmaf(sc[VR][k >> 4][k & 15], p.c, -mc);
                     asm volatile("" : "+v"(t));
-                    tq[k % 3] = t;
+                    tq[k & 3] = t;
                 }
                 if (k >= 1 && k <= 32) {
-                    float x = tq[(k - 1) % 3];
+                    float x = tq[(k - 1) & 3];
                     x = __builtin_amdgcn_exp2f(x);
                     asm volatile("" : "+v"(x));              // keeps the arithmetic at this place
-                    tq[(k - 1) % 3] = x;
+                    tq[(k - 1) & 3] = x;
                 }
                 if (k >= 2 && k <= 33) {
                     const int idx = k - 2, u = idx >> 4, e = idx & 15;
-                    const float x = tq[idx % 3];
-                    lsum += x;
+                    lsum += tq[idx & 3];
                     asm volatile("" : "+v"(lsum));
-                    sc[VR][u][e] = x;
-                    if (e & 1) {
-                        const f32x2 two = {sc[VR][u][e - 1], sc[VR][u][e]};
-                        const bf16x2 r = __builtin_convertvector(two, bf16x2);
-                        uint32_t packed = __builtin_bit_cast(uint32_t, r);
-                        asm volatile("" : "+v"(packed));
-                        const bf16x2 r2 = __builtin_bit_cast(bf16x2, packed);
-                        pb[VR][u][e >> 3][(e & 7) - 1] = r2[0];
-                        pb[VR][u][e >> 3][e & 7] = r2[1];
-                    }
+                    if (e & 1) pack_pair(u, e, tq[(idx - 1) & 3], tq[idx & 3]);
                 }
                 ++estep;
             }
         };
-        // 34 steps: over the 32 matrix instructions, or (MASKED) over the 26 behind the row maximum
+        // 34 steps: over the first 31 matrix instructions (in front of the last is the look at the sum), or (MASKED) over the 26 behind the row maximum
         auto expsteps_upto = [&](int target) __attribute__((always_inline)) {
             while (estep < target) expstep();
         };
         auto exp_share = [&](int j) __attribute__((always_inline)) {   // behind matrix instruction j
             if constexpr (MASKED) expsteps_upto(((j - 5) * 34 + 25) / 26);
-            else expsteps_upto(((j + 1) * 34 + 31) / 32);
+            else expsteps_upto(min(34, ((j + 1) * 34 + 30) / 31));
         };
         // ---- part 1: first matrix instructions | V fragments (X slot) | row maximum (MASKED) ----
         float mx0 = NEG_INF, mx1 = NEG_INF;
@@ -386,19 +380,49 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             }
             VS_FENCE();
         });
+        // mx: the lane's largest score of the stage; has the maximum moved?
+        auto rescale = [&](float mx) __attribute__((always_inline)) -> bool {
+            const float m_new = fmaxf(m_run[VR], half_swap_max(mx));
+            if (!__ballot((m_new - m_run[VR]) * p.c > kRescaleThreshold)) return false;
+            const float alpha = (m_new == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f((m_run[VR] - m_new) * p.c);
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) oacc[VR][db][e] *= alpha;
+            l_run[VR] *= alpha;
+            m_run[VR] = m_new;
+            return true;
+        };
         if constexpr (HAS_S && MASKED) {
-            const float m_new = fmaxf(m_run[VR], half_swap_max(fmaxf(mx0, mx1)));
-            if (__ballot((m_new - m_run[VR]) * p.c > kRescaleThreshold)) {
-                const float alpha = (m_new == NEG_INF) ? 1.f : __builtin_amdgcn_exp2f((m_run[VR] - m_new) * p.c);
-#pragma unroll
-                for (int db = 0; db < 4; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) oacc[VR][db][e] *= alpha;
-                l_run[VR] *= alpha;
-                m_run[VR] = m_new;
-            }
+            rescale(fmaxf(mx0, mx1));
             mc = m_run[VR] == NEG_INF ? 0.f : m_run[VR] * p.c;
         }
+        // the sum is complete: weigh the stage's scores anew if a row has grown
+        auto look_again = [&]() __attribute__((always_inline)) {
+            if (VS_MAY_HAVE_GROWN(lsum)) {                   // (P V of this stage and block is issued in the next slot)
+                float mx[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    mx[u] = fmaxf(fmaxf(sc[VR][u][0], sc[VR][u][1]), sc[VR][u][2]);
+#pragma unroll
+                    for (int e = 3; e < 15; e += 2) mx[u] = fmaxf(fmaxf(mx[u], sc[VR][u][e]), sc[VR][u][e + 1]);
+                    mx[u] = fmaxf(mx[u], sc[VR][u][15]);
+                }
+                if (rescale(fmaxf(mx[0], mx[1]))) {
+                    mc = m_run[VR] * p.c;
+                    lsum = 0.f;
+#pragma unroll
+                    for (int idx = 0; idx < 32; idx += 2) {
+                        const int u = idx >> 4, e = idx & 15;
+                        const float x0 = __builtin_amdgcn_exp2f(fmaf(sc[VR][u][e], p.c, -mc));
+                        const float x1 = __builtin_amdgcn_exp2f(fmaf(sc[VR][u][e + 1], p.c, -mc));
+                        lsum += x0;
+                        lsum += x1;
+                        pack_pair(u, e + 1, x0, x1);
+                    }
+                }
+            }
+        };
         // ---- part 2: remaining matrix instructions | K fragments (Y slot) | exponentials ----
         uint32_t kb[2];                                      // K fragments of stage sq + 1 (past the last stage: a stale slot, never used)
         if constexpr (MR == 1 && HAS_Q) {
@@ -420,6 +444,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         });
         unroll<0, 16>([&](auto index) __attribute__((always_inline)) {   // 16 P V products
             constexpr int j = decltype(index)::value;
+            if constexpr (HAS_S && !MASKED && j == 15) look_again();
             if constexpr (HAS_P) pmfma(j);
             VS_FENCE();
             if constexpr (DUO && MR == 1 && HAS_Q) {         // K of stage sq + 1, first and second tile
@@ -485,8 +510,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
         i = 2;
     }
     // from here on without a maximum, up to the diagonal
-    const int to = second || __ballot(m_run[0] == NEG_INF || m_run[1] == NEG_INF) ? 0 : min(nst, nfree);
-    const bool optimistic = i < to;
+    const int to = __ballot(m_run[0] == NEG_INF || m_run[1] == NEG_INF) ? 0 : min(nst, nfree);
     for (; i < to && (DUO ? i + 2 < to : i < nst - 3); ++i) {   // (stage i + 2 is loaded, and whole)
         slot(R0{}, T{}, T{}, T{}, F{}, T{}, i, i - 1);
         slot(R1{}, T{}, T{}, T{}, F{}, T{}, i, i);
@@ -501,23 +525,6 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     }
     slot(R0{}, F{}, T{}, T{}, T{}, F{}, nst, nst - 1);        // X(nst): P V of block 0; softmax of block 1
     slot(R1{}, F{}, T{}, F{}, T{}, F{}, nst, nst);            // Y(nst): P V of block 1
-
-    bool again = optimistic && (outgrown(oacc[0], l_run[0]) || outgrown(oacc[1], l_run[1]));
-    if constexpr (!DUO) {
-        // the stages are shared: if one wavefront has to, all start again (the ring is free: every wavefront has passed
-        // the barrier of Y(nst))
-        if (nst > 3 && !second) {                        // (else no wavefront had a stage without a maximum)
-            int* const flag = reinterpret_cast<int*>(smem);
-            if (lane == 0) flag[wave] = again ? 1 : 0;
-            __syncthreads();
-            again = (flag[0] | flag[1] | flag[2] | flag[3]) != 0;
-            __syncthreads();
-        }
-    }
-    if (again) {
-        second = true;
-        continue;
-    }
 
     if constexpr (DUO) {
         __syncthreads();                                     // every buffer is idle
@@ -551,8 +558,6 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
             if (p.lse && hh == 0)
                 p.lse[static_cast<size_t>(my_head[rb]) * p.nq + (row - p.pos0)] = l_tot > 0.f ? m_run[rb] * p.scale + __logf(l_tot) : NEG_INF;
         }
-    }
-    return;
     }
 }
 

@@ -43,8 +43,7 @@ constexpr int kRecPad = 2 * kStage;            // dead records after the last li
 constexpr size_t kRingBytes = 2 * kStage * kSlotBytes;
 constexpr size_t kRecOff = kRingBytes;
 constexpr size_t kGatherOff = kRecOff + (kListCap + 4 * kRecPad) * 16;
-constexpr size_t kFlagBytes = 64;              // behind everything else: a word per wavefront, has its row block outgrown the maximum
-constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4 + kFlagBytes;
+constexpr size_t kSparseLds = kGatherOff + kGatherCap * 4;
 static_assert(kPartialBytes + 8 * 4 <= kRingBytes, "partial results in the idle ring");
 static_assert(kSparseLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % (32 * kStage) == 0, "whole stages");
@@ -87,47 +86,58 @@ struct RowBlock {
     f32x16 oacc[4];
     float m_run, l_run;
     int settled;                                             // every row has a maximum, which stays as it is (vs_attn_device.h)
-    int second;                                              // second attempt: never settled
 
     // Q fragments: B operand of S^T = K Q^T; lane holds query qi, d = 16 kk + 8 hh .. +7
-    __device__ __forceinline__ void load_q(const AttnParams& p, int head, int first, int qi, int hh) {
+    __device__ __forceinline__ void init(const AttnParams& p, int head, int first, int qi, int hh) {
         const int row = min(first + qi, p.pos0 + p.nq - 1);  // rows that do not exist are not stored
         const uint16_t* src = p.q + (static_cast<size_t>(head) * p.nq + (row - p.pos0)) * kD + 8 * hh;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * kk));
         // (waited for here: at its first use, in the tile loop, the compiler would wait for every load in flight, in every tile)
         __builtin_amdgcn_s_waitcnt(0x0F70);
-    }
-    __device__ __forceinline__ void start(bool again) {
         m_run = -INFINITY;
         l_run = 0.f;
         settled = 0;
-        second = again ? 1 : 0;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
             for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
     }
-    __device__ __forceinline__ bool has_outgrown() { return settled && outgrown(oacc, l_run); }
-    __device__ __forceinline__ void new_maximum(const AttnParams& p, const f32x16& s) {
+    // has the maximum moved?
+    __device__ __forceinline__ bool new_maximum(const AttnParams& p, const f32x16& s) {
         float mx = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
         for (int e = 3; e < 15; e += 2) mx = fmaxf(fmaxf(mx, s[e]), s[e + 1]);
         const float m_new = fmaxf(m_run, half_swap_max(fmaxf(mx, s[15])));
-        if (__ballot((m_new - m_run) * p.c > kRescaleThreshold)) {   // false when both are -inf
-            const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * p.c);
+        if (!__ballot((m_new - m_run) * p.c > kRescaleThreshold)) return false;   // (false when both are -inf)
+        const float alpha = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f((m_run - m_new) * p.c);
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < 4; ++db)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
-            l_run *= alpha;
-            m_run = m_new;
+            for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+        l_run *= alpha;
+        m_run = m_new;
+        return true;
+    }
+    // weights of a tile in bf16 and the lane's sum of them
+    __device__ __forceinline__ float weigh(const AttnParams& p, const f32x16& s, bf16x8 (&pb)[2]) {
+        const float mc = (m_run == -INFINITY) ? 0.f : m_run * p.c;
+        float lsum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+            const float x0 = __builtin_amdgcn_exp2f(fmaf(s[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(s[e + 1], p.c, -mc));
+            lsum[0] += x0;
+            lsum[1] += x1;
+            const f32x2 two = {x0, x1};
+            const bf16x2 r = __builtin_convertvector(two, bf16x2);
+            pb[e >> 3][e & 7] = r[0];
+            pb[e >> 3][(e & 7) + 1] = r[1];
         }
-        settled = !second && __ballot(m_run == -INFINITY) == 0ull ? 1 : 0;
+        return lsum[0] + lsum[1];
     }
     // A tile: its K fragments are in registers, its V (v_there() waits for it) at `at`; kind: 0 nothing of it counts, 1 whole, 2 masked with the
     // keep-bits (bit 27 - 8a - c of element 4a + c) that keep() gives.  v_read(): the V fragments are in registers.
-    // SETTLED: the maximum stays as it is
+    // SETTLED: the maximum stays as it is, unless a row has grown
     template <bool SETTLED, class Keep, class Wait, class Load>
     __device__ __forceinline__ void tile(const AttnParams& p, const bf16x8 (&kf)[8], const Fragments& fr, const unsigned char* at, int kind,
                                          Keep keep, Wait v_there, Load v_read) {
@@ -145,20 +155,17 @@ struct RowBlock {
         __builtin_amdgcn_sched_barrier(0);
         if (kind == 2) mask_elements<0>(s, keep(), __float_as_uint(-INFINITY));
         if (kind) {
-            if constexpr (!SETTLED) new_maximum(p, s);
-            const float mc = (m_run == -INFINITY) ? 0.f : m_run * p.c;
-            float lsum[2] = {0.f, 0.f};
-#pragma unroll
-            for (int e = 0; e < 16; e += 2) {
-                const float x0 = __builtin_amdgcn_exp2f(fmaf(s[e], p.c, -mc)), x1 = __builtin_amdgcn_exp2f(fmaf(s[e + 1], p.c, -mc));
-                lsum[0] += x0;
-                lsum[1] += x1;
-                const f32x2 two = {x0, x1};
-                const bf16x2 r = __builtin_convertvector(two, bf16x2);
-                pb[e >> 3][e & 7] = r[0];
-                pb[e >> 3][(e & 7) + 1] = r[1];
+            if constexpr (!SETTLED) {
+                new_maximum(p, s);
+                settled = __builtin_amdgcn_readfirstlane(__ballot(m_run == -INFINITY) == 0ull ? 1 : 0);
             }
-            l_run += lsum[0] + lsum[1];
+            float lsum = weigh(p, s, pb);
+            if constexpr (SETTLED) {
+                if (VS_MAY_HAVE_GROWN(lsum)) {
+                    if (new_maximum(p, s)) lsum = weigh(p, s, pb);
+                }
+            }
+            l_run += lsum;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         v_read();
@@ -185,18 +192,6 @@ struct RowBlock {
     }
 };
 
-// Behind the last tile of a first attempt: does any wavefront of the workgroup ask for a second?  (The stages are shared.)  The barrier
-// also leaves every buffer idle.
-__device__ __forceinline__ bool any_outgrown(RowBlock& rb, int* flags, int wave) {
-    const bool bad = rb.has_outgrown();
-    if ((threadIdx.x & 63) == 0) flags[wave] = bad ? 1 : 0;
-    __syncthreads();
-    int any = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) any |= flags[w];
-    return __builtin_amdgcn_readfirstlane(any) != 0;
-}
-
 // keep-bits (bit 27 - 8a - c of element 4a + c) of a gathered tile: column <= row; cols: the tile's columns from 4 hh on
 __device__ __forceinline__ uint32_t causal_columns(const int* cols, int row) {
     uint32_t keep = 0u;
@@ -217,7 +212,6 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
     unsigned char* const kvbuf = smem;
     uint4* const list_rec = reinterpret_cast<uint4*>(smem + kRecOff);
     int* const glist = reinterpret_cast<int*>(smem + kGatherOff);
-    const float NEG_INF = -INFINITY;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -239,7 +233,7 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
     const uint16_t* __restrict__ vbase = p.v + static_cast<size_t>(g) * n * kD;
 
     RowBlock row_block;
-    row_block.load_q(p, my_head, my_i0, qi, hh);
+    row_block.init(p, my_head, my_i0, qi, hh);
     const Fragments fr(lane);
     // staging: wavefront w fills group w (rows 4 w + L / 16) of the K and of the V tile of every slot of the stage
     const int st_row = tid >> 4;
@@ -281,11 +275,8 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
         }
         __syncthreads();                                     // the ring and the lists are reused
     };
-    unsigned int tiles_done, staged_gather, staged_block;
-    int* const flags = reinterpret_cast<int*>(smem + (DENSE ? kRingBytes : kSparseLds - kFlagBytes));
-    for (bool again = false;; again = true) {
-    row_block.start(again);
-    tiles_done = staged_gather = staged_block = 0;
+    unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
+
     if constexpr (DENSE) {
         const int nblk = i_last / 32 + 1;
         run_phase(
@@ -372,8 +363,6 @@ __global__ __launch_bounds__(kThreads) void vs_short_kernel(const AttnParams p) 
                 });
         }
     }
-    if (DENSE || again || !any_outgrown(row_block, flags, wave)) break;
-    }
 
     // (the ring is idle: every phase ends with a barrier)
     row_block.merge<kSplits>(p, smem, rb, kRowBlocks, split, my_head, my_i0, DENSE ? nullptr : &tiles_done);
@@ -389,7 +378,7 @@ constexpr int kLone = kThreads / 64;           // wavefronts = tiles in flight
 constexpr size_t kLoneRing = kLone * kSlotBytes;
 constexpr size_t kLoneRecOff = kLoneRing;
 constexpr size_t kLoneGatherOff = kLoneRecOff + (kListCap + 1) * 16;
-constexpr size_t kLoneLds = kLoneGatherOff + kGatherCap * 4 + kFlagBytes;
+constexpr size_t kLoneLds = kLoneGatherOff + kGatherCap * 4;
 static_assert(kPartialBytes + 8 * 4 <= kLoneRing, "partial results in the idle buffers");
 static_assert(kLoneLds <= 160 * 1024, "one workgroup per compute unit");
 static_assert(kGatherCap % 32 == 0, "whole tiles");
@@ -399,7 +388,6 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
     uint4* const list_rec = reinterpret_cast<uint4*>(smem + kLoneRecOff);
     int* const glist = reinterpret_cast<int*>(smem + kLoneGatherOff);
-    const float NEG_INF = -INFINITY;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -414,7 +402,7 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
     unsigned char* const slot = smem + wave * kSlotBytes;
 
     RowBlock rb;
-    rb.load_q(p, my_head, my_i0, qi, hh);
+    rb.init(p, my_head, my_i0, qi, hh);
     const Fragments fr(lane);
     // staging: this wavefront fills all eight groups of its tile, lane L the piece of row 4 grp + L / 16
     const int st_rho = (lane >> 4) & 3;
@@ -422,7 +410,10 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
     const uint32_t st_bv = static_cast<uint32_t>(16 * (4 * ((((lane >> 2) & 3) - st_rho) & 3) + (lane & 3)));
     uint32_t off[8];                                         // byte offsets of the rows of the tile that is loaded next,
     int whole = -1;                                          // or its first row, if they all exist and stand one behind the other
-    auto load = [&](uint32_t piece, const uint16_t* base, unsigned char* dst) __attribute__((always_inline)) {
+    auto load = [&](uint32_t piece, const uint16_t* base, int offset) __attribute__((always_inline)) {   // into the own slot
+        int w = wave;
+        if constexpr (DENSE) asm volatile("" : "+s"(w));     // (the LDS addresses, merged over calls, ended up in vector registers)
+        unsigned char* const dst = smem + w * kSlotBytes + offset;
         if (DENSE && whole >= 0) {
             lds_load_tile(static_cast<uint32_t>(st_rho) * 256u + piece, base + static_cast<size_t>(whole) * kD, dst);
             return;
@@ -444,8 +435,8 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
         int t = wave;
         if (t >= ntiles) return;
         rows(t);
-        load(st_bk, kbase, slot);
-        load(st_bv, vbase, slot + kTileBytes);
+        load(st_bk, kbase, 0);
+        load(st_bv, vbase, kTileBytes);
         auto step = [&](auto settled) __attribute__((always_inline)) {
             const bool more = t + kLone < ntiles;
             const int kind = need(t);
@@ -454,7 +445,7 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
             bf16x8 kf[8];
             fr.read_k(slot, kf);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            if (more) load(st_bk, kbase, slot);
+            if (more) load(st_bk, kbase, 0);
             rb.tile<decltype(settled)::value>(
                 p, kf, fr, slot, kind, [&]() __attribute__((always_inline)) { return keep(t); },
                 [&]() __attribute__((always_inline)) {       // V of tile t (K of the next is younger)
@@ -462,7 +453,7 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
                     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 },
                 [&]() __attribute__((always_inline)) {
-                    if (more) load(st_bv, vbase, slot + kTileBytes);
+                    if (more) load(st_bv, vbase, kTileBytes);
                 });
             t += kLone;
         };
@@ -473,11 +464,7 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
             while (t < ntiles) step(std::false_type{});
         }
     };
-    unsigned int tiles_done, staged_gather, staged_block;
-    int* const flags = reinterpret_cast<int*>(smem + (DENSE ? kLoneRing : kLoneLds - kFlagBytes));
-    for (bool again = false;; again = true) {
-    rb.start(again);
-    tiles_done = staged_gather = staged_block = 0;
+    unsigned int tiles_done = 0, staged_gather = 0, staged_block = 0;
     if constexpr (DENSE) {
         auto dlt = [&](int t) { return my_i0 - 32 * t; };    // offset of (row 0, key 0)
         run(
@@ -546,19 +533,14 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
             __syncthreads();                                 // the lists are reused
         }
     }
-    if (!DENSE || again) {
-        __syncthreads();                                     // every buffer is idle: the partial results take their place
-        break;
-    }
-    if (!any_outgrown(rb, flags, wave)) break;
-    }
+    __syncthreads();                                         // every buffer is idle: the partial results take their place
     rb.merge<kLone>(p, smem, 0, 1, wave, my_head, my_i0, DENSE ? nullptr : &tiles_done);
     if (!DENSE && tid == 0) add_statistics(p, tiles_done, staged_gather, staged_block);
 }
 
 template <bool DENSE, int ROWS>
 int launch_short(AttnParams& p, hipStream_t stream) {
-    constexpr size_t lds = ROWS == 1 ? (DENSE ? kLoneRing + kFlagBytes : kLoneLds) : (DENSE ? kRingBytes + kFlagBytes : kSparseLds);
+    constexpr size_t lds = ROWS == 1 ? (DENSE ? kLoneRing : kLoneLds) : (DENSE ? kRingBytes : kSparseLds);
     void (*kernel)(AttnParams);
     if constexpr (ROWS == 1) kernel = &vs_lone_kernel<DENSE>;
     else kernel = &vs_short_kernel<DENSE, ROWS>;
