@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
                     if constexpr (JJ == 10 && HAS_P) asm volatile("s_waitcnt lgkmcnt(4)" ::: "memory");
                     if constexpr (JJ == 18) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                     int row0 = own_rows(sq, U);
-                    if constexpr (MASKED) row0 = row0 < 32 * nblk ? row0 : 0;   // (without a mask every tile is the workgroup's)
+                    if constexpr (!SPREAD) row0 = row0 < 32 * nblk ? row0 : 0;
                     load_own(whole, 1, U, std::integral_constant<int, (JJ - 10) % 8>{}, row0);
                 }
             }
@@ -503,25 +503,24 @@ __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) 
     }
     slot(R0{}, T{}, F{}, F{}, T{}, F{}, 0, 0);                // X(0): scores of block 0
     slot(R1{}, T{}, F{}, T{}, T{}, F{}, 0, 0);                // Y(0): scores of block 1; softmax of block 0
-    int i = 1;
-    if (nst > 1) {                                       // (X(1) has the softmax of block 1 for stage 0)
-        slot(R0{}, T{}, T{}, T{}, T{}, F{}, 1, 0);
-        slot(R1{}, T{}, T{}, T{}, T{}, F{}, 1, 1);
-        i = 2;
-    }
-    // from here on without a maximum, up to the diagonal
-    const int to = __ballot(m_run[0] == NEG_INF || m_run[1] == NEG_INF) ? 0 : min(nst, nfree);
-    for (; i < to && (DUO ? i + 2 < to : i < nst - 3); ++i) {   // (stage i + 2 is loaded, and whole)
-        slot(R0{}, T{}, T{}, T{}, F{}, T{}, i, i - 1);
-        slot(R1{}, T{}, T{}, T{}, F{}, T{}, i, i);
-    }
-    for (; i < to; ++i) {
-        slot(R0{}, T{}, T{}, T{}, F{}, F{}, i, i - 1);
-        slot(R1{}, T{}, T{}, T{}, F{}, F{}, i, i);
-    }
-    for (; i < nst; ++i) {
-        slot(R0{}, T{}, T{}, T{}, T{}, F{}, i, i - 1);
-        slot(R1{}, T{}, T{}, T{}, T{}, F{}, i, i);
+    if (nst > 1) {
+        slot(R0{}, T{}, T{}, T{}, T{}, F{}, 1, 0);            // X(1): softmax of block 1 for stage 0
+        // Y(i) and X(i + 1) have the softmax of stage i: from here on without a maximum, up to the diagonal
+        const int to = __ballot(m_run[0] == NEG_INF || m_run[1] == NEG_INF) ? 0 : min(nst - 1, nfree);
+        int i = 1;
+        for (; i < to && (DUO ? i + 2 < to : i < nst - 3); ++i) {   // (stage i + 2 is loaded, and whole)
+            slot(R1{}, T{}, T{}, T{}, F{}, T{}, i, i);
+            slot(R0{}, T{}, T{}, T{}, F{}, T{}, i + 1, i);
+        }
+        for (; i < to; ++i) {
+            slot(R1{}, T{}, T{}, T{}, F{}, F{}, i, i);
+            slot(R0{}, T{}, T{}, T{}, F{}, F{}, i + 1, i);
+        }
+        for (; i < nst - 1; ++i) {
+            slot(R1{}, T{}, T{}, T{}, T{}, F{}, i, i);
+            slot(R0{}, T{}, T{}, T{}, T{}, F{}, i + 1, i);
+        }
+        slot(R1{}, T{}, T{}, T{}, T{}, F{}, nst - 1, nst - 1);
     }
     slot(R0{}, F{}, T{}, T{}, T{}, F{}, nst, nst - 1);        // X(nst): P V of block 0; softmax of block 1
     slot(R1{}, F{}, T{}, F{}, T{}, F{}, nst, nst);            // Y(nst): P V of block 1
