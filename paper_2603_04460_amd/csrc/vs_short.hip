@@ -93,8 +93,6 @@ struct RowBlock {
         const uint16_t* src = p.q + (static_cast<size_t>(head) * p.nq + (row - p.pos0)) * kD + 8 * hh;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) qf[kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(src + 16 * kk));
-        // (waited for here: at its first use, in the tile loop, the compiler would wait for every load in flight, in every tile)
-        __builtin_amdgcn_s_waitcnt(0x0F70);
         m_run = -INFINITY;
         l_run = 0.f;
         settled = 0;
@@ -434,6 +432,8 @@ __global__ __launch_bounds__(kThreads) void vs_lone_kernel(const AttnParams p) {
     auto run = [&](int ntiles, auto rows, auto need, auto keep) __attribute__((always_inline)) {
         int t = wave;
         if (t >= ntiles) return;
+        // (Q is waited for here: at its first use, in the tile loop, the compiler would wait for every load in flight, in every tile)
+        __builtin_amdgcn_s_waitcnt(0x0F70);
         rows(t);
         load(st_bk, kbase, 0);
         load(st_bv, vbase, kTileBytes);
