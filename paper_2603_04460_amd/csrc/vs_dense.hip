@@ -53,7 +53,6 @@ __device__ __forceinline__ void unroll(F f) {
 
 constexpr int kShortUnits = 128;               // workgroups up to which the keys of a row block are split
 constexpr int kDuoKeys = 2048;
-constexpr int kDuoAverage = 2000;
 
 // DUO: few row blocks.  The workgroup has two row blocks, and every wavefront owns both; the keys are split over the wavefronts, which
 // take stages of two tiles in turn, each through a K and a V buffer of its own that it fills itself (no barrier): stage i of
@@ -638,18 +637,12 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
     const bool few_tiles = p.hc <= 2 && n_kv * p.hc <= 64;
     if (units <= kShortUnits && !few_tiles) {
         const int rows = vs::dense_lone(p.q_heads, p.nq, p.pos0) ? 1 : 2;
-        const int heads = p.hc = vs::short_heads(p.hc, rows);
+        p.hc = vs::short_heads(p.hc, rows);
         // Of these, more than 256 row blocks against at least 2048 keys: two row blocks per wavefront (DUO).  There / vs_short_kernel, us:
         // 8 x 2048 22 / 25, 16 / 4 x 2048 33 / 33, 12 x 2600 79 / 80, 32 / 8, 500 rows of 2048 24 / 26, 1024 of 4096 73 / 80, of 32768 567 / 648;
         // with fewer keys the fill and the larger stages cost as much: 16 / 4 x 1700 27 / 26, 24 x 1280 25 / 24, 32 / 8 x 1024 24 / 22,
         // 128 x 200 18 / 15 (but 8 / 2 x 1500 17 / 19).
-        // Two heads of a group in a workgroup, more than a round and a quarter of workgroups and less than 2000 keys to a row on average: vs_short_kernel,
-        // whose workgroups start faster (there / here: 8 / 2 x 2900 32.2 / 29.2, x 3534 39.0 / 37.7, 16 / 4 x 2048 32.5 / 29.3, 16 / 4 heads, 2000 rows of
-        // 2600 keys 41.1 / 38.7, 32 / 8, 750 of 2100 39.6 / 38.2, 12 / 6 x 2600 36.4 / 34.1; not: 8 / 2 x 2400 24.7 / 25.1, x 4000 45.1 / 45.5, 6 / 3 x 3000
-        // 26.6 / 30.9, 32 / 8, 1000 of 2600 46.4 / 47.0; one head of its own to a workgroup 12 x 2600 37 / 54).
-        const int64_t row_blocks = q_heads * ((n_q + 31) / 32);
-        const bool many_short = heads >= 2 && row_blocks > 640 && pos0 + n_q / 2 < kDuoAverage;
-        if (rows == 2 && n_kv >= kDuoKeys && !many_short) return launch_dense<true>(p, static_cast<hipStream_t>(stream));
+        if (rows == 2 && n_kv >= kDuoKeys) return launch_dense<true>(p, static_cast<hipStream_t>(stream));
         return vs::launch_short_dense(p, rows, static_cast<hipStream_t>(stream));
     }
     if (n_kv >= kDuoKeys && duo_is_faster(q_heads, n_q, pos0)) {

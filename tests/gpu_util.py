@@ -77,8 +77,7 @@ def dense_form(hq, hk, n_q, n, pos0=0):
             return "lone"
         if hq * blocks <= 2 * lone and last >= _number("vs_attn_device.h", "kLoneTiles") and 2 * (last - lone // hq) < last:
             return "lone"
-        many_short = _heads_per_workgroup(hq, hk, False) >= 2 and hq * blocks > 640 and pos0 + n_q // 2 < _number("vs_dense.hip", "kDuoAverage")
-        return "duo" if n >= keys and not many_short else "short"
+        return "duo" if n >= keys else "short"
     work = hq * (blocks * (last - blocks) + blocks * (blocks + 1) // 2)
     a, b, c, d = (float(x) for x in re.search(r"return ([\d.]+) \* static_cast<double>\(work\) / 1024.0 \+ ([\d.]+) \* static_cast<double>\(rounds\) <\s+"
                                               r"([\d.]+) \* ([\d.]+) \* static_cast<double>", open(os.path.join(CSRC, "vs_dense.hip")).read()).groups())
