@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kThreads, 2) void vs_sweep_kernel(const SweepParams
             if constexpr (!MASKED) {
                 // The maxima as they stand, if no entry is more than 2^8 above its row's (the sums say so; not true for NaN); else the
                 // tile is taken again and moves them, each time, or entries a little above would send every tile there.  (Maximum of every tile,
-                // moved beyond 2^8: 32 / 8 heads, n = 16384 1.02 ms, 45 vector instructions beside the exponentials of a block, now 33, 0.96.  Matrix
+                // moved beyond 2^8: 32 / 8 heads, n = 16384 1.02 ms, now 0.96; n = 131072 55 vector instructions a tile beside matrix and exponentials, now 41.  Matrix
                 // instructions issued between the exponentials, as in the column sweep: 1.00, three wavefronts share a SIMD here.)
                 if (settled) {
                     float sum[NB][2];

@@ -40,8 +40,10 @@
 // stands (vs_attn_device.h, "stages without a row maximum"): the exponentials of a tile then wait for nothing but its scores and run
 // beside the next tile's score products, the V fragment reads and the staging loads likewise, one behind each matrix instruction.
 // Against a joint maximum between the score products and P V: 32 / 8 heads x 32768, 1024 + 2048 listed 1517 -> 1448 us, the 128k
-// layer 7.45 -> 7.14 ms, short lists (layers of 4096 to 46000 positions) 0 to 2 %.  The matrix core is busy 56 % of the cycles (52 %), at
-// 1.75 GHz (1.80): like the dense kernel this one runs against the chip's power.
+// layer 7.45 -> 7.14 ms, short lists (layers of 4096 to 46000 positions) 0 to 2 %.  (Each tile's sum is looked at in front of its P V, which costs 1.2 %
+// of that.  One look at the scores of both tiles in front of P V of the first would give the bits of the joint maximum, but the second tile's
+// scores are then waited for: 1496 -> 1548 us, 128k layer +13 %.)  The matrix core is busy 54 % of the cycles (50 % before) at 1.64 GHz (1.79), in the
+// 128k layer: like the dense kernel this one runs against the chip's power.
 //
 // Staging: K / V rows go from global memory straight into LDS (global_load_lds_dwordx4: no staging registers, no LDS
 // store instructions).  Two stage buffers: the loads of stage s+1 are issued in step s, after its barrier,

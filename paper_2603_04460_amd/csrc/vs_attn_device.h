@@ -69,10 +69,10 @@ inline bool short_lone(int q_heads, int64_t nq) { return static_cast<int64_t>(q_
 // Dense calls of up to 512 row blocks as well, where the second round costs nothing: a workgroup of it starts when one of the first round
 // ends (longest first), and two from the middle of the order, each as long as row block 256, end before the longest does.  That is so for whole
 // sequences; with a long context before the chunk all row blocks are about as long.  From 36 tiles on; the start of a workgroup costs as much as that many.
-// Two row blocks (in a wavefront from 2048 keys on, else in a workgroup) / one, us: 8 / 2 x 1300 16.4 / 15.2, x 1700 19.8 / 18.2, 4 / 2 x 3000
-// 25.4 / 21.0, 4 x 2800 24.2 / 19.2, 2 / 1 x 6000 39.4 / 30.8, 2 x 8000 51.3 / 48.5, 6000 rows of 8000 51.2 / 48.6, 1 x 9000 53.8 / 46.6, 12000
-// 69 / 62, 16001 92 / 92; not: 64 x 200 10.2 / 12.3, 16 x 800 12.4 / 14.5, 1200 rows of 8192, 8 / 2 heads 51 / 75, 9000 rows of 20000, one head
-// 106 / 130, 8 / 2 x 2100 (528 row blocks) 21.8 / 25.4.
+// Two row blocks (in a wavefront from 2048 keys on, else in a workgroup) / one, us: 8 / 2 x 1300 17.4 / 15.8, x 1700 21.1 / 18.8, 4 / 2 x 3000
+// 25.1 / 22.0, 4 x 2800 23.1 / 19.5, 2 / 1 x 6000 39.3 / 32.9, 2 x 8000 53.6 / 52.3, 1 x 9000 53.2 / 45.4, 12000 69 / 63, 16001 97 / 98; not:
+// 64 x 200 10.3 / 10.7, 16 x 800 12.7 / 14.3, 1200 rows of 8192, 8 / 2 heads 55 / 80, 9000 rows of 20000, one head 110 / 135, 8 / 2 x 2100 (528 row
+// blocks) 21.6 / 25.1.
 constexpr int kLoneTiles = 36;
 inline bool dense_lone(int q_heads, int64_t nq, int64_t pos0) {
     if (short_lone(q_heads, nq)) return true;

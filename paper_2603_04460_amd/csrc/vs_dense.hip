@@ -6,9 +6,9 @@
 // arithmetic per row block (S^T = K Q^T, joint softmax over a stage of two 32-key tiles with a lazily updated
 // maximum, O^T = V^T P^T) and the LDS tile layout are those of the sparse kernel.
 //
-// One wavefront issues a vector instruction every 5 clocks (two on a SIMD every 2.5; an exponential 9, and 8.4), while a 32x32x16 matrix
-// instruction occupies the matrix core for 32 and overlaps with what fits beside it: a matrix instruction with scale, exponential,
-// sum and half a pack takes 34 clocks from one wavefront.  With one wavefront per SIMD nothing hides a wait, so the kernel is written to
+// One wavefront issues a vector instruction every 5.4 clocks (two on a SIMD one every 2.7; an exponential takes 8.8, and 8.3), while a 32x32x16
+// matrix instruction occupies the matrix core for 32 and overlaps with what stands beside it: with five vector instructions and an exponential
+// behind it 42 clocks from one wavefront, 39 from two (profiles/issue_rates.txt).  With one wavefront per SIMD nothing hides a wait, so the kernel is written to
 // give every matrix instruction such company and nothing in a burst: the two row blocks run half a stage apart and each slot is written
 // out in issue order, matrix and vector instructions, fragment reads and staging loads alternating.
 //   slot X(i): matrix: scores of block 0 for stage i, then P V of block 0 for stage i-1;  vector: softmax of block 1, stage i-1
@@ -16,11 +16,14 @@
 // V fragments of stage i-1 are read at the start of X(i), K fragments of stage i+1 in Y(i) after the scores of
 // block 1; one barrier per stage, in Y(i), publishes stage i+1 and frees the buffer of stage i-1 for stage i+2.
 //
-// Stages below the diagonal take the row maximum as it stands (vs_attn_device.h, "stages without a row maximum"): the search for it was 21 of 88
-// vector instructions per tile and held the exponentials back (32 / 8 heads x 8192 487 -> 458 us, x 16384 1857 -> 1737).  Their V fragments are
+// Stages below the diagonal but for the first take the row maximum as it stands (vs_attn_device.h, "stages without a row maximum"): with the
+// search for it a tile had 94 vector instructions, now 77, and it held the exponentials back (32 / 8 heads x 8192 487 -> 458 us, x 16384 1857 -> 1737).
+// The sum of a lane's weights is looked at in front of the last matrix instruction of their slot; where every stage moves the maximum (scores that
+// grow by 2^1000 over 8192 keys) the call takes 590 us, 515 with the search in every stage.  Their V fragments are
 // read one behind each score product (all within the first six of them the four wavefronts asked the LDS for three times what it
 // gives) and their staging loads are issued between the score products of block 1 (all eight behind the barrier kept the matrix core
-// waiting): 458 -> 435 and 1737 -> 1642 us; the matrix core is busy 73 % of the cycles (57 % before), at 1.48 GHz instead of 1.67.
+// waiting): 458 -> 435 and 1737 -> 1642 us; with all this the matrix core is busy 76 % of the cycles at 1.65 GHz (n = 131072; 60 % at 1.99 before: the
+// chip's power, not the instruction stream, is what bounds it now).
 // A row block behind the last position has no mask either: for it alone the others of its wavefront ran every stage with one
 // (32 / 8 heads x 3152, half of the last workgroup's rows missing, 104 -> 79 us, x 1500 50 -> 37, 8 / 2 x 15000 485 -> 364).
 //
@@ -63,7 +66,7 @@ constexpr int kDuoKeys = 2048;
 // Bound by matrix products and loads alike: 2048 clocks each for a stage of the four wavefronts (128 KB at 64 bytes a clock).  The loads go out one
 // behind each matrix instruction, 46 of them before their data is needed (all of K in the X slot and of V in the Y slot, half a slot and
 // a little more, had to wait), without address arithmetic: 270 -> 254 us, 1128 rows of 30575 keys 652 -> 597, one head of 16001 103 -> 93; the
-// matrix core is busy 68 % of the cycles at 1.73 GHz.
+// matrix core is busy 60 % of the cycles at 1.65 GHz (500 rows, profiles/cases_instruction_mix.txt).
 template <bool DUO>
 __global__ __launch_bounds__(kThreads) void vs_dense_kernel(const AttnParams p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -586,9 +589,11 @@ int launch_dense(AttnParams& p, hipStream_t stream) {
 // while the two-row-block form spreads the same work evenly, at a higher price per tile and per workgroup.  An estimate for the whole card
 // (256 compute units at the 1.8 to 2 GHz that it holds under these kernels); a card cut into partitions would want other numbers.  Long form: 0.93 us per tile
 // of the longest workgroup, or of the average over 256 compute units where that is more; DUO: 0.55 us per tile and row block of a SIMD and 7 us
-// per round of workgroups.  Here / there, us: 24 x 2048 (192 workgroups) 57 / 46, 16 x 4096 (256) 103 / 91, 8 / 2 x 6000 (188) 139 / 95, x 8192 (256)
-// 191 / 154, x 10000 (314) 301 / 232, 1 x 40000 (157) 1134 / 439, 32 / 8, 1500 rows of 8192 (188) 237 / 196, of 32768 927 / 776, 1100 of 32768
-// (144) 926 / 720; not: 32 / 8 x 2048 (256) 60 / 66, x 3000 (375) 84 / 108, 8 / 2 x 16000 (500) 448 / 543, 2048 rows of 8192 (256) 221 / 252.
+// per round of workgroups.  That was before stages without a row maximum, from which the long form has gained more (it is now 0.53 to 0.62 us per tile,
+// DUO 0.46), so the line leaves some time on the long form's side.  Here / there, us: 24 x 2048 (192 workgroups) 53 / 51, 8 / 2 x 6000 (188) 111 / 91,
+// x 8192 (256) 159 / 145, 1 x 40000 (157) 666 / 388, x 65536 1180 / 972, 2 / 1 x 30000 534 / 427; not: 32 / 8 x 2048 (256) 49 / 59, x 3000 (375) 73 / 105,
+// 8 / 2 x 16000 (500) 402 / 498, 2000 rows of 8192 (250) 197 / 233; on the wrong side: 16 x 4096 (256) 90 / 93, 8 / 2 x 10000 (314) 204 / 214, 32 / 8, 1500
+// rows of 8192 (188) 167 / 181, of 32768 646 / 700, 1100 of 32768 (144) 559 / 623.
 bool duo_is_faster(int q_heads, int64_t n_q, int64_t pos0) {
     const int64_t blocks = (n_q + 31) / 32, last = (pos0 + n_q + 31) / 32;
     const int64_t work = q_heads * (blocks * (last - blocks) + blocks * (blocks + 1) / 2);   // tiles x row blocks
@@ -639,9 +644,9 @@ int vs_dense_prefill_chunk(const void* q, const void* k, const void* v, int q_he
         const int rows = vs::dense_lone(p.q_heads, p.nq, p.pos0) ? 1 : 2;
         p.hc = vs::short_heads(p.hc, rows);
         // Of these, more than 256 row blocks against at least 2048 keys: two row blocks per wavefront (DUO).  There / vs_short_kernel, us:
-        // 8 x 2048 22 / 25, 16 / 4 x 2048 33 / 33, 12 x 2600 79 / 80, 32 / 8, 500 rows of 2048 24 / 26, 1024 of 4096 73 / 80, of 32768 567 / 648;
-        // with fewer keys the fill and the larger stages cost as much: 16 / 4 x 1700 27 / 26, 24 x 1280 25 / 24, 32 / 8 x 1024 24 / 22,
-        // 128 x 200 18 / 15 (but 8 / 2 x 1500 17 / 19).
+        // 8 x 2048 22 / 25, 16 / 4 x 2048 33 / 33, 12 x 2600 36 / 55, 8 / 2 x 2600 27 / 28, x 3800 40 / 44, 12 / 6 x 2600 35 / 36, 32 / 8, 500 rows of 2048 24 / 25,
+        // 750 of 2100 38 / 39, 1024 of 4096 71 / 80, of 32768 530 / 636; with fewer keys the fill and the larger stages cost as much: 16 / 4 x 1700 29 / 26,
+        // 24 x 1280 26 / 23, 32 / 8 x 1024 24 / 21.
         if (rows == 2 && n_kv >= kDuoKeys) return launch_dense<true>(p, static_cast<hipStream_t>(stream));
         return vs::launch_short_dense(p, rows, static_cast<hipStream_t>(stream));
     }

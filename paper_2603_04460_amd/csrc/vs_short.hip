@@ -85,7 +85,7 @@ struct RowBlock {
     bf16x8 qf[8];
     f32x16 oacc[4];
     float m_run, l_run;
-    int settled;                                             // every row has a maximum, which stays as it is (vs_attn_device.h)
+    int settled;                                             // every row has a maximum, which moves only where a row has grown (vs_attn_device.h)
 
     // Q fragments: B operand of S^T = K Q^T; lane holds query qi, d = 16 kk + 8 hh .. +7
     __device__ __forceinline__ void init(const AttnParams& p, int head, int first, int qi, int hh) {
