@@ -96,6 +96,23 @@ def test_sparse(hq, hk, n, pos0, gran, rows_per_workgroup, growth, big_v, later)
 
 
 @pytest.mark.parametrize("growth,big_v,later", [g for g in GROWTH if g[2]])
+@pytest.mark.parametrize("hq,hk,n,form,late,n_rows", [(64, 16, 1411, "long", 1344, 64), (16, 4, 2050, "duo", 1792, 32)])
+def test_dense_search_after_growth(hq, hk, n, form, late, n_rows, growth, big_v, later):
+    """The stage on the diagonal looks for a maximum.  Here it starts with the later key, so that every row block of the workgroup has it (and, with two
+    row blocks to a wavefront, the wavefront that has key n // 2): none is left whose sum alone shows that a row has grown."""
+    assert dense_form(hq, hk, n, n) == form
+    (q, k, v), (qb, kb, vb) = _inputs(4200 + n, hq, hk, n, growth, big_v)
+    k[::2, late, 0] = later / POWER
+    kb = synth.to_bits(k)
+    o, lse = torch.empty_like(q), torch.empty((hq, n), dtype=torch.float32, device="cuda")
+    vs.dense_prefill(q, k, v, o, lse)
+    torch.cuda.synchronize()
+    rows = np.arange(late, late + n_rows)
+    ref_o, ref_lse = oracle.dense_attention(qb, kb, vb, rows=rows)
+    _check(o, lse, ref_o, ref_lse, rows, big_v)
+
+
+@pytest.mark.parametrize("growth,big_v,later", [g for g in GROWTH if g[2]])
 @pytest.mark.parametrize("hq,hk", [(32, 8), (160, 160)])
 def test_sparse_search_after_growth(hq, hk, growth, big_v, later):
     """The kernel for many row blocks looks for a maximum where only one tile of a stage is live, the third of three gathered ones here; the
